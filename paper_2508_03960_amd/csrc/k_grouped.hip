@@ -1372,8 +1372,7 @@ hipError_t launch_gather_state4(int64_t K, const int32_t *inv, const float4 *m4,
 // the emissions' first entries are all loaded before any is added (job
 // indices clamped into the launch; a clamped duplicate is never written back).
 constexpr int kPartJobsPerThread = 4;
-typedef const __attribute__((address_space(1))) float4 *part_gptr;
-typedef __attribute__((address_space(1))) double2 *gsum_gptr;
+typedef __attribute__((address_space(1))) double *gsum_gptr;
 
 __global__ __launch_bounds__(256) void k_part_reduce(const PartJob *__restrict__ jobs, int n_jobs, int64_t n_groups,
                                                     const int32_t *__restrict__ xstart) {
@@ -1383,27 +1382,26 @@ __global__ __launch_bounds__(256) void k_part_reduce(const PartJob *__restrict__
     const int64_t w0 = s0 / kPartSlots, w1 = (xstart[g + 1] - 1) / kPartSlots;
     const bool head = s0 % kPartSlots == 0;
     const int j0 = blockIdx.y * kPartJobsPerThread;
-    part_gptr part[kPartJobsPerThread];
+    const float4 *part[kPartJobsPerThread];
     float4 v0[kPartJobsPerThread];
 #pragma unroll
     for (int q = 0; q < kPartJobsPerThread; ++q) {
-        part[q] = (part_gptr)jobs[min(j0 + q, n_jobs - 1)].part;
-        v0[q] = part[q][w0];
+        part[q] = jobs[min(j0 + q, n_jobs - 1)].part;
+        v0[q] = gather_row(part[q], (int)w0);
     }
 #pragma unroll
     for (int q = 0; q < kPartJobsPerThread; ++q) {
         double sr = head ? v0[q].x : v0[q].z, si = head ? v0[q].y : v0[q].w;
         for (int64_t w = w0 + 1; w <= w1; ++w) {
-            const float4 v = part[q][w];
+            const float4 v = gather_row(part[q], (int)w);
             sr += v.x;
             si += v.y;
         }
         if (j0 + q < n_jobs) {
-            gsum_gptr gs = (gsum_gptr)jobs[j0 + q].gsum + g;
-            double2 t = *gs;
-            t.x += sr;
-            t.y += si;
-            *gs = t;
+            gsum_gptr gs = (gsum_gptr)(jobs[j0 + q].gsum + g);
+            const double tr = gs[0] + sr, ti = gs[1] + si;
+            gs[0] = tr;
+            gs[1] = ti;
         }
     }
 }
