@@ -124,7 +124,8 @@ typedef struct gbs_stats {
     double pass_bytes;     /* algorithmic HBM bytes of the sweeps over all isochromats */
     double pass_kernel_ms; /* GBS_PROFILE: sum of the sweep kernel durations */
     int64_t n_sweeps;      /* sweep launches: runs of grouped operations applied in one pass */
-    double pass_flops;     /* algorithmic FP32 flops of the sweeps (factor products, maps, transitions, sums) */
+    double pass_flops;     /* algorithmic FP32 flops of the sweeps (factor products, maps, transitions, sums);
+                              stepped per run: of the runs' sums over their members and of the runs' operations */
     int64_t n_surrogate;   /* GBS_SURROGATE: distinct RF transitions taken from the network */
     int64_t n_surrogate_fallback; /* ... of which failed the spot check and were composed exactly */
     double surrogate_residual;    /* largest spot-check residual max|T_mlp - T_exact| (0 if none) */
@@ -198,7 +199,7 @@ int gbs_set_sequence(gbs_ctx *ctx, const gbs_block *blocks, int64_t n_blocks, co
  * Group the isochromats once (Sec. 2.4, Fig. 2): for each requested axis a
  * (GBS_AX_X | GBS_AX_Y | GBS_AX_Z) the key (r_a, T1, T2, dB0) is compared by
  * exact bit pattern (-0 == +0); equal keys form one group, numbered densely
- * in lexicographic key order.  GBS_AX_N adds the no-grads groups of key
+ * in lexicographic key order (z groups: of (T1, T2, dB0, z)).  GBS_AX_N adds the no-grads groups of key
  * (T1, T2, dB0), numbered in ascending (T1, T2, dB0) order: a with-RF
  * subsequence without gradients then composes one transition per such group
  * instead of one per x-group (the result is the same).  GBS_AX_XZ (with
@@ -229,7 +230,11 @@ int gbs_build_groups(gbs_ctx *ctx, uint32_t axes);
  *     combined-transition and map tables of every grouped subsequence
  *     (Eq. 7, Eq. 4/5), the FP64 group sums of every with-ADC subsequence
  *     (Eq. 9), partial sample sums when blocks are stepped, and the
- *     surrogate's buffers when one is attached (gbs_set_surrogate).
+ *     surrogate's buffers when one is attached (gbs_set_surrogate).  Where a
+ *     call from (0, 0, M0) steps the runs of equal (x, z, T1, T2, dB0)
+ *     instead of their members, room for their sums of M0 exp(-i phi_y): 8
+ *     bytes per run, coil and phase-encode line (of batches of runs when
+ *     many coils need much).
  *   GBS_CACHED: the FP64 state (24 bytes per isochromat), the transition
  *     cache of Sec. 2.2 (48 bytes per isochromat and distinct with-RF
  *     waveform) and partial sample sums.
@@ -260,6 +265,10 @@ int gbs_workspace_size(gbs_ctx *ctx, int mode, size_t *bytes);
  * rounded coefficients of a constant-gradient readout err the same way at
  * every step, far beyond 1e-5 of M over a long sequence).  GBS_PLAIN and
  * GBS_CACHED keep the state between launches in FP64.
+ * GBS_GROUPED from m_init = NULL steps one ratio M / M0 per run of equal (x, z,
+ * T1, T2, dB0), where no y moment precedes a transition and the readouts'
+ * y moments lie on an even grid: the members of a run then stay alike, and
+ * the readouts weight the ratio by the run's sum of M0 exp(-i phi_y).
  * GBS_CACHED recomposes its transition cache (3 float4 rows (A_i0, A_i1,
  * A_i2, b_i) of K per distinct with-RF waveform: bit-identical B1 and
  * gradients) in every call.  With-ADC blocks that play RF are stepped per

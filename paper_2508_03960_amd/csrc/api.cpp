@@ -33,6 +33,7 @@
 #include "pairs.hpp"
 #include "plain_coils.hpp"
 #include "plan.hpp"
+#include "runs.hpp"
 
 using namespace gbs;
 
@@ -144,6 +145,22 @@ struct GroupedPlan {
     int surr_n_check = 0;
     size_t o_rf_surr = 0;
     size_t s_tuples = 0, s_T32 = 0, s_exact = 0, s_res = 0, s_fb = 0;
+    // per-run form of the whole simulation (runs.hpp), for calls that start
+    // from (0, 0, M0): batches of runs whose Y fits the workspace
+    bool runs = false;
+    YLines lines{};
+    int64_t run_batch = 0;
+    double final_cy = 0.0;  // y phase of the last map, per isochromat
+    size_t w_runy = 0, w_runm = 0, run_ws_bytes = 0, o_runop = 0;
+    double run_flops = 0.0, run_bytes = 0.0;
+    // batches of whole x-groups: first run (a multiple of 16 is where its Y
+    // starts), and its wavefronts [wave0, wave0 + waves) of ctx->run_waves
+    struct RunBatch {
+        int64_t r0, r1;
+        int32_t wave0, waves;
+    };
+    std::vector<RunBatch> batches;
+    std::vector<RunPart> run_parts;
 };
 
 }  // namespace
@@ -176,6 +193,13 @@ struct gbs_ctx {
     // z-group); run of every 4-slot quad, and (x, T1, T2, df), z per run
     int64_t n_runs = -1;
     DevBuf run_of4, rtab, rz;
+    // the same runs whenever z groups are built (n_lruns, else 0): first quad,
+    // x- and z-group per run, run of each isochromat in the caller's order
+    int64_t n_lruns = 0;
+    DevBuf rfirst4, rgx, rgz, run_of;
+    std::vector<int32_t> xrun;  // first run of each x-group, and n_lruns (empty: runs too short for the per-run form)
+    DevBuf run_waves;           // grouped plan: run ranges of the run sweep's wavefronts, batch after batch
+    DevBuf run_ident;           // kRunIdentity
     // receive coils (gbs_set_coils; caller-owned views [n_coils][K] in natural
     // order) and their group-sorted copy (planes re, im per coil, Kpad each)
     int32_t n_coils = 1;
@@ -251,6 +275,8 @@ static int build_grouped_plan(gbs_ctx *ctx);
                                               std::to_string((size_t)(bytes)) + " bytes failed"); \
     } while (0)
 
+constexpr int64_t kRunMinMembers = 2;  // mean members per run from which the per-run form is used (plan_runs)
+
 static const char *status_text(int s) {
     switch (s) {
         case GBS_OK: return "ok";
@@ -305,7 +331,7 @@ int gbs_destroy(gbs_ctx *ctx) {
                       &ctx->t2i, &ctx->dfi, &ctx->m0i, &ctx->jobs, &ctx->samp, &ctx->flag, &ctx->surr_idx, &ctx->csurr_idx,
                       &ctx->adj_ops, &ctx->adj_samp, &ctx->adj_ckpt, &ctx->adj_sub, &ctx->adj_sig, &ctx->adj_grf,
                       &ctx->adj_gt, &ctx->csamp, &ctx->ttab, &ctx->tmap, &ctx->coil_l, &ctx->run_of4, &ctx->xstart,
-                      &ctx->rtab, &ctx->rz};
+                      &ctx->rtab, &ctx->rz, &ctx->rfirst4, &ctx->rgx, &ctx->rgz, &ctx->run_of, &ctx->run_waves, &ctx->run_ident};
     for (DevBuf *b : bufs) b->release();
     for (int a = 0; a < 3; ++a) {
         ctx->gid[a].release();
@@ -461,7 +487,7 @@ int gbs_build_groups(gbs_ctx *ctx, uint32_t axes) {
         ALLOC(ctx->gtab[a], sizeof(float4) * K);
         ALLOC(ctx->gcount[a], sizeof(int32_t) * K);
         int64_t G = 0;
-        hipError_t e = group_axis(K, coord[a], ctx->ph.t1, ctx->ph.t2, ctx->ph.df, scratch.p, scratch_bytes,
+        hipError_t e = group_axis(K, a == 2, coord[a], ctx->ph.t1, ctx->ph.t2, ctx->ph.df, scratch.p, scratch_bytes,
                                   gid_nat[a].as<int32_t>(), ctx->gtab[a].as<float4>(), ctx->gcount[a].as<int32_t>(),
                                   order.as<int32_t>(), &G, ctx->stream);
         if (e != hipSuccess) return fail_hip(e, "grouping failed");
@@ -522,45 +548,52 @@ int gbs_build_groups(gbs_ctx *ctx, uint32_t axes) {
         HIPCHK(launch_gather_f32(Kpad, Kpad, src, from[i], dst[i]->as<float>(), ctx->stream));
     }
     HIPCHK(launch_zero_padding(Kpad, ctx->perm.as<int32_t>(), ctx->m0i.as<float>(), ctx->stream));
-    // two-axis groups: the runs of equal (x-group, z-group) in the layout
+    // the runs of equal (x-group, z-group) in the layout (the two-axis groups)
     ctx->n_runs = -1;
-    if (axes & GBS_AX_XZ) {
+    ctx->n_lruns = 0;
+    if (axes & GBS_AX_Z) {
         const int64_t n4 = kint / 4;
-        DevBuf flags;
-        if (flags.ensure((size_t)n4) != hipSuccess) {
-            cleanup();
-            return fail(ctx, GBS_E_NOMEM, "run flag allocation failed");
-        }
-        HIPCHK(launch_run_flags(n4, ctx->gid[0].as<int32_t>(), ctx->gid[2].as<int32_t>(), flags.as<uint8_t>(),
-                                ctx->stream));
-        std::vector<uint8_t> hf((size_t)n4);
-        HIPCHK(hipMemcpyAsync(hf.data(), flags.p, (size_t)n4, hipMemcpyDeviceToHost, ctx->stream));
-        HIPCHK(hipStreamSynchronize(ctx->stream));
-        flags.release();
-        std::vector<int32_t> run_of((size_t)n4), first;
-        int32_t r = -1;
-        for (int64_t q = 0; q < n4; ++q) {
-            if (hf[q]) {
-                ++r;
-                first.push_back((int32_t)q);
-            }
-            run_of[q] = r;
-        }
-        const int64_t R = (int64_t)first.size();
-        DevBuf dfirst;
         ALLOC(ctx->run_of4, sizeof(int32_t) * (size_t)n4);
-        ALLOC(ctx->rtab, sizeof(float4) * (size_t)R);
-        ALLOC(ctx->rz, sizeof(float) * (size_t)R);
-        ALLOC(dfirst, sizeof(int32_t) * (size_t)R);
-        HIPCHK(hipMemcpy(ctx->run_of4.p, run_of.data(), sizeof(int32_t) * (size_t)n4, hipMemcpyHostToDevice));
-        HIPCHK(hipMemcpy(dfirst.p, first.data(), sizeof(int32_t) * (size_t)R, hipMemcpyHostToDevice));
-        HIPCHK(launch_run_table(R, dfirst.as<int32_t>(), ctx->xi.as<float>(), ctx->zi.as<float>(), ctx->t1i.as<float>(),
-                                ctx->t2i.as<float>(), ctx->dfi.as<float>(), ctx->rtab.as<float4>(), ctx->rz.as<float>(),
-                                ctx->stream));
-        HIPCHK(hipStreamSynchronize(ctx->stream));
-        ctx->n_runs = R;
-    } else {
+        ALLOC(ctx->run_of, sizeof(int32_t) * (size_t)K);
+        // (the scratch holds at least 8 int32 per isochromat and the layout at most 8 slots)
+        int64_t R = 0;
+        e = number_runs(n4, K, ctx->gid[0].as<int32_t>(), ctx->gid[2].as<int32_t>(), ctx->inv.as<int32_t>(), scratch.p,
+                        scratch_bytes, ctx->run_of4.as<int32_t>(), ctx->run_of.as<int32_t>(), &R, ctx->stream);
+        if (e != hipSuccess) return fail_hip(e, "run numbering failed");
+        ALLOC(ctx->rfirst4, sizeof(int32_t) * (size_t)(R + 1));
+        ALLOC(ctx->rgx, sizeof(int32_t) * (size_t)R);
+        ALLOC(ctx->rgz, sizeof(int32_t) * (size_t)R);
+        HIPCHK(launch_run_arrays(n4, ctx->run_of4.as<int32_t>(), ctx->gid[0].as<int32_t>(), ctx->gid[2].as<int32_t>(),
+                                 ctx->rfirst4.as<int32_t>(), ctx->rgx.as<int32_t>(), ctx->rgz.as<int32_t>(),
+                                 ctx->stream));
+        ctx->n_lruns = R;
+        ctx->xrun.clear();
+        if (K >= kRunMinMembers * R && R <= kRunMaxRuns) {
+            const int64_t Gx = ctx->ng[0];
+            if (scratch_bytes < sizeof(int32_t) * (size_t)(Gx + 1)) return fail_hip(hipErrorInvalidValue, "run ranges");
+            HIPCHK(launch_group_runs(R, ctx->rgx.as<int32_t>(), Gx, scratch.as<int32_t>(), ctx->stream));
+            ctx->xrun.resize((size_t)(Gx + 1));
+            HIPCHK(hipMemcpyAsync(ctx->xrun.data(), scratch.p, sizeof(int32_t) * (size_t)(Gx + 1), hipMemcpyDeviceToHost,
+                                  ctx->stream));
+            HIPCHK(hipStreamSynchronize(ctx->stream));
+        }
+        if (axes & GBS_AX_XZ) {
+            ALLOC(ctx->rtab, sizeof(float4) * (size_t)R);
+            ALLOC(ctx->rz, sizeof(float) * (size_t)R);
+            HIPCHK(launch_run_table(R, ctx->rfirst4.as<int32_t>(), ctx->xi.as<float>(), ctx->zi.as<float>(),
+                                    ctx->t1i.as<float>(), ctx->t2i.as<float>(), ctx->dfi.as<float>(),
+                                    ctx->rtab.as<float4>(), ctx->rz.as<float>(), ctx->stream));
+            ctx->n_runs = R;
+        }
+    }
+    if (!(axes & GBS_AX_Z)) {
         ctx->run_of4.release();
+        ctx->run_of.release();
+        ctx->rfirst4.release();
+        ctx->rgx.release();
+        ctx->rgz.release();
+    }
+    if (!(axes & GBS_AX_XZ)) {
         ctx->rtab.release();
         ctx->rz.release();
     }
@@ -806,6 +839,181 @@ static bool in_emit_kernel(int need, bool coils) {
 // k_sweep_emit), i.e. not the general or the coil sweep?
 static bool in_partial_kernel(int need, bool coils) {
     return !coils && !(need & (kNeedGy | kNeedZ | kForceGeneral));
+}
+
+// The per-run form of a grouped schedule (runs.hpp): rops stays empty when it
+// does not apply.  It needs every operation in one fused run (no stepped
+// blocks), transitions of x-, z- or two-axis groups, emissions of x-groups, no
+// y moment before a transition that meets a transverse magnetization (the
+// first one meets none), and the emissions' y moments on an even grid.
+// A run costs one lane of the sweep and, per 256 grid lines and coil, a fixed
+// part of a product besides its members' share; below kRunMinMembers members
+// the sweep over the isochromats is as fast.
+constexpr int kRunMaxLines = 2048;
+constexpr size_t kRunWsFloor = (size_t)64 << 20;  // Y of all runs at once up to this workspace
+constexpr size_t kRunWsCap = (size_t)2 << 30;     // and batches of kRunMinBatch runs up to this one
+constexpr int64_t kRunMinBatch = 65536;           // runs per launch that still fill the chip (64 per wavefront)
+
+static int plan_runs(gbs_ctx *ctx, const std::vector<SweepOp> &sops, std::vector<RunOp> &rops) {
+    GroupedPlan &g = ctx->gp;
+    const int64_t R = ctx->n_lruns;
+    if (sops.empty() || ctx->xrun.empty()) return GBS_OK;
+    for (const auto &it : g.exec)
+        if (it.first != 0) return GBS_OK;
+    std::vector<double> cy;
+    for (size_t i = 0; i < sops.size(); ++i) {
+        const SweepOp &o = sops[i];
+        if ((o.flags & kOpRf) && o.rf_axis == 1) return GBS_OK;
+        if ((o.flags & kOpEmit) && (o.emit_axis != 0 || o.emit_cz != 0.0)) return GBS_OK;
+        if (o.pre_cz != 0.0) return GBS_OK;
+        const bool final_map = i + 1 == sops.size() && !(o.flags & (kOpRf | kOpEmit));
+        if (o.pre_cy != 0.0 && !(i == 0 && (o.flags & kOpRf)) && !final_map) return GBS_OK;
+        if (o.flags & kOpEmit) cy.push_back(o.emit_cy);
+    }
+    // the grid: from the smallest moment in steps of the smallest difference
+    YLines L{};
+    int64_t span = 0;
+    double lo = 0.0;
+    if (!cy.empty()) {
+        std::vector<double> u(cy);
+        std::sort(u.begin(), u.end());
+        lo = u.front();
+        const double range = u.back() - lo;
+        double step = 0.0;  // differences of rounding size are equal moments
+        for (size_t i = 1; i < u.size(); ++i)
+            if (u[i] - u[i - 1] > 1e-9 && (step == 0.0 || u[i] - u[i - 1] < step)) step = u[i] - u[i - 1];
+        if (step > 0.0) {
+            if (range / step > kRunMaxLines) return GBS_OK;
+            span = std::llround(range / step);
+            L.d = range / (double)span;
+        }
+        for (double c : cy)  // phase error of the grid below 1e-9 cycles per metre
+            if (std::fabs(c - lo - L.d * (L.d > 0.0 ? std::round((c - lo) / L.d) : 0.0)) > 1e-9) return GBS_OK;
+    }
+    // few emissions spread over a wide grid: most lines would be made in vain
+    if (span + 1 > 256 && span + 1 > 4 * (int64_t)cy.size()) return GBS_OK;
+    L.nb = (int32_t)((span + 1 + 31) / 32);
+    L.n_lines = 32 * L.nb;
+    const int64_t shift = (L.n_lines - (span + 1)) / 2;  // line of the smallest moment
+    L.c0 = lo - L.d * ((double)shift - 0.5 * L.n_lines + 0.5);
+    // workspace: Y and the ratios take the place of the sweeps' state, or the
+    // room after the group sums where that is more (small phantoms, many coils)
+    const size_t tail = align256(std::max(g.w_gsum + sizeof(double2) * g.gsum_count,
+                                          g.surr_rf >= 0 ? g.w_surr + g.s_fb + sizeof(int32_t) : 0));
+    const size_t per_tile = sizeof(float2) * (size_t)kRunTile * (size_t)L.n_lines * (size_t)ctx->n_coils;
+    const int64_t tiles = (R + kRunTile - 1) / kRunTile;
+    const size_t batch_bytes = per_tile * (size_t)std::min<int64_t>(tiles, kRunMinBatch / kRunTile) +
+                               sizeof(float4) * (size_t)R + 1024;
+    const size_t limit = std::max(std::max(g.ws_bytes, kRunWsFloor), std::min(tail + batch_bytes, kRunWsCap));
+    const size_t state_room = g.w_tabs - g.w_state, tail_room = limit > tail ? limit - tail : 0;
+    WsCarve w;
+    w.off = state_room >= tail_room ? g.w_state : tail;
+    const size_t end = state_room >= tail_room ? g.w_tabs : limit;
+    g.w_runm = w.take(sizeof(float4) * (size_t)R);
+    int64_t fit = w.off + 256 < end ? std::min<int64_t>(tiles, (int64_t)((end - w.off - 256) / per_tile)) : 0;
+    if (fit < tiles && fit * kRunTile < kRunMinBatch) return GBS_OK;
+    // Batches of whole x-groups, each with at most fit tiles, its Y starting at
+    // the multiple of 16 at or below its first run; inside, wavefronts of whole
+    // x-groups (a group of more than 64 runs takes several, and a group that
+    // no batch can hold is cut).
+    std::vector<int32_t> waves;
+    g.batches.clear();
+    const int64_t cap = fit * kRunTile;
+    int64_t most = 0;
+    const std::vector<int32_t> &xr = ctx->xrun;
+    auto open_batch = [&](int64_t r) { g.batches.push_back({r, r, (int32_t)waves.size(), 0}); };
+    auto base_of = [&]() { return g.batches.back().r0 / kRunTile * kRunTile; };
+    auto close_batch = [&](int64_t r) {
+        g.batches.back().r1 = r;
+        g.batches.back().waves = (int32_t)waves.size() - g.batches.back().wave0;
+        waves.push_back((int32_t)r);
+        most = std::max(most, r - base_of());
+    };
+    open_batch(0);
+    int64_t wave_first = 0;  // first run of the open wavefront
+    auto end_wave = [&](int64_t r) {
+        if (r > wave_first) waves.push_back((int32_t)wave_first);
+        wave_first = r;
+    };
+    for (size_t gi = 0; gi + 1 < xr.size(); ++gi) {
+        int64_t r = xr[gi];
+        const int64_t e = xr[gi + 1];
+        if (e - wave_first > 64) end_wave(r);
+        if (e - base_of() > cap && r > g.batches.back().r0) {
+            end_wave(r);
+            close_batch(r);
+            open_batch(r);
+        }
+        for (; e - wave_first > 64; r = wave_first) {  // more runs than a wavefront holds
+            if (wave_first + 64 - base_of() > cap) {
+                close_batch(wave_first);
+                open_batch(wave_first);
+            }
+            end_wave(wave_first + 64);
+        }
+        if (e - base_of() > cap) {
+            close_batch(wave_first);
+            open_batch(wave_first);
+        }
+    }
+    end_wave(R);
+    close_batch(R);
+    ALLOC(ctx->run_waves, sizeof(int32_t) * waves.size());
+    HIPCHK(hipMemcpy(ctx->run_waves.p, waves.data(), sizeof(int32_t) * waves.size(), hipMemcpyHostToDevice));
+    g.run_batch = (most + kRunTile - 1) / kRunTile * kRunTile;
+    g.w_runy = w.take(per_tile * (size_t)(g.run_batch / kRunTile));
+    g.run_ws_bytes = w.off;
+    g.lines = L;
+    g.final_cy = 0.0;
+    ALLOC(ctx->run_ident, sizeof(kRunIdentity));
+    HIPCHK(hipMemcpy(ctx->run_ident.p, kRunIdentity, sizeof(kRunIdentity), hipMemcpyHostToDevice));
+    const float4 *one = ctx->run_ident.as<float4>(), *rows = one + 1;
+    rops.reserve(sops.size());
+    for (size_t i = 0; i < sops.size(); ++i) {
+        const SweepOp &o = sops[i];
+        RunOp r{};
+        r.flags = o.flags & (kOpPre | kOpRf | kOpEmit | kPreMz);
+        r.rf_axis = o.rf_axis;
+        auto pick = [&](auto *tab, auto *ident, int bit) {
+            if (tab) r.flags |= bit;
+            return tab ? tab : ident;
+        };
+        r.pre_xtab = pick(o.pre_xtab, one, kRunPreX);
+        r.pre_ztab = pick(o.pre_ztab, (const float2 *)one, kRunPreZ);
+        r.ttab = pick(o.ttab, rows, kRunRows);
+        r.emit_xtab = (o.flags & kOpEmit) ? o.emit_xtab : one;
+        r.emit_ztab = pick((o.flags & kOpEmit) ? o.emit_ztab : nullptr, (const float2 *)one, kRunEmitZ);
+        if (i + 1 == sops.size() && !(o.flags & (kOpRf | kOpEmit))) g.final_cy = o.pre_cy;
+        if (o.flags & kOpEmit) {
+            r.line = (int32_t)(shift + (L.d > 0.0 ? std::llround((o.emit_cy - lo) / L.d) : 0));
+            r.gsum_stride = o.gsum_stride;
+            r.gsum = o.gsum;
+        }
+        rops.push_back(r);
+    }
+    // parts: stretches of at least 16 operations that only emit, and the rest
+    g.run_parts.clear();
+    auto only = [&](size_t i) { return (rops[i].flags & (kOpPre | kOpRf | kOpEmit | kPreMz)) == kOpEmit; };
+    for (size_t i = 0; i < rops.size();) {
+        size_t e = i;
+        while (e < rops.size() && only(e)) ++e;
+        const bool eo = e - i >= 16 && g.run_parts.size() + 2 < (size_t)kRunMaxParts;
+        if (!eo) e = i + 1;
+        if (!eo && !g.run_parts.empty() && !g.run_parts.back().emit_only)
+            ++g.run_parts.back().n;
+        else
+            g.run_parts.push_back(RunPart{(int32_t)i, (int32_t)(e - i), eo ? 1 : 0});
+        i = e;
+    }
+    // 4 multiply-adds of the matrix cores per member, line and coil; per run
+    // the transitions, factors and sums of its operations
+    double fl = 0.0;
+    for (const auto &sg : g.segs) fl += sg.flops_per_iso;
+    g.run_flops = 4.0 * (double)ctx->Kint * 256.0 * ((L.nb + 7) / 8) * ctx->n_coils + fl * (double)R;
+    g.run_bytes = (8.0 + 8.0 * (ctx->coil_re ? ctx->n_coils : 0)) * (double)ctx->Kint +
+                  2.0 * (double)per_tile / kRunTile * (double)R + (20.0 + (g.final_cy != 0.0 ? 4.0 : 0.0)) * (double)ctx->K;
+    g.runs = true;
+    return GBS_OK;
 }
 
 static int build_grouped_plan(gbs_ctx *ctx) {
@@ -1353,6 +1561,9 @@ static int build_grouped_plan(gbs_ctx *ctx) {
         }
     }
     g.ws_bytes = w.off;
+    std::vector<RunOp> rops;
+    if (ctx->n_lruns > 0)
+        if (int rc = plan_runs(ctx, sops, rops)) return rc;
     for (auto &sg : g.segs) sg.bytes_per_iso = sweep_bytes_per_iso(sg.need, sg.write_m, false, false);
     g.n_ops = (int64_t)sops.size();
 
@@ -1369,7 +1580,8 @@ static int build_grouped_plan(gbs_ctx *ctx) {
     g.o_adclin = g.o_adc + align256(sizeof(AdcJobDev) * aj.size());
     g.o_sweep = g.o_adclin + align256(sizeof(AdcLinJob) * lj.size());
     g.o_part = g.o_sweep + align256(sizeof(SweepOp) * sops.size());
-    const size_t jbytes = g.o_part + sizeof(PartJob) * pj.size();
+    g.o_runop = g.o_part + align256(sizeof(PartJob) * pj.size());
+    const size_t jbytes = g.o_runop + sizeof(RunOp) * rops.size();
     ctx->host_jobs.assign(jbytes, 0);
     auto put = [&](size_t o, const void *src, size_t n) {
         if (n) std::memcpy(ctx->host_jobs.data() + o, src, n);
@@ -1382,6 +1594,7 @@ static int build_grouped_plan(gbs_ctx *ctx) {
     put(g.o_adclin, lj.data(), sizeof(AdcLinJob) * lj.size());
     put(g.o_sweep, sops.data(), sizeof(SweepOp) * sops.size());
     put(g.o_part, pj.data(), sizeof(PartJob) * pj.size());
+    put(g.o_runop, rops.data(), sizeof(RunOp) * rops.size());
     // the pointer fields that hold workspace offsets
     const std::vector<char> &img = ctx->host_jobs;
     add_relocs<RfJobDev>(g.relocs, img, g.o_rf, rj.size(), {offsetof(RfJobDev, out)});
@@ -1394,6 +1607,14 @@ static int build_grouped_plan(gbs_ctx *ctx) {
                         {offsetof(SweepOp, pre_xtab), offsetof(SweepOp, part), offsetof(SweepOp, pre_ztab),
                          offsetof(SweepOp, ttab), offsetof(SweepOp, emit_xtab), offsetof(SweepOp, emit_ztab),
                          offsetof(SweepOp, gsum)});
+    for (size_t i = 0; i < rops.size(); ++i) {  // identity rows are device addresses already
+        const size_t at = g.o_runop + i * sizeof(RunOp);
+        const std::pair<int, size_t> fields[] = {{kRunPreX, offsetof(RunOp, pre_xtab)}, {kRunPreZ, offsetof(RunOp, pre_ztab)},
+                                                 {kRunRows, offsetof(RunOp, ttab)},     {kOpEmit, offsetof(RunOp, emit_xtab)},
+                                                 {kRunEmitZ, offsetof(RunOp, emit_ztab)}, {kOpEmit, offsetof(RunOp, gsum)}};
+        for (const auto &f : fields)
+            if (rops[i].flags & f.first) g.relocs.push_back(at + f.second);
+    }
     add_relocs<PartJob>(g.relocs, img, g.o_part, pj.size(), {offsetof(PartJob, part), offsetof(PartJob, gsum)});
     ALLOC(ctx->jobs, jbytes);
     g.uploaded_ws = nullptr;
@@ -1444,7 +1665,35 @@ static int build_coil_layout(gbs_ctx *ctx) {
     return GBS_OK;
 }
 
-static int run_grouped(gbs_ctx *ctx, char *ws, const float *m_init, float *m_out, double *sig_out, bool profile,
+// The end of a grouped simulation: the ADC samples beside the final state's
+// copy on the side stream, and the counts.
+static int finish_grouped(gbs_ctx *ctx, const char *jb, double *sig_out, gbs_stats *st, int64_t n_sweeps, double bytes,
+                          double flops) {
+    const GroupedPlan &g = ctx->gp;
+    const Plan &plan = g.plan;
+    // ---- ADC samples from the group sums (Eq. 8, Eq. 10) --------------------
+    HIPCHK(launch_adc_eval((const AdcJobDev *)(jb + g.o_adc), g.n_adc, g.max_adc_groups, g.max_adc_samples,
+                           sig_out, ctx->stream));
+    HIPCHK(launch_adc_lin((const AdcLinJob *)(jb + g.o_adclin), g.n_adclin, g.max_adclin_groups, sig_out,
+                          ctx->stream));
+    if (st) HIPCHK(hipEventRecord(ctx->ev[3], ctx->stream));
+    HIPCHK(hipStreamWaitEvent(ctx->stream, ctx->join, 0));
+    if (st) {
+        st->n_passes = g.n_ops;
+        st->n_sweeps = n_sweeps;
+        st->n_emit_only = plan.n_emit_only;
+        st->n_rf_grouped = plan.n_rf_grouped;
+        st->n_adc_grouped = plan.n_adc_grouped;
+        st->n_fallback = plan.n_fallback;
+        st->n_distinct_rf = (int64_t)plan.rf.size();
+        st->n_b1zero = plan.n_b1zero;
+        st->pass_bytes = bytes;
+        st->pass_flops = flops;
+    }
+    return GBS_OK;
+}
+
+static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_init, float *m_out, double *sig_out, bool profile,
                        bool use_surr, gbs_stats *st, int *n_timed) {
     const int64_t K = ctx->K;
     const HostSeq &s = ctx->seq;
@@ -1504,6 +1753,55 @@ static int run_grouped(gbs_ctx *ctx, char *ws, const float *m_init, float *m_out
     HIPCHK(launch_fold((const FoldJob *)(jb + g.o_fold), g.n_fold, g.max_fold_groups, ctx->stream));
     HIPCHK(hipStreamWaitEvent(ctx->stream, ctx->join, 0));  // cleared group sums, map tables
     if (st) HIPCHK(hipEventRecord(ctx->ev[1], ctx->stream));
+
+    // ---- one step per run of the layout, when the members of a run stay alike
+    if (g.runs && !m_init && ws_bytes >= g.run_ws_bytes) {
+        RunYArgs ya{};
+        ya.n_runs = ctx->n_lruns;
+        ya.first4 = ctx->rfirst4.as<int32_t>();
+        ya.y = ctx->yi.as<float>();
+        ya.m0 = ctx->m0i.as<float>();
+        if (ctx->coil_re) {
+            if (!ctx->coil_l_valid) return fail(ctx, GBS_E_STATE, "no group-sorted coil sensitivities (a setter failed)");
+            ya.coil = ctx->coil_l.as<float>();
+            ya.coil_plane = ctx->Kpad;
+        }
+        ya.n_coils = ctx->n_coils;
+        ya.lines = g.lines;
+        ya.out = (float2 *)(ws + g.w_runy);
+        ya.out_coil = g.run_batch * g.lines.n_lines;
+        RunSweepArgs sa{};
+        sa.n_runs = ctx->n_lruns;
+        sa.gx = ctx->rgx.as<int32_t>();
+        sa.gz = ctx->rgz.as<int32_t>();
+        sa.ops = (const RunOp *)(jb + g.o_runop);
+        sa.n_parts = (int32_t)g.run_parts.size();
+        std::copy(g.run_parts.begin(), g.run_parts.end(), sa.parts);
+        sa.n_coils = ctx->n_coils;
+        sa.y = ya.out;
+        sa.n_lines = g.lines.n_lines;
+        sa.y_coil = ya.out_coil;
+        sa.m = (float4 *)(ws + g.w_runm);
+        if (profile) HIPCHK(hipEventRecord(ctx->pev[0], ctx->stream));
+        for (const auto &bt : g.batches) {
+            ya.r0 = sa.r0 = bt.r0 / kRunTile * kRunTile;
+            ya.n = bt.r1 - ya.r0;
+            sa.first = ctx->run_waves.as<int32_t>() + bt.wave0;
+            sa.n_waves = bt.waves;
+            if (plan.n_adc_grouped) HIPCHK(launch_run_y(ya, ctx->stream));
+            HIPCHK(launch_run_sweep(sa, ctx->stream));
+        }
+        if (profile) HIPCHK(hipEventRecord(ctx->pev[1], ctx->stream));
+        *n_timed = profile ? 1 : 0;
+        if (st) HIPCHK(hipEventRecord(ctx->ev[2], ctx->stream));
+        HIPCHK(hipEventRecord(ctx->fork, ctx->stream));
+        HIPCHK(hipStreamWaitEvent(ctx->side, ctx->fork, 0));
+        HIPCHK(launch_run_state(RunStateArgs{K, ctx->run_of.as<int32_t>(), ctx->ph.m0, ctx->ph.y, g.final_cy, sa.m, m_out,
+                                             m_out + K, m_out + 2 * K},
+                                ctx->side));
+        HIPCHK(hipEventRecord(ctx->join, ctx->side));
+        return finish_grouped(ctx, jb, sig_out, st, (int64_t)g.batches.size(), g.run_bytes, g.run_flops);
+    }
 
     // ---- sweeps of grouped ops (plain stepping between them) ----------------
     float *mx = (float *)(ws + g.w_state), *my = mx + ctx->Kpad, *mz = my + ctx->Kpad;
@@ -1598,26 +1896,7 @@ static int run_grouped(gbs_ctx *ctx, char *ws, const float *m_init, float *m_out
                                     ctx->side));
     HIPCHK(hipEventRecord(ctx->join, ctx->side));
 
-    // ---- ADC samples from the group sums (Eq. 8, Eq. 10) --------------------
-    HIPCHK(launch_adc_eval((const AdcJobDev *)(jb + g.o_adc), g.n_adc, g.max_adc_groups, g.max_adc_samples,
-                           sig_out, ctx->stream));
-    HIPCHK(launch_adc_lin((const AdcLinJob *)(jb + g.o_adclin), g.n_adclin, g.max_adclin_groups, sig_out,
-                          ctx->stream));
-    if (st) HIPCHK(hipEventRecord(ctx->ev[3], ctx->stream));
-    HIPCHK(hipStreamWaitEvent(ctx->stream, ctx->join, 0));
-    if (st) {
-        st->n_passes = g.n_ops;
-        st->n_sweeps = (int64_t)g.segs.size();
-        st->n_emit_only = plan.n_emit_only;
-        st->n_rf_grouped = plan.n_rf_grouped;
-        st->n_adc_grouped = plan.n_adc_grouped;
-        st->n_fallback = plan.n_fallback;
-        st->n_distinct_rf = (int64_t)plan.rf.size();
-        st->n_b1zero = plan.n_b1zero;
-        st->pass_bytes = bytes;
-        st->pass_flops = flops;
-    }
-    return GBS_OK;
+    return finish_grouped(ctx, jb, sig_out, st, (int64_t)g.segs.size(), bytes, flops);
 }
 
 // The conventional accelerated method (Sec. 2.2): per-isochromat combined
@@ -1885,7 +2164,9 @@ static int refresh_plans(gbs_ctx *ctx) {
 
 // Workspace bytes of `mode` for the current schedules (0 if the mode needs
 // none); -1 with the message set when the mode cannot run yet.
-static int workspace_bytes(gbs_ctx *ctx, int mode, size_t *bytes) {
+// For GBS_GROUPED *least is what the sweeps over the isochromats need; the
+// per-run form takes the larger *bytes.
+static int workspace_bytes(gbs_ctx *ctx, int mode, size_t *bytes, size_t *least) {
     if (!ctx->has_ph) return fail(ctx, GBS_E_STATE, "no phantom (gbs_set_phantom)");
     if (!ctx->has_seq) return fail(ctx, GBS_E_STATE, "no sequence (gbs_set_sequence)");
     if (mode != GBS_PLAIN && mode != GBS_GROUPED && mode != GBS_CACHED)
@@ -1901,20 +2182,32 @@ static int workspace_bytes(gbs_ctx *ctx, int mode, size_t *bytes) {
     } else {
         if (!ctx->groups_valid) return fail(ctx, GBS_E_STATE, "GBS_GROUPED needs gbs_build_groups on the current phantom");
         if (!ctx->gp.valid) return fail(ctx, GBS_E_STATE, "no grouped schedule (a setter failed)");
-        *bytes = ctx->gp.ws_bytes;
+        *bytes = std::max(ctx->gp.ws_bytes, ctx->gp.run_ws_bytes);
     }
+    *least = mode == GBS_GROUPED ? ctx->gp.ws_bytes : *bytes;
     return GBS_OK;
+}
+
+int gbs::ctx_least_workspace(gbs_ctx *ctx, int mode, size_t *bytes) {
+    size_t full = 0;
+    return workspace_bytes(ctx, mode, &full, bytes);
 }
 
 extern "C" int gbs_workspace_size(gbs_ctx *ctx, int mode, size_t *bytes) {
     if (!ctx) return GBS_E_INVALID;
     if (!bytes) return fail(ctx, GBS_E_INVALID, "null bytes");
     *bytes = 0;
-    return workspace_bytes(ctx, mode, bytes);
+    size_t least = 0;
+    return workspace_bytes(ctx, mode, bytes, &least);
 }
 
 extern "C" int gbs_simulate(gbs_ctx *ctx, int mode, uint32_t flags, void *workspace, size_t ws_bytes,
                             const float *m_init, float *m_out, double *sig_out, gbs_stats *stats) {
+    return gbs::simulate_in(ctx, mode, flags, workspace, ws_bytes, false, m_init, m_out, sig_out, stats);
+}
+
+int gbs::simulate_in(gbs_ctx *ctx, int mode, uint32_t flags, void *workspace, size_t ws_bytes, bool least,
+                     const float *m_init, float *m_out, double *sig_out, gbs_stats *stats) {
     if (!ctx) return GBS_E_INVALID;
     if (!ctx->has_ph) return fail(ctx, GBS_E_STATE, "gbs_simulate before gbs_set_phantom");
     if (!ctx->has_seq) return fail(ctx, GBS_E_STATE, "gbs_simulate before gbs_set_sequence");
@@ -1928,8 +2221,9 @@ extern "C" int gbs_simulate(gbs_ctx *ctx, int mode, uint32_t flags, void *worksp
     const bool use_surr = (flags & GBS_SURROGATE) != 0;
     if (use_surr && (mode == GBS_PLAIN || !ctx->mlp))
         return fail(ctx, GBS_E_INVALID, "GBS_SURROGATE needs GBS_GROUPED or GBS_CACHED and gbs_set_surrogate");
-    size_t need = 0;
-    if (int rc = workspace_bytes(ctx, mode, &need)) return rc;
+    size_t need = 0, need_least = 0;
+    if (int rc = workspace_bytes(ctx, mode, &need, &need_least)) return rc;
+    if (least) need = need_least;
     if (!workspace || ws_bytes < need)
         return fail(ctx, GBS_E_WORKSPACE, "workspace of " + std::to_string(workspace ? ws_bytes : 0) +
                                               " bytes; this mode needs " + std::to_string(need) +
@@ -1948,7 +2242,7 @@ extern "C" int gbs_simulate(gbs_ctx *ctx, int mode, uint32_t flags, void *worksp
     int n_timed = 0;
     int rc = mode == GBS_PLAIN ? run_plain(ctx, ws, m_init, m_out, sig_out, stats)
              : mode == GBS_CACHED ? run_cached(ctx, ws, m_init, m_out, sig_out, profile, use_surr, stats, &n_timed)
-                                  : run_grouped(ctx, ws, m_init, m_out, sig_out, profile, use_surr, stats, &n_timed);
+                                  : run_grouped(ctx, ws, ws_bytes, m_init, m_out, sig_out, profile, use_surr, stats, &n_timed);
     if (rc != GBS_OK) return rc;
     if (stats) HIPCHK(hipEventRecord(ctx->ev[4], ctx->stream));
     if (!(flags & GBS_ASYNC) || stats || profile) {

@@ -24,6 +24,7 @@
 #include "device_math.hpp"
 #include "kernels.hpp"
 #include "rotation.hpp"
+#include "sweep_math.hpp"
 
 namespace gbs {
 
@@ -293,64 +294,7 @@ static inline unsigned xcd_grid(int64_t blocks) {
 #endif
 constexpr int kSweepMaxCoils = 8;  // receive coils one sweep launch weights (gbs_set_coils' limit)
 
-__device__ __forceinline__ void cmul(float &ar, float &ai, float br, float bi) {
-    const float r = ar * br - ai * bi;
-    ai = ar * bi + ai * br;
-    ar = r;
-}
-
-__device__ __forceinline__ void ld4(const float4 *p, int64_t i, float v[4]) {
-    const float4 t = p[i];
-    v[0] = t.x;
-    v[1] = t.y;
-    v[2] = t.z;
-    v[3] = t.w;
-}
-__device__ __forceinline__ void ld4i(const int4 *p, int64_t i, int v[4]) {
-    const int4 t = p[i];
-    v[0] = t.x;
-    v[1] = t.y;
-    v[2] = t.z;
-    v[3] = t.w;
-}
-
-// Table gathers and group-sum atomics through the global address space (the
-// pointers come out of op descriptors and would otherwise be flat accesses).
-typedef const __attribute__((address_space(1))) float *global_f32_ptr;
-__device__ __forceinline__ float4 gather_row(const float4 *tab, int g) {
-    global_f32_ptr p = (global_f32_ptr)(tab + g);
-    return make_float4(p[0], p[1], p[2], p[3]);
-}
-__device__ __forceinline__ float2 gather_row(const float2 *tab, int g) {
-    global_f32_ptr p = (global_f32_ptr)(tab + g);
-    return make_float2(p[0], p[1]);
-}
-__device__ __forceinline__ void group_add(double *p, double v) {
-    __builtin_amdgcn_global_atomic_fadd_f64((__attribute__((address_space(1))) double *)p, v);
-}
-
-// Wave-uniform read of a table that no kernel writes while it runs: through
-// the constant address space, so a uniform index becomes one scalar load.
-typedef const __attribute__((address_space(4))) float *const_f32_ptr;
-__device__ __forceinline__ float4 uniform_row(const float4 *tab, int g) {
-    const_f32_ptr p = (const_f32_ptr)(tab + g);
-    return make_float4(p[0], p[1], p[2], p[3]);
-}
-
-typedef const __attribute__((address_space(4))) uint64_t *const_u64_ptr;
-static_assert(sizeof(SweepOp) % 8 == 0, "SweepOp is read as 64-bit words");
-
-// The op descriptor is the same for every lane: read it through the constant
-// address space so that it arrives in scalar registers.
-__device__ __forceinline__ SweepOp load_op(const SweepOp *ops, int o) {
-    uint64_t w[sizeof(SweepOp) / 8];
-    const_u64_ptr p = (const_u64_ptr)(ops + o);
-#pragma unroll
-    for (int i = 0; i < (int)(sizeof(SweepOp) / 8); ++i) w[i] = p[i];
-    SweepOp r;
-    __builtin_memcpy(&r, w, sizeof(SweepOp));
-    return r;
-}
+__device__ __forceinline__ SweepOp load_op(const SweepOp *ops, int o) { return load_desc(ops, o); }
 
 // x-group row: one scalar load when the wavefront sits inside one x-group.
 __device__ __forceinline__ float4 x_row(const float4 *tab, bool gx_uni, int gx0, int gx) {
@@ -440,26 +384,6 @@ __device__ __forceinline__ void emit_thread_part(int key, bool uni, float vr, fl
 }
 
 
-// v = v * a + b, the result in v's own register.  The compiler's accumulating
-// FMA form would land it in b's register instead, and the state then needs a
-// copy back on every pass of the op loop.
-__device__ __forceinline__ void fma_inplace(float &v, float a, float b) {
-    asm("v_fma_f32 %0, %0, %1, %2" : "+v"(v) : "v"(a), "v"(b));
-}
-
-// v = v * a - b in v's own register.
-__device__ __forceinline__ void fms_inplace(float &v, float a, float b) {
-    asm("v_fma_f32 %0, %0, %1, -%2" : "+v"(v) : "v"(a), "v"(b));
-}
-
-// (ar + i ai) <- (ar + i ai)(br + i bi) with the results in ar's and ai's own
-// registers, so that a value the loop carries needs no copy.
-__device__ __forceinline__ void cmul_inplace(float &ar, float &ai, float br, float bi) {
-    const float t = ai * bi, u = ar * bi;
-    fma_inplace(ai, br, u);
-    fms_inplace(ar, br, t);
-}
-
 // M <- T (M, m0) for one isochromat.  Each output's partial sum leaves out
 // the diagonal term, so that the last step updates the component in place
 // and no copies of the state are needed.
@@ -471,26 +395,6 @@ __device__ __forceinline__ void rf_apply(const float4 &r0, const float4 &r1, con
     fma_inplace(mx, r0.x, px);
     fma_inplace(my, r1.y, py);
     fma_inplace(mz, r2.z, pz);
-}
-
-// rf_apply on the state divided by M0 (see sweep_body): the affine part b
-// adds as it is.
-__device__ __forceinline__ void rf_apply_ratio(const float4 &r0, const float4 &r1, const float4 &r2, float &mx,
-                                               float &my, float &mz) {
-    const float px = fmaf(r0.y, my, fmaf(r0.z, mz, r0.w));
-    const float py = fmaf(r1.x, mx, fmaf(r1.z, mz, r1.w));
-    const float pz = fmaf(r2.x, mx, fmaf(r2.y, my, r2.w));
-    fma_inplace(mx, r0.x, px);
-    fma_inplace(my, r1.y, py);
-    fma_inplace(mz, r2.z, pz);
-}
-
-// Row of T applied after the transverse factor f = fr + i fi: the row acting
-// on (f (mx + i my)) equals the folded row acting on (mx + i my).
-__device__ __forceinline__ void fold_row(float4 &r, float fr, float fi) {
-    const float t = r.y * fi, u = r.x * fi;
-    fma_inplace(r.x, fr, t);
-    fms_inplace(r.y, fr, u);
 }
 
 // Real and imaginary parts of sum_c (mx_c + i my_c)(wr_c + i wi_c) as two

@@ -4,7 +4,8 @@
 // exact bit pattern with -0 folded onto +0.  Keys are made order-preserving
 // 32-bit words, packed as two 64-bit halves and sorted with two stable LSD
 // radix passes (low half, then high half), carrying the isochromat index.
-// Equal neighbours share a group id; ids are dense in lexicographic key order.
+// Equal neighbours share a group id; ids are dense in lexicographic key order
+// (z groups: of the key (T1, T2, dB0, z)).
 #include <rocprim/device/device_radix_sort.hpp>
 #include <rocprim/device/device_scan.hpp>
 
@@ -32,12 +33,12 @@ __device__ __forceinline__ uint32_t ordered_bits(float f) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-__global__ void k_keys(int64_t K, const float *__restrict__ c, const float *__restrict__ t1,
-                       const float *__restrict__ t2, const float *__restrict__ df, uint64_t *hi,
+__global__ void k_keys(int64_t K, const float *__restrict__ a, const float *__restrict__ b,
+                       const float *__restrict__ c, const float *__restrict__ d, uint64_t *hi,
                        uint64_t *lo, int32_t *idx) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < K; i += (int64_t)gridDim.x * blockDim.x) {
-        hi[i] = ((uint64_t)ordered_bits(c[i]) << 32) | ordered_bits(t1[i]);
-        lo[i] = ((uint64_t)ordered_bits(t2[i]) << 32) | ordered_bits(df[i]);
+        hi[i] = ((uint64_t)ordered_bits(a[i]) << 32) | ordered_bits(b[i]);
+        lo[i] = ((uint64_t)ordered_bits(c[i]) << 32) | ordered_bits(d[i]);
         idx[i] = (int32_t)i;
     }
 }
@@ -275,6 +276,94 @@ hipError_t build_layout(int64_t K, const int32_t *gid_x, const int32_t *gid_z, v
     return hipSuccess;
 }
 
+// ---- runs of the layout -------------------------------------------------------
+__global__ void k_run_ids(int64_t n4, int32_t *__restrict__ ids, const int32_t *__restrict__ gid_x,
+                          const int32_t *__restrict__ gid_z, int32_t *__restrict__ first4, int32_t *__restrict__ gx,
+                          int32_t *__restrict__ gz) {
+    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n4; q += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t r = ids[q];  // inclusive scan of the run starts, 1-based
+        const int32_t x = gid_x[4 * q], z = gid_z[4 * q];
+        if (q == 0 || x != gid_x[4 * q - 4] || z != gid_z[4 * q - 4]) {
+            first4[r - 1] = (int32_t)q;
+            gx[r - 1] = x;
+            gz[r - 1] = z;
+        }
+        if (q == n4 - 1) first4[r] = (int32_t)n4;
+    }
+}
+
+// xrun[g] <- first run of x-group g, xrun[G] <- the number of runs
+__global__ void k_group_runs(int64_t n_runs, const int32_t *__restrict__ gx, int64_t n_groups,
+                             int32_t *__restrict__ xrun) {
+    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r <= n_runs; r += (int64_t)gridDim.x * blockDim.x) {
+        if (r == n_runs)
+            xrun[n_groups] = (int32_t)n_runs;
+        else if (r == 0 || gx[r - 1] != gx[r])
+            xrun[gx[r]] = (int32_t)r;
+    }
+}
+
+__global__ void k_run_starts(int64_t n4, const int32_t *__restrict__ gid_x, const int32_t *__restrict__ gid_z,
+                             int32_t *__restrict__ flag) {
+    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n4; q += (int64_t)gridDim.x * blockDim.x)
+        flag[q] = q == 0 || gid_x[4 * q] != gid_x[4 * q - 4] || gid_z[4 * q] != gid_z[4 * q - 4];
+}
+
+// run of isochromat k (caller's order) and, per quad, the 0-based run
+__global__ void k_run_of(int64_t K, const int32_t *__restrict__ inv, const int32_t *__restrict__ ids,
+                         int32_t *__restrict__ run) {
+    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < K; k += (int64_t)gridDim.x * blockDim.x)
+        run[k] = ids[inv[k] >> 2] - 1;
+}
+
+__global__ void k_minus_one(int64_t n, int32_t *v) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        v[i] -= 1;
+}
+
+// Numbers the runs of equal (x-group, z-group) of the layout's n4 quads in
+// layout order: run_of4[q], and the run of every isochromat of the caller's
+// order; the count through *n_runs (synchronizes the stream).  scratch: room
+// for n4 int32 and the scan's temporary memory.
+hipError_t number_runs(int64_t n4, int64_t K, const int32_t *gid_x, const int32_t *gid_z, const int32_t *inv,
+                       void *scratch, size_t scratch_bytes, int32_t *run_of4, int32_t *run, int64_t *n_runs,
+                       hipStream_t st) {
+    int32_t *flag = (int32_t *)scratch;
+    const size_t used = (4 * (size_t)n4 + 255) & ~(size_t)255;
+    if (used > scratch_bytes) return hipErrorInvalidValue;
+    size_t tmp_bytes = 0;
+    hipError_t e = inclusive_sum(nullptr, &tmp_bytes, nullptr, nullptr, n4, st);
+    if (e != hipSuccess) return e;
+    if (used + tmp_bytes > scratch_bytes) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_run_starts, grid_for(n4), dim3(256), 0, st, n4, gid_x, gid_z, flag);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = inclusive_sum((char *)scratch + used, &tmp_bytes, flag, run_of4, n4, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_run_of, grid_for(K), dim3(256), 0, st, K, inv, run_of4, run);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    int32_t last = 0;
+    if ((e = hipMemcpyAsync(&last, run_of4 + (n4 - 1), sizeof(int32_t), hipMemcpyDeviceToHost, st)) != hipSuccess)
+        return e;
+    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    *n_runs = last;
+    return hipSuccess;
+}
+
+// first4[r] (and n4 after the last run), x- and z-group of every run from the
+// numbering of number_runs, whose run_of4 becomes 0-based.
+hipError_t launch_run_arrays(int64_t n4, int32_t *run_of4, const int32_t *gid_x, const int32_t *gid_z,
+                             int32_t *first4, int32_t *gx, int32_t *gz, hipStream_t st) {
+    hipLaunchKernelGGL(k_run_ids, grid_for(n4), dim3(256), 0, st, n4, run_of4, gid_x, gid_z, first4, gx, gz);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_minus_one, grid_for(n4), dim3(256), 0, st, n4, run_of4);
+    return hipGetLastError();
+}
+
+hipError_t launch_group_runs(int64_t n_runs, const int32_t *gx, int64_t n_groups, int32_t *xrun, hipStream_t st) {
+    hipLaunchKernelGGL(k_group_runs, grid_for(n_runs + 1), dim3(256), 0, st, n_runs, gx, n_groups, xrun);
+    return hipGetLastError();
+}
+
 __global__ void k_invert(int64_t n, const int32_t *__restrict__ perm, int32_t *__restrict__ inv) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         if (perm[i] >= 0) inv[perm[i]] = (int32_t)i;
@@ -303,12 +392,15 @@ size_t group_scratch_bytes(int64_t K) {
     return 4 * sizeof(uint64_t) * K + 7 * sizeof(int32_t) * K + tmp + 16 * 256;
 }
 
-// Group one axis.  coord = r_a of every isochromat (natural order).  Writes
+// Group one axis, ids in the order of (coord, T1, T2, df) or, with coord_last,
+// (T1, T2, df, coord): the z-groups of one tissue then are neighbours, and so
+// are the transition rows that the runs of an x-group read (one tissue,
+// successive z).  coord = r_a of every isochromat (natural order).  Writes
 // gid_nat[K] (natural order), gtab[n_groups] = (coord, T1, T2, df) and
 // gcount[n_groups] (gtab and gcount need room for K entries), order[K] =
 // isochromat indices sorted by key (stable), and returns the group count
 // through *n_groups (synchronizes the stream).
-hipError_t group_axis(int64_t K, const float *coord, const float *t1, const float *t2, const float *df,
+hipError_t group_axis(int64_t K, bool coord_last, const float *coord, const float *t1, const float *t2, const float *df,
                       void *scratch, size_t scratch_bytes, int32_t *gid_nat, float4 *gtab,
                       int32_t *gcount, int32_t *order, int64_t *n_groups, hipStream_t st) {
     char *p = (char *)scratch;
@@ -326,7 +418,10 @@ hipError_t group_axis(int64_t K, const float *coord, const float *t1, const floa
     size_t tmp_bytes = scratch_bytes - used;
     const dim3 g = grid_for(K);
     hipError_t e;
-    hipLaunchKernelGGL(k_keys, g, dim3(256), 0, st, K, coord, t1, t2, df, hi, lo, idx0);
+    if (coord_last)
+        hipLaunchKernelGGL(k_keys, g, dim3(256), 0, st, K, t1, t2, df, coord, hi, lo, idx0);
+    else
+        hipLaunchKernelGGL(k_keys, g, dim3(256), 0, st, K, coord, t1, t2, df, hi, lo, idx0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // LSD: low half first (carry indices), then the high half of the same records.
     if ((e = sort_pairs(tmp, &tmp_bytes, lo, k2, idx0, idx1, K, st)) != hipSuccess) return e;

@@ -11,12 +11,6 @@
 
 namespace gbs {
 
-__global__ void k_run_flags(int64_t n4, const int32_t *__restrict__ gid_x, const int32_t *__restrict__ gid_z,
-                            uint8_t *__restrict__ flag) {
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n4; q += (int64_t)gridDim.x * blockDim.x)
-        flag[q] = q == 0 || gid_x[4 * q] != gid_x[4 * q - 4] || gid_z[4 * q] != gid_z[4 * q - 4];
-}
-
 __global__ void k_run_table(int64_t n_runs, const int32_t *__restrict__ first, const float *__restrict__ xi,
                             const float *__restrict__ zi, const float *__restrict__ t1i,
                             const float *__restrict__ t2i, const float *__restrict__ dfi, float4 *__restrict__ rtab,
@@ -93,12 +87,6 @@ static dim3 grid_of(int64_t n) {
     if (g > 8192) g = 8192;
     if (g < 1) g = 1;
     return dim3((unsigned)g);
-}
-
-hipError_t launch_run_flags(int64_t n4, const int32_t *gid_x, const int32_t *gid_z, uint8_t *flag, hipStream_t st) {
-    if (n4 <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_run_flags, grid_of(n4), dim3(256), 0, st, n4, gid_x, gid_z, flag);
-    return hipGetLastError();
 }
 
 hipError_t launch_run_table(int64_t n_runs, const int32_t *first, const float *xi, const float *zi,

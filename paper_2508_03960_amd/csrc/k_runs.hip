@@ -1,0 +1,414 @@
+// Grouped simulation per run of the layout on gfx950 (see runs.hpp).
+//
+//  k_run_y      Y_r(c) of every run and y moment c on an even grid, as a matrix
+//               product over the members: a line's phase is the product of one
+//               of 8 a-phases and one of 8 b-phases per 256 lines,
+//                 c = c0 + d (+-(i + 1/2) +- (16 j + 8)),
+//               so per member 16 rows {cos, sin}(a_i y) and 16 columns
+//               {cos, sin}(b_j y), weighted by the real and by the imaginary
+//               part of the member's weight, give all 256 lines (both signs
+//               share the four real products): two v_mfma_f32_16x16x4_f32 per
+//               four members, 4 flops per member and line.
+//  k_run_sweep  all operations of a simulation with one run per lane.
+//  k_run_state  the final state in the caller's order from the runs' ratios.
+#include <algorithm>
+#include <type_traits>
+
+#include "device_math.hpp"
+#include "kernels.hpp"
+#include "runs.hpp"
+#include "sweep_math.hpp"
+
+namespace gbs {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// ---------------------------------------------------------------- k_run_y
+// One workgroup per 16 runs (a row of the Y layout), four runs per wavefront.
+// A wavefront takes a run's members 64 at a time: each lane makes one member's
+// weight (with the phase of c0) and leaves it with the member's y in LDS; then
+// every step of the product reads four members, lane l holding row l % 16 and
+// column l % 16 of member l / 16.  The phases are formed and reduced modulo one
+// turn (v_cos_f32 takes turns; sin is the cos a quarter turn back).
+// What bounds it is the VALU work of the two phases per step, about 90 cycles
+// against 64 of the matrix core.
+struct RunMember {
+    float y, wr, wi, pad;
+};
+
+// A phase coefficient (turns per metre) as two floats: c y mod 1 then takes
+// four FP32 instructions with one rounding of the reduced phase (the FMA of
+// hi y - rint(hi y) is exact up to it), instead of five at FP64.
+struct Coef {
+    float hi, lo;
+};
+__device__ __forceinline__ Coef coef_of(double c) {
+    const float h = (float)c;
+    return Coef{h, (float)(c - (double)h)};
+}
+__device__ __forceinline__ float turns(const Coef &c, float y, float off) {
+    const float e = fmaf(c.hi, y, -rintf(c.hi * y));
+    return e + fmaf(c.lo, y, off);
+}
+
+template <bool COILS>
+__global__ __launch_bounds__(256) void k_run_y(RunYArgs a) {
+    __shared__ RunMember member[4][64];
+    __shared__ float2 tile[kRunLinesSet][kRunTile + 1];  // + 1: the lines of a store fall into different banks
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int set = blockIdx.y % ((a.lines.nb + 7) / 8), coil = blockIdx.y / ((a.lines.nb + 7) / 8);
+    const int i = lane & 15, kq = lane >> 4;
+    const Coef ca = coef_of(((i >> 1) + 0.5) * a.lines.d), cb = coef_of((16 * ((i >> 1) + 8 * set) + 8) * a.lines.d);
+    const Coef c0 = coef_of(a.lines.c0);
+    const float off = (i & 1) ? -0.25f : 0.f;
+    const int64_t tile0 = a.r0 + (int64_t)blockIdx.x * kRunTile;  // first run of the workgroup
+    const int64_t rend = a.r0 + a.n;
+    const int64_t last = 4 * (int64_t)a.first4[a.n_runs] - 1;     // last slot of the layout
+    const float *sre = COILS ? a.coil + 2 * coil * a.coil_plane : nullptr;
+    const float *sim = COILS ? sre + a.coil_plane : nullptr;
+    int64_t slot = 0;
+    float yv = 0.f, mv = 0.f, cr = 1.f, ci = 0.f;
+    auto fetch = [&](int64_t base) {  // members of the next 64 slots (the layout's last slot past its end)
+        slot = base + lane;
+        const int64_t s = slot < last ? slot : last;
+        yv = a.y[s];
+        mv = a.m0[s];
+        if (COILS) {
+            cr = sre[s];
+            ci = sim[s];
+        }
+    };
+    const int64_t rw = tile0 + 4 * wave;  // the wavefront's runs rw .. rw + 3
+    if (rw < rend) fetch(4 * (int64_t)a.first4[rw]);
+    for (int j = 0; j < 4; ++j) {
+        const int64_t r = rw + j;
+        f32x4 dr = {0.f, 0.f, 0.f, 0.f}, di = {0.f, 0.f, 0.f, 0.f};
+        if (r < rend) {
+            const int64_t s1 = 4 * (int64_t)a.first4[r + 1];
+            for (int64_t base = 4 * (int64_t)a.first4[r]; base < s1; base += 64) {
+                const float ph = turns(c0, yv, 0.f);
+                const float s = __builtin_amdgcn_sinf(ph), c = __builtin_amdgcn_cosf(ph);
+                const float wr = slot < s1 ? mv : 0.f;
+                RunMember m;
+                m.y = yv;
+                if (COILS) {  // m0 S(k, p) e^{-i phi}
+                    const float pr = wr * cr, pi = wr * ci;
+                    m.wr = fmaf(pr, c, pi * s);
+                    m.wi = fmaf(pi, c, -pr * s);
+                } else {
+                    m.wr = wr * c;
+                    m.wi = -wr * s;
+                }
+                member[wave][lane] = m;
+                const int64_t left = s1 - base;
+                fetch(left > 64 ? base + 64 : s1);
+                const int steps = left > 64 ? 16 : (int)(left + 3) / 4;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                // (runs are padded to multiples of 8: an even number of steps)
+                for (int t = 0; t < steps; t += 2) {
+                    const RunMember q0 = member[wave][4 * t + kq], q1 = member[wave][4 * t + 4 + kq];
+                    const float ra0 = __builtin_amdgcn_cosf(turns(ca, q0.y, off));
+                    const float rb0 = __builtin_amdgcn_cosf(turns(cb, q0.y, off));
+                    const float ra1 = __builtin_amdgcn_cosf(turns(ca, q1.y, off));
+                    const float rb1 = __builtin_amdgcn_cosf(turns(cb, q1.y, off));
+                    dr = __builtin_amdgcn_mfma_f32_16x16x4f32(ra0, rb0 * q0.wr, dr, 0, 0, 0);
+                    di = __builtin_amdgcn_mfma_f32_16x16x4f32(ra0, rb0 * q0.wi, di, 0, 0, 0);
+                    dr = __builtin_amdgcn_mfma_f32_16x16x4f32(ra1, rb1 * q1.wr, dr, 0, 0, 0);
+                    di = __builtin_amdgcn_mfma_f32_16x16x4f32(ra1, rb1 * q1.wi, di, 0, 0, 0);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            }
+        }
+        // lane (column 2 jb + t, rows 4 kq ..): element v of the tiles is
+        // {cos, sin}(a_{2 kq + v / 2}) times {cos, sin}(b_jb); neighbouring
+        // lanes trade halves, then lane parity picks the a index
+        const bool odd = lane & 1;
+        auto trade = [&](const f32x4 &v, float &cc, float &sc, float &cs, float &ss) {
+            const float g0 = dpp_f32<0xb1>(odd ? v[0] : v[2]), g1 = dpp_f32<0xb1>(odd ? v[1] : v[3]);
+            cc = odd ? g0 : v[0];
+            sc = odd ? g1 : v[1];
+            cs = odd ? v[2] : g0;
+            ss = odd ? v[3] : g1;
+        };
+        float rcc, rsc, rcs, rss, icc, isc, ics, iss;
+        trade(dr, rcc, rsc, rcs, rss);
+        trade(di, icc, isc, ics, iss);
+        const int ia = 2 * kq + (lane & 1), jb = i >> 1;
+        // sum (wr + i wi)(cos t - i sin t), t = sa a + sb b
+        auto put = [&](int line, float sa, float sb) {
+            const float wrc = fmaf(-sa * sb, rss, rcc), wrs = fmaf(sa, rsc, sb * rcs);
+            const float wic = fmaf(-sa * sb, iss, icc), wis = fmaf(sa, isc, sb * ics);
+            tile[line][4 * wave + j] = make_float2(wrc + wis, wic - wrs);
+        };
+        // lines 0 .. 127: -b of the set (descending), 128 .. 255: +b
+        put(128 + 16 * jb + 8 + ia, 1.f, 1.f);
+        put(128 + 16 * jb + 7 - ia, -1.f, 1.f);
+        put(128 - 16 * jb - 8 + ia, 1.f, -1.f);
+        put(128 - 16 * jb - 9 - ia, -1.f, -1.f);
+    }
+    __syncthreads();
+    const int half = 16 * a.lines.nb, n_lines = a.lines.n_lines;
+    float2 *out = a.out + coil * a.out_coil + ((int64_t)blockIdx.x * n_lines) * kRunTile;
+    for (int e = threadIdx.x; e < kRunLinesSet * kRunTile; e += 256) {
+        const int ll = e / kRunTile, rr = e % kRunTile;
+        const int line = ll < 128 ? half - 128 * (set + 1) + ll : half + 128 * set + (ll - 128);
+        if (line >= 0 && line < n_lines) out[(int64_t)line * kRunTile + rr] = tile[ll][rr];
+    }
+}
+
+hipError_t launch_run_y(const RunYArgs &a, hipStream_t st) {
+    if (a.n <= 0) return hipSuccess;
+    if (a.lines.nb < 1 || a.lines.n_lines != 32 * a.lines.nb || a.r0 % kRunTile) return hipErrorInvalidValue;
+    const int64_t tiles = (a.n + kRunTile - 1) / kRunTile;
+    const int64_t gy = (int64_t)((a.lines.nb + 7) / 8) * a.n_coils;
+    if (tiles > 0x7fffffff || gy > 65535) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)tiles, (unsigned)gy);
+    if (a.coil)
+        hipLaunchKernelGGL(k_run_y<true>, grid, dim3(256), 0, st, a);
+    else
+        hipLaunchKernelGGL(k_run_y<false>, grid, dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------- k_run_sweep
+// One run per lane, one wavefront per workgroup.  Every load of an operation
+// depends on its descriptor and the lane's groups alone, and every operation
+// of a part of the list issues the same loads in the same order: so the rows
+// of the next kDepth operations are in flight during this one's arithmetic, and
+// the wait for one operation's rows counts the later loads off instead of
+// draining them (Y comes from HBM, a microsecond or two away).  The group sums
+// of an emission are a segmented scan over the lanes (the runs of an x-group
+// are neighbours): six DPP steps with the lane's masks, made once.  Wavefronts
+// take whole x-groups, so a group's sum is one store; only a group of more than
+// 64 runs adds its parts with atomics to the cleared sum (FP64 atomics of two
+// neighbours per wavefront and emission made the sweep three times slower).
+template <int CTRL>
+__device__ __forceinline__ void seg_add(float mask, float &v) {
+    v = fmaf(__int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true)), mask, v);
+}
+
+template <int MC>
+__global__ __launch_bounds__(64) void k_run_sweep(RunSweepArgs a) {
+    const int lane = threadIdx.x;
+    const int64_t w0 = a.first[blockIdx.x], w1 = a.first[blockIdx.x + 1];
+    const bool act = w0 + lane < w1;
+    const int64_t r = act ? w0 + lane : w1 - 1;
+    const int64_t rl = r - a.r0;
+    const int gx = a.gx[r], gz = a.gz[r];
+    const int key = act ? gx : -1;
+    // masks of the segmented scan
+    auto mask_of = [&](bool has, int src) {
+        const int k = __shfl(key, src & 63);  // (by every lane, also those without a source)
+        return has && k == key ? 1.f : 0.f;
+    };
+    const int row = lane >> 4;
+    const float m1 = mask_of((lane & 15) >= 1, lane - 1), m2 = mask_of((lane & 15) >= 2, lane - 2);
+    const float m4 = mask_of((lane & 15) >= 4, lane - 4), m8 = mask_of((lane & 15) >= 8, lane - 8);
+    const float mb15 = mask_of(row & 1, 16 * row - 1), mb31 = mask_of(row >= 2, 31);
+    const int knext = __shfl_down(key, 1);
+    const bool end = act && (lane == 63 || knext != key);
+    // does the x-group go on before or after the wavefront's runs?
+    const bool own = key != (w0 > 0 ? a.gx[w0 - 1] : -1) && key != (w1 < a.n_runs ? a.gx[w1] : -1);
+    // byte offsets (32 bits: checked at the launch); lanes of a wavefront lie in
+    // at most five tiles of Y from its first one on
+    const int64_t t0 = (w0 - a.r0) / kRunTile;
+    const float2 *yb = a.y + t0 * (int64_t)a.n_lines * kRunTile;
+    const uint32_t oy = (uint32_t)(8 * ((rl / kRunTile - t0) * (int64_t)a.n_lines * kRunTile + rl % kRunTile));
+    const uint32_t ox = 16u * (uint32_t)gx, oz = 8u * (uint32_t)gz;
+    const uint32_t otx = 48u * (uint32_t)gx, otz = 48u * (uint32_t)gz, otr = 48u * (uint32_t)r;
+
+    const int n_coils = a.n_coils;
+    const int64_t y_coil = a.y_coil;
+    struct Meta {  // of an operation whose rows are in flight
+        int flags, stride;
+        double2 *gsum;
+    };
+    struct Rows {
+        float4 px, t0, t1, t2;
+        float2 pz, ex, ez, y[MC];
+    };
+    auto fetch_emit = [&](const RunOp &op, Rows &d) {
+        d.ex = gather_at((const float2 *)op.emit_xtab, (op.flags & kOpEmit) ? ox : 0u);
+        d.ez = gather_at(op.emit_ztab, (op.flags & kRunEmitZ) ? oz : 0u);
+#pragma unroll
+        for (int p = 0; p < MC; ++p)
+            d.y[p] = gather_at(yb + min(p, n_coils - 1) * y_coil + op.line * kRunTile, oy);
+    };
+    auto fetch_full = [&](const RunOp &op, Rows &d) {
+        d.px = gather_at(op.pre_xtab, (op.flags & kRunPreX) ? ox : 0u);
+        d.pz = gather_at(op.pre_ztab, (op.flags & kRunPreZ) ? oz : 0u);
+        // (the asm makes them values: a choice between the captured variables
+        // themselves would go through memory)
+        uint32_t o0 = otx, o2 = otz, o3 = otr;
+        asm("" : "+v"(o0), "+v"(o2), "+v"(o3));
+        uint32_t ot = op.rf_axis == 0 ? o0 : op.rf_axis == 2 ? o2 : o3;
+        ot = (op.flags & kRunRows) ? ot : 0u;
+        d.t0 = gather_at(op.ttab, ot);
+        d.t1 = gather_at(op.ttab + 1, ot);
+        d.t2 = gather_at(op.ttab + 2, ot);
+        fetch_emit(op, d);
+    };
+    float mx = 0.f, my = 0.f, mz = 1.f;  // M / M0
+    auto emit = [&](const Meta &op, const Rows &d) {
+        float er = d.ex.x, ei = d.ex.y;
+        cmul(er, ei, d.ez.x, d.ez.y);
+        cmul(er, ei, mx, my);
+        if (!act) er = ei = 0.f;
+#pragma unroll
+        for (int p = 0; p < MC; ++p) {
+            if (p >= n_coils) break;
+            float sr = er, si = ei;
+            cmul(sr, si, d.y[p].x, d.y[p].y);
+            seg_add<0x111>(m1, sr);
+            seg_add<0x111>(m1, si);
+            seg_add<0x112>(m2, sr);
+            seg_add<0x112>(m2, si);
+            seg_add<0x114>(m4, sr);
+            seg_add<0x114>(m4, si);
+            seg_add<0x118>(m8, sr);
+            seg_add<0x118>(m8, si);
+            seg_add<0x142>(mb15, sr);
+            seg_add<0x142>(mb15, si);
+            seg_add<0x143>(mb31, sr);
+            seg_add<0x143>(mb31, si);
+            if (end) {
+                double2 *g = op.gsum + (int64_t)p * op.stride + gx;
+                if (own) {
+                    store_pair(g, (double)sr, (double)si);
+                } else {
+                    group_add(&g->x, (double)sr);
+                    group_add(&g->y, (double)si);
+                }
+            }
+        }
+    };
+    auto full = [&](const Meta &op, const Rows &d) {
+        float fr = d.px.x, fi = d.px.y;
+        cmul(fr, fi, d.pz.x, d.pz.y);
+        cmul(mx, my, fr, fi);
+        if (op.flags & kPreMz) mz = fmaf(d.px.z, mz - 1.f, 1.f);
+        if (op.flags & kOpRf) {
+            const float nx = fmaf(d.t0.x, mx, fmaf(d.t0.y, my, fmaf(d.t0.z, mz, d.t0.w)));
+            const float ny = fmaf(d.t1.x, mx, fmaf(d.t1.y, my, fmaf(d.t1.z, mz, d.t1.w)));
+            const float nz = fmaf(d.t2.x, mx, fmaf(d.t2.y, my, fmaf(d.t2.z, mz, d.t2.w)));
+            mx = nx;
+            my = ny;
+            mz = nz;
+        }
+        if (op.flags & kOpEmit) emit(op, d);
+    };
+    // Rows d[k] belong to operation o + k: used, then filled again kDepth ahead
+    // (a copy of a register that a load still fills would wait for it).
+    auto walk = [&](auto depth, const RunPart &part, auto fetch, auto apply) {
+        constexpr int kDepth = decltype(depth)::value;
+        const RunOp *ops = a.ops + part.first;
+        const int n = part.n;
+        Meta meta[kDepth];
+        Rows d[kDepth];
+#pragma unroll
+        for (int k = 0; k < kDepth; ++k) {
+            const RunOp op = load_desc(ops, min(k, n - 1));
+            meta[k] = Meta{op.flags, op.gsum_stride, op.gsum};
+            fetch(op, d[k]);
+        }
+        int o = 0;
+        for (; o + kDepth <= n; o += kDepth) {
+#pragma unroll
+            for (int k = 0; k < kDepth; ++k) {
+                const RunOp op = load_desc(ops, min(o + k + kDepth, n - 1));
+                apply(meta[k], d[k]);
+                meta[k] = Meta{op.flags, op.gsum_stride, op.gsum};
+                fetch(op, d[k]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kDepth - 1; ++k)
+            if (o + k < n) apply(meta[k], d[k]);
+    };
+    for (int q = 0; q < a.n_parts; ++q) {
+        const RunPart part = a.parts[q];
+        if (part.emit_only)
+            walk(std::integral_constant<int, MC == 1 ? 8 : 4>{}, part, fetch_emit, emit);
+        else
+            walk(std::integral_constant<int, MC == 1 ? 4 : 2>{}, part, fetch_full, full);
+    }
+    if (act) a.m[r] = make_float4(mx, my, mz, 0.f);
+}
+
+hipError_t launch_run_sweep(const RunSweepArgs &a, hipStream_t st) {
+    if (a.n_waves <= 0) return hipSuccess;
+    if (a.n_parts < 1 || a.n_parts > kRunMaxParts || a.n_coils < 1 || a.n_coils > 8 || a.r0 % kRunTile) return hipErrorInvalidValue;
+    if (a.n_runs > kRunMaxRuns || a.n_lines > (1 << 20)) return hipErrorInvalidValue;  // 32-bit byte offsets
+    const int32_t blocks = a.n_waves;
+    if (a.n_coils == 1)
+        hipLaunchKernelGGL(k_run_sweep<1>, dim3((unsigned)blocks), dim3(64), 0, st, a);
+    else if (a.n_coils <= 4)
+        hipLaunchKernelGGL(k_run_sweep<4>, dim3((unsigned)blocks), dim3(64), 0, st, a);
+    else
+        hipLaunchKernelGGL(k_run_sweep<8>, dim3((unsigned)blocks), dim3(64), 0, st, a);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------- k_run_state
+// One read of M0, the run index and the run's ratio (16 bytes, in L2) and one
+// write of M per isochromat: 20 bytes of memory traffic.  V = 4: four
+// isochromats per thread with 16-byte accesses.  A workgroup takes neighbouring
+// tiles: grid rows of a volume that lie next to each other mostly read the
+// same runs, which are then in the CU's own cache.
+template <int V>
+__global__ __launch_bounds__(256) void k_run_state(RunStateArgs a, int64_t n, int rounds) {
+  for (int it = 0; it < rounds; ++it) {
+    const int64_t q = ((int64_t)blockIdx.x * rounds + it) * 256 + threadIdx.x;
+    if (q >= n) return;
+    int run[V];
+    float m0[V], yv[V], o[3][V];
+    if (V == 4) {
+        ld4i((const int4 *)a.run, q, run);
+        ld4((const float4 *)a.m0, q, m0);
+        if (a.cy != 0.0) ld4((const float4 *)a.y, q, yv);
+    } else {
+        run[0] = a.run[q];
+        m0[0] = a.m0[q];
+        if (a.cy != 0.0) yv[0] = a.y[q];
+    }
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+        const float4 m = gather_row(a.m, run[c]);
+        float mx = m.x, my = m.y;
+        if (a.cy != 0.0) {
+            float s, co;
+            sincos_rev(a.cy * (double)yv[c], &s, &co);
+            cmul(mx, my, co, -s);
+        }
+        o[0][c] = mx * m0[c];
+        o[1][c] = my * m0[c];
+        o[2][c] = m.z * m0[c];
+    }
+    float *out[3] = {a.ox, a.oy, a.oz};
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        if (V == 4)
+            ((float4 *)out[p])[q] = make_float4(o[p][0], o[p][1], o[p][2], o[p][3]);
+        else
+            out[p][q] = o[p][0];
+    }
+  }
+}
+
+hipError_t launch_run_state(const RunStateArgs &a, hipStream_t st) {
+    // ox, oy, oz are K floats apart
+    const bool by4 = a.K % 4 == 0 && ((uintptr_t)a.ox | (uintptr_t)a.m0 | (uintptr_t)a.y | (uintptr_t)a.run) % 16 == 0;
+    const int64_t n = by4 ? a.K / 4 : a.K, tiles = (n + 255) / 256;
+    if (tiles == 0) return hipSuccess;
+    // up to 8 tiles per workgroup where enough workgroups remain
+    const int rounds = (int)std::max<int64_t>(1, std::min<int64_t>(8, tiles / 2048));
+    const int64_t blocks = (tiles + rounds - 1) / rounds;
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    if (by4)
+        hipLaunchKernelGGL(k_run_state<4>, dim3((unsigned)blocks), dim3(256), 0, st, a, n, rounds);
+    else
+        hipLaunchKernelGGL(k_run_state<1>, dim3((unsigned)blocks), dim3(256), 0, st, a, n, rounds);
+    return hipGetLastError();
+}
+
+}  // namespace gbs

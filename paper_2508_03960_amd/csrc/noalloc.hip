@@ -57,11 +57,11 @@ extern "C" int gbs_simulate_static(gbs_ctx *ctx, int mode, uint32_t flags, const
     }
     if (!ws) return gbs::ctx_fail(ctx, GBS_E_HIP, "static scratch of this device was not set up");
     size_t need = 0;
-    if (int rc = gbs_workspace_size(ctx, mode, &need)) return rc;
+    if (int rc = gbs::ctx_least_workspace(ctx, mode, &need)) return rc;
     if (need > kStaticScratchBytes) {
         const std::string msg = "this call needs " + std::to_string(need) + " bytes of workspace; the static scratch "
                                 "holds " + std::to_string(kStaticScratchBytes) + " (use gbs_simulate)";
         return gbs::ctx_fail(ctx, GBS_E_WORKSPACE, msg.c_str());
     }
-    return gbs_simulate(ctx, mode, flags, ws, kStaticScratchBytes, m_init, m_out, sig_out, stats);
+    return gbs::simulate_in(ctx, mode, flags, ws, kStaticScratchBytes, true, m_init, m_out, sig_out, stats);
 }

@@ -11,8 +11,6 @@
 
 namespace gbs {
 
-// flag[q] = 1 where 4-slot quad q starts a run of equal (gid_x, gid_z), q < n4
-hipError_t launch_run_flags(int64_t n4, const int32_t *gid_x, const int32_t *gid_z, uint8_t *flag, hipStream_t st);
 // Per run r (first quad first[r]): rtab = (x, T1, T2, dB0 in Hz), rz = z, from the layout arrays
 hipError_t launch_run_table(int64_t n_runs, const int32_t *first, const float *xi, const float *zi,
                             const float *t1i, const float *t2i, const float *dfi, float4 *rtab, float *rz,
