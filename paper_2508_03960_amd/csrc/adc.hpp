@@ -18,6 +18,36 @@ struct AdcLinJob {
     int64_t sig_offset;
 };
 
+// The readouts of equal sample times, moments and groups (the echoes and shots
+// of a repeated timing, and the coils) as one matrix product: rows are
+// readouts, the inner dimension their groups, columns the samples.
+struct AdcClass {
+    double tau0, dtau, cyc0, dcyc;  // as AdcLinJob
+    const float4 *gtab;
+    int32_t n_groups, n_samples;
+    int32_t split;    // groups per workgroup, a multiple of kAdcMmSub up to kAdcMmSplit
+    int32_t n_split;  // ceil(n_groups / split)
+};
+struct AdcRow {
+    const double2 *gsum;
+    int64_t sig_offset;
+    int64_t part;  // first entry of the row in a split's partial sums
+    int32_t cls, pad;
+};
+struct AdcTile {  // rows [row, row + n_rows) of one class, samples from n0 on
+    int32_t cls, row, n_rows, n0;
+};
+constexpr int kAdcMmRows = 64;    // rows per workgroup
+constexpr int kAdcMmCols = 128;   // samples per workgroup
+constexpr int kAdcMmSub = 32;     // groups staged at a time
+constexpr int kAdcMmSplit = 224;  // most groups whose terms add in FP32 (as in k_adc_lin: 28 per thread, 8 threads)
+constexpr int kAdcMmMinRows = 4;
+
+// part[split * part_stride + row.part + n] <- the partial sums (FP32), then
+// sig += their FP64 sums
+hipError_t launch_adc_mm(const AdcClass *cls, const AdcRow *rows, const AdcTile *tiles, int n_tiles, int max_split,
+                         int n_rows, int max_samples, float2 *part, int64_t part_stride, double *sig, hipStream_t st);
+
 hipError_t launch_adc_lin(const AdcLinJob *jobs, int n_jobs, int max_groups, double *sig, hipStream_t st);
 
 }  // namespace gbs

@@ -16,6 +16,7 @@
 #include <array>
 #include <cmath>
 #include <cstring>
+#include <map>
 #include <string>
 #include <unordered_set>
 #include <vector>
@@ -145,6 +146,12 @@ struct GroupedPlan {
     int surr_n_check = 0;
     size_t o_rf_surr = 0;
     size_t s_tuples = 0, s_T32 = 0, s_exact = 0, s_res = 0, s_fb = 0;
+    // readouts of equal timing as matrix products (AdcClass); the readouts of
+    // lin_rest are not in one.  Used when the workspace reaches adc_end.
+    std::vector<AdcLinJob> lin_rest;
+    int n_adccls = 0, n_adcrow = 0, n_adctile = 0, adc_max_split = 0, adc_max_ns = 0, max_adcrest_groups = 0;
+    size_t o_adccls = 0, o_adcrow = 0, o_adctile = 0, o_adcrest = 0, w_adcpart = 0, adc_end = 0;
+    int64_t adc_stride = 0;
     // per-run form of the whole simulation (runs.hpp), for calls that start
     // from (0, 0, M0): batches of runs whose Y fits the workspace
     bool runs = false;
@@ -1266,6 +1273,69 @@ static int build_grouped_plan(gbs_ctx *ctx) {
         }
     }
 
+    // readouts of equal timing: classes with enough rows become matrix products
+    std::vector<AdcClass> acls;
+    std::vector<AdcRow> arow;
+    std::vector<AdcTile> atile;
+    {
+        std::vector<int> cls_of(lj.size(), -1);
+        std::vector<std::pair<AdcLinJob, int>> timing;  // first readout, count
+        std::map<std::array<uint64_t, 7>, int> seen;
+        for (size_t i = 0; i < lj.size(); ++i) {
+            const AdcLinJob &j = lj[i];
+            std::array<uint64_t, 7> key{};
+            const double v[4] = {j.tau0, j.dtau, j.cyc0, j.dcyc};
+            std::memcpy(key.data(), v, sizeof(v));
+            key[4] = (uint64_t)j.n_samples;
+            key[5] = (uint64_t)j.n_groups;
+            key[6] = (uint64_t)(uintptr_t)j.gtab;
+            const auto it = seen.emplace(key, (int)timing.size());
+            if (it.second) timing.emplace_back(j, 0);
+            cls_of[i] = it.first->second;
+            ++timing[(size_t)cls_of[i]].second;
+        }
+        std::vector<std::vector<size_t>> members(timing.size());
+        for (size_t i = 0; i < lj.size(); ++i) members[(size_t)cls_of[i]].push_back(i);
+        int64_t off = 0;
+        for (size_t c = 0; c < timing.size(); ++c) {
+            const AdcLinJob &j = timing[c].first;
+            const int n_rows = timing[c].second;
+            if (n_rows < kAdcMmMinRows) {
+                for (size_t i : members[c]) {
+                    g.lin_rest.push_back(lj[i]);
+                    g.max_adcrest_groups = std::max(g.max_adcrest_groups, lj[i].n_groups);
+                }
+                continue;
+            }
+            const int64_t tiles = (int64_t)((n_rows + kAdcMmRows - 1) / kAdcMmRows) *
+                                  ((j.n_samples + kAdcMmCols - 1) / kAdcMmCols);
+            // groups per workgroup: the most that FP32 adds, fewer while the product has less than 512 workgroups
+            int split = kAdcMmSplit;
+            while (split > kAdcMmSub && tiles * ((j.n_groups + split - 1) / split) < 512) split -= kAdcMmSub;
+            const int n_split = (j.n_groups + split - 1) / split;
+            const int row0 = (int)arow.size();
+            for (size_t i : members[c]) {
+                arow.push_back(AdcRow{lj[i].gsum, lj[i].sig_offset, off, (int32_t)acls.size(), 0});
+                off += j.n_samples;
+            }
+            for (int r = 0; r < n_rows; r += kAdcMmRows)
+                for (int n = 0; n < j.n_samples; n += kAdcMmCols)
+                    atile.push_back(AdcTile{(int32_t)acls.size(), row0 + r, std::min(kAdcMmRows, n_rows - r), n});
+            acls.push_back(AdcClass{j.tau0, j.dtau, j.cyc0, j.dcyc, j.gtab, j.n_groups, j.n_samples, split, n_split});
+            g.adc_max_split = std::max(g.adc_max_split, n_split);
+            g.adc_max_ns = std::max(g.adc_max_ns, j.n_samples);
+        }
+        g.adc_stride = off;
+        if (atile.size() > 65535 || g.adc_max_ns > 64 * 65535) {  // (grid limits: millions of readouts or of samples) all of them one by one
+            acls.clear();
+            arow.clear();
+            atile.clear();
+        }
+        g.n_adccls = (int)acls.size();
+        g.n_adcrow = (int)arow.size();
+        g.n_adctile = (int)atile.size();
+    }
+
     // ---- sweep ops: grouped ops in schedule order; consecutive ones fuse
     auto ptr4 = [&](size_t o) { return o == kNone ? (const float4 *)nullptr : (const float4 *)tb(o); };
     auto ptr2 = [&](size_t o) { return o == kNone ? (const float2 *)nullptr : (const float2 *)tb(o); };
@@ -1564,6 +1634,10 @@ static int build_grouped_plan(gbs_ctx *ctx) {
     std::vector<RunOp> rops;
     if (ctx->n_lruns > 0)
         if (int rc = plan_runs(ctx, sops, rops)) return rc;
+    if (g.n_adccls) {  // partial sums of the readout products, after everything else
+        g.w_adcpart = align256(std::max(g.ws_bytes, g.run_ws_bytes));
+        g.adc_end = align256(g.w_adcpart + sizeof(float2) * (size_t)g.adc_stride * (size_t)g.adc_max_split);
+    }
     for (auto &sg : g.segs) sg.bytes_per_iso = sweep_bytes_per_iso(sg.need, sg.write_m, false, false);
     g.n_ops = (int64_t)sops.size();
 
@@ -1581,7 +1655,11 @@ static int build_grouped_plan(gbs_ctx *ctx) {
     g.o_sweep = g.o_adclin + align256(sizeof(AdcLinJob) * lj.size());
     g.o_part = g.o_sweep + align256(sizeof(SweepOp) * sops.size());
     g.o_runop = g.o_part + align256(sizeof(PartJob) * pj.size());
-    const size_t jbytes = g.o_runop + sizeof(RunOp) * rops.size();
+    g.o_adccls = g.o_runop + align256(sizeof(RunOp) * rops.size());
+    g.o_adcrow = g.o_adccls + align256(sizeof(AdcClass) * acls.size());
+    g.o_adctile = g.o_adcrow + align256(sizeof(AdcRow) * arow.size());
+    g.o_adcrest = g.o_adctile + align256(sizeof(AdcTile) * atile.size());
+    const size_t jbytes = g.o_adcrest + sizeof(AdcLinJob) * g.lin_rest.size();
     ctx->host_jobs.assign(jbytes, 0);
     auto put = [&](size_t o, const void *src, size_t n) {
         if (n) std::memcpy(ctx->host_jobs.data() + o, src, n);
@@ -1595,6 +1673,10 @@ static int build_grouped_plan(gbs_ctx *ctx) {
     put(g.o_sweep, sops.data(), sizeof(SweepOp) * sops.size());
     put(g.o_part, pj.data(), sizeof(PartJob) * pj.size());
     put(g.o_runop, rops.data(), sizeof(RunOp) * rops.size());
+    put(g.o_adccls, acls.data(), sizeof(AdcClass) * acls.size());
+    put(g.o_adcrow, arow.data(), sizeof(AdcRow) * arow.size());
+    put(g.o_adctile, atile.data(), sizeof(AdcTile) * atile.size());
+    put(g.o_adcrest, g.lin_rest.data(), sizeof(AdcLinJob) * g.lin_rest.size());
     // the pointer fields that hold workspace offsets
     const std::vector<char> &img = ctx->host_jobs;
     add_relocs<RfJobDev>(g.relocs, img, g.o_rf, rj.size(), {offsetof(RfJobDev, out)});
@@ -1603,6 +1685,8 @@ static int build_grouped_plan(gbs_ctx *ctx) {
     add_relocs<TabJob>(g.relocs, img, g.o_tab, tjobs.size(), {offsetof(TabJob, out)});
     add_relocs<AdcJobDev>(g.relocs, img, g.o_adc, aj.size(), {offsetof(AdcJobDev, gsum)});
     add_relocs<AdcLinJob>(g.relocs, img, g.o_adclin, lj.size(), {offsetof(AdcLinJob, gsum)});
+    add_relocs<AdcLinJob>(g.relocs, img, g.o_adcrest, g.lin_rest.size(), {offsetof(AdcLinJob, gsum)});
+    add_relocs<AdcRow>(g.relocs, img, g.o_adcrow, arow.size(), {offsetof(AdcRow, gsum)});
     add_relocs<SweepOp>(g.relocs, img, g.o_sweep, sops.size(),
                         {offsetof(SweepOp, pre_xtab), offsetof(SweepOp, part), offsetof(SweepOp, pre_ztab),
                          offsetof(SweepOp, ttab), offsetof(SweepOp, emit_xtab), offsetof(SweepOp, emit_ztab),
@@ -1667,15 +1751,23 @@ static int build_coil_layout(gbs_ctx *ctx) {
 
 // The end of a grouped simulation: the ADC samples beside the final state's
 // copy on the side stream, and the counts.
-static int finish_grouped(gbs_ctx *ctx, const char *jb, double *sig_out, gbs_stats *st, int64_t n_sweeps, double bytes,
+static int finish_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const char *jb, double *sig_out, gbs_stats *st, int64_t n_sweeps, double bytes,
                           double flops) {
     const GroupedPlan &g = ctx->gp;
     const Plan &plan = g.plan;
     // ---- ADC samples from the group sums (Eq. 8, Eq. 10) --------------------
     HIPCHK(launch_adc_eval((const AdcJobDev *)(jb + g.o_adc), g.n_adc, g.max_adc_groups, g.max_adc_samples,
                            sig_out, ctx->stream));
-    HIPCHK(launch_adc_lin((const AdcLinJob *)(jb + g.o_adclin), g.n_adclin, g.max_adclin_groups, sig_out,
-                          ctx->stream));
+    if (g.n_adccls && ws_bytes >= g.adc_end) {
+        HIPCHK(launch_adc_mm((const AdcClass *)(jb + g.o_adccls), (const AdcRow *)(jb + g.o_adcrow),
+                             (const AdcTile *)(jb + g.o_adctile), g.n_adctile, g.adc_max_split, g.n_adcrow, g.adc_max_ns,
+                             (float2 *)(ws + g.w_adcpart), g.adc_stride, sig_out, ctx->stream));
+        HIPCHK(launch_adc_lin((const AdcLinJob *)(jb + g.o_adcrest), (int)g.lin_rest.size(), g.max_adcrest_groups,
+                              sig_out, ctx->stream));
+    } else {
+        HIPCHK(launch_adc_lin((const AdcLinJob *)(jb + g.o_adclin), g.n_adclin, g.max_adclin_groups, sig_out,
+                              ctx->stream));
+    }
     if (st) HIPCHK(hipEventRecord(ctx->ev[3], ctx->stream));
     HIPCHK(hipStreamWaitEvent(ctx->stream, ctx->join, 0));
     if (st) {
@@ -1800,7 +1892,7 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
                                              m_out + K, m_out + 2 * K},
                                 ctx->side));
         HIPCHK(hipEventRecord(ctx->join, ctx->side));
-        return finish_grouped(ctx, jb, sig_out, st, (int64_t)g.batches.size(), g.run_bytes, g.run_flops);
+        return finish_grouped(ctx, ws, ws_bytes, jb, sig_out, st, (int64_t)g.batches.size(), g.run_bytes, g.run_flops);
     }
 
     // ---- sweeps of grouped ops (plain stepping between them) ----------------
@@ -1896,7 +1988,7 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
                                     ctx->side));
     HIPCHK(hipEventRecord(ctx->join, ctx->side));
 
-    return finish_grouped(ctx, jb, sig_out, st, (int64_t)g.segs.size(), bytes, flops);
+    return finish_grouped(ctx, ws, ws_bytes, jb, sig_out, st, (int64_t)g.segs.size(), bytes, flops);
 }
 
 // The conventional accelerated method (Sec. 2.2): per-isochromat combined
@@ -2182,7 +2274,7 @@ static int workspace_bytes(gbs_ctx *ctx, int mode, size_t *bytes, size_t *least)
     } else {
         if (!ctx->groups_valid) return fail(ctx, GBS_E_STATE, "GBS_GROUPED needs gbs_build_groups on the current phantom");
         if (!ctx->gp.valid) return fail(ctx, GBS_E_STATE, "no grouped schedule (a setter failed)");
-        *bytes = std::max(ctx->gp.ws_bytes, ctx->gp.run_ws_bytes);
+        *bytes = std::max(ctx->gp.ws_bytes, std::max(ctx->gp.run_ws_bytes, ctx->gp.adc_end));
     }
     *least = mode == GBS_GROUPED ? ctx->gp.ws_bytes : *bytes;
     return GBS_OK;

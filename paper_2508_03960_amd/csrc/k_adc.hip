@@ -20,6 +20,11 @@
 // slices of a wavefront that share a chunk add in FP32 through lane shuffles;
 // those sums go through LDS, and the workgroup's rows and the workgroups add
 // in FP64 (one FP64 atomic pair per sample and workgroup).
+//
+// k_adc_mm: the same for many readouts of equal timing at once, as a matrix
+// product (below).  k_adc_lin takes what is left: timings with fewer than
+// kAdcMmMinRows readouts, whose rows would fill too little of a tile, and calls
+// whose workspace has no room for the product's partial sums.
 #include "adc.hpp"
 #include "device_math.hpp"
 
@@ -178,6 +183,183 @@ __global__ __launch_bounds__(kAdcLinWG) void k_adc_lin(const AdcLinJob *__restri
         }
         __syncthreads();
     }
+}
+
+// ---------------------------------------------------------------- k_adc_mm
+// A workgroup takes 64 readouts of one class, 128 samples and up to 224 groups:
+// A = the readouts' group sums (rounded to FP32, staged 32 groups at a time),
+// B = e^{-tau_n/T2} e^{-i phi_g(n)}, evaluated directly per (group, sample) in
+// the lanes that hold it, four real v_mfma_f32_16x16x4_f32 per complex 16 x 16
+// tile and four groups.  A wavefront holds all 64 rows of its 32 samples, so
+// each factor is made once per 64 readouts: VALU work is a fifth of the matrix
+// core's, which bounds the kernel.  Partial sums of at most 224 groups in FP32
+// (as in k_adc_lin), FP64 from there (k_adc_mm_sum); no atomics.
+typedef float adc_f32x4 __attribute__((ext_vector_type(4)));
+
+struct AdcGroup {
+    double x, df;
+};
+
+__global__ __launch_bounds__(256) void k_adc_mm(const AdcClass *__restrict__ classes, const AdcRow *__restrict__ rows,
+                                                const AdcTile *__restrict__ tiles, float2 *__restrict__ part,
+                                                int64_t part_stride) {
+    constexpr int ET = kAdcMmRows / 16, NT = kAdcMmCols / 64;
+    constexpr int LD = kAdcMmSub + 4;
+    __shared__ float2 sA[kAdcMmRows * LD];
+    __shared__ AdcGroup sg[kAdcMmSub];
+    __shared__ float sr2[kAdcMmSub];
+    const AdcTile tl = tiles[blockIdx.y];
+    const AdcClass c = classes[tl.cls];
+    const int g0 = blockIdx.x * c.split;
+    if ((int)blockIdx.x >= c.n_split) return;  // uniform
+    const int g1 = min(g0 + c.split, c.n_groups);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int i = lane & 15, kq = lane >> 4;
+    // staging: thread t loads group t % 32 of the rows t / 32 + 8 q
+    const int sgp = threadIdx.x & 31, srow = threadIdx.x >> 5;
+    const double2 *src[kAdcMmRows / 8];
+#pragma unroll
+    for (int q = 0; q < kAdcMmRows / 8; ++q) src[q] = rows[tl.row + min(srow + 8 * q, tl.n_rows - 1)].gsum;
+    double2 sv[kAdcMmRows / 8];
+    float4 gv = make_float4(0.f, 1.f, 1.f, 0.f);
+    auto load = [&](int g) {  // groups g .. g + 31 (indices clamped; groups past the end are zeroed when stored)
+        const int k = min(g + sgp, g1 - 1);
+#pragma unroll
+        for (int q = 0; q < kAdcMmRows / 8; ++q) sv[q] = adc_sum(src[q], k);
+        if (threadIdx.x < kAdcMmSub) gv = adc_row(c.gtab, k);
+    };
+    double cyc[NT], tau[NT];
+    float mtau[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int n = tl.n0 + 16 * (NT * wave + t) + i;
+        tau[t] = c.tau0 + n * c.dtau;
+        cyc[t] = c.cyc0 + n * c.dcyc;
+        mtau[t] = -(float)tau[t];
+    }
+    adc_f32x4 dr[ET][NT], di[ET][NT];
+#pragma unroll
+    for (int e = 0; e < ET; ++e)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) dr[e][t] = di[e][t] = adc_f32x4{0.f, 0.f, 0.f, 0.f};
+    const bool live = tl.n0 + 16 * NT * wave < c.n_samples;
+    load(g0);
+    for (int g = g0; g < g1; g += kAdcMmSub) {
+        __syncthreads();  // the previous groups have been read
+        const bool in = g + sgp < g1;
+#pragma unroll
+        for (int q = 0; q < kAdcMmRows / 8; ++q)
+            sA[(srow + 8 * q) * LD + sgp] = in ? make_float2((float)sv[q].x, (float)sv[q].y) : make_float2(0.f, 0.f);
+        if (threadIdx.x < kAdcMmSub) {
+            sg[threadIdx.x] = AdcGroup{(double)gv.x, (double)gv.w};
+            sr2[threadIdx.x] = __builtin_amdgcn_rcpf(gv.z);
+        }
+        __syncthreads();
+        if (g + kAdcMmSub < g1) load(g + kAdcMmSub);
+        if (!live) continue;
+        const int steps = (min(kAdcMmSub, g1 - g) + 3) / 4;
+        for (int s = 0; s < steps; ++s) {
+            const AdcGroup p = sg[4 * s + kq];
+            const float r2 = sr2[4 * s + kq];
+            float fr[NT], fi[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                float sn, co;
+                sincos_rev(cyc[t] * p.x + p.df * tau[t], &sn, &co);
+                const float e = __expf(mtau[t] * r2);
+                fr[t] = e * co;
+                fi[t] = -e * sn;
+            }
+#pragma unroll
+            for (int e = 0; e < ET; ++e) {
+                const float2 a = sA[(16 * e + i) * LD + 4 * s + kq];
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    dr[e][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, fr[t], dr[e][t], 0, 0, 0);
+                    di[e][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, fi[t], di[e][t], 0, 0, 0);
+                    dr[e][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, -fi[t], dr[e][t], 0, 0, 0);
+                    di[e][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, fr[t], di[e][t], 0, 0, 0);
+                }
+            }
+        }
+    }
+    if (!live) return;
+    // element v of a tile: row 4 kq + v, column i
+    float2 *out = part + (int64_t)blockIdx.x * part_stride;
+#pragma unroll
+    for (int e = 0; e < ET; ++e)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int r = 16 * e + 4 * kq + v;
+            if (r >= tl.n_rows) continue;
+            float2 *o = out + rows[tl.row + r].part;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const int n = tl.n0 + 16 * (NT * wave + t) + i;
+                if (n < c.n_samples) o[n] = make_float2(dr[e][t][v], di[e][t][v]);
+            }
+        }
+}
+
+// sig += the splits' partial sums, FP64: 64 samples per workgroup, wavefront w
+// of 16 adding the splits w, w + 16, ... in order, then the 16 sums in order
+// (few rows with many splits are a chain of loads; four wavefronts took twice
+// as long for 128 rows of 290 splits).
+constexpr int kAdcSumWaves = 16;
+__global__ __launch_bounds__(64 * kAdcSumWaves) void k_adc_mm_sum(const AdcClass *__restrict__ classes, const AdcRow *__restrict__ rows,
+                                                    const float2 *__restrict__ part, int64_t part_stride,
+                                                    double *__restrict__ sig) {
+    __shared__ double2 red[kAdcSumWaves][64];
+    const AdcRow r = rows[blockIdx.x];
+    const int ns = classes[r.cls].n_samples, n_split = classes[r.cls].n_split;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int n = blockIdx.y * 64 + lane;
+    if ((int)blockIdx.y * 64 >= ns) return;  // uniform
+    const float2 *p = part + r.part + min(n, ns - 1);
+    double sr = 0.0, si = 0.0;
+    int s = wave;
+    constexpr int W = kAdcSumWaves;
+    for (; s + 3 * W < n_split; s += 4 * W) {  // four loads in flight
+        float2 v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = p[(int64_t)(s + W * q) * part_stride];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            sr += v[q].x;
+            si += v[q].y;
+        }
+    }
+    for (; s < n_split; s += W) {
+        const float2 v = p[(int64_t)s * part_stride];
+        sr += v.x;
+        si += v.y;
+    }
+    red[wave][lane] = make_double2(sr, si);
+    __syncthreads();
+    if (wave == 0 && n < ns) {
+        sr = si = 0.0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            sr += red[w][lane].x;
+            si += red[w][lane].y;
+        }
+        double *o = sig + 2 * (r.sig_offset + n);
+        o[0] += sr;
+        o[1] += si;
+    }
+}
+
+hipError_t launch_adc_mm(const AdcClass *cls, const AdcRow *rows, const AdcTile *tiles, int n_tiles, int max_split,
+                         int n_rows, int max_samples, float2 *part, int64_t part_stride, double *sig, hipStream_t st) {
+    if (n_tiles <= 0 || max_split <= 0 || n_rows <= 0) return hipSuccess;
+    if (n_tiles > 65535 || max_samples > 64 * 65535) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_adc_mm, dim3((unsigned)max_split, (unsigned)n_tiles), dim3(256), 0, st, cls, rows, tiles, part,
+                       part_stride);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_adc_mm_sum, dim3((unsigned)n_rows, (unsigned)((max_samples + 63) / 64)),
+                       dim3(64 * kAdcSumWaves), 0, st, cls, rows, part, part_stride, sig);
+    return hipGetLastError();
 }
 
 hipError_t launch_adc_lin(const AdcLinJob *jobs, int n_jobs, int max_groups, double *sig, hipStream_t st) {

@@ -149,3 +149,28 @@ def test_batches_of_runs(gb):
     Mb, sb = grouped(gb, ph, seq, sens, explicit=True)
     rel = np.linalg.norm(sa - sb, axis=1) / np.linalg.norm(sb, axis=1)  # per coil
     assert np.max(np.abs(Ma - Mb)) <= DM_TOL and rel.max() <= SIG_TOL
+
+
+@pytest.mark.parametrize("lines,n_read,nx", [
+    (3, 5, 6),       # too few readouts of one timing: evaluated one by one
+    (4, 1, 1), (4, 16, 3), (5, 17, 8), (63, 31, 9), (64, 127, 5), (65, 128, 4), (129, 129, 3),
+    (6, 40, 40), (6, 40, 230),  # groups around the chunks of 32 and the splits
+])
+def test_readout_products(gb, lines, n_read, nx):
+    """Readouts of equal timing as matrix products: rows, samples and groups
+    around the edges of the tiles."""
+    seq = sequence(range(-(lines // 2), lines - lines // 2), n_read=n_read)
+    check(gb, f"lines={lines} read={n_read} nx={nx}", phantom(nx, 11, 2, seed=nx), seq)
+
+
+def test_readouts_of_two_timings(gb):
+    """Two classes of readouts, and one readout of a third timing."""
+    sb = SeqBuilder(1e-6, "mixed")
+    b1 = synth.sinc_pulse(40, 1e-6, np.deg2rad(40.0))
+    for i in range(11):
+        sb.rf(b1, (0.0, 0.0, 0.02))
+        sb.relax(1e-3, (-2e-9, (i - 5) / (GAMMA_BAR * 0.2), -4e-7))
+        s = 1.0 if i % 2 else -1.0
+        sb.adc(40, (s * 2e-4, 0.0, 0.0), 4 * np.arange(10) + (2 if i != 7 else 1))
+        sb.relax(3e-3, (1e-9, -(i - 5) / (GAMMA_BAR * 0.2), 3e-7))
+    check(gb, "two timings", phantom(9, 21, 3, seed=77), sb.build())
