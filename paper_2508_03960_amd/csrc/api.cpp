@@ -204,6 +204,7 @@ struct gbs_ctx {
     // x- and z-group per run, run of each isochromat in the caller's order
     int64_t n_lruns = 0;
     DevBuf rfirst4, rgx, rgz, run_of;
+    DevBuf rslot;  // place of a run's ratio: the runs in the order of their first isochromat (run_of holds places too)
     std::vector<int32_t> xrun;  // first run of each x-group, and n_lruns (empty: runs too short for the per-run form)
     DevBuf run_waves;           // grouped plan: run ranges of the run sweep's wavefronts, batch after batch
     DevBuf run_ident;           // kRunIdentity
@@ -338,7 +339,7 @@ int gbs_destroy(gbs_ctx *ctx) {
                       &ctx->t2i, &ctx->dfi, &ctx->m0i, &ctx->jobs, &ctx->samp, &ctx->flag, &ctx->surr_idx, &ctx->csurr_idx,
                       &ctx->adj_ops, &ctx->adj_samp, &ctx->adj_ckpt, &ctx->adj_sub, &ctx->adj_sig, &ctx->adj_grf,
                       &ctx->adj_gt, &ctx->csamp, &ctx->ttab, &ctx->tmap, &ctx->coil_l, &ctx->run_of4, &ctx->xstart,
-                      &ctx->rtab, &ctx->rz, &ctx->rfirst4, &ctx->rgx, &ctx->rgz, &ctx->run_of, &ctx->run_waves, &ctx->run_ident};
+                      &ctx->rtab, &ctx->rz, &ctx->rfirst4, &ctx->rgx, &ctx->rgz, &ctx->run_of, &ctx->rslot, &ctx->run_waves, &ctx->run_ident};
     for (DevBuf *b : bufs) b->release();
     for (int a = 0; a < 3; ++a) {
         ctx->gid[a].release();
@@ -564,18 +565,23 @@ int gbs_build_groups(gbs_ctx *ctx, uint32_t axes) {
         ALLOC(ctx->run_of, sizeof(int32_t) * (size_t)K);
         // (the scratch holds at least 8 int32 per isochromat and the layout at most 8 slots)
         int64_t R = 0;
-        e = number_runs(n4, K, ctx->gid[0].as<int32_t>(), ctx->gid[2].as<int32_t>(), ctx->inv.as<int32_t>(), scratch.p,
-                        scratch_bytes, ctx->run_of4.as<int32_t>(), ctx->run_of.as<int32_t>(), &R, ctx->stream);
+        e = number_runs(n4, ctx->gid[0].as<int32_t>(), ctx->gid[2].as<int32_t>(), scratch.p, scratch_bytes,
+                        ctx->run_of4.as<int32_t>(), &R, ctx->stream);
         if (e != hipSuccess) return fail_hip(e, "run numbering failed");
+        ALLOC(ctx->rslot, sizeof(int32_t) * (size_t)R);
         ALLOC(ctx->rfirst4, sizeof(int32_t) * (size_t)(R + 1));
         ALLOC(ctx->rgx, sizeof(int32_t) * (size_t)R);
         ALLOC(ctx->rgz, sizeof(int32_t) * (size_t)R);
         HIPCHK(launch_run_arrays(n4, ctx->run_of4.as<int32_t>(), ctx->gid[0].as<int32_t>(), ctx->gid[2].as<int32_t>(),
                                  ctx->rfirst4.as<int32_t>(), ctx->rgx.as<int32_t>(), ctx->rgz.as<int32_t>(),
                                  ctx->stream));
+        e = place_runs(K, R, ctx->rfirst4.as<int32_t>(), ctx->run_of4.as<int32_t>(), ctx->perm.as<int32_t>(),
+                       ctx->inv.as<int32_t>(), scratch.p, scratch_bytes, ctx->rslot.as<int32_t>(),
+                       ctx->run_of.as<int32_t>(), ctx->stream);
+        if (e != hipSuccess) return fail_hip(e, "run numbering failed");
         ctx->n_lruns = R;
         ctx->xrun.clear();
-        if (K >= kRunMinMembers * R && R <= kRunMaxRuns) {
+        if (K >= kRunMinMembers * R && R <= kRunMaxRuns && kint <= kRunMaxSlots) {
             const int64_t Gx = ctx->ng[0];
             if (scratch_bytes < sizeof(int32_t) * (size_t)(Gx + 1)) return fail_hip(hipErrorInvalidValue, "run ranges");
             HIPCHK(launch_group_runs(R, ctx->rgx.as<int32_t>(), Gx, scratch.as<int32_t>(), ctx->stream));
@@ -596,6 +602,7 @@ int gbs_build_groups(gbs_ctx *ctx, uint32_t axes) {
     if (!(axes & GBS_AX_Z)) {
         ctx->run_of4.release();
         ctx->run_of.release();
+        ctx->rslot.release();
         ctx->rfirst4.release();
         ctx->rgx.release();
         ctx->rgz.release();
@@ -1832,6 +1839,31 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
     HIPCHK(launch_fill_f64((double *)(ws + g.w_gsum), 2 * (int64_t)g.gsum_count, ctx->side));
     HIPCHK(launch_tables((const TabJob *)(jb + g.o_tab), g.n_tab, (int)g.max_tab, ctx->gtab[0].as<float4>(),
                          zbuilt ? ctx->gtab[2].as<float4>() : nullptr, ctx->side));
+    // the per-run form's sums over the members need the phantom alone: those of
+    // the first batch run on the side stream beside the compositions (after
+    // those of two-axis groups: their workgroups, fewer than the CUs, run for a
+    // millisecond where they are placed, and the sums' workgroups made them share
+    // CUs: oblique FSE 3.4M 2.40 ms in turn, 2.80 side by side)
+    const bool use_runs = g.runs && !m_init && ws_bytes >= g.run_ws_bytes;
+    RunYArgs ya{};
+    if (use_runs) {
+        ya.n_runs = ctx->n_lruns;
+        ya.first4 = ctx->rfirst4.as<int32_t>();
+        ya.y = ctx->yi.as<float>();
+        ya.m0 = ctx->m0i.as<float>();
+        if (ctx->coil_re) {
+            if (!ctx->coil_l_valid) return fail(ctx, GBS_E_STATE, "no group-sorted coil sensitivities (a setter failed)");
+            ya.coil = ctx->coil_l.as<float>();
+            ya.coil_plane = ctx->Kpad;
+        }
+        ya.n_coils = ctx->n_coils;
+        ya.lines = g.lines;
+        ya.out = (float2 *)(ws + g.w_runy);
+        ya.out_coil = g.run_batch * g.lines.n_lines;
+        ya.r0 = 0;
+        ya.n = g.batches.front().r1;
+        if (plan.n_adc_grouped && g.pair_jobs.empty()) HIPCHK(launch_run_y(ya, ctx->side));
+    }
     HIPCHK(hipEventRecord(ctx->join, ctx->side));
     for (const auto &pj : g.pair_jobs) {
         const RfJob &r = plan.rf[pj.second];
@@ -1847,25 +1879,12 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
     if (st) HIPCHK(hipEventRecord(ctx->ev[1], ctx->stream));
 
     // ---- one step per run of the layout, when the members of a run stay alike
-    if (g.runs && !m_init && ws_bytes >= g.run_ws_bytes) {
-        RunYArgs ya{};
-        ya.n_runs = ctx->n_lruns;
-        ya.first4 = ctx->rfirst4.as<int32_t>();
-        ya.y = ctx->yi.as<float>();
-        ya.m0 = ctx->m0i.as<float>();
-        if (ctx->coil_re) {
-            if (!ctx->coil_l_valid) return fail(ctx, GBS_E_STATE, "no group-sorted coil sensitivities (a setter failed)");
-            ya.coil = ctx->coil_l.as<float>();
-            ya.coil_plane = ctx->Kpad;
-        }
-        ya.n_coils = ctx->n_coils;
-        ya.lines = g.lines;
-        ya.out = (float2 *)(ws + g.w_runy);
-        ya.out_coil = g.run_batch * g.lines.n_lines;
+    if (use_runs) {
         RunSweepArgs sa{};
         sa.n_runs = ctx->n_lruns;
         sa.gx = ctx->rgx.as<int32_t>();
         sa.gz = ctx->rgz.as<int32_t>();
+        sa.slot = ctx->rslot.as<int32_t>();
         sa.ops = (const RunOp *)(jb + g.o_runop);
         sa.n_parts = (int32_t)g.run_parts.size();
         std::copy(g.run_parts.begin(), g.run_parts.end(), sa.parts);
@@ -1880,7 +1899,7 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
             ya.n = bt.r1 - ya.r0;
             sa.first = ctx->run_waves.as<int32_t>() + bt.wave0;
             sa.n_waves = bt.waves;
-            if (plan.n_adc_grouped) HIPCHK(launch_run_y(ya, ctx->stream));
+            if (plan.n_adc_grouped && (bt.r0 > 0 || !g.pair_jobs.empty())) HIPCHK(launch_run_y(ya, ctx->stream));
             HIPCHK(launch_run_sweep(sa, ctx->stream));
         }
         if (profile) HIPCHK(hipEventRecord(ctx->pev[1], ctx->stream));

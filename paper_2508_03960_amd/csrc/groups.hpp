@@ -13,9 +13,11 @@ hipError_t group_axis(int64_t K, bool coord_last, const float *coord, const floa
                       int32_t *gcount, int32_t *order, int64_t *n_groups, hipStream_t st);
 hipError_t build_layout(int64_t K, const int32_t *gid_x, const int32_t *gid_z, void *scratch, size_t scratch_bytes,
                         int32_t *perm, int32_t *src, int64_t Kpad_cap, int64_t *kint, hipStream_t st);
-hipError_t number_runs(int64_t n4, int64_t K, const int32_t *gid_x, const int32_t *gid_z, const int32_t *inv,
-                       void *scratch, size_t scratch_bytes, int32_t *run_of4, int32_t *run, int64_t *n_runs,
-                       hipStream_t st);
+hipError_t number_runs(int64_t n4, const int32_t *gid_x, const int32_t *gid_z, void *scratch, size_t scratch_bytes,
+                       int32_t *run_of4, int64_t *n_runs, hipStream_t st);
+hipError_t place_runs(int64_t K, int64_t R, const int32_t *first4, const int32_t *run_of4, const int32_t *perm,
+                      const int32_t *inv, void *scratch, size_t scratch_bytes, int32_t *slot, int32_t *run,
+                      hipStream_t st);
 hipError_t launch_run_arrays(int64_t n4, int32_t *run_of4, const int32_t *gid_x, const int32_t *gid_z,
                              int32_t *first4, int32_t *gx, int32_t *gz, hipStream_t st);
 hipError_t launch_group_runs(int64_t n_runs, const int32_t *gx, int64_t n_groups, int32_t *xrun, hipStream_t st);

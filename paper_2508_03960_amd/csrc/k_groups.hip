@@ -309,11 +309,27 @@ __global__ void k_run_starts(int64_t n4, const int32_t *__restrict__ gid_x, cons
         flag[q] = q == 0 || gid_x[4 * q] != gid_x[4 * q - 4] || gid_z[4 * q] != gid_z[4 * q - 4];
 }
 
-// run of isochromat k (caller's order) and, per quad, the 0-based run
-__global__ void k_run_of(int64_t K, const int32_t *__restrict__ inv, const int32_t *__restrict__ ids,
-                         int32_t *__restrict__ run) {
+__global__ void k_first_flags(int64_t R, const int32_t *__restrict__ first4, const int32_t *__restrict__ perm,
+                              int32_t *__restrict__ flag) {
+    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < R; r += (int64_t)gridDim.x * blockDim.x)
+        flag[perm[4 * (int64_t)first4[r]]] = 1;  // a run's first slot holds its first isochromat
+}
+
+__global__ void k_run_slots(int64_t R, const int32_t *__restrict__ first4, const int32_t *__restrict__ perm,
+                            const int32_t *__restrict__ rank, int32_t *__restrict__ slot) {
+    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < R; r += (int64_t)gridDim.x * blockDim.x)
+        slot[r] = rank[perm[4 * (int64_t)first4[r]]];
+}
+
+__global__ void k_run_of(int64_t K, const int32_t *__restrict__ inv, const int32_t *__restrict__ run_of4,
+                         const int32_t *__restrict__ slot, int32_t *__restrict__ run) {
     for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < K; k += (int64_t)gridDim.x * blockDim.x)
-        run[k] = ids[inv[k] >> 2] - 1;
+        run[k] = slot[run_of4[inv[k] >> 2]];
+}
+
+__global__ void k_zero_i32(int64_t n, int32_t *v) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        v[i] = 0;
 }
 
 __global__ void k_minus_one(int64_t n, int32_t *v) {
@@ -322,12 +338,11 @@ __global__ void k_minus_one(int64_t n, int32_t *v) {
 }
 
 // Numbers the runs of equal (x-group, z-group) of the layout's n4 quads in
-// layout order: run_of4[q], and the run of every isochromat of the caller's
-// order; the count through *n_runs (synchronizes the stream).  scratch: room
-// for n4 int32 and the scan's temporary memory.
-hipError_t number_runs(int64_t n4, int64_t K, const int32_t *gid_x, const int32_t *gid_z, const int32_t *inv,
-                       void *scratch, size_t scratch_bytes, int32_t *run_of4, int32_t *run, int64_t *n_runs,
-                       hipStream_t st) {
+// layout order: run_of4[q] (1-based until launch_run_arrays), and the count
+// through *n_runs (synchronizes the stream).  scratch: room for n4 int32 and
+// the scan's temporary memory.
+hipError_t number_runs(int64_t n4, const int32_t *gid_x, const int32_t *gid_z, void *scratch, size_t scratch_bytes,
+                       int32_t *run_of4, int64_t *n_runs, hipStream_t st) {
     int32_t *flag = (int32_t *)scratch;
     const size_t used = (4 * (size_t)n4 + 255) & ~(size_t)255;
     if (used > scratch_bytes) return hipErrorInvalidValue;
@@ -338,14 +353,32 @@ hipError_t number_runs(int64_t n4, int64_t K, const int32_t *gid_x, const int32_
     hipLaunchKernelGGL(k_run_starts, grid_for(n4), dim3(256), 0, st, n4, gid_x, gid_z, flag);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = inclusive_sum((char *)scratch + used, &tmp_bytes, flag, run_of4, n4, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_run_of, grid_for(K), dim3(256), 0, st, K, inv, run_of4, run);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     int32_t last = 0;
     if ((e = hipMemcpyAsync(&last, run_of4 + (n4 - 1), sizeof(int32_t), hipMemcpyDeviceToHost, st)) != hipSuccess)
         return e;
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
     *n_runs = last;
     return hipSuccess;
+}
+
+// slot[r]: rank of run r by its first isochromat in the caller's order; run[k]:
+// slot of isochromat k's run.  run_of4 0-based.  scratch: 2 K int32 and the scan.
+hipError_t place_runs(int64_t K, int64_t R, const int32_t *first4, const int32_t *run_of4, const int32_t *perm,
+                      const int32_t *inv, void *scratch, size_t scratch_bytes, int32_t *slot, int32_t *run,
+                      hipStream_t st) {
+    const size_t one = (4 * (size_t)K + 255) & ~(size_t)255;
+    int32_t *flag = (int32_t *)scratch, *rank = (int32_t *)((char *)scratch + one);
+    size_t tmp_bytes = 0;
+    hipError_t e = exclusive_sum(nullptr, &tmp_bytes, nullptr, nullptr, K, st);
+    if (e != hipSuccess) return e;
+    if (2 * one + tmp_bytes > scratch_bytes) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_zero_i32, grid_for(K), dim3(256), 0, st, K, flag);
+    hipLaunchKernelGGL(k_first_flags, grid_for(R), dim3(256), 0, st, R, first4, perm, flag);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = exclusive_sum((char *)scratch + 2 * one, &tmp_bytes, flag, rank, K, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_run_slots, grid_for(R), dim3(256), 0, st, R, first4, perm, rank, slot);
+    hipLaunchKernelGGL(k_run_of, grid_for(K), dim3(256), 0, st, K, inv, run_of4, slot, run);
+    return hipGetLastError();
 }
 
 // first4[r] (and n4 after the last run), x- and z-group of every run from the

@@ -11,7 +11,6 @@
 //               four members, 4 flops per member and line.
 //  k_run_sweep  all operations of a simulation with one run per lane.
 //  k_run_state  the final state in the caller's order from the runs' ratios.
-#include <algorithm>
 #include <type_traits>
 
 #include "device_math.hpp"
@@ -25,17 +24,14 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------- k_run_y
 // One workgroup per 16 runs (a row of the Y layout), four runs per wavefront.
-// A wavefront takes a run's members 64 at a time: each lane makes one member's
-// weight (with the phase of c0) and leaves it with the member's y in LDS; then
-// every step of the product reads four members, lane l holding row l % 16 and
-// column l % 16 of member l / 16.  The phases are formed and reduced modulo one
-// turn (v_cos_f32 takes turns; sin is the cos a quarter turn back).
-// What bounds it is the VALU work of the two phases per step, about 90 cycles
-// against 64 of the matrix core.
-struct RunMember {
-    float y, wr, wi, pad;
-};
-
+// A wavefront takes a run's members 32 at a time.  Lane l first makes the
+// eight a-phases (l < 32) or b-phases (l >= 32) of member l % 32: the first one,
+// the step and four steps directly (v_sin / v_cos take turns), the others by at
+// most four products of those, and the weight with the phase of c0; all of it
+// goes to LDS.  Then every step of the product reads four members, lane l
+// holding row l % 16 and column l % 16 of member l / 16.  Evaluated in the lanes
+// of the product instead, the 32 phases of a member took 95 VALU cycles per
+// step, against 64 of the matrix core (27.3M members, 256 lines: 555 us).
 // A phase coefficient (turns per metre) as two floats: c y mod 1 then takes
 // four FP32 instructions with one rounding of the reduced phase (the FMA of
 // hi y - rint(hi y) is exact up to it), instead of five at FP64.
@@ -46,75 +42,114 @@ __device__ __forceinline__ Coef coef_of(double c) {
     const float h = (float)c;
     return Coef{h, (float)(c - (double)h)};
 }
-__device__ __forceinline__ float turns(const Coef &c, float y, float off) {
-    const float e = fmaf(c.hi, y, -rintf(c.hi * y));
-    return e + fmaf(c.lo, y, off);
+__device__ __forceinline__ float turns(const Coef &c, float y) {
+    return fmaf(c.lo, y, fmaf(c.hi, y, -rintf(c.hi * y)));
 }
 
-template <bool COILS>
+__device__ __forceinline__ float2 phase_at(const Coef &c, float y) {  // (cos, sin)
+    const float t = turns(c, y);
+    return make_float2(__builtin_amdgcn_cosf(t), __builtin_amdgcn_sinf(t));
+}
+__device__ __forceinline__ float2 turned(const float2 &p, const float2 &q) {
+    return make_float2(fmaf(p.x, q.x, -p.y * q.y), fmaf(p.x, q.y, p.y * q.x));
+}
+
+constexpr int kRunChunk = 32;
+
+// HALF: at most 128 lines (b-phases 0 .. 3), columns 0 .. 7 with the real and
+// 8 .. 15 with the imaginary part of the weight: one matrix instruction per step.
+template <bool COILS, bool HALF>
 __global__ __launch_bounds__(256) void k_run_y(RunYArgs a) {
-    __shared__ RunMember member[4][64];
+    __shared__ __attribute__((aligned(16))) float phases[4][2][kRunChunk][20];  // {cos, sin} of the a, of the b; 16 used (20: free of bank conflicts)
+    __shared__ float2 weight[4][kRunChunk];
     __shared__ float2 tile[kRunLinesSet][kRunTile + 1];  // + 1: the lines of a store fall into different banks
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int set = blockIdx.y % ((a.lines.nb + 7) / 8), coil = blockIdx.y / ((a.lines.nb + 7) / 8);
     const int i = lane & 15, kq = lane >> 4;
-    const Coef ca = coef_of(((i >> 1) + 0.5) * a.lines.d), cb = coef_of((16 * ((i >> 1) + 8 * set) + 8) * a.lines.d);
-    const Coef c0 = coef_of(a.lines.c0);
-    const float off = (i & 1) ? -0.25f : 0.f;
+    const int half = lane >> 5, mb = lane & 31;  // the lane's share of the phases
+    const Coef f0 = coef_of((half ? 128 * set + 8 : 0.5) * a.lines.d), f1 = coef_of((half ? 16 : 1) * a.lines.d),
+               f4 = coef_of((half ? 64 : 4) * a.lines.d), c0 = coef_of(a.lines.c0);
     const int64_t tile0 = a.r0 + (int64_t)blockIdx.x * kRunTile;  // first run of the workgroup
     const int64_t rend = a.r0 + a.n;
-    const int64_t last = 4 * (int64_t)a.first4[a.n_runs] - 1;     // last slot of the layout
-    const float *sre = COILS ? a.coil + 2 * coil * a.coil_plane : nullptr;
+    // slots relative to the workgroup's first one (32 bits: the layout has at most kRunMaxSlots)
+    const int64_t slot0 = 4 * (int64_t)a.first4[tile0];
+    const int last = (int)(4 * (int64_t)a.first4[a.n_runs] - 1 - slot0);
+    const float *y = a.y + slot0, *m0 = a.m0 + slot0;
+    const float *sre = COILS ? a.coil + 2 * coil * a.coil_plane + slot0 : nullptr;
     const float *sim = COILS ? sre + a.coil_plane : nullptr;
-    int64_t slot = 0;
+    int slot = 0;
     float yv = 0.f, mv = 0.f, cr = 1.f, ci = 0.f;
-    auto fetch = [&](int64_t base) {  // members of the next 64 slots (the layout's last slot past its end)
-        slot = base + lane;
-        const int64_t s = slot < last ? slot : last;
-        yv = a.y[s];
-        mv = a.m0[s];
+    auto fetch = [&](int base) {  // members of the next slots (the layout's last slot past its end)
+        slot = base + mb;
+        const uint32_t s = 4u * (uint32_t)min(slot, last);
+        yv = *at_bytes(y, s);
+        mv = *at_bytes(m0, s);
         if (COILS) {
-            cr = sre[s];
-            ci = sim[s];
+            cr = *at_bytes(sre, s);
+            ci = *at_bytes(sim, s);
         }
     };
-    const int64_t rw = tile0 + 4 * wave;  // the wavefront's runs rw .. rw + 3
-    if (rw < rend) fetch(4 * (int64_t)a.first4[rw]);
-    for (int j = 0; j < 4; ++j) {
-        const int64_t r = rw + j;
+    auto first_slot = [&](int64_t r) { return (int)(4 * (int64_t)a.first4[r] - slot0); };
+    // The wavefronts take the workgroup's runs one by one (the lengths differ
+    // widely: with fixed shares the longest held the others up).  A run is
+    // taken before the one ahead of it is summed, so its first members are
+    // loaded in time.
+    __shared__ int taken;
+    if (threadIdx.x == 0) taken = 4;
+    __syncthreads();
+    int j = wave;
+    if (tile0 + j < rend) fetch(first_slot(tile0 + j));
+    while (j < kRunTile) {
+        int nj = 0;
+        if (lane == 0) nj = atomicAdd(&taken, 1);
+        nj = __builtin_amdgcn_readfirstlane(nj);
+        const int64_t r = tile0 + j, rn = tile0 + nj;
+        const int next = nj < kRunTile && rn < rend ? first_slot(rn) : last;
         f32x4 dr = {0.f, 0.f, 0.f, 0.f}, di = {0.f, 0.f, 0.f, 0.f};
         if (r < rend) {
-            const int64_t s1 = 4 * (int64_t)a.first4[r + 1];
-            for (int64_t base = 4 * (int64_t)a.first4[r]; base < s1; base += 64) {
-                const float ph = turns(c0, yv, 0.f);
-                const float s = __builtin_amdgcn_sinf(ph), c = __builtin_amdgcn_cosf(ph);
-                const float wr = slot < s1 ? mv : 0.f;
-                RunMember m;
-                m.y = yv;
-                if (COILS) {  // m0 S(k, p) e^{-i phi}
-                    const float pr = wr * cr, pi = wr * ci;
-                    m.wr = fmaf(pr, c, pi * s);
-                    m.wi = fmaf(pi, c, -pr * s);
+            const int s1 = first_slot(r + 1);
+            for (int base = first_slot(r); base < s1; base += kRunChunk) {
+                float2 p[8];
+                p[0] = phase_at(f0, yv);
+                const float2 q1 = phase_at(f1, yv), q4 = phase_at(f4, yv), w = phase_at(c0, yv);
+#pragma unroll
+                for (int e = 1; e < 4; ++e) p[e] = turned(p[e - 1], q1);
+#pragma unroll
+                for (int e = 4; e < 8; ++e) p[e] = turned(p[e - 4], q4);
+                const float m = slot < s1 ? mv : 0.f;
+                float2 v;  // m0 S(k, p) e^{-i phi}
+                if (COILS) {
+                    const float pr = m * cr, pi = m * ci;
+                    v = make_float2(fmaf(pr, w.x, pi * w.y), fmaf(pi, w.x, -pr * w.y));
                 } else {
-                    m.wr = wr * c;
-                    m.wi = -wr * s;
+                    v = make_float2(m * w.x, -m * w.y);
                 }
-                member[wave][lane] = m;
-                const int64_t left = s1 - base;
-                fetch(left > 64 ? base + 64 : s1);
-                const int steps = left > 64 ? 16 : (int)(left + 3) / 4;
+                float4 *ph = (float4 *)phases[wave][half][mb];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ph[e] = make_float4(p[2 * e].x, p[2 * e].y, p[2 * e + 1].x, p[2 * e + 1].y);
+                if (!half) weight[wave][mb] = v;
+                const int left = s1 - base;
+                fetch(left > kRunChunk ? base + kRunChunk : next);
+                const int steps = min(left, kRunChunk) / 4;
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                // (runs are padded to multiples of 8: an even number of steps)
-                for (int t = 0; t < steps; t += 2) {
-                    const RunMember q0 = member[wave][4 * t + kq], q1 = member[wave][4 * t + 4 + kq];
-                    const float ra0 = __builtin_amdgcn_cosf(turns(ca, q0.y, off));
-                    const float rb0 = __builtin_amdgcn_cosf(turns(cb, q0.y, off));
-                    const float ra1 = __builtin_amdgcn_cosf(turns(ca, q1.y, off));
-                    const float rb1 = __builtin_amdgcn_cosf(turns(cb, q1.y, off));
-                    dr = __builtin_amdgcn_mfma_f32_16x16x4f32(ra0, rb0 * q0.wr, dr, 0, 0, 0);
-                    di = __builtin_amdgcn_mfma_f32_16x16x4f32(ra0, rb0 * q0.wi, di, 0, 0, 0);
-                    dr = __builtin_amdgcn_mfma_f32_16x16x4f32(ra1, rb1 * q1.wr, dr, 0, 0, 0);
-                    di = __builtin_amdgcn_mfma_f32_16x16x4f32(ra1, rb1 * q1.wi, di, 0, 0, 0);
+                for (int t = 0; t < steps; t += 4) {  // (members past the run's end have weight 0)
+                    float pa[4], pb[4];
+                    float2 pw[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int k = 4 * (t + e) + kq;
+                        pa[e] = phases[wave][0][k][i];
+                        pb[e] = phases[wave][1][k][HALF ? i & 7 : i];
+                        if (HALF)
+                            pw[e].x = ((const float *)&weight[wave][k])[i >> 3];
+                        else
+                            pw[e] = weight[wave][k];
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        dr = __builtin_amdgcn_mfma_f32_16x16x4f32(pa[e], pb[e] * pw[e].x, dr, 0, 0, 0);
+                        if (!HALF) di = __builtin_amdgcn_mfma_f32_16x16x4f32(pa[e], pb[e] * pw[e].y, di, 0, 0, 0);
+                    }
                 }
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             }
@@ -122,6 +157,14 @@ __global__ __launch_bounds__(256) void k_run_y(RunYArgs a) {
         // lane (column 2 jb + t, rows 4 kq ..): element v of the tiles is
         // {cos, sin}(a_{2 kq + v / 2}) times {cos, sin}(b_jb); neighbouring
         // lanes trade halves, then lane parity picks the a index
+        if (HALF) {  // the other weight's sums from the lane eight columns away
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float o = dpp_f32<0x128>(dr[v]);  // row_ror:8
+                di[v] = i < 8 ? o : dr[v];
+                dr[v] = i < 8 ? dr[v] : o;
+            }
+        }
         const bool odd = lane & 1;
         auto trade = [&](const f32x4 &v, float &cc, float &sc, float &cs, float &ss) {
             const float g0 = dpp_f32<0xb1>(odd ? v[0] : v[2]), g1 = dpp_f32<0xb1>(odd ? v[1] : v[3]);
@@ -133,25 +176,32 @@ __global__ __launch_bounds__(256) void k_run_y(RunYArgs a) {
         float rcc, rsc, rcs, rss, icc, isc, ics, iss;
         trade(dr, rcc, rsc, rcs, rss);
         trade(di, icc, isc, ics, iss);
-        const int ia = 2 * kq + (lane & 1), jb = i >> 1;
+        const int ia = 2 * kq + (lane & 1), jb = HALF ? (i & 7) >> 1 : i >> 1;
         // sum (wr + i wi)(cos t - i sin t), t = sa a + sb b
         auto put = [&](int line, float sa, float sb) {
             const float wrc = fmaf(-sa * sb, rss, rcc), wrs = fmaf(sa, rsc, sb * rcs);
             const float wic = fmaf(-sa * sb, iss, icc), wis = fmaf(sa, isc, sb * ics);
-            tile[line][4 * wave + j] = make_float2(wrc + wis, wic - wrs);
+            tile[line][j] = make_float2(wrc + wis, wic - wrs);
         };
         // lines 0 .. 127: -b of the set (descending), 128 .. 255: +b
-        put(128 + 16 * jb + 8 + ia, 1.f, 1.f);
-        put(128 + 16 * jb + 7 - ia, -1.f, 1.f);
-        put(128 - 16 * jb - 8 + ia, 1.f, -1.f);
-        put(128 - 16 * jb - 9 - ia, -1.f, -1.f);
+        // (HALF: a line from one of the two lanes that hold its sums)
+        if (!HALF || i < 8) {
+            put(128 + 16 * jb + 8 + ia, 1.f, 1.f);
+            put(128 + 16 * jb + 7 - ia, -1.f, 1.f);
+        }
+        if (!HALF || i >= 8) {
+            put(128 - 16 * jb - 8 + ia, 1.f, -1.f);
+            put(128 - 16 * jb - 9 - ia, -1.f, -1.f);
+        }
+        j = nj;
     }
     __syncthreads();
-    const int half = 16 * a.lines.nb, n_lines = a.lines.n_lines;
+    const int mid = 16 * a.lines.nb, n_lines = a.lines.n_lines;
     float2 *out = a.out + coil * a.out_coil + ((int64_t)blockIdx.x * n_lines) * kRunTile;
-    for (int e = threadIdx.x; e < kRunLinesSet * kRunTile; e += 256) {
+    constexpr int l0 = HALF ? 64 : 0, l1 = HALF ? 192 : kRunLinesSet;
+    for (int e = l0 * kRunTile + threadIdx.x; e < l1 * kRunTile; e += 256) {
         const int ll = e / kRunTile, rr = e % kRunTile;
-        const int line = ll < 128 ? half - 128 * (set + 1) + ll : half + 128 * set + (ll - 128);
+        const int line = ll < 128 ? mid - 128 * (set + 1) + ll : mid + 128 * set + (ll - 128);
         if (line >= 0 && line < n_lines) out[(int64_t)line * kRunTile + rr] = tile[ll][rr];
     }
 }
@@ -163,10 +213,15 @@ hipError_t launch_run_y(const RunYArgs &a, hipStream_t st) {
     const int64_t gy = (int64_t)((a.lines.nb + 7) / 8) * a.n_coils;
     if (tiles > 0x7fffffff || gy > 65535) return hipErrorInvalidValue;
     const dim3 grid((unsigned)tiles, (unsigned)gy);
-    if (a.coil)
-        hipLaunchKernelGGL(k_run_y<true>, grid, dim3(256), 0, st, a);
+    const bool half = a.lines.nb <= 4;
+    if (a.coil && half)
+        hipLaunchKernelGGL((k_run_y<true, true>), grid, dim3(256), 0, st, a);
+    else if (a.coil)
+        hipLaunchKernelGGL((k_run_y<true, false>), grid, dim3(256), 0, st, a);
+    else if (half)
+        hipLaunchKernelGGL((k_run_y<false, true>), grid, dim3(256), 0, st, a);
     else
-        hipLaunchKernelGGL(k_run_y<false>, grid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL((k_run_y<false, false>), grid, dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
@@ -332,7 +387,7 @@ __global__ __launch_bounds__(64) void k_run_sweep(RunSweepArgs a) {
         else
             walk(std::integral_constant<int, MC == 1 ? 4 : 2>{}, part, fetch_full, full);
     }
-    if (act) a.m[r] = make_float4(mx, my, mz, 0.f);
+    if (act) a.m[a.slot[r]] = make_float4(mx, my, mz, 0.f);
 }
 
 hipError_t launch_run_sweep(const RunSweepArgs &a, hipStream_t st) {
@@ -352,13 +407,12 @@ hipError_t launch_run_sweep(const RunSweepArgs &a, hipStream_t st) {
 // ------------------------------------------------------------- k_run_state
 // One read of M0, the run index and the run's ratio (16 bytes, in L2) and one
 // write of M per isochromat: 20 bytes of memory traffic.  V = 4: four
-// isochromats per thread with 16-byte accesses.  A workgroup takes neighbouring
-// tiles: grid rows of a volume that lie next to each other mostly read the
-// same runs, which are then in the CU's own cache.
+// isochromats per thread with 16-byte accesses.  The ratios lie in the order of
+// the runs' first isochromats, so that neighbours of a grid row read
+// neighbouring rows.
 template <int V>
-__global__ __launch_bounds__(256) void k_run_state(RunStateArgs a, int64_t n, int rounds) {
-  for (int it = 0; it < rounds; ++it) {
-    const int64_t q = ((int64_t)blockIdx.x * rounds + it) * 256 + threadIdx.x;
+__global__ __launch_bounds__(256) void k_run_state(RunStateArgs a, int64_t n) {
+    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (q >= n) return;
     int run[V];
     float m0[V], yv[V], o[3][V];
@@ -392,22 +446,18 @@ __global__ __launch_bounds__(256) void k_run_state(RunStateArgs a, int64_t n, in
         else
             out[p][q] = o[p][0];
     }
-  }
 }
 
 hipError_t launch_run_state(const RunStateArgs &a, hipStream_t st) {
     // ox, oy, oz are K floats apart
     const bool by4 = a.K % 4 == 0 && ((uintptr_t)a.ox | (uintptr_t)a.m0 | (uintptr_t)a.y | (uintptr_t)a.run) % 16 == 0;
-    const int64_t n = by4 ? a.K / 4 : a.K, tiles = (n + 255) / 256;
-    if (tiles == 0) return hipSuccess;
-    // up to 8 tiles per workgroup where enough workgroups remain
-    const int rounds = (int)std::max<int64_t>(1, std::min<int64_t>(8, tiles / 2048));
-    const int64_t blocks = (tiles + rounds - 1) / rounds;
+    const int64_t n = by4 ? a.K / 4 : a.K, blocks = (n + 255) / 256;
+    if (blocks == 0) return hipSuccess;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     if (by4)
-        hipLaunchKernelGGL(k_run_state<4>, dim3((unsigned)blocks), dim3(256), 0, st, a, n, rounds);
+        hipLaunchKernelGGL(k_run_state<4>, dim3((unsigned)blocks), dim3(256), 0, st, a, n);
     else
-        hipLaunchKernelGGL(k_run_state<1>, dim3((unsigned)blocks), dim3(256), 0, st, a, n, rounds);
+        hipLaunchKernelGGL(k_run_state<1>, dim3((unsigned)blocks), dim3(256), 0, st, a, n);
     return hipGetLastError();
 }
 

@@ -24,7 +24,8 @@ struct YLines {
 };
 
 constexpr int64_t kRunMaxRuns = UINT32_MAX / 48;  // 48-byte rows at 32-bit offsets
-constexpr int kRunTile = 16;      // runs per row of the Y layout
+constexpr int64_t kRunMaxSlots = (int64_t)1 << 30;  // 4-byte slots at 32-bit offsets
+constexpr int kRunTile = 8;      // runs per row of the Y layout
 constexpr int kRunLinesSet = 256;  // lines of one 16 x 16 pair of tiles
 
 // Y[coil][run / 16][line][run % 16] for the runs [r0, r0 + n) (r0 a multiple
@@ -72,7 +73,7 @@ struct RunSweepArgs {
     int64_t n_runs;
     const int32_t *first;    // wavefront w of the launch takes the runs [first[w], first[w + 1]), at most 64
     int32_t n_waves;
-    const int32_t *gx, *gz;
+    const int32_t *gx, *gz, *slot;  // groups, and the place of the ratio in m, per run
     const RunOp *ops;
     RunPart parts[kRunMaxParts];
     int32_t n_parts;
@@ -80,13 +81,13 @@ struct RunSweepArgs {
     const float2 *y;   // as written by launch_run_y for the same runs
     int32_t n_lines;
     int64_t y_coil;
-    float4 *m;         // final (mx, my, mz, 0) / M0 per run, all runs
+    float4 *m;         // final (mx, my, mz, 0) / M0 of all runs
 };
 
 // M_k = M0_k m_r e^{-2 pi i cy y_k} (transverse) in the caller's order.
 struct RunStateArgs {
     int64_t K;
-    const int32_t *run;  // run of isochromat k
+    const int32_t *run;  // place of the ratio of isochromat k's run in m
     const float *m0, *y;
     double cy;
     const float4 *m;
