@@ -251,6 +251,8 @@ struct gbs_ctx {
     bool cplan_valid = false;
     Plan cplan;
     std::vector<int64_t> csamp_off;
+    std::vector<int> clin;         // per operation: its entry of clin_samp, or -1 (samples not arithmetic, or few)
+    std::vector<LinSamples> clin_samp;
     DevBuf csamp;
     std::vector<int> cprof_kind;
 };
@@ -2030,6 +2032,8 @@ static int build_cached_plan(gbs_ctx *ctx) {
         // its first s raster steps
         std::vector<double4> tab;
         ctx->csamp_off.assign(plan.ops.size(), -1);
+        ctx->clin.assign(plan.ops.size(), -1);
+        ctx->clin_samp.clear();
         int64_t mom_block = -1;
         std::vector<double> mom[3];
         for (size_t oi = 0; oi < plan.ops.size(); ++oi) {
@@ -2051,6 +2055,25 @@ static int build_cached_plan(gbs_ctx *ctx) {
                 const int32_t sn = ctx->seq.adc_idx[b.sample_offset + n];
                 tab.push_back(make_double4(kGammaBar * (c.pre.m[0] + mom[0][sn]), kGammaBar * (c.pre.m[1] + mom[1][sn]),
                                            kGammaBar * (c.pre.m[2] + mom[2][sn]), c.pre.tau + (double)sn * dt));
+            }
+            const int ns = c.sample_hi - c.sample_lo;
+            if (ns >= kAdcProductMinSamples) {
+                const double4 *t = tab.data() + ctx->csamp_off[oi];
+                const double n1 = ns - 1;
+                LinSamples ls{{t[0].x, t[0].y, t[0].z},
+                              {(t[ns - 1].x - t[0].x) / n1, (t[ns - 1].y - t[0].y) / n1, (t[ns - 1].z - t[0].z) / n1},
+                              t[0].w,
+                              (t[ns - 1].w - t[0].w) / n1};
+                bool lin = true;  // model within 1e-9 cycles per metre and 1e-15 s, as for the grouped readouts
+                for (int n = 0; n < ns && lin; ++n)
+                    lin = std::fabs(t[n].x - (ls.c0[0] + n * ls.dc[0])) <= 1e-9 &&
+                          std::fabs(t[n].y - (ls.c0[1] + n * ls.dc[1])) <= 1e-9 &&
+                          std::fabs(t[n].z - (ls.c0[2] + n * ls.dc[2])) <= 1e-9 &&
+                          std::fabs(t[n].w - (ls.tau0 + n * ls.dtau)) <= 1e-15;
+                if (lin) {
+                    ctx->clin[oi] = (int)ctx->clin_samp.size();
+                    ctx->clin_samp.push_back(ls);
+                }
             }
         }
         ALLOC(ctx->csamp, sizeof(double4) * std::max<size_t>(tab.size(), 1));
@@ -2175,10 +2198,15 @@ static int run_cached(gbs_ctx *ctx, char *ws, const float *m_init, float *m_out,
             a.coil_re = ctx->coil_re;
             a.coil_im = ctx->coil_im;
             a.n_coils = ctx->coil_re ? ctx->n_coils : 1;
-            HIPCHK(launch_direct_adc(a, agrid, ctx->stream));
+            const int lin = ctx->clin[oi];
+            const int sgrid = lin >= 0 ? std::min(adc_product_grid(K), agrid) : agrid;
+            if (lin >= 0)
+                HIPCHK(launch_adc_product(a, ctx->clin_samp[(size_t)lin], sgrid, ctx->stream));
+            else
+                HIPCHK(launch_direct_adc(a, sgrid, ctx->stream));
             for (int32_t p = 0; p < a.n_coils; ++p)  // partials of coil p: [grid][n_samples] block p
                 HIPCHK(launch_plain_finalize(
-                    ctx->partial + (size_t)p * agrid * a.n_samples, agrid, a.n_samples,
+                    ctx->partial + (size_t)p * sgrid * a.n_samples, sgrid, a.n_samples,
                     sig_out + 2 * ((int64_t)p * ctx->seq.total_samples + b.sample_offset + c.sample_lo), ctx->stream));
         } else {  // 2: cached transition (composed at first use); 4: final map
             const CachedOp &c = op.cached;

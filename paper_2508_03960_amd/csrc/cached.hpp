@@ -66,6 +66,18 @@ struct DirectAdcArgs {
 
 constexpr int kMaxCoils = 8;
 
+// The same samples when they are arithmetic in n: phase (c0 + n dc) . r +
+// (tau0 + n dtau) df, decay over tau0 + n dtau (k_adc_product).
+struct LinSamples {
+    double c0[3], dc[3], tau0, dtau;
+};
+// Samples from which the product is the faster one: its cost hardly falls below
+// 128 samples (2.1M isochromats: 297 us per 256 samples by k_direct_adc, which
+// is proportional to them).
+constexpr int kAdcProductMinSamples = 48;
+int adc_product_grid(int64_t K);
+hipError_t launch_adc_product(const DirectAdcArgs &a, const LinSamples &l, int grid, hipStream_t st);
+
 hipError_t launch_cached(const CachedArgs &a, int mode, hipStream_t st);
 int direct_adc_grid(int64_t K);
 hipError_t launch_direct_adc(const DirectAdcArgs &a, int grid, hipStream_t st);

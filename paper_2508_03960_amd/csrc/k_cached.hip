@@ -17,6 +17,10 @@
 // reduction runs per sample.  The phase is formed and reduced modulo one cycle
 // in FP64 and evaluated with the hardware sin/cos; the T2 decay uses the
 // hardware exp2.
+//
+// k_adc_product: the same for samples arithmetic in n, as a matrix product.
+#include <algorithm>
+
 #include "cached.hpp"
 #include "consts.hpp"
 #include "device_math.hpp"
@@ -239,6 +243,176 @@ __global__ __launch_bounds__(kAdcBlock) void k_direct_adc(DirectAdcArgs a) {
             a.partial[((int64_t)p * gridDim.x + blockIdx.x) * ns + t] = make_double2(re, im);
         }
     }
+}
+
+// ---------------------------------------------------------------- k_adc_product
+// Sample n = i + 16 j of isochromat k is A_i B_j with A_i = z^i, B_j = M f z^{16 j}
+// (z: phase and decay of one sample step, f: of the first sample), so up to 256
+// samples are a complex 16 x 16 product over the isochromats: two row tiles
+// {Re, Im} A_{0..7}, A_{8..15} and two column tiles {Re, Im} B_{0..7}, B_{8..15},
+// four v_mfma_f32_16x16x4_f32 per four isochromats (samples <= 128: two).  A
+// wavefront takes 32 isochromats at a time: lane l makes the 16 values of A
+// (l < 32) or B of isochromat l % 32, each directly (phase reduced in FP64,
+// hardware sin/cos and exp2, as k_direct_adc per sample), and leaves them in
+// LDS for the lanes of the product.  Per isochromat that is 32 evaluations in
+// place of 256; the rest is 32 cycles of the matrix core per SIMD.  FP32 sums of
+// at most 256 isochromats, then FP64, as in k_direct_adc.
+typedef float cached_f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kProdChunk = 32;
+constexpr int kProdFlush = 256 / kProdChunk;  // chunks whose terms add in FP32
+constexpr int kProdPad = 36;                  // floats per isochromat and side; 32 used (36: 16-byte rows, fewer bank conflicts)
+
+template <int NT>  // column tiles: 8 values of j each
+__global__ __launch_bounds__(256) void k_adc_product(DirectAdcArgs a, LinSamples l) {
+    __shared__ __attribute__((aligned(16))) float val[4][2][kProdChunk][kProdPad];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int i = lane & 15, kq = lane >> 4;
+    const int half = lane >> 5, mb = lane & 31;
+    const int64_t K = a.K;
+    const int coil = blockIdx.y;
+    const float *sre = a.coil_re ? a.coil_re + (int64_t)coil * K : nullptr;
+    const float *sim = a.coil_im ? a.coil_im + (int64_t)coil * K : nullptr;
+    const double tau0 = half ? l.tau0 : 0.0, dtau = half ? 16.0 * l.dtau : l.dtau;
+    cached_f32x4 d[2][NT];
+    double acc[2][NT][4];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int c = 0; c < NT; ++c) {
+            d[r][c] = cached_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[r][c][v] = 0.0;
+        }
+    auto flush = [&]() {
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int c = 0; c < NT; ++c) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[r][c][v] += (double)d[r][c][v];
+                d[r][c] = cached_f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+    };
+    const int64_t stride = (int64_t)gridDim.x * 4 * kProdChunk;
+    int64_t base = ((int64_t)blockIdx.x * 4 + wave) * kProdChunk;
+    // the next chunk's isochromats are loaded during this one's product
+    float x = 0.f, y = 0.f, z = 0.f, df = 0.f, t2 = 1.f, cr = 1.f, ci = 0.f;
+    double mx = 0.0, my = 0.0;
+    auto load = [&](int64_t b) {
+        const int64_t k = min(b + mb, K - 1);
+        x = a.ph.x[k];
+        y = a.ph.y[k];
+        z = a.ph.z[k];
+        df = a.ph.df[k];
+        t2 = a.ph.t2[k];
+        if (a.s64_in) {
+            mx = a.s64_in[k];
+            my = a.s64_in[K + k];
+        } else if (a.min_x) {
+            mx = a.min_x[k];
+            my = a.min_y[k];
+        }
+        if (sre) {
+            cr = sre[k];
+            ci = sim[k];
+        }
+    };
+    if (base < K) load(base);
+    for (int n = 1; base < K; base += stride, ++n) {
+        const double step = fma(l.dc[0], (double)x, fma(l.dc[1], (double)y, fma(l.dc[2], (double)z, l.dtau * (double)df)));
+        const double first = fma(l.c0[0], (double)x, fma(l.c0[1], (double)y, fma(l.c0[2], (double)z, l.tau0 * (double)df)));
+        double p0 = half ? first - rint(first) : 0.0, dp = step - rint(step);
+        if (half) {
+            dp *= 16.0;
+            dp -= rint(dp);
+        }
+        const double r2 = -kLog2e / (double)t2;
+        const float e0 = (float)(tau0 * r2), de = (float)(dtau * r2);
+        // the factor of every value of this side: 1 (A), or M S (B; 0 past the end)
+        float wr = 1.f, wi = 0.f;
+        if (half) {
+            wr = base + mb < K ? (float)mx : 0.f;
+            wi = base + mb < K ? (float)my : 0.f;
+            if (sre) {
+                const float t = wr * cr - wi * ci;
+                wi = wr * ci + wi * cr;
+                wr = t;
+            }
+        }
+        float4 *out = (float4 *)val[wave][half][mb];
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+            float o[4];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                float s, c;
+                sincos_rev(fma((double)(e + q), dp, p0), &s, &c);
+                const float g = __builtin_amdgcn_exp2f(fmaf((float)(e + q), de, e0));
+                const float ur = g * wr, ui = g * wi;
+                o[2 * q] = fmaf(ur, c, ui * s);  // (wr + i wi) g (c - i s)
+                o[2 * q + 1] = fmaf(ui, c, -ur * s);
+            }
+            out[e / 2] = make_float4(o[0], o[1], o[2], o[3]);
+        }
+        if (base + stride < K) load(base + stride);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int t = 0; t < kProdChunk / 4; ++t) {
+            const float *pa = val[wave][0][4 * t + kq], *pb = val[wave][1][4 * t + kq];
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int c = 0; c < NT; ++c)
+                    d[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(pa[16 * r + i], pb[16 * c + i], d[r][c], 0, 0, 0);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (n % kProdFlush == 0) flush();
+    }
+    flush();
+    // Element v of tile (r, c): row 4 kq + v = {Re, Im} A_{8 r + 2 kq + v / 2}, column
+    // i = {Re, Im} B_{8 c + i / 2}.  The neighbouring lane holds the other part of B.
+    double2 *sum = (double2 *)val;  // [wave][sample]
+    __syncthreads();
+    const bool odd = lane & 1;
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int c = 0; c < NT; ++c)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const double re = acc[r][c][2 * u], im = acc[r][c][2 * u + 1];  // Re A x, Im A x (x: this lane's part of B)
+                const double ore = dpp_f64<0xb1>(re), oim = dpp_f64<0xb1>(im);
+                if (!odd)
+                    sum[256 * wave + 8 * r + 2 * kq + u + 16 * (8 * c + (i >> 1))] = make_double2(re - oim, im + ore);
+            }
+    __syncthreads();
+    for (int n = threadIdx.x; n < a.n_samples; n += 256) {
+        double sr = 0.0, si = 0.0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            sr += sum[256 * w + n].x;
+            si += sum[256 * w + n].y;
+        }
+        a.partial[((int64_t)coil * gridDim.x + blockIdx.x) * a.n_samples + n] = make_double2(sr, si);
+    }
+}
+
+// Four workgroups per CU fill the chip; fewer partial sums than k_direct_adc's.
+int adc_product_grid(int64_t K) {
+    const int64_t blocks = (K + 4 * kProdChunk - 1) / (4 * kProdChunk);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(blocks, 1024));
+}
+
+hipError_t launch_adc_product(const DirectAdcArgs &a, const LinSamples &l, int grid, hipStream_t st) {
+    static_assert(sizeof(float) * 4 * 2 * kProdChunk * kProdPad >= sizeof(double2) * 4 * 256, "sums fit the values' LDS");
+    if (a.n_samples < 1 || a.n_samples > 256 || grid < 1 || grid > kAdcMaxGrid || a.K < 1) return hipErrorInvalidValue;
+    if (!a.coil_re != !a.coil_im || a.n_coils < 1 || a.n_coils > kMaxCoils) return hipErrorInvalidValue;
+    const dim3 g((unsigned)grid, (unsigned)a.n_coils);
+    if (a.n_samples <= 128)
+        hipLaunchKernelGGL(k_adc_product<1>, g, dim3(256), 0, st, a, l);
+    else
+        hipLaunchKernelGGL(k_adc_product<2>, g, dim3(256), 0, st, a, l);
+    return hipGetLastError();
 }
 
 hipError_t launch_cached(const CachedArgs &a, int mode, hipStream_t st) {

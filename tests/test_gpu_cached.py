@@ -133,3 +133,43 @@ def test_cached_agrees_with_grouped_and_plain(gb):
         dm, rel = errors(Mc, sc, M, s)
         say(f"[gpu] cached vs {name}: max|dM|={dm:.3e} rel_sig={rel:.3e}")
         assert dm <= DM_TOL and rel <= SIG_TOL
+
+
+@pytest.mark.parametrize("n_read,k,coils", [
+    (47, 40, 1), (48, 1, 1), (48, 31, 1), (49, 32, 2), (127, 33, 1), (128, 127, 1), (129, 128, 3), (255, 129, 1),
+    (256, 640, 1), (300, 65, 8),
+])
+def test_cached_readout_products(gb, n_read, k, coils):
+    """Arithmetic readouts as matrix products: samples and isochromats around
+    the edges of the tiles and chunks, all three gradients, from an initial
+    state and after a transition; per readout and coil."""
+    import torch
+    rng = np.random.default_rng(n_read + k)
+    ph = synth.gre_phantom(k, 1, 1, seed=k)
+    ph.y, ph.z = (rng.uniform(-0.05, 0.05, k).astype(np.float32) for _ in range(2))
+    ph.m0 = rng.uniform(0.2, 1.0, k).astype(np.float32)
+    sb = SeqBuilder(1e-6, "products")
+    sb.adc(2 * n_read, (3e-3, -2e-3, 1e-3), 2 * np.arange(n_read) + 1)
+    sb.rf(synth.sinc_pulse(60, 1e-6, 0.9), (0, 0, 0.01))
+    sb.relax(1e-3, (-1e-8, 2e-8, 0.0))
+    sb.adc(3 * n_read, (0.0, 1e-3, 0.0), 3 * np.arange(n_read))
+    seq = sb.build()
+    m_init = rng.uniform(-0.5, 0.5, (3, k)).astype(np.float32)
+    sens = (rng.uniform(0.5, 1.0, (coils, k)) * np.exp(1j * rng.uniform(-3, 3, (coils, k)))).astype(np.complex64)
+    if coils > 1:
+        Mr, sr = oracle.simulate_coils(ph, seq, sens, m_init=m_init)
+    else:
+        Mr, sr = oracle.simulate(ph, seq, m_init=m_init)
+    sim = gb.Simulator(0)
+    sim.set_phantom(ph)
+    sim.set_sequence(seq)
+    if coils > 1:
+        sim.set_coils(sens)
+    M, s = sim.simulate(gb.GBS_CACHED, m_init=torch.from_numpy(m_init))
+    torch.cuda.synchronize()
+    a, b = s.cpu().numpy().reshape(-1, n_read), np.asarray(sr).reshape(-1, n_read)
+    rel = np.linalg.norm(a - b, axis=1) / np.linalg.norm(b, axis=1)
+    dm = float(np.max(np.abs(M.cpu().numpy() - Mr)))
+    sim.close()
+    say(f"[gpu] cached products: n={n_read} K={k} P={coils} max|dM|={dm:.2e} rel {rel.max():.2e}")
+    assert dm <= DM_TOL and rel.max() <= SIG_TOL
