@@ -1200,11 +1200,11 @@ static int build_grouped_plan(gbs_ctx *ctx) {
         }
         if (r.axis == kTissueAxis) {  // no gradients: the coordinate column of the table is unused
             rj[i] = RfJobDev{0, (int32_t)r.n_steps, ctx->n_tissue, ctx->d_wave.as<StepW>() + r.step_offset,
-                             ctx->ttab.as<float4>(), (double *)tb(comp_off[i])};
+                             ctx->ttab.as<float4>(), (double *)tb(comp_off[i]), r.sym};
             continue;
         }
         rj[i] = RfJobDev{r.axis, (int32_t)r.n_steps, ctx->ng[r.axis], ctx->d_wave.as<StepW>() + r.step_offset,
-                         ctx->gtab[r.axis].as<float4>(), (double *)tb(g.rf_off[i])};
+                         ctx->gtab[r.axis].as<float4>(), (double *)tb(g.rf_off[i]), r.sym};
     }
     std::vector<RfJobDev> rj_surr(rj);  // GBS_SURROGATE: the network's transition is not composed
     if (g.surr_rf >= 0) rj_surr[g.surr_rf].n_groups = 0;
@@ -1870,7 +1870,7 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
     for (const auto &pj : g.pair_jobs) {
         const RfJob &r = plan.rf[pj.second];
         HIPCHK(launch_compose_pair(ctx->n_runs, ctx->rtab.as<float4>(), ctx->rz.as<float>(),
-                                   ctx->d_wave.as<StepW>() + r.step_offset, (int32_t)r.n_steps, s.dt,
+                                   ctx->d_wave.as<StepW>() + r.step_offset, (int32_t)r.n_steps, s.dt, r.sym,
                                    (double *)(tb + pj.first), ctx->stream));
     }
     for (const auto &e : g.expand)
@@ -2239,6 +2239,7 @@ static int run_cached(gbs_ctx *ctx, char *ws, const float *m_init, float *m_out,
                 mode = c.compose ? kCacheCompose : kCacheApply;
                 a.wave = ctx->d_wave.as<StepW>() + b.step_offset;
                 a.n_steps = (int32_t)b.n_steps;
+                a.sym = plan.rf[c.entry].sym;
             }
             if (mode == kCacheCompose && surr && c.entry == ctx->csurr_entry) {
                 // the network fills the entry for every isochromat; n_check of

@@ -38,6 +38,7 @@ struct CachedArgs {
     float4 *cache;      // rows [3][K] of the entry (apply, compose)
     const StepW *wave;  // compose: first raster step of the block
     int32_t n_steps;    // compose
+    WaveSym sym;        // compose
     double dt;
     double gdt;  // gamma * dt (rad / T)
     // optional: the launch does nothing unless *gate == gate_value (a device

@@ -5,7 +5,8 @@
 // its 3x4 homogeneous transition [A | b] (M' = A M + b M0) by D R for every
 // raster step of the block in FP64 (Eq. 7 with U = D R of Eq. A1, A2; the
 // step's waveform values are wave-uniform scalar loads), rounds it to FP32
-// into the cache and applies it.  Later occurrences of the same waveform read
+// into the cache and applies it (half the steps for symmetric pulses,
+// compose.hpp).  Later occurrences of the same waveform read
 // the 48 cached bytes instead (dynamic caching).  The state between operations
 // is FP64, 24 bytes per isochromat.
 //
@@ -22,6 +23,7 @@
 #include <algorithm>
 
 #include "cached.hpp"
+#include "compose.hpp"
 #include "consts.hpp"
 #include "device_math.hpp"
 #include "rotation.hpp"
@@ -76,52 +78,21 @@ __global__ __launch_bounds__(kCachedBlock) void k_cached(CachedArgs a) {
         vy = ny;
         vz = nz;
     } else if (MODE == kCacheCompose) {
-        const double X = a.ph.x[k], Y = a.ph.y[k], Z = a.ph.z[k];
-        const double boff = (double)a.ph.df[k] / kGammaBar;  // off-resonance as a field (T)
         const double t1 = a.ph.t1[k], t2 = a.ph.t2[k];
-        const double e1 = exp(-a.dt / t1), e2 = exp(-a.dt / t2), e1m = -expm1(-a.dt / t1);
-        const double gdt = a.gdt, k2 = gdt * gdt;
-        // T = [A | b], starting from the identity map
-        double T[3][4] = {{1.0, 0.0, 0.0, 0.0}, {0.0, 1.0, 0.0, 0.0}, {0.0, 0.0, 1.0, 0.0}}, U[3][4];
-        const StepW *__restrict__ wave = a.wave;
-        // V = (D R)_j V0 for raster step j, then the T1 recovery toward M0
-        auto step = [&](const double (&V0)[3][4], double (&V)[3][4], int j) {
-            const StepW w = wave[j];
-            const double bx = w.b1r, by = w.b1i;
-            const double bz = fma((double)w.gx, X, fma((double)w.gy, Y, fma((double)w.gz, Z, boff)));
-            const double B2 = fma(bx, bx, fma(by, by, bz * bz));
-            double ca, cb;  // R = (1 - cb |B|^2) I + ca [B]x + cb B B^T
-            rot_coeffs(B2, gdt, k2, ca, cb);
-            const double c0 = fma(-cb, B2, 1.0);
-            const double qx = cb * bx, qy = cb * by, qz = cb * bz;
-            const double pxy = qx * by, pxz = qx * bz, pyz = qy * bz;
-            const double sx = ca * bx, sy = ca * by, sz = ca * bz;
-            // rows of D R: transverse rows decay by E2, the z row by E1
-            const double r00 = e2 * fma(qx, bx, c0), r01 = e2 * (pxy - sz), r02 = e2 * (pxz + sy);
-            const double r10 = e2 * (pxy + sz), r11 = e2 * fma(qy, by, c0), r12 = e2 * (pyz - sx);
-            const double r20 = e1 * (pxz - sy), r21 = e1 * (pyz + sx), r22 = e1 * fma(qz, bz, c0);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const double u0 = V0[0][c], u1 = V0[1][c], u2 = V0[2][c];
-                V[0][c] = fma(r00, u0, fma(r01, u1, r02 * u2));
-                V[1][c] = fma(r10, u0, fma(r11, u1, r12 * u2));
-                V[2][c] = fma(r20, u0, fma(r21, u1, r22 * u2));
-            }
-            V[2][3] += e1m;
-        };
-        // two steps per iteration, T -> U -> T, so that the loop carries no
-        // register copies of the twelve entries
-        int j = 0;
-        for (; j + 1 < a.n_steps; j += 2) {
-            step(T, U, j);
-            step(U, T, j + 1);
-        }
-        if (j < a.n_steps) {
-            step(T, U, j);
+        // (off-resonance as a field, T)
+        const StepConst c{a.ph.x[k], a.ph.y[k], a.ph.z[k], (double)a.ph.df[k] / kGammaBar, exp(-a.dt / t1), exp(-a.dt / t2),
+                          -expm1(-a.dt / t1), a.gdt, a.gdt * a.gdt};
+        Stretch st;
+        double T[3][4];
+        if (a.sym.sym && __all(can_mirror(c))) {
+            compose_steps<true>(c, a.wave, 0, a.n_steps / 2, st);
+            finish_mirrored(c, a.wave[a.n_steps / 2], a.n_steps, a.sym.nx, a.sym.ny, st, T);
+        } else {
+            compose_steps<false>(c, a.wave, 0, a.n_steps, st);
 #pragma unroll
             for (int r = 0; r < 3; ++r)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) T[r][c] = U[r][c];
+                for (int q = 0; q < 4; ++q) T[r][q] = st.a[r][q];
         }
         a.cache[k] = make_float4((float)T[0][0], (float)T[0][1], (float)T[0][2], (float)T[0][3]);
         a.cache[K + k] = make_float4((float)T[1][0], (float)T[1][1], (float)T[1][2], (float)T[1][3]);

@@ -3,7 +3,8 @@
 //  k_compose   combined transition T = U_{N-1} ... U_0 (Eq. 7) once per group,
 //              FP64.  One wavefront per group: each lane composes a contiguous
 //              chunk of steps, then the 64 partial products are combined in a
-//              log2 tree through LDS (later chunk on the left).
+//              log2 tree through LDS (later chunk on the left).  Symmetric
+//              pulses take half the steps (compose.hpp).
 //  k_fold      per operation, T' = T o P with the tissue part and the
 //              own-axis phase of the preceding B1 = 0 map P (Eq. 4, 5), FP64,
 //              rounded once to FP32.
@@ -21,6 +22,7 @@
 //              does not start it from (0, 0, M0) itself) and back into the
 //              caller's order (from the last sweep's 16-byte rows, or from the
 //              per-component arrays after plain stepping).
+#include "compose.hpp"
 #include "device_math.hpp"
 #include "kernels.hpp"
 #include "rotation.hpp"
@@ -55,7 +57,7 @@ __device__ __forceinline__ void aff_compose(const Aff &L, const Aff &R, Aff &r) 
 }
 
 __global__ __launch_bounds__(256) void k_compose(const RfJobDev *__restrict__ jobs, double dt) {
-    __shared__ double lds[kComposeGroupsPerWG][64][12];
+    __shared__ double lds[kComposeGroupsPerWG][64][15];  // A, b, sum of the partial products' z rows
     const RfJobDev j = jobs[blockIdx.y];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t g = (int64_t)blockIdx.x * kComposeGroupsPerWG + wave;
@@ -65,13 +67,15 @@ __global__ __launch_bounds__(256) void k_compose(const RfJobDev *__restrict__ jo
     const double boff = (double)p.w / kGammaBar;
     const double e1 = exp(-dt / t1), e2 = exp(-dt / t2);
     const double gdt = kTwoPi * kGammaBar * dt, k2 = gdt * gdt;
-    const int n = j.n_steps;
+    const StepConst sc{coord, 0.0, 0.0, boff, e1, e2, -expm1(-dt / t1), gdt, k2};
+    const bool half = j.sym.sym && can_mirror(sc);  // one group per wavefront: uniform
+    const int n = half ? j.n_steps / 2 : j.n_steps;
     const int lo = (int)(((int64_t)n * lane) >> 6), hi = (int)(((int64_t)n * (lane + 1)) >> 6);
     // (B1 re, B1 im, gradient on the job's axis) of step s, through the
     // global address space, the index clamped into the waveform
     const int gcol = 3 + j.axis;  // gx, gy, gz follow b1r, b1i, b1sq in StepW
     auto step_in = [&](int s) {
-        const compose_gf32 w = (compose_gf32)(j.wave + min(s, n - 1));
+        const compose_gf32 w = (compose_gf32)(j.wave + min(s, j.n_steps - 1));
         return make_float3(w[0], w[1], w[gcol]);
     };
     // U = D R (Eq. A1, Eq. A2) with R = (1 - cb |B|^2) I + ca [B]x + cb B B^T,
@@ -104,6 +108,12 @@ __global__ __launch_bounds__(256) void k_compose(const RfJobDev *__restrict__ jo
     // and T2 for the same reason.
     Aff T, T2, U;
     aff_identity(T);
+    double z0 = 0.0, z1 = 0.0, z2 = 0.0;
+    auto rows = [&](const Aff &t) {
+        z0 += t.a[6];
+        z1 += t.a[7];
+        z2 += t.a[8];
+    };
     float3 w0, w1, w2, w3;
     if (lo < hi) {
         w0 = step_in(lo);
@@ -115,19 +125,24 @@ __global__ __launch_bounds__(256) void k_compose(const RfJobDev *__restrict__ jo
     for (; s + 4 <= hi; s += 4) {
         step_u(w0, U);
         w0 = step_in(s + 4);
+        rows(T);
         aff_compose(U, T, T2);
         step_u(w1, U);
         w1 = step_in(s + 5);
+        rows(T2);
         aff_compose(U, T2, T);
         step_u(w2, U);
         w2 = step_in(s + 6);
+        rows(T);
         aff_compose(U, T, T2);
         step_u(w3, U);
         w3 = step_in(s + 7);
+        rows(T2);
         aff_compose(U, T2, T);
     }
     for (int k = 0; s < hi; ++s, ++k) {  // the last one to three steps
         step_u(k == 0 ? w0 : (k == 1 ? w1 : w2), U);
+        rows(T);
         aff_compose(U, T, T2);
         T = T2;
     }
@@ -136,9 +151,13 @@ __global__ __launch_bounds__(256) void k_compose(const RfJobDev *__restrict__ jo
     lds[wave][lane][9] = T.b[0];
     lds[wave][lane][10] = T.b[1];
     lds[wave][lane][11] = T.b[2];
+    lds[wave][lane][12] = z0;
+    lds[wave][lane][13] = z1;
+    lds[wave][lane][14] = z2;
     __syncthreads();
     for (int d = 1; d < 64; d <<= 1) {
         Aff L, R, r;
+        double zr[3];
         const bool doit = (lane & (2 * d - 1)) == 0;
         if (doit) {
 #pragma unroll
@@ -151,6 +170,10 @@ __global__ __launch_bounds__(256) void k_compose(const RfJobDev *__restrict__ jo
                 R.b[i] = lds[wave][lane][9 + i];
                 L.b[i] = lds[wave][lane + d][9 + i];
             }
+            const double *lz = &lds[wave][lane + d][12];
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                zr[i] = lds[wave][lane][12 + i] + (lz[0] * R.a[i] + lz[1] * R.a[3 + i] + lz[2] * R.a[6 + i]);
             aff_compose(L, R, r);
         }
         __syncthreads();
@@ -158,10 +181,36 @@ __global__ __launch_bounds__(256) void k_compose(const RfJobDev *__restrict__ jo
 #pragma unroll
             for (int i = 0; i < 9; ++i) lds[wave][lane][i] = r.a[i];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) lds[wave][lane][9 + i] = r.b[i];
+            for (int i = 0; i < 3; ++i) {
+                lds[wave][lane][9 + i] = r.b[i];
+                lds[wave][lane][12 + i] = zr[i];
+            }
         }
         __syncthreads();
     }
+    if (half && lane == 0) {  // the second half of a symmetric pulse
+        const double *t = lds[wave][0];
+        Stretch p;
+        double o[3][4];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) p.a[i / 3][i % 3] = t[i];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            p.a[i][3] = t[9 + i];
+            p.s[i] = t[12 + i];
+        }
+        StepW mid{};  // the field of the middle step as step_u takes it: the job's axis alone
+        const float3 w = step_in(n);
+        mid.b1r = w.x;
+        mid.b1i = w.y;
+        mid.gx = w.z;
+        finish_mirrored(sc, mid, j.n_steps, j.sym.nx, j.sym.ny, p, o);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) lds[wave][0][i] = o[i / 3][i % 3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) lds[wave][0][9 + i] = o[i][3];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     if (act && lane < 12) j.out[12 * g + lane] = lds[wave][0][lane];
 }
 

@@ -1,10 +1,14 @@
 // Two-axis (x, z) groups on gfx950: the runs of the group-sorted layout and
 // one combined transition per run for Gx+Gz with-RF subsequences.
 //
-// k_compose_pair: one thread per run composes its 3x4 homogeneous transition
-// in FP64 (the same product as the per-isochromat composition of the cached
-// method, with the run's x, z, T1, T2, dB0); the step's waveform values are
-// wave-uniform scalar loads.
+// k_compose_pair: 64 runs per workgroup, one per lane; each wavefront composes a
+// segment of the steps in FP64 (the same step as the per-isochromat composition
+// of the cached method, with the run's x, z, T1, T2, dB0; the waveform values
+// are wave-uniform scalar loads), and the first one multiplies the segments.
+// The steps are a serial chain of FP64 latencies: with one wavefront per 64 runs
+// 57,000 runs leave one wavefront per SIMD (1.00 ms for 3000 steps); segments
+// give each SIMD several.  Symmetric pulses take half the steps (compose.hpp).
+#include "compose.hpp"
 #include "consts.hpp"
 #include "pairs.hpp"
 #include "rotation.hpp"
@@ -23,61 +27,67 @@ __global__ void k_run_table(int64_t n_runs, const int32_t *__restrict__ first, c
     }
 }
 
-__global__ __launch_bounds__(256) void k_compose_pair(int64_t n_runs, const float4 *__restrict__ rtab,
-                                                      const float *__restrict__ rz, const StepW *__restrict__ wave,
-                                                      int32_t n_steps, double dt, double *__restrict__ out) {
-    const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (r >= n_runs) return;
+__device__ __forceinline__ void pair_segment(const StepConst &c, const StepW *wave, int n, bool half, int seg, int S,
+                                            Stretch &t) {
+    const int m = half ? n / 2 : n;
+    const int lo = (int)((int64_t)m * seg / S), hi = (int)((int64_t)m * (seg + 1) / S);
+    if (half)
+        compose_steps<true>(c, wave, lo, hi, t);
+    else
+        compose_steps<false>(c, wave, lo, hi, t);
+}
+
+__global__ __launch_bounds__(512) void k_compose_pair(int64_t n_runs, const float4 *__restrict__ rtab,
+                                                       const float *__restrict__ rz, const StepW *__restrict__ wave,
+                                                       int32_t n_steps, double dt, WaveSym sym, double *__restrict__ out) {
+    extern __shared__ double seg_sum[];  // [segment - 1][15][lane]
+    const int seg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, S = blockDim.x >> 6;
+    const int64_t r0 = (int64_t)blockIdx.x * 64 + lane, r = r0 < n_runs ? r0 : n_runs - 1;
     const float4 g = rtab[r];
-    const double X = g.x, Z = rz[r], t1 = g.y, t2 = g.z;
-    const double boff = (double)g.w / kGammaBar;
-    const double e1 = exp(-dt / t1), e2 = exp(-dt / t2), e1m = -expm1(-dt / t1);
-    const double gdt = kTwoPi * kGammaBar * dt, k2 = gdt * gdt;
-    double T[3][4] = {{1.0, 0.0, 0.0, 0.0}, {0.0, 1.0, 0.0, 0.0}, {0.0, 0.0, 1.0, 0.0}}, U[3][4];
-    // V = (D R)_j V0 for raster step j, then the T1 recovery toward M0
-    auto step = [&](const double (&V0)[3][4], double (&V)[3][4], int j) {
-        const StepW w = wave[j];
-        const double bx = w.b1r, by = w.b1i;
-        const double bz = fma((double)w.gx, X, fma((double)w.gz, Z, boff));
-        const double B2 = fma(bx, bx, fma(by, by, bz * bz));
-        double ca, cb;  // R = (1 - cb |B|^2) I + ca [B]x + cb B B^T
-        rot_coeffs(B2, gdt, k2, ca, cb);
-        const double c0 = fma(-cb, B2, 1.0);
-        const double qx = cb * bx, qy = cb * by, qz = cb * bz;
-        const double pxy = qx * by, pxz = qx * bz, pyz = qy * bz;
-        const double sx = ca * bx, sy = ca * by, sz = ca * bz;
-        // rows of D R: transverse rows decay by E2, the z row by E1
-        const double r00 = e2 * fma(qx, bx, c0), r01 = e2 * (pxy - sz), r02 = e2 * (pxz + sy);
-        const double r10 = e2 * (pxy + sz), r11 = e2 * fma(qy, by, c0), r12 = e2 * (pyz - sx);
-        const double r20 = e1 * (pxz - sy), r21 = e1 * (pyz + sx), r22 = e1 * fma(qz, bz, c0);
+    const double t1 = g.y, t2 = g.z;
+    const double gdt = kTwoPi * kGammaBar * dt;
+    const StepConst c{g.x, 0.0, rz[r], (double)g.w / kGammaBar, exp(-dt / t1), exp(-dt / t2), -expm1(-dt / t1), gdt,
+                      gdt * gdt};
+    const bool half = sym.sym && __all(can_mirror(c));  // (the same in all wavefronts: they hold the same runs)
+    Stretch t;
+    pair_segment(c, wave, n_steps, half, seg, S, t);
+    if (S > 1) {
+        double *mine = seg_sum + (int64_t)(seg - 1) * 15 * 64 + lane;
+        if (seg > 0) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const double u0 = V0[0][c], u1 = V0[1][c], u2 = V0[2][c];
-            V[0][c] = fma(r00, u0, fma(r01, u1, r02 * u2));
-            V[1][c] = fma(r10, u0, fma(r11, u1, r12 * u2));
-            V[2][c] = fma(r20, u0, fma(r21, u1, r22 * u2));
+            for (int i = 0; i < 12; ++i) mine[64 * i] = t.a[i / 4][i % 4];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) mine[64 * (12 + i)] = t.s[i];
         }
-        V[2][3] += e1m;
-    };
-    // two steps per iteration, T -> U -> T: the loop carries no register
-    // copies of the twelve entries
-    int j = 0;
-    for (; j + 1 < n_steps; j += 2) {
-        step(T, U, j);
-        step(U, T, j + 1);
+        __syncthreads();
+        if (seg > 0) return;
+        for (int q = 1; q < S; ++q) {  // the later segment on the left
+            const double *o = seg_sum + (int64_t)(q - 1) * 15 * 64 + lane;
+            double L[3][4], R[3][4];
+#pragma unroll
+            for (int i = 0; i < 12; ++i) {
+                L[i / 4][i % 4] = o[64 * i];
+                R[i / 4][i % 4] = t.a[i / 4][i % 4];
+            }
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                t.s[k] += o[64 * 12] * R[0][k] + o[64 * 13] * R[1][k] + o[64 * 14] * R[2][k];
+            compose_after(L, R, t.a);
+        }
     }
-    if (j < n_steps) {
-        step(T, U, j);
+    if (r0 >= n_runs) return;
+    double T[3][4];
+    if (half) {
+        finish_mirrored(c, wave[n_steps / 2], n_steps, sym.nx, sym.ny, t, T);
+    } else {
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) T[i][c] = U[i][c];
+        for (int i = 0; i < 12; ++i) T[i / 4][i % 4] = t.a[i / 4][i % 4];
     }
     double *o = out + 12 * r;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) o[3 * i + c] = T[i][c];
+        for (int k = 0; k < 3; ++k) o[3 * i + k] = T[i][k];
         o[9 + i] = T[i][3];
     }
 }
@@ -98,12 +108,15 @@ hipError_t launch_run_table(int64_t n_runs, const int32_t *first, const float *x
 }
 
 hipError_t launch_compose_pair(int64_t n_runs, const float4 *rtab, const float *rz, const StepW *wave,
-                               int32_t n_steps, double dt, double *out, hipStream_t st) {
+                               int32_t n_steps, double dt, const WaveSym &sym, double *out, hipStream_t st) {
     if (n_runs <= 0) return hipSuccess;
-    const int64_t blocks = (n_runs + 255) / 256;
+    const int64_t blocks = (n_runs + 63) / 64;
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_compose_pair, dim3((unsigned)blocks), dim3(256), 0, st, n_runs, rtab, rz, wave, n_steps,
-                       dt, out);
+    int S = 1;  // segments: up to 8, until there are four wavefronts per SIMD, each with at least 32 steps
+    while (S < 8 && blocks * S < 4096 && n_steps / (4 * S) >= 32) S *= 2;
+    const size_t lds = sizeof(double) * 15 * 64 * (size_t)(S - 1);
+    hipLaunchKernelGGL(k_compose_pair, dim3((unsigned)blocks), dim3(64 * S), lds, st, n_runs, rtab, rz, wave, n_steps, dt,
+                       sym, out);
     return hipGetLastError();
 }
 

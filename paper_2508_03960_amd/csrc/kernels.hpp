@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "wavesym.hpp"
+
 namespace gbs {
 
 // One raster step of the sequence as the kernels read it (32 bytes, so a
@@ -172,6 +174,7 @@ struct RfJobDev {
     const StepW *wave;
     const float4 *gtab;  // (coord, T1, T2, df) per group
     double *out;         // 12 doubles (A row-major, b) per group
+    WaveSym sym;
 };
 
 // T' = T o P for one operation: P is the tissue part (decay, off-resonance,

@@ -18,6 +18,6 @@ hipError_t launch_run_table(int64_t n_runs, const int32_t *first, const float *x
 // T = U_{N-1} ... U_0 (Eq. 7, U = D R of Eq. A1, A2) per run in FP64, with
 // B_z = Gx x + Gz z + dB0: 12 doubles per run (A row-major, then b)
 hipError_t launch_compose_pair(int64_t n_runs, const float4 *rtab, const float *rz, const StepW *wave,
-                               int32_t n_steps, double dt, double *out, hipStream_t st);
+                               int32_t n_steps, double dt, const WaveSym &sym, double *out, hipStream_t st);
 
 }  // namespace gbs

@@ -149,6 +149,26 @@ static void add_step_ops(Plan &p, const HostSeq &s, int64_t b, const Map &pre, b
     }
 }
 
+WaveSym symmetric_pulse(const HostSeq &s, int64_t offset, int64_t n) {
+    const float *w[5] = {s.rf_re.data() + offset, s.rf_im.data() + offset, s.gx.data() + offset, s.gy.data() + offset,
+                         s.gz.data() + offset};
+    double peak = 0.0, re = 1.0, im = 0.0;
+    for (int64_t j = 0; j < n; ++j) {
+        for (const float *v : w)
+            if (v[j] != v[n - 1 - j]) return WaveSym{0, 0, 0.0, 0.0};
+        const double m = std::hypot((double)w[0][j], (double)w[1][j]);
+        if (m > peak) {
+            peak = m;
+            re = w[0][j] / m;
+            im = w[1][j] / m;
+        }
+    }
+    // out of plane by less than rounding of the FP64 products
+    for (int64_t j = 0; j < n; ++j)
+        if (std::fabs(re * w[1][j] - im * w[0][j]) > 1e-15 * peak) return WaveSym{0, 0, 0.0, 0.0};
+    return WaveSym{1, 0, -im, re};
+}
+
 Plan plan_plain(const HostSeq &s, int32_t max_samples) {
     Plan p;
     Map P;
@@ -205,7 +225,7 @@ static int rf_lookup(Plan &p, std::vector<uint64_t> &hashes, const HostSeq &s, i
         }
         if (same) return (int)i;
     }
-    p.rf.push_back(RfJob{axis, k.step_offset, k.n_steps});
+    p.rf.push_back(RfJob{axis, k.step_offset, k.n_steps, symmetric_pulse(s, k.step_offset, k.n_steps)});
     hashes.push_back(h);
     return (int)p.rf.size() - 1;
 }

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "gbloch.h"
+#include "wavesym.hpp"
 
 namespace gbs {
 
@@ -104,6 +105,7 @@ struct Op {
 struct RfJob {  // one distinct combined transition (Eq. 7) per group of `axis` (or kTissueAxis)
     int axis;
     int64_t step_offset, n_steps;
+    WaveSym sym;  // symmetric_pulse
 };
 
 struct AdcJob {  // one grouped with-ADC subsequence (Eq. 8-10)
@@ -121,6 +123,10 @@ struct Plan {
     int64_t n_passes = 0, n_emit_only = 0;
     int64_t n_rf_cached = 0, n_adc_direct = 0;  // plan_cached
 };
+
+// Steps [offset, offset + n) of a waveform: symmetric in time, bit for bit, with
+// B1 in one plane through the z axis?
+WaveSym symmetric_pulse(const HostSeq &s, int64_t offset, int64_t n);
 
 // Largest number of ADC samples one stepping launch accumulates (LDS bound).
 constexpr int32_t kMaxSamplesPerLaunch = 256;

@@ -173,3 +173,53 @@ def test_cached_readout_products(gb, n_read, k, coils):
     sim.close()
     say(f"[gpu] cached products: n={n_read} K={k} P={coils} max|dM|={dm:.2e} rel {rel.max():.2e}")
     assert dm <= DM_TOL and rel.max() <= SIG_TOL
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 8, 63, 64, 65, 400, 401])
+@pytest.mark.parametrize("form", ["x", "y", "phase", "ramped", "two lobes", "shifted", "chirp", "short T"])
+def test_symmetric_pulses(gb, n, form):
+    """Transitions from half the steps (pulses symmetric in time with one B1
+    phase) and from all of them, one pulse from a random state, cached and
+    grouped (Gz alone, and Gx with Gz).  Bars: the FP64 transition acts on the
+    FP64 state in the cached mode, so M errs by its FP32 output, 6e-8 of 1; the
+    grouped mode rounds the transition's entries to FP32 (four terms, 2.4e-7)."""
+    import torch
+    rng = np.random.default_rng(n)
+    k = 300
+    ph = synth.gre_phantom(15, 5, 4, seed=n)
+    ph.m0 = rng.uniform(0.2, 1.0, k).astype(np.float32)
+    ph.t1[7] = ph.t2[7] = np.inf
+    if form == "short T":  # a raster step and less: the second half cannot come from the first
+        ph.t1[::3] = 5e-7
+        ph.t2[::3] = 3e-7
+    rf = synth.sinc_pulse(n, 1e-6, np.deg2rad(110.0))
+    gz = np.full(n, 0.02)
+    if form == "y":
+        rf = synth.sinc_pulse(n, 1e-6, np.deg2rad(110.0), phase=np.pi / 2)
+    elif form == "phase":
+        rf = rf * np.exp(1.1j)
+    elif form == "ramped":
+        gz = 0.02 * np.minimum(1.0, np.minimum(np.arange(n) + 1, np.arange(n, 0, -1)) / 10.0)
+    elif form == "two lobes":
+        rf = rf * np.cos(np.linspace(-3, 3, n)) if n > 1 else rf
+    elif form == "shifted":
+        rf = np.roll(rf, 1)
+    elif form == "chirp":
+        rf = rf * np.exp(1j * np.linspace(-1, 1, n) ** 2)
+    m_init = rng.uniform(-0.55, 0.55, (3, k)).astype(np.float32)
+    for g in ((0.0, 0.0, gz), (0.3 * gz, 0.0, gz)):
+        sb = SeqBuilder(1e-6, form)
+        sb.rf(rf, g)
+        seq = sb.build()
+        Mr, _ = oracle.simulate(ph, seq, m_init=m_init)
+        for mode, bar in ((gb.GBS_CACHED, 2e-7), (gb.GBS_GROUPED, 6e-7)):
+            sim = gb.Simulator(0)
+            sim.set_phantom(ph)
+            sim.set_sequence(seq)
+            sim.build_groups()
+            M, _ = sim.simulate(mode, m_init=torch.from_numpy(m_init))
+            torch.cuda.synchronize()
+            dm = float(np.max(np.abs(M.cpu().numpy() - Mr)))
+            sim.close()
+            say(f"[gpu] pulse {form} n={n} mode={mode}: max|dM|={dm:.2e}")
+            assert dm <= bar, (form, n, mode, dm)
