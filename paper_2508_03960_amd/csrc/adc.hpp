@@ -42,6 +42,10 @@ constexpr int kAdcMmCols = 128;   // samples per workgroup
 constexpr int kAdcMmSub = 32;     // groups staged at a time
 constexpr int kAdcMmSplit = 224;  // most groups whose terms add in FP32 (as in k_adc_lin: 28 per thread, 8 threads)
 constexpr int kAdcMmMinRows = 4;
+// Terms (rows x samples x groups) from which the product is the faster one: 97 x 131
+// x 8700 take 42 us either way, 32 x 64 x 700 take 8.9 us in k_adc_lin's one
+// launch and 12 us in the product's two.
+constexpr double kAdcMmMinTerms = 1.5e8;
 
 // part[split * part_stride + row.part + n] <- the partial sums (FP32), then
 // sig += their FP64 sums

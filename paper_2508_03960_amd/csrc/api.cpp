@@ -168,6 +168,7 @@ struct GroupedPlan {
     };
     std::vector<RunBatch> batches;
     std::vector<RunPart> run_parts;
+    bool run_cut = false;  // an x-group spans wavefronts: its sums are added to cleared ones
 };
 
 }  // namespace
@@ -285,6 +286,7 @@ static int build_grouped_plan(gbs_ctx *ctx);
                                               std::to_string((size_t)(bytes)) + " bytes failed"); \
     } while (0)
 
+constexpr int64_t kSideMinK = 1 << 22;  // isochromats from which a grouped simulation forks onto the side stream
 constexpr int64_t kRunMinMembers = 2;  // mean members per run from which the per-run form is used (plan_runs)
 
 static const char *status_text(int s) {
@@ -961,6 +963,7 @@ static int plan_runs(gbs_ctx *ctx, const std::vector<SweepOp> &sops, std::vector
             open_batch(r);
         }
         for (; e - wave_first > 64; r = wave_first) {  // more runs than a wavefront holds
+            g.run_cut = true;
             if (wave_first + 64 - base_of() > cap) {
                 close_batch(wave_first);
                 open_batch(wave_first);
@@ -968,6 +971,7 @@ static int plan_runs(gbs_ctx *ctx, const std::vector<SweepOp> &sops, std::vector
             end_wave(wave_first + 64);
         }
         if (e - base_of() > cap) {
+            g.run_cut = true;
             close_batch(wave_first);
             open_batch(wave_first);
         }
@@ -1309,7 +1313,7 @@ static int build_grouped_plan(gbs_ctx *ctx) {
         for (size_t c = 0; c < timing.size(); ++c) {
             const AdcLinJob &j = timing[c].first;
             const int n_rows = timing[c].second;
-            if (n_rows < kAdcMmMinRows) {
+            if (n_rows < kAdcMmMinRows || (double)n_rows * j.n_samples * j.n_groups < kAdcMmMinTerms) {
                 for (size_t i : members[c]) {
                     g.lin_rest.push_back(lj[i]);
                     g.max_adcrest_groups = std::max(g.max_adcrest_groups, lj[i].n_groups);
@@ -1778,7 +1782,7 @@ static int finish_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const char *j
                               ctx->stream));
     }
     if (st) HIPCHK(hipEventRecord(ctx->ev[3], ctx->stream));
-    HIPCHK(hipStreamWaitEvent(ctx->stream, ctx->join, 0));
+    if (ctx->K >= kSideMinK) HIPCHK(hipStreamWaitEvent(ctx->stream, ctx->join, 0));
     if (st) {
         st->n_passes = g.n_ops;
         st->n_sweeps = n_sweeps;
@@ -1816,7 +1820,11 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
     // before this point (a previous call's sweeps read the same buffers).  The
     // side stream's kernels are submitted after the compositions, so that the
     // compositions' few workgroups are placed first.
-    HIPCHK(hipEventRecord(ctx->fork, ctx->stream));
+    // Small phantoms take one stream: there a fork and a join cost more than the
+    // overlap gives (4096 isochromats: 77 us, 122 us with the side stream).
+    const bool forked = K >= kSideMinK;
+    const hipStream_t side = forked ? ctx->side : ctx->stream;
+    if (forked) HIPCHK(hipEventRecord(ctx->fork, ctx->stream));
     if (surr) {
         // network transitions for every z group, exact ones for the checked groups,
         // then exact for all groups only if the check failed (gated on the device)
@@ -1837,16 +1845,17 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
     }
     HIPCHK(launch_compose((const RfJobDev *)(jb + (surr ? g.o_rf_surr : g.o_rf)), g.n_rf, g.max_rf_groups, s.dt,
                           ctx->stream));
-    HIPCHK(hipStreamWaitEvent(ctx->side, ctx->fork, 0));
-    HIPCHK(launch_fill_f64((double *)(ws + g.w_gsum), 2 * (int64_t)g.gsum_count, ctx->side));
+    if (forked) HIPCHK(hipStreamWaitEvent(side, ctx->fork, 0));
+    const bool use_runs = g.runs && !m_init && ws_bytes >= g.run_ws_bytes;
+    if (!use_runs || g.run_cut)  // (wavefronts that hold whole x-groups store every sum)
+        HIPCHK(launch_fill_f64((double *)(ws + g.w_gsum), 2 * (int64_t)g.gsum_count, side));
     HIPCHK(launch_tables((const TabJob *)(jb + g.o_tab), g.n_tab, (int)g.max_tab, ctx->gtab[0].as<float4>(),
-                         zbuilt ? ctx->gtab[2].as<float4>() : nullptr, ctx->side));
+                         zbuilt ? ctx->gtab[2].as<float4>() : nullptr, side));
     // the per-run form's sums over the members need the phantom alone: those of
     // the first batch run on the side stream beside the compositions (after
     // those of two-axis groups: their workgroups, fewer than the CUs, run for a
     // millisecond where they are placed, and the sums' workgroups made them share
     // CUs: oblique FSE 3.4M 2.40 ms in turn, 2.80 side by side)
-    const bool use_runs = g.runs && !m_init && ws_bytes >= g.run_ws_bytes;
     RunYArgs ya{};
     if (use_runs) {
         ya.n_runs = ctx->n_lruns;
@@ -1864,9 +1873,9 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
         ya.out_coil = g.run_batch * g.lines.n_lines;
         ya.r0 = 0;
         ya.n = g.batches.front().r1;
-        if (plan.n_adc_grouped && g.pair_jobs.empty()) HIPCHK(launch_run_y(ya, ctx->side));
+        if (plan.n_adc_grouped && g.pair_jobs.empty()) HIPCHK(launch_run_y(ya, side));
     }
-    HIPCHK(hipEventRecord(ctx->join, ctx->side));
+    if (forked) HIPCHK(hipEventRecord(ctx->join, side));
     for (const auto &pj : g.pair_jobs) {
         const RfJob &r = plan.rf[pj.second];
         HIPCHK(launch_compose_pair(ctx->n_runs, ctx->rtab.as<float4>(), ctx->rz.as<float>(),
@@ -1877,7 +1886,7 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
         HIPCHK(launch_expand_rows((const double *)(tb + e.first), ctx->tmap.as<int32_t>(), ctx->ng[0],
                                   (double *)(tb + e.second), ctx->stream));
     HIPCHK(launch_fold((const FoldJob *)(jb + g.o_fold), g.n_fold, g.max_fold_groups, ctx->stream));
-    HIPCHK(hipStreamWaitEvent(ctx->stream, ctx->join, 0));  // cleared group sums, map tables
+    if (forked) HIPCHK(hipStreamWaitEvent(ctx->stream, ctx->join, 0));  // cleared group sums, map tables
     if (st) HIPCHK(hipEventRecord(ctx->ev[1], ctx->stream));
 
     // ---- one step per run of the layout, when the members of a run stay alike
@@ -1907,12 +1916,14 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
         if (profile) HIPCHK(hipEventRecord(ctx->pev[1], ctx->stream));
         *n_timed = profile ? 1 : 0;
         if (st) HIPCHK(hipEventRecord(ctx->ev[2], ctx->stream));
-        HIPCHK(hipEventRecord(ctx->fork, ctx->stream));
-        HIPCHK(hipStreamWaitEvent(ctx->side, ctx->fork, 0));
+        if (forked) {
+            HIPCHK(hipEventRecord(ctx->fork, ctx->stream));
+            HIPCHK(hipStreamWaitEvent(side, ctx->fork, 0));
+        }
         HIPCHK(launch_run_state(RunStateArgs{K, ctx->run_of.as<int32_t>(), ctx->ph.m0, ctx->ph.y, g.final_cy, sa.m, m_out,
                                              m_out + K, m_out + 2 * K},
-                                ctx->side));
-        HIPCHK(hipEventRecord(ctx->join, ctx->side));
+                                side));
+        if (forked) HIPCHK(hipEventRecord(ctx->join, side));
         return finish_grouped(ctx, ws, ws_bytes, jb, sig_out, st, (int64_t)g.batches.size(), g.run_bytes, g.run_flops);
     }
 
@@ -2000,15 +2011,15 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
     if (st) HIPCHK(hipEventRecord(ctx->ev[2], ctx->stream));
 
     // ---- final state into the caller's order, on the side stream ------------
-    HIPCHK(hipEventRecord(ctx->fork, ctx->stream));
-    HIPCHK(hipStreamWaitEvent(ctx->side, ctx->fork, 0));
+    if (forked) {
+        HIPCHK(hipEventRecord(ctx->fork, ctx->stream));
+        HIPCHK(hipStreamWaitEvent(side, ctx->fork, 0));
+    }
     if (final4)
-        HIPCHK(launch_gather_state4(K, ctx->inv.as<int32_t>(), m_final, m_out, m_out + K, m_out + 2 * K, ctx->side));
+        HIPCHK(launch_gather_state4(K, ctx->inv.as<int32_t>(), m_final, m_out, m_out + K, m_out + 2 * K, side));
     else
-        HIPCHK(launch_gather_state(K, ctx->inv.as<int32_t>(), mx, my, mz, m_out, m_out + K, m_out + 2 * K,
-                                    ctx->side));
-    HIPCHK(hipEventRecord(ctx->join, ctx->side));
-
+        HIPCHK(launch_gather_state(K, ctx->inv.as<int32_t>(), mx, my, mz, m_out, m_out + K, m_out + 2 * K, side));
+    if (forked) HIPCHK(hipEventRecord(ctx->join, side));
     return finish_grouped(ctx, ws, ws_bytes, jb, sig_out, st, (int64_t)g.segs.size(), bytes, flops);
 }
 
