@@ -192,7 +192,8 @@ struct gbs_ctx {
     int64_t ng[3] = {-1, -1, -1};
     int64_t Kint = 0;  // isochromats in the padded group-sorted layout (multiple of 8)
     int64_t Kpad = 0;
-    DevBuf perm, inv, xi, yi, zi, t1i, t2i, dfi, m0i, gid[3], gtab[3], gcount[3];
+    DevBuf perm, inv, xi, yi, zi, t1i, t2i, dfi, m0i, gid[3], gtab[3];
+    DevBuf gscratch;  // of gbs_build_groups: 60 to 80 bytes per isochromat
     DevBuf xstart;  // first layout slot of every x-group, and Kint after the last
     // no-grads groups (GBS_AX_N): (0, T1, T2, df) per group, and the group of each x-group
     int64_t n_tissue = -1;
@@ -343,12 +344,12 @@ int gbs_destroy(gbs_ctx *ctx) {
                       &ctx->t2i, &ctx->dfi, &ctx->m0i, &ctx->jobs, &ctx->samp, &ctx->flag, &ctx->surr_idx, &ctx->csurr_idx,
                       &ctx->adj_ops, &ctx->adj_samp, &ctx->adj_ckpt, &ctx->adj_sub, &ctx->adj_sig, &ctx->adj_grf,
                       &ctx->adj_gt, &ctx->csamp, &ctx->ttab, &ctx->tmap, &ctx->coil_l, &ctx->run_of4, &ctx->xstart,
-                      &ctx->rtab, &ctx->rz, &ctx->rfirst4, &ctx->rgx, &ctx->rgz, &ctx->run_of, &ctx->rslot, &ctx->run_waves, &ctx->run_ident};
+                      &ctx->rtab, &ctx->rz, &ctx->rfirst4, &ctx->rgx, &ctx->rgz, &ctx->run_of, &ctx->rslot, &ctx->run_waves, &ctx->run_ident,
+                      &ctx->gscratch};
     for (DevBuf *b : bufs) b->release();
     for (int a = 0; a < 3; ++a) {
         ctx->gid[a].release();
         ctx->gtab[a].release();
-        ctx->gcount[a].release();
     }
     for (auto &e : ctx->ev)
         if (e) (void)hipEventDestroy(e);
@@ -462,53 +463,57 @@ int gbs_build_groups(gbs_ctx *ctx, uint32_t axes) {
     ctx->gp.valid = false;
     ctx->coil_l_valid = false;
     const int64_t K = ctx->K;
-    const int64_t cap = (8 * K + 1023) / 1024 * 1024;  // padded layout is at most 8 K long
-    const size_t scratch_bytes = group_scratch_bytes(K) + 4096;
-    DevBuf scratch, gid_nat[3], order, perm_tmp, src_tmp;
-    auto cleanup = [&]() {
-        scratch.release();
-        for (auto &g : gid_nat) g.release();
-        order.release();
-        perm_tmp.release();
-        src_tmp.release();
-    };
-    auto fail_hip = [&](hipError_t e, const char *what) {
-        cleanup();
-        return fail(ctx, e == hipErrorOutOfMemory ? GBS_E_NOMEM : GBS_E_HIP,
-                    std::string(what) + ": " + hipGetErrorString(e));
-    };
-    if (scratch.ensure(scratch_bytes) != hipSuccess || order.ensure(4 * K) != hipSuccess ||
-        perm_tmp.ensure(4 * cap) != hipSuccess || src_tmp.ensure(4 * cap) != hipSuccess) {
-        cleanup();
-        return fail(ctx, GBS_E_NOMEM, "grouping scratch allocation failed");
-    }
-    // 1. group every requested axis by its key (r_a, T1, T2, dB0)
+    // scratch: the ids in natural order of all three axes, and the grouping's own
+    const size_t gid_bytes = align256(sizeof(int32_t) * (size_t)K), scratch_bytes = group_scratch_bytes(K);
+    ALLOC(ctx->gscratch, 3 * gid_bytes + scratch_bytes);
+    int32_t *gid_nat[3];
     const float *coord[3] = {ctx->ph.x, ctx->ph.y, ctx->ph.z};
     for (int a = 0; a < 3; ++a) {
+        gid_nat[a] = (axes & (1u << a)) ? (int32_t *)(ctx->gscratch.as<char>() + a * gid_bytes) : nullptr;
         ctx->ng[a] = -1;
-        if (!(axes & (1u << a))) {
-            ctx->gid[a].release();
-            ctx->gtab[a].release();
-            ctx->gcount[a].release();
-            continue;
+        if (gid_nat[a]) continue;
+        coord[a] = nullptr;
+        ctx->gid[a].release();
+        ctx->gtab[a].release();
+    }
+    void *scratch = ctx->gscratch.as<char>() + 3 * gid_bytes;
+    ctx->n_tissue = -1;
+    if (!(axes & GBS_AX_N)) {
+        ctx->ttab.release();
+        ctx->tmap.release();
+    }
+    // 1. group every requested axis by its key (r_a, T1, T2, dB0)
+    DenseGroups dense;
+    bool done = false;
+    HIPCHK(dense_groups(K, coord, ctx->ph.t1, ctx->ph.t2, ctx->ph.df, scratch, scratch_bytes, gid_nat, &dense, &done,
+                        ctx->stream));
+    if (done) {
+        float4 *gtab[3] = {nullptr, nullptr, nullptr};
+        for (int a = 0; a < 3; ++a) {
+            if (!coord[a]) continue;
+            ctx->ng[a] = dense.total[a] - (a ? dense.total[a - 1] : 0);
+            ALLOC(ctx->gtab[a], sizeof(float4) * (size_t)ctx->ng[a]);
+            gtab[a] = ctx->gtab[a].as<float4>();
         }
-        if (gid_nat[a].ensure(4 * K) != hipSuccess) {
-            cleanup();
-            return fail(ctx, GBS_E_NOMEM, "grouping scratch allocation failed");
+        if (axes & GBS_AX_N) {  // the tissues themselves, and the tissue of each x-group
+            ctx->n_tissue = dense.total[3] - dense.total[2];
+            ALLOC(ctx->ttab, sizeof(float4) * (size_t)ctx->n_tissue);
+            ALLOC(ctx->tmap, sizeof(int32_t) * (size_t)ctx->ng[0]);
         }
-        ALLOC(ctx->gtab[a], sizeof(float4) * K);
-        ALLOC(ctx->gcount[a], sizeof(int32_t) * K);
-        int64_t G = 0;
-        hipError_t e = group_axis(K, a == 2, coord[a], ctx->ph.t1, ctx->ph.t2, ctx->ph.df, scratch.p, scratch_bytes,
-                                  gid_nat[a].as<int32_t>(), ctx->gtab[a].as<float4>(), ctx->gcount[a].as<int32_t>(),
-                                  order.as<int32_t>(), &G, ctx->stream);
-        if (e != hipSuccess) return fail_hip(e, "grouping failed");
-        ctx->ng[a] = G;
+        HIPCHK(dense_tables(dense, gtab, ctx->ttab.as<float4>(), ctx->tmap.as<int32_t>(), ctx->stream));
+    }
+    for (int a = 0; a < 3 && !done; ++a) {
+        if (!coord[a]) continue;
+        SortedAxis sorted;
+        HIPCHK(group_axis(K, a == 2, coord[a], ctx->ph.t1, ctx->ph.t2, ctx->ph.df, scratch, scratch_bytes, gid_nat[a],
+                          &sorted, &ctx->ng[a], ctx->stream));
+        ALLOC(ctx->gtab[a], sizeof(float4) * (size_t)ctx->ng[a]);
+        HIPCHK(sorted_table(K, sorted, coord[a], ctx->ph.t1, ctx->ph.t2, ctx->ph.df, ctx->gtab[a].as<float4>(),
+                            ctx->stream));
     }
     // no-grads groups: the distinct (T1, T2, dB0) of the x-group keys, each x
     // group mapped to its own (every x-group key contains exactly one)
-    ctx->n_tissue = -1;
-    if (axes & GBS_AX_N) {
+    if ((axes & GBS_AX_N) && !done) {
         const int64_t Gx = ctx->ng[0];
         std::vector<float4> xt((size_t)Gx);
         HIPCHK(hipMemcpyAsync(xt.data(), ctx->gtab[0].p, sizeof(float4) * (size_t)Gx, hipMemcpyDeviceToHost,
@@ -530,67 +535,67 @@ int gbs_build_groups(gbs_ctx *ctx, uint32_t axes) {
         HIPCHK(hipMemcpy(ctx->ttab.p, tt.data(), sizeof(float4) * tt.size(), hipMemcpyHostToDevice));
         HIPCHK(hipMemcpy(ctx->tmap.p, map.data(), sizeof(int32_t) * map.size(), hipMemcpyHostToDevice));
         ctx->n_tissue = (int64_t)uniq.size();
-    } else {
-        ctx->ttab.release();
-        ctx->tmap.release();
     }
     // 2. the padded group-sorted layout: (x-group, z-group) runs of multiples of 8
-    int64_t kint = 0;
-    hipError_t e = build_layout(K, gid_nat[0].as<int32_t>(), (axes & GBS_AX_Z) ? gid_nat[2].as<int32_t>() : nullptr,
-                                scratch.p, scratch_bytes, perm_tmp.as<int32_t>(), src_tmp.as<int32_t>(), cap, &kint,
-                                ctx->stream);
-    if (e != hipSuccess) return fail_hip(e, "layout failed");
-    const int64_t Kpad = (kint + 1023) / 1024 * 1024;
+    const bool zg = (axes & GBS_AX_Z) != 0;
+    Layout lay;
+    HIPCHK(build_layout(K, gid_nat[0], ctx->ng[0], gid_nat[2], zg ? ctx->ng[2] : 0, scratch, scratch_bytes, &lay,
+                        ctx->stream));
+    const int64_t kint = lay.kint, Kpad = (kint + 1023) / 1024 * 1024, R = lay.R;
+    LayoutOut o{};
+    o.Kpad = Kpad;
+    o.ph = ctx->ph;
+    o.gtab_x = ctx->gtab[0].as<float4>();
+    o.gtab_z = zg ? ctx->gtab[2].as<float4>() : nullptr;
+    o.nat_x = gid_nat[0];
+    o.nat_y = gid_nat[1];
+    o.nat_z = gid_nat[2];
     ALLOC(ctx->perm, 4 * Kpad);
-    HIPCHK(hipMemcpyAsync(ctx->perm.p, perm_tmp.p, 4 * Kpad, hipMemcpyDeviceToDevice, ctx->stream));
     ALLOC(ctx->inv, 4 * K);
-    HIPCHK(launch_invert(Kpad, ctx->perm.as<int32_t>(), ctx->inv.as<int32_t>(), ctx->stream));
-    const int32_t *src = src_tmp.as<int32_t>();
-    for (int a = 0; a < 3; ++a) {
-        if (!(axes & (1u << a))) continue;
-        ALLOC(ctx->gid[a], sizeof(int32_t) * Kpad);
-        HIPCHK(launch_gather_i32(Kpad, Kpad, src, gid_nat[a].as<int32_t>(), ctx->gid[a].as<int32_t>(), ctx->stream));
-    }
-    ALLOC(ctx->xstart, sizeof(int32_t) * (size_t)(ctx->ng[0] + 1));
-    HIPCHK(launch_group_starts(kint, ctx->gid[0].as<int32_t>(), ctx->ng[0], ctx->xstart.as<int32_t>(), ctx->stream));
+    o.perm = ctx->perm.as<int32_t>();
+    o.inv = ctx->inv.as<int32_t>();
     DevBuf *dst[7] = {&ctx->xi, &ctx->yi, &ctx->zi, &ctx->t1i, &ctx->t2i, &ctx->dfi, &ctx->m0i};
-    const float *from[7] = {ctx->ph.x, ctx->ph.y, ctx->ph.z, ctx->ph.t1, ctx->ph.t2, ctx->ph.df, ctx->ph.m0};
+    float **out[7] = {&o.x, &o.y, &o.z, &o.t1, &o.t2, &o.df, &o.m0};
     for (int i = 0; i < 7; ++i) {
         ALLOC(*dst[i], 4 * Kpad);
-        HIPCHK(launch_gather_f32(Kpad, Kpad, src, from[i], dst[i]->as<float>(), ctx->stream));
+        *out[i] = dst[i]->as<float>();
     }
-    HIPCHK(launch_zero_padding(Kpad, ctx->perm.as<int32_t>(), ctx->m0i.as<float>(), ctx->stream));
+    int32_t **gout[3] = {&o.gid_x, &o.gid_y, &o.gid_z};
+    for (int a = 0; a < 3; ++a) {
+        if (!coord[a]) continue;
+        ALLOC(ctx->gid[a], sizeof(int32_t) * Kpad);
+        *gout[a] = ctx->gid[a].as<int32_t>();
+    }
     // the runs of equal (x-group, z-group) in the layout (the two-axis groups)
     ctx->n_runs = -1;
     ctx->n_lruns = 0;
-    if (axes & GBS_AX_Z) {
-        const int64_t n4 = kint / 4;
-        ALLOC(ctx->run_of4, sizeof(int32_t) * (size_t)n4);
+    ctx->xrun.clear();
+    if (zg) {
+        ALLOC(ctx->run_of4, sizeof(int32_t) * (size_t)(kint / 4));
         ALLOC(ctx->run_of, sizeof(int32_t) * (size_t)K);
-        // (the scratch holds at least 8 int32 per isochromat and the layout at most 8 slots)
-        int64_t R = 0;
-        e = number_runs(n4, ctx->gid[0].as<int32_t>(), ctx->gid[2].as<int32_t>(), scratch.p, scratch_bytes,
-                        ctx->run_of4.as<int32_t>(), &R, ctx->stream);
-        if (e != hipSuccess) return fail_hip(e, "run numbering failed");
         ALLOC(ctx->rslot, sizeof(int32_t) * (size_t)R);
         ALLOC(ctx->rfirst4, sizeof(int32_t) * (size_t)(R + 1));
         ALLOC(ctx->rgx, sizeof(int32_t) * (size_t)R);
         ALLOC(ctx->rgz, sizeof(int32_t) * (size_t)R);
-        HIPCHK(launch_run_arrays(n4, ctx->run_of4.as<int32_t>(), ctx->gid[0].as<int32_t>(), ctx->gid[2].as<int32_t>(),
-                                 ctx->rfirst4.as<int32_t>(), ctx->rgx.as<int32_t>(), ctx->rgz.as<int32_t>(),
-                                 ctx->stream));
-        e = place_runs(K, R, ctx->rfirst4.as<int32_t>(), ctx->run_of4.as<int32_t>(), ctx->perm.as<int32_t>(),
-                       ctx->inv.as<int32_t>(), scratch.p, scratch_bytes, ctx->rslot.as<int32_t>(),
-                       ctx->run_of.as<int32_t>(), ctx->stream);
-        if (e != hipSuccess) return fail_hip(e, "run numbering failed");
+        HIPCHK(place_runs(lay, ctx->rslot.as<int32_t>(), ctx->stream));
+        o.slot = ctx->rslot.as<int32_t>();
+        o.run_of4 = ctx->run_of4.as<int32_t>();
+        o.run_of = ctx->run_of.as<int32_t>();
+        o.run_first4 = ctx->rfirst4.as<int32_t>();
+        o.run_gx = ctx->rgx.as<int32_t>();
+        o.run_gz = ctx->rgz.as<int32_t>();
+    }
+    HIPCHK(write_layout(lay, o, ctx->stream));
+    ALLOC(ctx->xstart, sizeof(int32_t) * (size_t)(ctx->ng[0] + 1));
+    HIPCHK(launch_group_starts(kint, ctx->gid[0].as<int32_t>(), ctx->ng[0], ctx->xstart.as<int32_t>(), ctx->stream));
+    if (zg) {
         ctx->n_lruns = R;
-        ctx->xrun.clear();
         if (K >= kRunMinMembers * R && R <= kRunMaxRuns && kint <= kRunMaxSlots) {
             const int64_t Gx = ctx->ng[0];
-            if (scratch_bytes < sizeof(int32_t) * (size_t)(Gx + 1)) return fail_hip(hipErrorInvalidValue, "run ranges");
-            HIPCHK(launch_group_runs(R, ctx->rgx.as<int32_t>(), Gx, scratch.as<int32_t>(), ctx->stream));
+            int32_t *xrun = nullptr;
+            HIPCHK(group_runs(lay, Gx, &xrun, ctx->stream));
             ctx->xrun.resize((size_t)(Gx + 1));
-            HIPCHK(hipMemcpyAsync(ctx->xrun.data(), scratch.p, sizeof(int32_t) * (size_t)(Gx + 1), hipMemcpyDeviceToHost,
+            HIPCHK(hipMemcpyAsync(ctx->xrun.data(), xrun, sizeof(int32_t) * (size_t)(Gx + 1), hipMemcpyDeviceToHost,
                                   ctx->stream));
             HIPCHK(hipStreamSynchronize(ctx->stream));
         }
@@ -603,7 +608,7 @@ int gbs_build_groups(gbs_ctx *ctx, uint32_t axes) {
             ctx->n_runs = R;
         }
     }
-    if (!(axes & GBS_AX_Z)) {
+    if (!zg) {
         ctx->run_of4.release();
         ctx->run_of.release();
         ctx->rslot.release();
@@ -616,7 +621,6 @@ int gbs_build_groups(gbs_ctx *ctx, uint32_t axes) {
         ctx->rz.release();
     }
     HIPCHK(hipStreamSynchronize(ctx->stream));
-    cleanup();
     ctx->axes = axes;
     ctx->Kint = kint;
     ctx->Kpad = Kpad;
