@@ -437,9 +437,12 @@ int gbs_set_sequence(gbs_ctx *ctx, const gbs_block *blocks, int64_t n_blocks, co
     copy_sequence(ctx->seq, blocks, n_blocks, rf_re, rf_im, gx, gy, gz, total_steps, adc_idx, total_samples, dt);
     ctx->cls = classify(ctx->seq);
     std::vector<StepW> w((size_t)total_steps);
-    for (int64_t j = 0; j < total_steps; ++j) {
+    for (int64_t j = total_steps - 1; j >= 0; --j) {
         const double re = rf_re[j], im = rf_im[j];
-        w[j] = StepW{rf_re[j], rf_im[j], (float)(re * re + im * im), gx[j], gy[j], gz[j], 0.f, 0.f};
+        w[j] = StepW{rf_re[j], rf_im[j], (float)(re * re + im * im), gx[j], gy[j], gz[j], 1, 0.f};
+        // (bit for bit: -0 and +0 differ)
+        if (j + 1 < total_steps && w[j + 1].same < INT32_MAX && !std::memcmp(&w[j], &w[j + 1], 6 * sizeof(float)))
+            w[j].same = w[j + 1].same + 1;
     }
     ALLOC(ctx->d_wave, sizeof(StepW) * (size_t)total_steps);
     ALLOC(ctx->d_adc, sizeof(int32_t) * (size_t)total_samples);
@@ -741,13 +744,13 @@ static int32_t step_samples(const gbs_ctx *ctx) {
 // One stepping launch with its samples: the coil sums when the context has coil
 // maps (sensitivities of the launch's isochromats: re + p * stride), then one
 // finalize per coil into row p of the signal.
-static int launch_steps(gbs_ctx *ctx, const PlainArgs &a, bool b1, int grid, const float *cre,
+static int launch_steps(gbs_ctx *ctx, const PlainArgs &a, bool b1, int iso, int grid, const float *cre,
                         const float *cim, int64_t cstride, double *sig_out, int64_t first_sample) {
     const int32_t P = ctx->coil_re ? ctx->n_coils : 1;
     if (ctx->coil_re && a.n_samples > 0)
-        HIPCHK(launch_plain_coils(a, PlainCoils{cre, cim, cstride, P}, b1, grid, ctx->stream));
+        HIPCHK(launch_plain_coils(a, PlainCoils{cre, cim, cstride, P}, b1, iso, grid, ctx->stream));
     else
-        HIPCHK(launch_plain(a, b1, grid, ctx->stream));
+        HIPCHK(launch_plain(a, b1, iso, grid, ctx->stream));
     for (int32_t p = 0; p < P && a.n_samples > 0; ++p)
         HIPCHK(launch_plain_finalize(ctx->partial + (size_t)p * grid * a.n_samples, grid, a.n_samples,
                                      sig_out + 2 * ((int64_t)p * ctx->seq.total_samples + first_sample), ctx->stream));
@@ -770,7 +773,7 @@ static void build_plain_plan(gbs_ctx *ctx) {
 // between launches when there is more than one.
 static size_t plain_ws(const gbs_ctx *ctx, size_t *o_partial, size_t *o_state) {
     WsCarve w;
-    *o_partial = w.take(sizeof(double2) * (size_t)plain_grid(ctx->K) * kMaxSamplesPerLaunch);
+    *o_partial = w.take(sizeof(double2) * (size_t)plain_grid(ctx->K, plain_iso(ctx->K)) * kMaxSamplesPerLaunch);
     *o_state = ctx->pplan.ops.size() > 1 ? w.take(sizeof(double) * 3 * (size_t)ctx->K) : 0;
     return w.off;
 }
@@ -778,7 +781,7 @@ static size_t plain_ws(const gbs_ctx *ctx, size_t *o_partial, size_t *o_state) {
 static int run_plain(gbs_ctx *ctx, char *ws, const float *m_init, float *m_out, double *sig_out, gbs_stats *st) {
     const int64_t K = ctx->K;
     const Plan &plan = ctx->pplan;
-    const int grid = plain_grid(K);
+    const int iso = plain_iso(K), grid = plain_grid(K, iso);
     size_t o_partial = 0, o_state = 0;
     plain_ws(ctx, &o_partial, &o_state);
     ctx->partial = (double2 *)(ws + o_partial);
@@ -815,7 +818,7 @@ static int run_plain(gbs_ctx *ctx, char *ws, const float *m_init, float *m_out, 
         }
         const bool b1 = op.step.block >= 0 && ctx->cls[op.step.block].has_b1;
         const int64_t s0 = op.step.block >= 0 ? ctx->seq.blocks[op.step.block].sample_offset + op.step.sample_lo : 0;
-        if (int rc = launch_steps(ctx, a, b1, grid, ctx->coil_re, ctx->coil_im, K, sig_out, s0)) return rc;
+        if (int rc = launch_steps(ctx, a, b1, iso, grid, ctx->coil_re, ctx->coil_im, K, sig_out, s0)) return rc;
         first = false;
     }
     if (st) st->n_fallback = 0;
@@ -2007,7 +2010,7 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
             const int64_t s0 = op.step.block >= 0 ? s.blocks[op.step.block].sample_offset + op.step.sample_lo : 0;
             const float *cl = ctx->coil_re ? ctx->coil_l.as<float>() : nullptr;  // planes re, im per coil
             const int64_t Kp = ctx->Kpad;
-            if (int rc = launch_steps(ctx, a, b1, grid, cl, cl ? cl + Kp : nullptr, 2 * Kp, sig_out, s0))
+            if (int rc = launch_steps(ctx, a, b1, 2, grid, cl, cl ? cl + Kp : nullptr, 2 * Kp, sig_out, s0))
                 return rc;
         }
     }
@@ -2191,7 +2194,7 @@ static int run_cached(gbs_ctx *ctx, char *ws, const float *m_init, float *m_out,
             a.mout64_y = s64 + K;
             a.mout64_z = s64 + 2 * K;
             const int64_t s0 = ctx->seq.blocks[op.step.block].sample_offset + op.step.sample_lo;
-            if (int rc = launch_steps(ctx, a, ctx->cls[op.step.block].has_b1, pgrid, ctx->coil_re, ctx->coil_im,
+            if (int rc = launch_steps(ctx, a, ctx->cls[op.step.block].has_b1, 2, pgrid, ctx->coil_re, ctx->coil_im,
                                       K, sig_out, s0))
                 return rc;
             from_init = false;

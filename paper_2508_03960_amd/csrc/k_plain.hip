@@ -3,10 +3,11 @@
 //
 // One thread carries kIso isochromats in registers through every raster step
 // of a block: U = D R (Eq. 2, Eq. A1, Eq. A2).  The waveform value of a step
-// is the same for every lane, so it is one scalar load per step.
+// is the same for every lane, so it is one scalar load per step, and steps of
+// equal values (a constant gradient under a readout) share their coefficients.
 //
 // The step is applied in increment form:
-//   R M = M + a (B x M) + b (B (B . M) - |B|^2 M),
+//   R M = M + B x (a M + b (B x M)),
 //   a = sin(theta)/|B|,  b = (1 - cos theta)/|B|^2,  theta = -gamma |B| dt,
 // with a, b from their power series in q = theta^2 (no sqrt, no division, and
 // R = I falls out at B = 0); relaxation as M -= (1 - E) M with
@@ -18,7 +19,11 @@
 // coherently over tens of thousands of steps to far more than 1e-5 of M;
 // removing that with compensated FP32 arithmetic (double-float coefficients
 // and a compensated state) costs more instructions than FP64, which issues at
-// the non-packed FP32 rate on this target.
+// the non-packed FP32 rate on this target.  FP64 issue bounds the kernel: a
+// step with B1 is 44 FP64 instructions (of 75) and takes 480 cycles of a
+// wavefront that is alone on its SIMD, 240 where four share it.  The rare wide
+// rotations are behind a call, which leaves the loop's scalars in registers.
+// 66483 isochromats, 16 GRE lines (42240 steps): 16.9 ms before, 9.6 now.
 //
 // ADC samples (Eq. 6): at each sample boundary a wavefront sums its lanes with
 // DPP, lane 63 adds the wave total into a per-wave FP64 LDS accumulator;
@@ -33,8 +38,6 @@
 namespace gbs {
 
 constexpr int kPlainBlock = 256;
-constexpr int kIso = 2;
-constexpr int kTile = kPlainBlock * kIso;
 
 // Per-wave ADC accumulator in LDS (FP64).
 struct SampleAcc {
@@ -48,10 +51,66 @@ struct SampleAcc {
     static __device__ __forceinline__ double wave_sum(double x) { return wave_sum_lane63_f64(x); }
 };
 
-template <bool HAS_B1, bool COILS>
+// A step's values through the constant address space: in scalar registers,
+// also behind the call that a wide rotation makes (after which the compiler
+// takes vector loads for ordinary pointers, and waits for each step's).
+__device__ __forceinline__ StepW load_step(const StepW *wave, int j) {
+    typedef const __attribute__((address_space(4))) uint64_t *const_ptr;
+    static_assert(sizeof(StepW) == 32, "read as four 64-bit words");
+    uint64_t v[4];
+    const const_ptr q = (const_ptr)(wave + j);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = q[i];
+    StepW w;
+    __builtin_memcpy(&w, v, sizeof(w));
+    return w;
+}
+
+// B of a step and its rotation coefficients (without B1: those of the rotation
+// about z, a bz and b bz^2) for N isochromats.
+template <int N>
+struct Coefs {
+    double b1r, b1i, b1sq, gx, gy, gz;
+    double bz[N], B2[N], a[N], b[N];
+    __device__ __forceinline__ void set(const StepW &w) {
+        b1r = w.b1r;
+        b1i = w.b1i;
+        b1sq = w.b1sq;
+        gx = w.gx;
+        gy = w.gy;
+        gz = w.gz;
+    }
+    template <bool HAS_B1>
+    __device__ __forceinline__ bool series(const double (&X)[N], const double (&Y)[N], const double (&Z)[N],
+                                           const double (&boff)[N], double gdt, double k2) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            bz[i] = fma(gx, X[i], fma(gy, Y[i], fma(gz, Z[i], boff[i])));
+            B2[i] = HAS_B1 ? fma(bz[i], bz[i], b1sq) : bz[i] * bz[i];
+        }
+        const bool small = rot_coeffs_small(B2, gdt, k2, a, b);
+        if (!HAS_B1) about_z();
+        return small;
+    }
+    template <bool HAS_B1>
+    __device__ __forceinline__ void fix(double gdt, double k2) {
+        rot_coeffs_fix(B2, gdt, k2, a, b);
+        if (!HAS_B1) about_z();
+    }
+    __device__ __forceinline__ void about_z() {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            a[i] *= bz[i];
+            b[i] *= B2[i];
+        }
+    }
+};
+
+template <bool HAS_B1, bool COILS, int kIso>
 __global__ __launch_bounds__(kPlainBlock) void k_plain(PlainArgs a, PlainCoils cl) {
     using R = double;
     using Acc = SampleAcc;
+    constexpr int kTile = kPlainBlock * kIso;
     constexpr int MC = COILS ? kPlainMaxCoils : 1;
     extern __shared__ char lds_raw[];
     Acc *acc = reinterpret_cast<Acc *>(lds_raw);  // [4 waves][n_samples][coils]
@@ -125,44 +184,64 @@ __global__ __launch_bounds__(kPlainBlock) void k_plain(PlainArgs a, PlainCoils c
             }
         }
 
-        int j = 0;
+        // Runs of equal steps share their coefficients.  Those of the next run
+        // are computed with the first step of this one, from values loaded a
+        // run earlier.
+        Coefs<kIso> cur, next;
+        const int last = a.n_steps - 1;
+        int j = 0, head = 0, end = 0, next_end = 0;
+        StepW w{};
+        if (a.n_steps > 0) {
+            w = load_step(wave_ptr, 0);
+            cur.set(w);
+            next_end = end = min(w.same, a.n_steps);
+            w = load_step(wave_ptr, min(end, last));
+            if (!cur.template series<HAS_B1>(X, Y, Z, boff, gdt, k2)) cur.template fix<HAS_B1>(gdt, k2);
+        }
+        auto apply = [&]() {
+#pragma unroll
+            for (int i = 0; i < kIso; ++i) {
+                const R bz = cur.bz[i], ca = cur.a[i], cb = cur.b[i];
+                if (HAS_B1) {  // M += B x v, v = a M + b (B x M)
+                    const R b1r = cur.b1r, b1i = cur.b1i;
+                    const R cx = fma(b1i, mz[i], -(bz * my[i]));
+                    const R cy = fma(bz, mx[i], -(b1r * mz[i]));
+                    const R cz = fma(b1r, my[i], -(b1i * mx[i]));
+                    const R vx = fma(cb, cx, ca * mx[i]);
+                    const R vy = fma(cb, cy, ca * my[i]);
+                    const R vz = fma(cb, cz, ca * mz[i]);
+                    mx[i] = fma(b1i, vz, fma(-bz, vy, mx[i]));
+                    my[i] = fma(bz, vx, fma(-b1r, vz, my[i]));
+                    mz[i] = fma(b1r, vy, fma(-b1i, vx, mz[i]));
+                } else {  // B = (0, 0, bz): rotation about z by a bz, b bz^2
+                    const R nx = fma(-ca, my[i], fma(-cb, mx[i], mx[i]));
+                    const R ny = fma(ca, mx[i], fma(-cb, my[i], my[i]));
+                    mx[i] = nx;
+                    my[i] = ny;
+                }
+                mx[i] = fma(-e2m[i], mx[i], mx[i]);  // D: T2 decay, T1 recovery
+                my[i] = fma(-e2m[i], my[i], my[i]);
+                mz[i] = fma(e1m[i], M0[i] - mz[i], mz[i]);
+            }
+        };
         for (int n = 0; n <= ns; ++n) {
             const int jend = n < ns ? sidx[n] - a.step_base : a.n_steps;
-            // not unrolled: the Horner steps are inline asm, which the compiler
-            // treats as convergent; at 124-126 VGPRs four waves share a SIMD
-            for (; j < jend; ++j) {
-                const StepW w = wave_ptr[j];
-                const R b1r = w.b1r, b1i = w.b1i, b1sq = w.b1sq;
-                const R gx = w.gx, gy = w.gy, gz = w.gz;
-#pragma unroll
-                for (int i = 0; i < kIso; ++i) {
-                    const R bz = fma(gx, X[i], fma(gy, Y[i], fma(gz, Z[i], boff[i])));
-                    R ca, cb;
-                    if (HAS_B1) {
-                        const R B2 = fma(bz, bz, b1sq);
-                        rot_coeffs(B2, gdt, k2, ca, cb);
-                        const R cx = b1i * mz[i] - bz * my[i];
-                        const R cy = bz * mx[i] - b1r * mz[i];
-                        const R cz = b1r * my[i] - b1i * mx[i];
-                        const R d = fma(b1r, mx[i], fma(b1i, my[i], bz * mz[i]));
-                        const R dx = fma(ca, cx, cb * fma(b1r, d, -B2 * mx[i]));
-                        const R dy = fma(ca, cy, cb * fma(b1i, d, -B2 * my[i]));
-                        const R dz = fma(ca, cz, cb * fma(bz, d, -B2 * mz[i]));
-                        mx[i] += dx;
-                        my[i] += dy;
-                        mz[i] += dz;
-                    } else {  // B = (0, 0, bz): rotation about z
-                        const R B2 = bz * bz;
-                        rot_coeffs(B2, gdt, k2, ca, cb);
-                        const R p = ca * bz, r = cb * B2;
-                        const R nx = fma(-p, my[i], fma(-r, mx[i], mx[i]));
-                        const R ny = fma(p, mx[i], fma(-r, my[i], my[i]));
-                        mx[i] = nx;
-                        my[i] = ny;
-                    }
-                    mx[i] = fma(-e2m[i], mx[i], mx[i]);  // D: T2 decay, T1 recovery
-                    my[i] = fma(-e2m[i], my[i], my[i]);
-                    mz[i] = fma(e1m[i], M0[i] - mz[i], mz[i]);
+            while (j < jend) {
+                if (j == head) {
+                    next.set(w);
+                    next_end = min(end + w.same, a.n_steps);
+                    w = load_step(wave_ptr, min(next_end, last));
+                    const bool small = next.template series<HAS_B1>(X, Y, Z, boff, gdt, k2);
+                    apply();
+                    ++j;
+                    if (__builtin_expect(!small, 0)) next.template fix<HAS_B1>(gdt, k2);
+                }
+                const int stop = min(jend, end);
+                for (; j < stop; ++j) apply();
+                if (j == end) {
+                    cur = next;
+                    head = end;
+                    end = next_end;
                 }
             }
             if (n < ns && COILS) {  // one sum per coil: S(k, p) (Mx + i My)
@@ -251,29 +330,44 @@ __global__ __launch_bounds__(256) void k_plain_finalize(const double2 *__restric
     }
 }
 
-int plain_grid(int64_t K) {
-    const int64_t tiles = (K + kTile - 1) / kTile;
+int plain_grid(int64_t K, int iso) {
+    const int64_t tile = (int64_t)kPlainBlock * iso, tiles = (K + tile - 1) / tile;
     const int64_t cap = 2048;  // 8 workgroups per CU on 256 CUs
     return (int)(tiles < cap ? (tiles > 0 ? tiles : 1) : cap);
 }
 
-hipError_t launch_plain(const PlainArgs &a, bool has_b1, int grid, hipStream_t st) {
+// One isochromat per thread up to three wavefronts per SIMD, two beyond: a
+// second one in the thread shares the step's conversions and scalar work, but
+// fills the chip with half the wavefronts.  ms of 4 GRE lines (8000 steps with
+// B1, 2560 without), one and two per thread: 66 k isochromats 2.40 and 2.45,
+// 147 k 3.15 and 3.69, 230 k 3.93 and 3.70, 360 k 5.57 and 5.20.
+int plain_iso(int64_t K) { return K <= 3 * 64 * 1024 ? 1 : 2; }
+
+template <bool COILS, int ISO>
+static void launch_iso(const PlainArgs &a, const PlainCoils &c, bool has_b1, int grid, size_t lds, hipStream_t st) {
+    if (has_b1)
+        hipLaunchKernelGGL((k_plain<true, COILS, ISO>), dim3(grid), dim3(kPlainBlock), lds, st, a, c);
+    else
+        hipLaunchKernelGGL((k_plain<false, COILS, ISO>), dim3(grid), dim3(kPlainBlock), lds, st, a, c);
+}
+
+hipError_t launch_plain(const PlainArgs &a, bool has_b1, int iso, int grid, hipStream_t st) {
     const size_t lds = sizeof(SampleAcc) * 4 * (size_t)a.n_samples;
     const PlainCoils none{nullptr, nullptr, 0, 1};
-    if (has_b1)
-        hipLaunchKernelGGL((k_plain<true, false>), dim3(grid), dim3(kPlainBlock), lds, st, a, none);
+    if (iso == 1)
+        launch_iso<false, 1>(a, none, has_b1, grid, lds, st);
     else
-        hipLaunchKernelGGL((k_plain<false, false>), dim3(grid), dim3(kPlainBlock), lds, st, a, none);
+        launch_iso<false, 2>(a, none, has_b1, grid, lds, st);
     return hipGetLastError();
 }
 
-hipError_t launch_plain_coils(const PlainArgs &a, const PlainCoils &c, bool has_b1, int grid, hipStream_t st) {
+hipError_t launch_plain_coils(const PlainArgs &a, const PlainCoils &c, bool has_b1, int iso, int grid, hipStream_t st) {
     if (!c.re || !c.im || c.n < 1 || c.n > kPlainMaxCoils || a.n_samples * c.n > 256) return hipErrorInvalidValue;
     const size_t lds = sizeof(SampleAcc) * 4 * (size_t)a.n_samples * (size_t)c.n;
-    if (has_b1)
-        hipLaunchKernelGGL((k_plain<true, true>), dim3(grid), dim3(kPlainBlock), lds, st, a, c);
+    if (iso == 1)
+        launch_iso<true, 1>(a, c, has_b1, grid, lds, st);
     else
-        hipLaunchKernelGGL((k_plain<false, true>), dim3(grid), dim3(kPlainBlock), lds, st, a, c);
+        launch_iso<true, 2>(a, c, has_b1, grid, lds, st);
     return hipGetLastError();
 }
 

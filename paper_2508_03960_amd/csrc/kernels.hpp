@@ -11,7 +11,9 @@ namespace gbs {
 // One raster step of the sequence as the kernels read it (32 bytes, so a
 // wave-uniform step is one scalar load).  b1sq = |B1|^2.
 struct StepW {
-    float b1r, b1i, b1sq, gx, gy, gz, pad0, pad1;
+    float b1r, b1i, b1sq, gx, gy, gz;
+    int32_t same;  // steps from this one on with the same values, itself included
+    float pad;
 };
 
 struct PhantomPtrs {
@@ -200,10 +202,12 @@ struct AdcJobDev {
 };
 
 // ---- launchers (all asynchronous on `st`) -----------------------------------
-hipError_t launch_plain(const PlainArgs &a, bool has_b1, int grid, hipStream_t st);
+// iso: isochromats per thread, 1 or 2; the grid and `partial` are those of plain_grid(K, iso)
+hipError_t launch_plain(const PlainArgs &a, bool has_b1, int iso, int grid, hipStream_t st);
 hipError_t launch_plain_finalize(const double2 *partial, int nblk, int n_samples, double *sig,
                                  hipStream_t st);
-int plain_grid(int64_t K);
+int plain_grid(int64_t K, int iso = 2);
+int plain_iso(int64_t K);  // isochromats per thread of the plain mode
 
 hipError_t launch_sweep(const SweepArgs &a, hipStream_t st);
 hipError_t launch_tables(const TabJob *jobs, int n_jobs, int max_n, const float4 *gtab_x,

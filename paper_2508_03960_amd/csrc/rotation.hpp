@@ -92,4 +92,43 @@ __device__ __forceinline__ void rot_coeffs(double B2, double gdt, double k2, dou
     }
 }
 
+// The same behind a call: for the step loops that keep only the short series'
+// coefficients in scalar registers.  With all three branches inline, k_plain's
+// loop reloaded 151 spilled scalars.
+__device__ __attribute__((noinline)) double2 rot_coeffs_any(double B2, double gdt, double k2) {
+    double a, b;
+    rot_coeffs(B2, gdt, k2, a, b);
+    return make_double2(a, b);
+}
+
+// a, b of N angles by the short series alone; true if it holds for all of them
+// in the whole wavefront.  rot_coeffs_fix then gives the ones that rot_coeffs
+// would.
+template <int N>
+__device__ __forceinline__ bool rot_coeffs_small(const double (&B2)[N], double gdt, double k2, double (&a)[N],
+                                                 double (&b)[N]) {
+    bool small = true;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const double q = k2 * B2[i];
+        small = small && q <= 0.0625;
+        double S, C;
+        Series::coeffs_short(q, S, C);
+        a[i] = -gdt * S;
+        b[i] = k2 * C;
+    }
+    return __all(small);
+}
+
+template <int N>
+__device__ __forceinline__ void rot_coeffs_fix(const double (&B2)[N], double gdt, double k2, double (&a)[N],
+                                               double (&b)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const double2 r = rot_coeffs_any(B2[i], gdt, k2);
+        a[i] = r.x;
+        b[i] = r.y;
+    }
+}
+
 }  // namespace gbs
