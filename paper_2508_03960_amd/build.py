@@ -21,7 +21,7 @@ LIB = os.path.join(PKG, "libgbloch.so")
 ARCH = os.environ.get("GBLOCH_ARCH", "gfx950")
 
 SOURCES = ["api.cpp", "api_mlp.cpp", "plan.cpp", "k_plain.hip", "k_grouped.hip", "k_groups.hip", "k_mlp.hip",
-           "k_adjoint.hip", "k_adc.hip", "k_cached.hip",
+           "k_adjoint.hip", "k_adjgroup.hip", "k_adc.hip", "k_cached.hip",
            "k_pairs.hip", "k_runs.hip", "pulseq.cpp", "noalloc.hip"]
 
 COMMON = [

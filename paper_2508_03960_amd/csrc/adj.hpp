@@ -46,11 +46,83 @@ struct AdjArgs {
     double2 *gt_part;    // backward: [grid][n_classes] (dL/dT1, dL/dT2)
 };
 
+// ---- by groups (k_adjgroup.hip) ---------------------------------------------
+constexpr int kAdjSeg = 16;          // raster steps per segment of a pulse
+constexpr int kAdjGroupMin = 4;      // isochromats per group from which the pulses are walked per group
+
+struct AdjStep {  // raster step of a pulse
+    float b1r, b1i, gx, gy, gz;
+    int32_t param;  // sample of the parameter pulse that replaces B1, or -1
+};
+
+struct AdjSeg {
+    int32_t step0, n;  // steps [step0, step0 + n)
+};
+
+// One operation for the isochromats, and the samples at the boundary before it
+// (list positions [sample0, sample0 + samples)); a closing entry holds the
+// samples at the end.
+struct AdjGOp {
+    int32_t pulse;  // distinct pulse, or -1: relaxation
+    int32_t coef;   // relaxations: equal (tau, cyc) have equal numbers
+    int32_t sample0, samples;
+    double tau, cyc[3];
+};
+
+struct AdjPulseArgs {
+    int64_t G;
+    const float4 *gtab;    // (x, y, z, dB0) of every group (coordinates that no pulse sees: 0)
+    const int32_t *gcls;
+    const float *t1c, *t2c;
+    int32_t n_classes;
+    const float2 *rfp;
+    double dt;
+    const AdjStep *steps;
+    const AdjSeg *segs;    // [n_segs], pulse after pulse
+    const int2 *pulses;    // [n_pulses] segments [x, y)
+    int32_t n_pulses, n_segs;
+    double *seg_t, *prefix, *suffix;  // [n_segs][12][G]
+    double *total, *gsum;             // [n_pulses][12][G]
+    double *tsum;                     // [n_segs][2][G]
+    double *acc_rf, *acc_t;           // [n_rf][2], [n_classes][2]
+};
+
+struct AdjGroupArgs {
+    int64_t K, G;
+    const int32_t *order, *gid;  // [K] isochromats sorted by group, and their groups
+    const float *x, *y, *z, *df, *m0;
+    const int32_t *cls;
+    const float *t1c, *t2c;
+    int32_t n_classes;
+    const AdjGOp *ops;  // [n_ops + 1]
+    int32_t n_ops;
+    const int32_t *sid;
+    int32_t every;
+    float *ckpt, *sub;  // [n_ckpt][3][K], [every / kAdjSub][3][K]
+    int32_t N;
+    double2 *sig_part;  // [grid][N]
+    const double2 *w;
+    double2 *gt_part;   // [grid][n_classes]
+    const double *total;
+    double *gsum;
+    const float2 *decay;  // [relaxations' coef][n_classes]: 1 - exp(-tau / T1), 1 - exp(-tau / T2)
+};
+
+hipError_t launch_adjg_transitions(const AdjPulseArgs &a, hipStream_t st);
+// tau: duration of every coef; fills decay
+hipError_t launch_adjg_forward(const AdjGroupArgs &a, int n_coef, const double *tau, float2 *decay, hipStream_t st);
+hipError_t launch_adjg_backward(const AdjGroupArgs &a, const AdjPulseArgs &p, hipStream_t st);
+hipError_t launch_adjg_results(const AdjPulseArgs &p, int n_rf, float *grad_rf, double *g1, double *g2, hipStream_t st);
+
+// out[c] = sum over the rows r of part[r * n + c], in FP64
+hipError_t launch_adj_rows(const double2 *part, int rows, int n, double *out, hipStream_t st);
 hipError_t launch_adj_forward(const AdjArgs &a, hipStream_t st);
 hipError_t launch_adj_backward(const AdjArgs &a, hipStream_t st);
 hipError_t launch_adj_validate(int64_t K, const int32_t *cls, int n_classes, const float *t1c, const float *t2c,
                                int *flag, hipStream_t st);
 hipError_t launch_adj_finalize(const AdjArgs &a, double *sig, float *grad_rf, double *grad_t1, double *grad_t2,
                                bool forward, hipStream_t st);
+// g1, g2 <- sums of the rows [rows][C]
+hipError_t launch_adj_class_rows(const double2 *part, int rows, int C, double *g1, double *g2, hipStream_t st);
 
 }  // namespace gbs

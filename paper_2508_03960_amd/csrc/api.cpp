@@ -244,6 +244,12 @@ struct gbs_ctx {
     DevBuf adj_ops, adj_samp, adj_ckpt, adj_sub, adj_sig, adj_grf, adj_gt;
     AdjArgs adj{};
     bool adj_ready = false;
+    // the adjoint by groups (adj_grouped: the last forward pass took it): sorted
+    // isochromats and group table, pulses, and the arrays of AdjPulseArgs
+    DevBuf adj_order, adj_pulse, adj_group;
+    AdjGroupArgs adjg{};
+    AdjPulseArgs adjp{};
+    bool adj_grouped = false;
     bool pplan_valid = false;
     Plan pplan;  // plain schedule
     // conventional method with per-isochromat transition caching (GBS_CACHED):
@@ -345,7 +351,7 @@ int gbs_destroy(gbs_ctx *ctx) {
                       &ctx->adj_ops, &ctx->adj_samp, &ctx->adj_ckpt, &ctx->adj_sub, &ctx->adj_sig, &ctx->adj_grf,
                       &ctx->adj_gt, &ctx->csamp, &ctx->ttab, &ctx->tmap, &ctx->coil_l, &ctx->run_of4, &ctx->xstart,
                       &ctx->rtab, &ctx->rz, &ctx->rfirst4, &ctx->rgx, &ctx->rgz, &ctx->run_of, &ctx->rslot, &ctx->run_waves, &ctx->run_ident,
-                      &ctx->gscratch};
+                      &ctx->gscratch, &ctx->adj_order, &ctx->adj_pulse, &ctx->adj_group};
     for (DevBuf *b : bufs) b->release();
     for (int a = 0; a < 3; ++a) {
         ctx->gid[a].release();
@@ -2485,6 +2491,185 @@ extern "C" int gbs_set_surrogate(gbs_ctx *ctx, gbs_mlp *m, float tol, int32_t n_
 }
 
 // ------------------------------------------------------------------ adjoint
+// The schedule of the adjoint by groups: runs of raster operations between two
+// sample boundaries become pulses (equal ones one pulse), cut into segments.
+struct AdjSchedule {
+    std::vector<AdjGOp> ops;  // and a closing entry
+    std::vector<AdjStep> steps;
+    std::vector<AdjSeg> segs;
+    std::vector<int2> pulses;
+    std::vector<double> tau;  // of every coef
+    int64_t n_raster = 0, n_played = 0;  // raster steps, pulses played
+    uint32_t axes = 0;                   // axes of their gradients
+};
+
+static void schedule_pulses(const std::vector<AdjOp> &ops, const int32_t *sstart, AdjSchedule &g) {
+    const int64_t n_ops = (int64_t)ops.size();
+    std::vector<std::pair<int32_t, int32_t>> range;  // steps of every pulse
+    std::map<std::array<double, 4>, int32_t> coef;
+    std::vector<AdjStep> run;
+    auto at = [&](int64_t p) { return AdjGOp{-1, -1, sstart[p], sstart[p + 1] - sstart[p], 0.0, {0.0, 0.0, 0.0}}; };
+    for (int64_t p = 0; p < n_ops;) {
+        AdjGOp o = at(p);
+        if (ops[p].kind != 0) {
+            o.tau = ops[p].tau;
+            for (int i = 0; i < 3; ++i) o.cyc[i] = ops[p].cyc[i];
+            const auto it = coef.emplace(std::array<double, 4>{o.tau, o.cyc[0], o.cyc[1], o.cyc[2]}, (int32_t)coef.size());
+            if (it.second) g.tau.push_back(o.tau);
+            o.coef = it.first->second;
+            g.ops.push_back(o);
+            ++p;
+            continue;
+        }
+        run.clear();
+        int64_t e = p;
+        do {
+            const AdjOp &s = ops[e];
+            run.push_back(AdjStep{s.b1r, s.b1i, s.gx, s.gy, s.gz, s.param});
+            g.axes |= (s.gx != 0.f ? 1u : 0u) | (s.gy != 0.f ? 2u : 0u) | (s.gz != 0.f ? 4u : 0u);
+            ++e;
+        } while (e < n_ops && ops[e].kind == 0 && sstart[e + 1] == sstart[e]);
+        p = e;
+        const int32_t n = (int32_t)run.size();
+        size_t id = 0;
+        while (id < range.size() && !(range[id].second == n &&
+                                      !std::memcmp(&g.steps[range[id].first], run.data(), sizeof(AdjStep) * run.size())))
+            ++id;
+        if (id == range.size()) {
+            const int32_t s0 = (int32_t)g.steps.size(), seg0 = (int32_t)g.segs.size();
+            range.emplace_back(s0, n);
+            g.steps.insert(g.steps.end(), run.begin(), run.end());
+            for (int32_t j = 0; j < n; j += kAdjSeg) g.segs.push_back(AdjSeg{s0 + j, std::min(kAdjSeg, n - j)});
+            g.pulses.push_back(int2{seg0, (int32_t)g.segs.size()});
+        }
+        o.pulse = (int32_t)id;
+        g.n_raster += n;
+        ++g.n_played;
+        g.ops.push_back(o);
+        // too many short or different pulses for the form: the caller steps every isochromat
+        if (g.n_raster < kAdjSeg * g.n_played && g.n_played > 64) return;
+        if (g.segs.size() > 65535) return;
+    }
+    g.ops.push_back(at(n_ops));
+}
+
+// Sets the context up for the adjoint by groups and runs its forward pass;
+// *done stays false where the isochromats have to be stepped one by one: no
+// long pulses, fewer than kAdjGroupMin isochromats per group, or more memory
+// than the stepping's checkpoints (old_bytes) and 64 MiB.
+static int adj_forward_groups(gbs_ctx *ctx, const AdjArgs &old, const std::vector<AdjOp> &ops, const int32_t *sstart,
+                              size_t old_bytes, double *sig_out, bool *done) {
+    AdjSchedule g;
+    schedule_pulses(ops, sstart, g);
+    if (g.n_played == 0 || g.n_raster < kAdjSeg * g.n_played || g.segs.size() > 65535) return GBS_OK;
+    const int64_t K = old.K, np = (int64_t)g.pulses.size(), ns = (int64_t)g.segs.size();
+    const size_t per_group = sizeof(double) * (size_t)(38 * ns + 24 * np);
+    const int64_t fit = (int64_t)(std::max(old_bytes, (size_t)64 << 20) / per_group);
+    const int64_t most = std::min(K / kAdjGroupMin, fit);
+    if (most < 1) return GBS_OK;
+    WsCarve w;
+    const size_t o_order = w.take(4 * (size_t)K), o_gid = w.take(4 * (size_t)K), o_tab = w.take(sizeof(float4) * (size_t)most),
+                 o_cls = w.take(4 * (size_t)most);
+    ALLOC(ctx->adj_order, w.off);
+    char *b = ctx->adj_order.as<char>();
+    ALLOC(ctx->gscratch, adjoint_group_scratch(K));
+    const float *coord[3] = {(g.axes & 1) ? old.x : nullptr, (g.axes & 2) ? old.y : nullptr, (g.axes & 4) ? old.z : nullptr};
+    int64_t G = 0;
+    HIPCHK(adjoint_groups(K, coord, old.df, old.cls, old.n_classes, most, ctx->gscratch.p, adjoint_group_scratch(K),
+                          (int32_t *)(b + o_order), (int32_t *)(b + o_gid), (float4 *)(b + o_tab),
+                          (int32_t *)(b + o_cls), &G, ctx->stream));
+    if (G < 0) return GBS_OK;
+    // schedule arrays
+    WsCarve v;
+    const size_t o_ops = v.take(sizeof(AdjGOp) * g.ops.size()), o_steps = v.take(sizeof(AdjStep) * g.steps.size()),
+                 o_segs = v.take(sizeof(AdjSeg) * g.segs.size()), o_pulses = v.take(sizeof(int2) * g.pulses.size()),
+                 o_tau = v.take(sizeof(double) * g.tau.size());
+    ALLOC(ctx->adj_pulse, v.off);
+    std::vector<char> h(v.off);
+    std::memcpy(&h[o_ops], g.ops.data(), sizeof(AdjGOp) * g.ops.size());
+    std::memcpy(&h[o_steps], g.steps.data(), sizeof(AdjStep) * g.steps.size());
+    std::memcpy(&h[o_segs], g.segs.data(), sizeof(AdjSeg) * g.segs.size());
+    std::memcpy(&h[o_pulses], g.pulses.data(), sizeof(int2) * g.pulses.size());
+    if (!g.tau.empty()) std::memcpy(&h[o_tau], g.tau.data(), sizeof(double) * g.tau.size());
+    HIPCHK(hipMemcpy(ctx->adj_pulse.p, h.data(), v.off, hipMemcpyHostToDevice));
+    const char *pb = ctx->adj_pulse.as<char>();
+    // group arrays
+    WsCarve u;
+    const size_t seg = sizeof(double) * 12 * (size_t)ns * (size_t)G, pul = sizeof(double) * 12 * (size_t)np * (size_t)G;
+    const size_t o_t = u.take(seg), o_pre = u.take(seg), o_suf = u.take(seg), o_tot = u.take(pul), o_sum = u.take(pul),
+                 o_ts = u.take(sizeof(double) * 2 * (size_t)ns * (size_t)G),
+                 o_acc = u.take(sizeof(double) * 2 * (size_t)(old.n_rf + old.n_classes)),
+                 o_decay = u.take(sizeof(float2) * std::max<size_t>(g.tau.size(), 1) * (size_t)old.n_classes);
+    ALLOC(ctx->adj_group, u.off);
+    char *ub = ctx->adj_group.as<char>();
+    AdjPulseArgs p{};
+    p.G = G;
+    p.gtab = (const float4 *)(b + o_tab);
+    p.gcls = (const int32_t *)(b + o_cls);
+    p.t1c = old.t1c;
+    p.t2c = old.t2c;
+    p.n_classes = old.n_classes;
+    p.rfp = old.rfp;
+    p.dt = old.dt;
+    p.steps = (const AdjStep *)(pb + o_steps);
+    p.segs = (const AdjSeg *)(pb + o_segs);
+    p.pulses = (const int2 *)(pb + o_pulses);
+    p.n_pulses = (int32_t)np;
+    p.n_segs = (int32_t)ns;
+    p.seg_t = (double *)(ub + o_t);
+    p.prefix = (double *)(ub + o_pre);
+    p.suffix = (double *)(ub + o_suf);
+    p.total = (double *)(ub + o_tot);
+    p.gsum = (double *)(ub + o_sum);
+    p.tsum = (double *)(ub + o_ts);
+    p.acc_rf = (double *)(ub + o_acc);
+    p.acc_t = p.acc_rf + 2 * (size_t)old.n_rf;
+    const int64_t n_ops = (int64_t)g.ops.size() - 1, n_sub = (n_ops + kAdjSub - 1) / kAdjSub;
+    const size_t state = sizeof(float) * 3 * (size_t)K;
+    const int grid = (int)((K + kAdjWG - 1) / kAdjWG);
+    // the few operations that are left: the forward pass keeps the start of every
+    // sub-segment where that takes no more than the stepping's checkpoints, and
+    // the backward pass steps everything once less
+    const int32_t every = state * (size_t)n_sub <= old_bytes ? kAdjSub : old.every;
+    ALLOC(ctx->adj_ckpt, state * (size_t)((n_ops + every - 1) / every));
+    ALLOC(ctx->adj_sub, every == kAdjSub ? 1 : state * (size_t)std::min<int64_t>(every / kAdjSub, n_sub));
+    ALLOC(ctx->adj_sig, sizeof(double2) * (size_t)grid * (size_t)std::max(old.N, 1));
+    ALLOC(ctx->adj_gt, sizeof(double2) * (size_t)grid * (size_t)old.n_classes);
+    AdjGroupArgs a{};
+    a.K = K;
+    a.G = G;
+    a.order = (const int32_t *)(b + o_order);
+    a.gid = (const int32_t *)(b + o_gid);
+    a.x = old.x;
+    a.y = old.y;
+    a.z = old.z;
+    a.df = old.df;
+    a.m0 = old.m0;
+    a.cls = old.cls;
+    a.t1c = old.t1c;
+    a.t2c = old.t2c;
+    a.n_classes = old.n_classes;
+    a.ops = (const AdjGOp *)(pb + o_ops);
+    a.n_ops = (int32_t)n_ops;
+    a.sid = old.sid;
+    a.every = every;
+    a.ckpt = ctx->adj_ckpt.as<float>();
+    a.sub = ctx->adj_sub.as<float>();
+    a.N = old.N;
+    a.sig_part = ctx->adj_sig.as<double2>();
+    a.gt_part = ctx->adj_gt.as<double2>();
+    a.total = p.total;
+    a.gsum = p.gsum;
+    a.decay = (const float2 *)(ub + o_decay);
+    HIPCHK(launch_adjg_transitions(p, ctx->stream));
+    HIPCHK(launch_adjg_forward(a, (int)g.tau.size(), (const double *)(pb + o_tau), (float2 *)(ub + o_decay), ctx->stream));
+    HIPCHK(launch_adj_rows(a.sig_part, grid, a.N, sig_out, ctx->stream));
+    ctx->adjg = a;
+    ctx->adjp = p;
+    *done = true;
+    return GBS_OK;
+}
+
 extern "C" int gbs_adj_forward(gbs_ctx *ctx, const int32_t *cls, int32_t n_classes, const float *t1c,
                                const float *t2c, const float *rf_param, int64_t n_rf, const int32_t *param_blocks,
                                int32_t n_param_blocks, int32_t every, double *sig_out) {
@@ -2584,13 +2769,7 @@ extern "C" int gbs_adj_forward(gbs_ctx *ctx, const int32_t *cls, int32_t n_class
     const int64_t K = ctx->K;
     const int grid = (int)((K + kAdjWG - 1) / kAdjWG);
     const int64_t n_ckpt = (n_ops + every - 1) / every;
-    ALLOC(ctx->adj_ops, sizeof(AdjOp) * (size_t)std::max<int64_t>(n_ops, 1));
     ALLOC(ctx->adj_samp, sizeof(int32_t) * samp.size());
-    ALLOC(ctx->adj_ckpt, sizeof(float) * 3 * (size_t)K * (size_t)std::max<int64_t>(n_ckpt, 1));
-    ALLOC(ctx->adj_sub, sizeof(float) * 3 * (size_t)K * (size_t)(every / kAdjSub));
-    ALLOC(ctx->adj_sig, sizeof(double2) * (size_t)grid * (size_t)std::max<int64_t>(N, 1));
-    ALLOC(ctx->adj_grf, sizeof(float2) * (size_t)grid * (size_t)n_rf);
-    ALLOC(ctx->adj_gt, sizeof(double2) * (size_t)grid * (size_t)n_classes);
     ALLOC(ctx->flag, 256);
     // inputs: class indices in range, T1/T2 > 0 (checked on the device)
     HIPCHK(launch_fill_f64(ctx->flag.as<double>(), 1, ctx->stream));
@@ -2599,7 +2778,6 @@ extern "C" int gbs_adj_forward(gbs_ctx *ctx, const int32_t *cls, int32_t n_class
     HIPCHK(hipMemcpyAsync(&bad, ctx->flag.p, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
     if (bad) return fail(ctx, GBS_E_INVALID, "class index out of range or T1/T2 <= 0");
-    if (n_ops > 0) HIPCHK(hipMemcpy(ctx->adj_ops.p, ops.data(), sizeof(AdjOp) * (size_t)n_ops, hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(ctx->adj_samp.p, samp.data(), sizeof(int32_t) * samp.size(), hipMemcpyHostToDevice));
     AdjArgs a{};
     a.K = K;
@@ -2612,7 +2790,6 @@ extern "C" int gbs_adj_forward(gbs_ctx *ctx, const int32_t *cls, int32_t n_class
     a.t1c = t1c;
     a.t2c = t2c;
     a.n_classes = n_classes;
-    a.ops = ctx->adj_ops.as<AdjOp>();
     a.n_ops = (int32_t)n_ops;
     a.rfp = (const float2 *)rf_param;
     a.n_rf = (int32_t)n_rf;
@@ -2620,9 +2797,28 @@ extern "C" int gbs_adj_forward(gbs_ctx *ctx, const int32_t *cls, int32_t n_class
     a.sid = ctx->adj_samp.as<int32_t>() + n_ops + 2;
     a.dt = s.dt;
     a.every = every;
+    a.N = (int32_t)N;
+    const size_t ckpt_bytes = sizeof(float) * 3 * (size_t)K * (size_t)std::max<int64_t>(n_ckpt, 1),
+                 sub_bytes = sizeof(float) * 3 * (size_t)K * (size_t)(every / kAdjSub);
+    ctx->adj_grouped = false;
+    if (int rc = adj_forward_groups(ctx, a, ops, samp.data(), ckpt_bytes + sub_bytes, sig_out, &ctx->adj_grouped)) return rc;
+    if (ctx->adj_grouped) {
+        HIPCHK(hipStreamSynchronize(ctx->stream));
+        HIPCHK(hipGetLastError());
+        ctx->adj = a;
+        ctx->adj_ready = true;
+        return GBS_OK;
+    }
+    ALLOC(ctx->adj_ops, sizeof(AdjOp) * (size_t)std::max<int64_t>(n_ops, 1));
+    ALLOC(ctx->adj_ckpt, ckpt_bytes);
+    ALLOC(ctx->adj_sub, sub_bytes);
+    ALLOC(ctx->adj_sig, sizeof(double2) * (size_t)grid * (size_t)std::max<int64_t>(N, 1));
+    ALLOC(ctx->adj_grf, sizeof(float2) * (size_t)grid * (size_t)n_rf);
+    ALLOC(ctx->adj_gt, sizeof(double2) * (size_t)grid * (size_t)n_classes);
+    if (n_ops > 0) HIPCHK(hipMemcpy(ctx->adj_ops.p, ops.data(), sizeof(AdjOp) * (size_t)n_ops, hipMemcpyHostToDevice));
+    a.ops = ctx->adj_ops.as<AdjOp>();
     a.ckpt = ctx->adj_ckpt.as<float>();
     a.sub = ctx->adj_sub.as<float>();
-    a.N = (int32_t)N;
     a.sig_part = ctx->adj_sig.as<double2>();
     a.grf_part = ctx->adj_grf.as<float2>();
     a.gt_part = ctx->adj_gt.as<double2>();
@@ -2642,6 +2838,20 @@ extern "C" int gbs_adj_backward(gbs_ctx *ctx, const double *grad_sig, float *gra
     if ((ctx->adj.N > 0 && !grad_sig) || !grad_rf || !grad_t1 || !grad_t2)
         return fail(ctx, GBS_E_INVALID, "null argument");
     HIPCHK(hipSetDevice(ctx->device));
+    if (ctx->adj_grouped) {
+        AdjGroupArgs g = ctx->adjg;
+        const AdjPulseArgs &p = ctx->adjp;
+        g.w = (const double2 *)grad_sig;
+        const int grid = (int)((g.K + kAdjWG - 1) / kAdjWG);
+        HIPCHK(launch_fill_f64(p.gsum, 12 * p.n_pulses * p.G, ctx->stream));
+        HIPCHK(launch_fill_f64(p.acc_rf, 2 * (int64_t)(ctx->adj.n_rf + p.n_classes), ctx->stream));
+        HIPCHK(launch_adjg_backward(g, p, ctx->stream));
+        HIPCHK(launch_adj_class_rows(g.gt_part, grid, g.n_classes, grad_t1, grad_t2, ctx->stream));
+        HIPCHK(launch_adjg_results(p, ctx->adj.n_rf, grad_rf, grad_t1, grad_t2, ctx->stream));
+        HIPCHK(hipStreamSynchronize(ctx->stream));
+        HIPCHK(hipGetLastError());
+        return GBS_OK;
+    }
     AdjArgs a = ctx->adj;
     a.w = (const double2 *)grad_sig;
     HIPCHK(launch_adj_backward(a, ctx->stream));

@@ -90,6 +90,15 @@ hipError_t dense_groups(int64_t K, const float *const coord[3], const float *t1,
                         void *scratch, size_t scratch_bytes, int32_t *const gid[3], DenseGroups *d, bool *done,
                         hipStream_t st);
 hipError_t dense_tables(const DenseGroups &d, float4 *const gtab[3], float4 *ttab, int32_t *tmap, hipStream_t st);
+// Groups of the adjoint: isochromats of equal coord[a] (null: not compared),
+// dB0 and class, in that order.  Writes order and gid[K] (isochromats sorted by
+// group, their groups), and per group (coordinates or 0, dB0) and the class.
+// *n_groups = -1: too many distinct values, or more than max_groups groups.
+// scratch: adjoint_group_scratch bytes.  Synchronizes the stream.
+size_t adjoint_group_scratch(int64_t K);
+hipError_t adjoint_groups(int64_t K, const float *const coord[3], const float *df, const int32_t *cls,
+                          int32_t n_classes, int64_t max_groups, void *scratch, size_t scratch_bytes, int32_t *order,
+                          int32_t *gid, float4 *gtab, int32_t *gcls, int64_t *n_groups, hipStream_t st);
 hipError_t group_axis(int64_t K, bool coord_last, const float *coord, const float *t1, const float *t2, const float *df,
                       void *scratch, size_t scratch_bytes, int32_t *gid_nat, SortedAxis *s, int64_t *n_groups,
                       hipStream_t st);

@@ -404,42 +404,62 @@ __global__ __launch_bounds__(kAdjWG) __attribute__((amdgpu_waves_per_eu(4))) voi
 }
 
 // -------------------------------------------------------------- finalize
-__global__ __launch_bounds__(256) void k_adj_sum_sig(const double2 *part, int grid, int N, double *sig) {
-    const int n = blockIdx.x * 256 + threadIdx.x;
-    if (n >= N) return;
+// Column sums over the workgroups' rows: 8 columns and 32 lanes of rows per
+// workgroup.  One thread per column left the chain of row loads exposed: 2.7 ms
+// for 4096 rows of 3000 samples.
+template <typename In, typename Store>
+__device__ __forceinline__ void sum_rows(const In *__restrict__ part, int rows, int n, Store store) {
+    __shared__ double2 red[32][8];
+    const int col = threadIdx.x & 7, lane = threadIdx.x >> 3, c = blockIdx.x * 8 + col;
     double re = 0.0, im = 0.0;
-    for (int g = 0; g < grid; ++g) {
-        const double2 p = part[(int64_t)g * N + n];
-        re += p.x;
-        im += p.y;
-    }
-    sig[2 * n] = re;
-    sig[2 * n + 1] = im;
-}
-
-__global__ __launch_bounds__(256) void k_adj_sum_grad(const float2 *grf, const double2 *gt, int grid, int n_rf, int C,
-                                                      float *grad_rf, double *g1, double *g2) {
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j < n_rf) {
-        double re = 0.0, im = 0.0;
-        for (int g = 0; g < grid; ++g) {
-            const float2 p = grf[(int64_t)g * n_rf + j];
+    if (c < n) {
+#pragma unroll 8
+        for (int r = lane; r < rows; r += 32) {
+            const In p = part[(int64_t)r * n + c];
             re += p.x;
             im += p.y;
         }
-        grad_rf[2 * j] = (float)re;
-        grad_rf[2 * j + 1] = (float)im;
     }
-    if (j < C) {
-        double a = 0.0, b = 0.0;
-        for (int g = 0; g < grid; ++g) {
-            const double2 p = gt[(int64_t)g * C + j];
-            a += p.x;
-            b += p.y;
+    red[lane][col] = make_double2(re, im);
+    __syncthreads();
+    if (lane == 0 && c < n) {
+        for (int l = 1; l < 32; ++l) {
+            re += red[l][col].x;
+            im += red[l][col].y;
         }
-        g1[j] = a;
-        g2[j] = b;
+        store(c, re, im);
     }
+}
+
+__global__ __launch_bounds__(256) void k_adj_sum_sig(const double2 *part, int rows, int n, double *out) {
+    sum_rows(part, rows, n, [=](int c, double re, double im) {
+        out[2 * c] = re;
+        out[2 * c + 1] = im;
+    });
+}
+
+__global__ __launch_bounds__(256) void k_adj_sum_rf(const float2 *part, int rows, int n, float *out) {
+    sum_rows(part, rows, n, [=](int c, double re, double im) {
+        out[2 * c] = (float)re;
+        out[2 * c + 1] = (float)im;
+    });
+}
+
+__global__ __launch_bounds__(256) void k_adj_sum_classes(const double2 *part, int rows, int n, double *g1, double *g2) {
+    sum_rows(part, rows, n, [=](int c, double re, double im) {
+        g1[c] = re;
+        g2[c] = im;
+    });
+}
+
+hipError_t launch_adj_rows(const double2 *part, int rows, int n, double *out, hipStream_t st) {
+    if (n > 0) hipLaunchKernelGGL(k_adj_sum_sig, dim3((n + 7) / 8), dim3(256), 0, st, part, rows, n, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_adj_class_rows(const double2 *part, int rows, int C, double *g1, double *g2, hipStream_t st) {
+    hipLaunchKernelGGL(k_adj_sum_classes, dim3((C + 7) / 8), dim3(256), 0, st, part, rows, C, g1, g2);
+    return hipGetLastError();
 }
 
 static int adj_grid(const AdjArgs &a) { return (int)((a.K + kAdjWG - 1) / kAdjWG); }
@@ -461,15 +481,9 @@ hipError_t launch_adj_backward(const AdjArgs &a, hipStream_t st) {
 hipError_t launch_adj_finalize(const AdjArgs &a, double *sig, float *grad_rf, double *grad_t1, double *grad_t2,
                                bool forward, hipStream_t st) {
     const int grid = adj_grid(a);
-    if (forward) {
-        if (a.N > 0)
-            hipLaunchKernelGGL(k_adj_sum_sig, dim3((a.N + 255) / 256), dim3(256), 0, st, a.sig_part, grid, a.N, sig);
-    } else {
-        const int n = a.n_rf > a.n_classes ? a.n_rf : a.n_classes;
-        hipLaunchKernelGGL(k_adj_sum_grad, dim3((n + 255) / 256), dim3(256), 0, st, a.grf_part, a.gt_part, grid,
-                           a.n_rf, a.n_classes, grad_rf, grad_t1, grad_t2);
-    }
-    return hipGetLastError();
+    if (forward) return launch_adj_rows(a.sig_part, grid, a.N, sig, st);
+    hipLaunchKernelGGL(k_adj_sum_rf, dim3((a.n_rf + 7) / 8), dim3(256), 0, st, a.grf_part, grid, a.n_rf, grad_rf);
+    return launch_adj_class_rows(a.gt_part, grid, a.n_classes, grad_t1, grad_t2, st);
 }
 
 }  // namespace gbs

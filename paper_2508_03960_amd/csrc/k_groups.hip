@@ -387,6 +387,19 @@ static bool carve_fields(const float *const val[kFields], Carve &w, Fields &f) {
     return true;
 }
 
+// Tables of the fields' values and their counts (synchronizes the stream).
+static hipError_t rank_fields(int64_t K, const Fields &f, int32_t (&count)[kFields], hipStream_t st) {
+    hipLaunchKernelGGL(k_zero_i32, grid_for(kFieldZero), dim3(256), 0, st, (int64_t)kFieldZero, f.count);
+    const int64_t need = (K + 255) / 256;
+    hipLaunchKernelGGL(k_field_values, dim3((unsigned)(need < kValueBlocks ? need : kValueBlocks), kFields), dim3(256), 0,
+                       st, K, f);
+    hipLaunchKernelGGL(k_field_ranks, dim3(kFieldCap / 256, kFields), dim3(256), 0, st, f);
+    hipError_t e;
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = hipMemcpyAsync(count, f.count, sizeof(count), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
+    return hipStreamSynchronize(st);
+}
+
 // Groups of all requested axes (coord[a] null: not requested) by cells; gid[a]
 // has room for K.  *done stays false if the phantom needs the sorted way.
 // Otherwise gid[a] holds the groups (natural order), d->total the group counts
@@ -401,15 +414,9 @@ hipError_t dense_groups(int64_t K, const float *const coord[3], const float *t1,
     Cells &c = d->c;
     const float *const val[kFields] = {coord[0], coord[1], coord[2], t1, t2, df};
     if (!carve_fields(val, w, f)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_zero_i32, grid_for(kFieldZero), dim3(256), 0, st, (int64_t)kFieldZero, f.count);
-    const int64_t need = (K + 255) / 256;
-    hipLaunchKernelGGL(k_field_values, dim3((unsigned)(need < kValueBlocks ? need : kValueBlocks), kFields), dim3(256), 0, st, K, f);
-    hipLaunchKernelGGL(k_field_ranks, dim3(kFieldCap / 256, kFields), dim3(256), 0, st, f);
-    hipError_t e;
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     int32_t count[kFields];
-    if ((e = hipMemcpyAsync(count, f.count, sizeof(count), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    hipError_t e = rank_fields(K, f, count, st);
+    if (e != hipSuccess) return e;
     if (!cell_blocks(count, dense_cell_limit(K), c)) return hipSuccess;
     const int64_t n = c.base[4];
     d->d_total = w.take<int32_t>(4);
@@ -439,6 +446,112 @@ hipError_t dense_tables(const DenseGroups &d, float4 *const gtab[3], float4 *tta
     hipLaunchKernelGGL(k_cell_tables, dim3((unsigned)((d.c.base[4] + 255) / 256)), dim3(256), 0, st, d.f, d.c,
                        (const int32_t *)d.d_total, gtab[0], gtab[1], gtab[2], ttab, tmap);
     return hipGetLastError();
+}
+
+// ---- groups of the adjoint ------------------------------------------------------
+// cell = (((x ny + y) nz + z) nd + dB0) C + class, of the values' ranks
+struct AdjCells {
+    int64_t n;
+    int32_t nv[4], C;  // values of x, y, z (1: not compared), dB0; classes
+    int32_t shift[4];
+    int32_t *flag, *ids;
+};
+
+__device__ __forceinline__ int64_t adj_cell(const Fields &f, const AdjCells &c, const int32_t *cls, int64_t i) {
+    int64_t cell = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (f.val[q]) cell = cell * c.nv[q] + rank_of(f.rank[q], c.shift[q], f.val[q][i]);
+    return cell * c.C + cls[i];
+}
+
+__global__ __launch_bounds__(256) void k_adj_cells(int64_t K, Fields f, AdjCells c, const int32_t *__restrict__ cls,
+                                                   int32_t *__restrict__ cell) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < K; i += (int64_t)gridDim.x * 256) {
+        const int64_t v = adj_cell(f, c, cls, i);
+        cell[i] = (int32_t)v;
+        mark(c.flag, v);
+    }
+}
+
+__global__ __launch_bounds__(256) void k_adj_tables(Fields f, AdjCells c, float4 *__restrict__ gtab,
+                                                    int32_t *__restrict__ gcls) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= c.n || !c.flag[i]) return;
+    const int32_t g = c.ids[i] - 1;
+    int64_t r = i / c.C;
+    float v[4];
+#pragma unroll
+    for (int q = 3; q >= 0; --q) {
+        v[q] = f.val[q] ? from_ordered(f.sorted[q][r % c.nv[q]]) : 0.f;
+        r /= c.nv[q];
+    }
+    gtab[g] = make_float4(v[0], v[1], v[2], v[3]);
+    gcls[g] = (int32_t)(i % c.C);
+}
+
+__global__ __launch_bounds__(256) void k_adj_keys(int64_t K, const int32_t *__restrict__ ids, uint32_t *__restrict__ key,
+                                                  int32_t *__restrict__ idx) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < K; i += (int64_t)gridDim.x * 256) {
+        key[i] = (uint32_t)(ids[key[i]] - 1);
+        idx[i] = (int32_t)i;
+    }
+}
+
+static int bits_for(int64_t n) {  // of the numbers below n
+    int b = 0;
+    while (b < 32 && ((int64_t)1 << b) < n) ++b;
+    return b;
+}
+
+size_t adjoint_group_scratch(int64_t K) { return group_scratch_bytes(K) + 8 * (size_t)K + 1024; }
+
+hipError_t adjoint_groups(int64_t K, const float *const coord[3], const float *df, const int32_t *cls,
+                          int32_t n_classes, int64_t max_groups, void *scratch, size_t scratch_bytes, int32_t *order,
+                          int32_t *gid, float4 *gtab, int32_t *gcls, int64_t *n_groups, hipStream_t st) {
+    *n_groups = -1;
+    Carve w{(char *)scratch, scratch_bytes};
+    Fields f;
+    const float *const val[kFields] = {coord[0], coord[1], coord[2], df, nullptr, nullptr};
+    if (!carve_fields(val, w, f)) return hipErrorInvalidValue;
+    int32_t count[kFields];
+    hipError_t e = rank_fields(K, f, count, st);
+    if (e != hipSuccess) return e;
+    AdjCells c{};
+    c.n = c.C = n_classes;
+    for (int q = 0; q < 4; ++q) {
+        if (count[q] > kFieldCap) return hipSuccess;
+        c.nv[q] = f.val[q] ? count[q] : 1;
+        c.shift[q] = rank_shift(count[q]);
+        c.n *= c.nv[q];
+        if (c.n > dense_cell_limit(K)) return hipSuccess;
+    }
+    c.flag = w.take<int32_t>((size_t)c.n);
+    c.ids = w.take<int32_t>((size_t)c.n);
+    uint32_t *key = w.take<uint32_t>(K);
+    int32_t *idx = w.take<int32_t>(K);
+    size_t b1 = 0, b2 = 0;
+    if ((e = inclusive_sum(nullptr, &b1, (const int32_t *)nullptr, nullptr, c.n, st)) != hipSuccess) return e;
+    if ((e = sort_pairs(nullptr, &b2, key, (uint32_t *)gid, idx, order, K, 32, st)) != hipSuccess) return e;
+    char *tmp = w.take<char>(b1 > b2 ? b1 : b2);
+    if (!c.flag || !c.ids || !key || !idx || !tmp) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_zero_i32, grid_for(c.n), dim3(256), 0, st, c.n, c.flag);
+    hipLaunchKernelGGL(k_adj_cells, grid_for(K), dim3(256), 0, st, K, f, c, cls, (int32_t *)key);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = inclusive_sum(tmp, &b1, (const int32_t *)c.flag, c.ids, c.n, st)) != hipSuccess) return e;
+    int32_t G = 0;
+    if ((e = hipMemcpyAsync(&G, c.ids + (c.n - 1), sizeof(G), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
+    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    if (G > max_groups) return hipSuccess;
+    hipLaunchKernelGGL(k_adj_tables, dim3((unsigned)((c.n + 255) / 256)), dim3(256), 0, st, f, c, gtab, gcls);
+    hipLaunchKernelGGL(k_adj_keys, grid_for(K), dim3(256), 0, st, K, c.ids, key, idx);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const int bits = bits_for(G) < 1 ? 1 : bits_for(G);
+    if ((e = sort_pairs(nullptr, &b2, key, (uint32_t *)gid, idx, order, K, (unsigned)bits, st)) != hipSuccess) return e;
+    if (b2 > w.left + (size_t)(w.p - tmp)) return hipErrorInvalidValue;
+    if ((e = sort_pairs(tmp, &b2, key, (uint32_t *)gid, idx, order, K, (unsigned)bits, st)) != hipSuccess) return e;
+    *n_groups = G;
+    return hipSuccess;
 }
 
 // ---- padded group-sorted layout ---------------------------------------------
@@ -497,12 +610,6 @@ static hipError_t sort_runs(Layout *l, const int32_t *gid_x, const int32_t *gid_
     if ((e = inclusive_sum(tmp, &b2, head_flags(key2), l->rid, l->K, st)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_run_start<Key>, g, dim3(256), 0, st, l->K, key2, zbits, l->rid, l->rstart, l->gx, l->gz);
     return hipGetLastError();
-}
-
-static int bits_for(int64_t n) {  // of the numbers below n
-    int b = 0;
-    while (b < 32 && ((int64_t)1 << b) < n) ++b;
-    return b;
 }
 
 // Order and runs of the layout from natural-order x (and optional z) group ids
