@@ -15,8 +15,8 @@
 //                   then the Adam update of the FP32 master weights and the
 //                   repacked BF16 MFMA fragments, one gradient tile per
 //                   workgroup.
-//  k_mlp_infer      forward pass only, weights staged in LDS, 32 samples per
-//                   wavefront and iteration, then K = K_ref + Y / scale and
+//  k_mlp_infer      forward pass only, weights staged in LDS, 16 samples per
+//                   wavefront and pass, then K = K_ref + Y / scale and
 //                   T = P(a) K P(a).
 //
 // MFMA 16x16x32 lane layout (lane l, g = l / 16): A holds row l % 16 and
@@ -65,17 +65,33 @@ __device__ __forceinline__ bf16x8 ld_frag(const uint4 *frags, int F, int lane) {
     return r;
 }
 
+// Two values at once: one packed conversion for the high parts and one for the
+// low ones, and each difference v - hi (exact) is one dot product of the packed
+// high parts with (-1, 0) or (0, -1).  Converted one by one, the halves cost
+// four instructions per value instead of two.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void split2(float a, float b, bf16x2 &h, bf16x2 &l) {
+    h = bf16x2{(__bf16)a, (__bf16)b};
+    // (the pairs in registers: as constants the compiler writes them as inline
+    // operands, which the instruction takes for other pairs)
+    uint32_t lo = 0x0000bf80u, hi = 0xbf800000u;
+    asm("" : "+s"(lo), "+s"(hi));
+    bf16x2 first, second;
+    __builtin_memcpy(&first, &lo, 4);
+    __builtin_memcpy(&second, &hi, 4);
+    const float la = __builtin_amdgcn_fdot2_f32_bf16(h, first, a, false);
+    const float lb = __builtin_amdgcn_fdot2_f32_bf16(h, second, b, false);
+    l = bf16x2{(__bf16)la, (__bf16)lb};
+}
+
 __device__ __forceinline__ void make_frag(const float *lo4, const float *hi4, bf16x8 &fh, bf16x8 &fl) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        __bf16 h, l;
-        split(lo4[i], h, l);
-        fh[i] = h;
-        fl[i] = l;
-        split(hi4[i], h, l);
-        fh[4 + i] = h;
-        fl[4 + i] = l;
-    }
+    bf16x2 h[4], l[4];
+    split2(lo4[0], lo4[1], h[0], l[0]);
+    split2(lo4[2], lo4[3], h[1], l[1]);
+    split2(hi4[0], hi4[1], h[2], l[2]);
+    split2(hi4[2], hi4[3], h[3], l[3]);
+    __builtin_memcpy(&fh, h, sizeof(fh));
+    __builtin_memcpy(&fl, l, sizeof(fl));
 }
 
 // Logistic function with the hardware reciprocal (v_rcp_f32, within 1 ulp):
@@ -731,7 +747,12 @@ __device__ __forceinline__ void frags_from(const float (*h)[4], bf16x8 *fh, bf16
 }
 
 // -------------------------------------------------------------- k_mlp_infer
-constexpr int kInferWG = 512;  // 8 wavefronts share one LDS copy of the weights
+// 16 wavefronts share one LDS copy of the weights, four per SIMD, to cover the
+// chains of exp and rcp; VALU issue bounds the kernel (1088 instructions per 16
+// samples, 192 of them exp and rcp, beside 152 MFMAs).  Two wavefronts per
+// SIMD with 32 samples each read a weight fragment half as often, but took 250
+// us for 1 M tuples; this takes 214.
+constexpr int kInferWG = 1024;
 
 // Tuple s of an inference launch (s < N).
 __device__ __forceinline__ void infer_tuple(const MlpInferArgs &a, int64_t s, float tp[5]) {
@@ -748,105 +769,107 @@ __device__ __forceinline__ void infer_tuple(const MlpInferArgs &a, int64_t s, fl
     }
 }
 
-__global__ __launch_bounds__(kInferWG) void k_mlp_infer(MlpInferArgs a) {
+// z -> SiLU(z) of the lane's 32 neurons, as the next layer's B operands.
+__device__ __forceinline__ void silu_frags(const f32x4 *acc, bf16x8 *fh, bf16x8 *fl) {
+    float h[8][4];
+#pragma unroll
+    for (int m = 0; m < 8; m += 2) {  // eight at a time: one value's chain of exp and rcp behind the others'
+        float e[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) e[r] = __expf(-acc[m + r / 4][r % 4]);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) e[r] = __builtin_amdgcn_rcpf(1.f + e[r]);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) h[m + r / 4][r % 4] = acc[m + r / 4][r % 4] * e[r];
+    }
+    frags_from(h, fh, fl);
+}
+
+// A wavefront takes `per` times 16 samples through the network and then, one
+// sample per lane, back to transitions in FP64 (the reference transition and
+// the frame: a quarter of the kernel with half of the lanes idle).
+__global__ __launch_bounds__(kInferWG) void k_mlp_infer(MlpInferArgs a, int per) {
     __shared__ uint4 sw[kFragFwd * 64];
-    __shared__ float sk[kInferWG / 64][32][12];
+    __shared__ float sk[kInferWG / 64][64][12];
     for (int i = threadIdx.x; i < kFragFwd * 64; i += kInferWG) sw[i] = a.wf[i];
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int g = lane >> 4, col = lane & 15;
-    const int64_t n_tiles = (a.N + 31) / 32;
-    constexpr int kWaves = kInferWG / 64;
-    for (int64_t tile = (int64_t)blockIdx.x * kWaves + wave; tile < n_tiles; tile += (int64_t)gridDim.x * kWaves) {
-        f32x4 acc[2][8];
-        bf16x8 fh[2][4], fl[2][4];
-        // layer 1
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-            const int64_t s = tile * 32 + nt * 16 + col;
-            float u[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-            if (s < a.N) {
-                float tp[5];
-                infer_tuple(a, s, tp);
-                features(tp, a.norm, u);
-            }
-            input_frag(u, g, fh[nt][0], fl[nt][0]);
-            bias_init(acc[nt], a.params + kOffB1, g);
-        }
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            const bf16x8 A = ld_frag(sw, kFragFwdL1 + m, lane);
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
-                acc[nt][m] = mfma(A, fh[nt][0], acc[nt][m]);
-                acc[nt][m] = mfma(A, fl[nt][0], acc[nt][m]);
-            }
-        }
-        // layers 2, 3
-#pragma unroll
-        for (int layer = 0; layer < 2; ++layer) {
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
-                float h[8][4];
-#pragma unroll
-                for (int m = 0; m < 8; ++m)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float z = acc[nt][m][r];
-                        h[m][r] = z * sigmoid(z);
-                    }
-                frags_from(h, fh[nt], fl[nt]);
-                bias_init(acc[nt], a.params + (layer == 0 ? kOffB2 : kOffB3), g);
-            }
-            const int fb = layer == 0 ? kFragFwdL2 : kFragFwdL3;
-#pragma unroll
-            for (int m = 0; m < 8; ++m)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const bf16x8 A = ld_frag(sw, fb + 4 * m + c, lane);
-#pragma unroll
-                    for (int nt = 0; nt < 2; ++nt) {
-                        acc[nt][m] = mfma(A, fh[nt][c], acc[nt][m]);
-                        acc[nt][m] = mfma(A, fl[nt][c], acc[nt][m]);
-                    }
+    const int size = 16 * per;
+    const int64_t n_tiles = (a.N + size - 1) / size;
+    // consecutive tiles on different CUs, so that few tiles use many of them
+    for (int64_t tile = (int64_t)wave * gridDim.x + blockIdx.x; tile < n_tiles;
+         tile += (int64_t)gridDim.x * (kInferWG / 64)) {
+        for (int q = 0; q < per; ++q) {
+            // (the fragments and biases are the same in every pass: kept out of the
+            // loop, they would take more registers than there are)
+            int ln = lane;
+            const float *params = a.params;
+            asm volatile("" : "+v"(ln), "+s"(params));
+            f32x4 acc[8];
+            bf16x8 fh[4], fl[4];
+            // layer 1
+            {
+                const int64_t s = tile * size + 16 * q + col;
+                float u[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+                if (s < a.N) {
+                    float tp[5];
+                    infer_tuple(a, s, tp);
+                    features(tp, a.norm, u);
                 }
-        }
-        // layer 4
-        f32x4 y[2];
+                input_frag(u, g, fh[0], fl[0]);
+                bias_init(acc, params + kOffB1, g);
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-            float h[8][4];
+                for (int m0 = 0; m0 < 8; m0 += 4) {
+                    bf16x8 A[4];
 #pragma unroll
-            for (int m = 0; m < 8; ++m)
+                    for (int m = 0; m < 4; ++m) A[m] = ld_frag(sw, kFragFwdL1 + m0 + m, ln);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float z = acc[nt][m][r];
-                    h[m][r] = z * sigmoid(z);
+                    for (int m = 0; m < 4; ++m) acc[m0 + m] = mfma(A[m], fh[0], acc[m0 + m]);
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) acc[m0 + m] = mfma(A[m], fl[0], acc[m0 + m]);
                 }
-            frags_from(h, fh[nt], fl[nt]);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) y[nt][r] = (4 * g + r < 12) ? a.params[kOffB4 + ((4 * g + r) % 12)] : 0.f;
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const bf16x8 A = ld_frag(sw, kFragFwdL4 + c, lane);
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
-                y[nt] = mfma(A, fh[nt][c], y[nt]);
-                y[nt] = mfma(A, fl[nt][c], y[nt]);
             }
-        }
-        // gather the 12 outputs of each sample in one lane, then T = P(a) K P(a)
+            // layers 2, 3
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
+            for (int layer = 0; layer < 2; ++layer) {
+                silu_frags(acc, fh, fl);
+                bias_init(acc, params + (layer == 0 ? kOffB2 : kOffB3), g);
+                const int fb = layer == 0 ? kFragFwdL2 : kFragFwdL3;
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int m0 = 0; m0 < 8; m0 += 4) {  // four sums between two products of one
+                        bf16x8 A[4];
+#pragma unroll
+                        for (int m = 0; m < 4; ++m) A[m] = ld_frag(sw, fb + 4 * (m0 + m) + c, ln);
+#pragma unroll
+                        for (int m = 0; m < 4; ++m) acc[m0 + m] = mfma(A[m], fh[c], acc[m0 + m]);
+#pragma unroll
+                        for (int m = 0; m < 4; ++m) acc[m0 + m] = mfma(A[m], fl[c], acc[m0 + m]);
+                    }
+            }
+            // layer 4
+            silu_frags(acc, fh, fl);
+            f32x4 y;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) y[r] = (4 * g + r < 12) ? params[kOffB4 + ((4 * g + r) % 12)] : 0.f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const bf16x8 A = ld_frag(sw, kFragFwdL4 + c, ln);
+                y = mfma(A, fh[c], y);
+                y = mfma(A, fl[c], y);
+            }
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                if (4 * g + r < 12) sk[wave][nt * 16 + col][4 * g + r] = y[nt][r];
+                if (4 * g + r < 12) sk[wave][16 * q + col][4 * g + r] = y[r];
+        }
+        // the 12 outputs of each sample in one lane, then T = P(a) K P(a)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const int64_t s = tile * 32 + lane;
-        if (lane < 32 && s < a.N) {
+        const int64_t s = tile * size + lane;
+        if (lane < size && s < a.N) {
             double k[12], T[12], c, sn;
             float tp[5];
             infer_tuple(a, s, tp);
@@ -875,10 +898,13 @@ __global__ __launch_bounds__(kInferWG) void k_mlp_infer(MlpInferArgs a) {
 hipError_t launch_mlp_infer(const MlpInferArgs &a, hipStream_t st) {
     if (a.N <= 0) return hipSuccess;
     if (!a.norm.ref || (!a.rows && !a.out) || (!a.src_z && !a.tuples)) return hipErrorInvalidValue;
-    const int64_t tiles = (a.N + 31) / 32;
-    const int64_t wgs = (tiles + kInferWG / 64 - 1) / (kInferWG / 64);
-    const unsigned grid = (unsigned)(wgs < 256 ? wgs : 256);  // one resident workgroup per CU
-    hipLaunchKernelGGL(k_mlp_infer, dim3(grid), dim3(kInferWG), 0, st, a);
+    // samples per wavefront: 16 while that leaves no wavefront a second tile, then 32, 64
+    constexpr int64_t kWaves = 256 * (kInferWG / 64);  // one resident workgroup per CU
+    int per = 1;
+    while (per < 4 && (a.N + 16 * per - 1) / (16 * per) > kWaves) per *= 2;
+    const int64_t tiles = (a.N + 16 * per - 1) / (16 * per);
+    const unsigned grid = (unsigned)(tiles < 256 ? tiles : 256);
+    hipLaunchKernelGGL(k_mlp_infer, dim3(grid), dim3(kInferWG), 0, st, a, per);
     return hipGetLastError();
 }
 
