@@ -378,8 +378,8 @@ struct TrainBufs {
         a.targets = K;
         a.N = n;
         a.pa = 1;
-        a.pc = 0;
-        a.j0 = 0;
+        a.first = 0;
+        a.inv_n = (uint64_t)n < (1ull << 52) / (uint64_t)(B + 1) ? 1.0 / (double)n : 0.0;
         a.B = B;
         a.wf = (const uint4 *)m->wf;
         a.wb = (const uint4 *)m->wb;
@@ -456,8 +456,7 @@ int gbs_mlp_train(gbs_mlp *m, const float *tuples, const double *T_exact, int64_
         for (int64_t b = 0; b < per_epoch; ++b, ++k) {
             MlpTrainArgs a = tb.train_args(m, tuples, n, B, dloss + k);
             a.pa = pa;
-            a.pc = pc;
-            a.j0 = b * B;
+            a.first = (uint64_t)(((unsigned __int128)pa * (uint64_t)(b * B) + pc) % (uint64_t)n);
             MCHK(launch_mlp_train_fb(a, m->stream));
             m->t += 1;
             const double frac = (double)k / (double)total;  // first step at lr_max

@@ -28,12 +28,12 @@
 namespace gbs {
 
 // rocPRIM device primitives on int32 counts (stable LSD radix sort of the low
-// `bits` bits of 32- or 64-bit keys with an int32 payload; inclusive and
-// exclusive sums).  With tmp null they report the temporary bytes they need in
+// `bits` bits of 64-bit keys with an int32 payload; inclusive and exclusive
+// sums).  One key type for all sorts: a second one doubles the code to load for
+// a tenth of a pass.  With tmp null they report the temporary bytes they need in
 // *bytes.
-template <typename Key>
-static hipError_t sort_pairs(void *tmp, size_t *bytes, const Key *kin, Key *kout, const int32_t *vin, int32_t *vout,
-                             int64_t n, unsigned int bits, hipStream_t st) {
+static hipError_t sort_pairs(void *tmp, size_t *bytes, const uint64_t *kin, uint64_t *kout, const int32_t *vin,
+                             int32_t *vout, int64_t n, unsigned int bits, hipStream_t st) {
     return rocprim::radix_sort_pairs(tmp, *bytes, kin, kout, vin, vout, (unsigned int)n, 0u, bits, st);
 }
 template <typename In>
@@ -45,14 +45,12 @@ static hipError_t exclusive_sum(void *tmp, size_t *bytes, const int32_t *in, int
 }
 
 // 1 where a sorted key differs from the one before it
-template <typename Key>
 struct HeadFlag {
-    const Key *key;
+    const uint64_t *key;
     __device__ int32_t operator()(int64_t i) const { return i == 0 || key[i] != key[i - 1] ? 1 : 0; }
 };
-template <typename Key>
-static auto head_flags(const Key *key) {
-    return rocprim::make_transform_iterator(rocprim::make_counting_iterator<int64_t>(0), HeadFlag<Key>{key});
+static auto head_flags(const uint64_t *key) {
+    return rocprim::make_transform_iterator(rocprim::make_counting_iterator<int64_t>(0), HeadFlag{key});
 }
 
 __device__ __forceinline__ uint32_t ordered_bits(float f) {
@@ -466,10 +464,10 @@ __device__ __forceinline__ int64_t adj_cell(const Fields &f, const AdjCells &c, 
 }
 
 __global__ __launch_bounds__(256) void k_adj_cells(int64_t K, Fields f, AdjCells c, const int32_t *__restrict__ cls,
-                                                   int32_t *__restrict__ cell) {
+                                                   uint64_t *__restrict__ cell) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < K; i += (int64_t)gridDim.x * 256) {
         const int64_t v = adj_cell(f, c, cls, i);
-        cell[i] = (int32_t)v;
+        cell[i] = (uint64_t)v;
         mark(c.flag, v);
     }
 }
@@ -490,12 +488,16 @@ __global__ __launch_bounds__(256) void k_adj_tables(Fields f, AdjCells c, float4
     gcls[g] = (int32_t)(i % c.C);
 }
 
-__global__ __launch_bounds__(256) void k_adj_keys(int64_t K, const int32_t *__restrict__ ids, uint32_t *__restrict__ key,
+__global__ __launch_bounds__(256) void k_adj_keys(int64_t K, const int32_t *__restrict__ ids, uint64_t *__restrict__ key,
                                                   int32_t *__restrict__ idx) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < K; i += (int64_t)gridDim.x * 256) {
-        key[i] = (uint32_t)(ids[key[i]] - 1);
+        key[i] = (uint64_t)(ids[key[i]] - 1);
         idx[i] = (int32_t)i;
     }
+}
+
+__global__ __launch_bounds__(256) void k_adj_gids(int64_t K, const uint64_t *__restrict__ key, int32_t *__restrict__ gid) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < K; i += (int64_t)gridDim.x * 256) gid[i] = (int32_t)key[i];
 }
 
 static int bits_for(int64_t n) {  // of the numbers below n
@@ -504,7 +506,7 @@ static int bits_for(int64_t n) {  // of the numbers below n
     return b;
 }
 
-size_t adjoint_group_scratch(int64_t K) { return group_scratch_bytes(K) + 8 * (size_t)K + 1024; }
+size_t adjoint_group_scratch(int64_t K) { return group_scratch_bytes(K) + 20 * (size_t)K + 2048; }
 
 hipError_t adjoint_groups(int64_t K, const float *const coord[3], const float *df, const int32_t *cls,
                           int32_t n_classes, int64_t max_groups, void *scratch, size_t scratch_bytes, int32_t *order,
@@ -528,15 +530,15 @@ hipError_t adjoint_groups(int64_t K, const float *const coord[3], const float *d
     }
     c.flag = w.take<int32_t>((size_t)c.n);
     c.ids = w.take<int32_t>((size_t)c.n);
-    uint32_t *key = w.take<uint32_t>(K);
+    uint64_t *key = w.take<uint64_t>(K), *sorted = w.take<uint64_t>(K);
     int32_t *idx = w.take<int32_t>(K);
     size_t b1 = 0, b2 = 0;
     if ((e = inclusive_sum(nullptr, &b1, (const int32_t *)nullptr, nullptr, c.n, st)) != hipSuccess) return e;
-    if ((e = sort_pairs(nullptr, &b2, key, (uint32_t *)gid, idx, order, K, 32, st)) != hipSuccess) return e;
+    if ((e = sort_pairs(nullptr, &b2, key, sorted, idx, order, K, 64, st)) != hipSuccess) return e;
     char *tmp = w.take<char>(b1 > b2 ? b1 : b2);
-    if (!c.flag || !c.ids || !key || !idx || !tmp) return hipErrorInvalidValue;
+    if (!c.flag || !c.ids || !key || !sorted || !idx || !tmp) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_zero_i32, grid_for(c.n), dim3(256), 0, st, c.n, c.flag);
-    hipLaunchKernelGGL(k_adj_cells, grid_for(K), dim3(256), 0, st, K, f, c, cls, (int32_t *)key);
+    hipLaunchKernelGGL(k_adj_cells, grid_for(K), dim3(256), 0, st, K, f, c, cls, key);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = inclusive_sum(tmp, &b1, (const int32_t *)c.flag, c.ids, c.n, st)) != hipSuccess) return e;
     int32_t G = 0;
@@ -547,11 +549,12 @@ hipError_t adjoint_groups(int64_t K, const float *const coord[3], const float *d
     hipLaunchKernelGGL(k_adj_keys, grid_for(K), dim3(256), 0, st, K, c.ids, key, idx);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const int bits = bits_for(G) < 1 ? 1 : bits_for(G);
-    if ((e = sort_pairs(nullptr, &b2, key, (uint32_t *)gid, idx, order, K, (unsigned)bits, st)) != hipSuccess) return e;
+    if ((e = sort_pairs(nullptr, &b2, key, sorted, idx, order, K, (unsigned)bits, st)) != hipSuccess) return e;
     if (b2 > w.left + (size_t)(w.p - tmp)) return hipErrorInvalidValue;
-    if ((e = sort_pairs(tmp, &b2, key, (uint32_t *)gid, idx, order, K, (unsigned)bits, st)) != hipSuccess) return e;
+    if ((e = sort_pairs(tmp, &b2, key, sorted, idx, order, K, (unsigned)bits, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_adj_gids, grid_for(K), dim3(256), 0, st, K, sorted, gid);
     *n_groups = G;
-    return hipSuccess;
+    return hipGetLastError();
 }
 
 // ---- padded group-sorted layout ---------------------------------------------
@@ -561,26 +564,24 @@ hipError_t adjoint_groups(int64_t K, const float *const coord[3], const float *d
 // share both groups.  The sort takes the bits that the group counts need: 3
 // passes of 8 bits instead of 8, for the 6.8 M isochromats above 0.2 ms
 // instead of 0.65.
-template <typename Key>
 __global__ void k_pair_keys(int64_t K, const int32_t *__restrict__ gx, const int32_t *__restrict__ gz, int zbits,
-                            Key *__restrict__ key, int32_t *__restrict__ idx) {
+                            uint64_t *__restrict__ key, int32_t *__restrict__ idx) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < K; i += (int64_t)gridDim.x * blockDim.x) {
-        key[i] = ((Key)(uint32_t)gx[i] << zbits) | (Key)(gz ? (uint32_t)gz[i] : 0u);
+        key[i] = ((uint64_t)(uint32_t)gx[i] << zbits) | (gz ? (uint32_t)gz[i] : 0u);
         idx[i] = (int32_t)i;
     }
 }
 
 // rid = inclusive scan of the run starts (1-based); rstart and the run's groups
-template <typename Key>
-__global__ void k_run_start(int64_t K, const Key *__restrict__ key, int zbits, const int32_t *__restrict__ rid,
+__global__ void k_run_start(int64_t K, const uint64_t *__restrict__ key, int zbits, const int32_t *__restrict__ rid,
                             int32_t *__restrict__ rstart, int32_t *__restrict__ gx, int32_t *__restrict__ gz) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < K; i += (int64_t)gridDim.x * blockDim.x) {
         const int32_t r = rid[i] - 1;
         if (i == 0 || rid[i - 1] - 1 != r) {
-            const Key k = key[i];
+            const uint64_t k = key[i];
             rstart[r] = (int32_t)i;
             gx[r] = (int32_t)(k >> zbits);
-            gz[r] = (int32_t)(k & (((Key)1 << zbits) - 1));
+            gz[r] = (int32_t)(k & (((uint64_t)1 << zbits) - 1));
         }
     }
 }
@@ -592,10 +593,9 @@ __global__ void k_run_plen(int64_t R, int64_t K, const int32_t *__restrict__ rst
     }
 }
 
-template <typename Key>
 static hipError_t sort_runs(Layout *l, const int32_t *gid_x, const int32_t *gid_z, int zbits, int bits, Carve w,
                             hipStream_t st) {
-    Key *key = w.take<Key>(l->K), *key2 = w.take<Key>(l->K);
+    uint64_t *key = w.take<uint64_t>(l->K), *key2 = w.take<uint64_t>(l->K);
     int32_t *idx = w.take<int32_t>(l->K);
     size_t b1 = 0, b2 = 0;
     hipError_t e;
@@ -604,11 +604,11 @@ static hipError_t sort_runs(Layout *l, const int32_t *gid_x, const int32_t *gid_
     char *tmp = w.take<char>(b1 > b2 ? b1 : b2);
     if (!key || !key2 || !idx || !tmp) return hipErrorInvalidValue;
     const dim3 g = grid_for(l->K);
-    hipLaunchKernelGGL(k_pair_keys<Key>, g, dim3(256), 0, st, l->K, gid_x, gid_z, zbits, key, idx);
+    hipLaunchKernelGGL(k_pair_keys, g, dim3(256), 0, st, l->K, gid_x, gid_z, zbits, key, idx);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = sort_pairs(tmp, &b1, key, key2, idx, l->order, l->K, (unsigned)bits, st)) != hipSuccess) return e;
     if ((e = inclusive_sum(tmp, &b2, head_flags(key2), l->rid, l->K, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_run_start<Key>, g, dim3(256), 0, st, l->K, key2, zbits, l->rid, l->rstart, l->gx, l->gz);
+    hipLaunchKernelGGL(k_run_start, g, dim3(256), 0, st, l->K, key2, zbits, l->rid, l->rstart, l->gx, l->gz);
     return hipGetLastError();
 }
 
@@ -623,8 +623,7 @@ hipError_t build_layout(int64_t K, const int32_t *gid_x, int64_t Gx, const int32
     for (int32_t **a : arr)
         if (!(*a = w.take<int32_t>(K))) return hipErrorInvalidValue;
     const int zbits = gid_z ? bits_for(Gz) : 0, bits = zbits + bits_for(Gx);
-    hipError_t e = bits <= 32 ? sort_runs<uint32_t>(l, gid_x, gid_z, zbits, bits < 1 ? 1 : bits, w, st)
-                              : sort_runs<uint64_t>(l, gid_x, gid_z, zbits, bits, w, st);
+    hipError_t e = sort_runs(l, gid_x, gid_z, zbits, bits < 1 ? 1 : bits, w, st);
     if (e != hipSuccess) return e;
     int32_t R = 0;
     if ((e = hipMemcpyAsync(&R, l->rid + (K - 1), sizeof(int32_t), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
@@ -810,13 +809,12 @@ hipError_t group_runs(const Layout &l, int64_t n_groups, int32_t **xrun, hipStre
 }
 
 size_t group_scratch_bytes(int64_t K) {
-    size_t b[4] = {0, 0, 0, 0};
+    size_t b[3] = {0, 0, 0};
     const int64_t n = dense_cell_limit(K);  // >= K
     const bool sized =
-        sort_pairs(nullptr, &b[0], (const uint64_t *)nullptr, (uint64_t *)nullptr, nullptr, nullptr, K, 64, 0) == hipSuccess &&
-        sort_pairs(nullptr, &b[1], (const uint32_t *)nullptr, (uint32_t *)nullptr, nullptr, nullptr, K, 32, 0) == hipSuccess &&
-        inclusive_sum(nullptr, &b[2], (const int32_t *)nullptr, nullptr, n, 0) == hipSuccess &&
-        exclusive_sum(nullptr, &b[3], nullptr, nullptr, n, 0) == hipSuccess;
+        sort_pairs(nullptr, &b[0], nullptr, nullptr, nullptr, nullptr, K, 64, 0) == hipSuccess &&
+        inclusive_sum(nullptr, &b[1], (const int32_t *)nullptr, nullptr, n, 0) == hipSuccess &&
+        exclusive_sum(nullptr, &b[2], nullptr, nullptr, n, 0) == hipSuccess;
     size_t tmp = 0;
     for (size_t v : b) tmp = v > tmp ? v : tmp;
     // a failed size query leaves generous room; the sorts and scans report their own errors

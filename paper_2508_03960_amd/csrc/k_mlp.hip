@@ -422,6 +422,18 @@ __device__ __forceinline__ void load_a4(const uint4 *frags, int F, int lane, bf1
     for (int c = 0; c < 4; ++c) A[c] = ld_frag(frags, F + c, lane);
 }
 
+// Sample s of the batch: (pa (j0 + s) + pc) mod N = (first + pa s) mod N.  While
+// the products stay below 2^52 the quotient comes from a reciprocal, off by one
+// at most; two 64-bit divisions were the first 0.8 us of every step.
+__device__ __forceinline__ int64_t batch_sample(const MlpTrainArgs &a, int s) {
+    const uint64_t n = (uint64_t)a.N, x = a.first + a.pa * (uint64_t)s;
+    if (a.inv_n == 0.0) return (int64_t)(x % n);
+    int64_t r = (int64_t)(x - (uint64_t)((double)x * a.inv_n) * n);
+    if (r < 0) r += a.N;
+    if (r >= a.N) r -= a.N;
+    return r;
+}
+
 __global__ __launch_bounds__(64 * kTrainWaves) void k_mlp_train_fb(MlpTrainArgs a) {
     __shared__ TileHL xch[2][kTrainWaves][64];
     const int lane = threadIdx.x & 63;
@@ -430,8 +442,7 @@ __global__ __launch_bounds__(64 * kTrainWaves) void k_mlp_train_fb(MlpTrainArgs 
     const int row = 16 * w + 4 * g;  // first neuron of the lane's rows in tile w
     const int B = a.B;
     const int s = blockIdx.x * 16 + col;  // < B by the launch
-    const int64_t j = (a.j0 + s) % a.N;
-    const int64_t idx = (int64_t)(((uint64_t)a.pa * (uint64_t)j + a.pc) % (uint64_t)a.N);
+    const int64_t idx = batch_sample(a, s);
     // Every global load of the pass is issued here: only the LDS exchanges
     // then separate the layers.
     float u[5], tgt[4];
@@ -635,7 +646,13 @@ __device__ __forceinline__ int param_of(int tile, int row, int col) {
 
 __global__ __launch_bounds__(64 * kGradWaves) void k_mlp_grad_adam(MlpGradAdamArgs a) {
     __shared__ float part[kGradWaves][256];
-    const int tile = blockIdx.x;
+    // Workgroups go to the 8 dies in turn: each takes the tiles of one row of 16
+    // output neurons in layers 1 to 3 and one of layer 4, so that it reads an
+    // eighth of the dZ rows, and each of its rows once.
+    const int die = blockIdx.x & 7, k = blockIdx.x >> 3;
+    const int tile = k < 9 ? 16 + 9 * die + k : k < 18 ? 88 + 9 * die + (k - 9) : k < 20 ? 2 * die + (k - 18)
+                     : k == 20 ? 160 + die : 168;
+    if (k > 21 - (die > 0)) return;
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int g = lane >> 4, col = lane & 15;
     int arow, brow, it;
@@ -728,7 +745,8 @@ __global__ __launch_bounds__(64 * kGradWaves) void k_mlp_grad_adam(MlpGradAdamAr
 
 hipError_t launch_mlp_grad_adam(const MlpGradAdamArgs &a, hipStream_t st) {
     if (a.B <= 0 || a.B % 32) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_mlp_grad_adam, dim3(kGradTiles), dim3(64 * kGradWaves), 0, st, a);
+    static_assert(kGradTiles == 8 * 21 + 1, "21 tiles per die and one more");
+    hipLaunchKernelGGL(k_mlp_grad_adam, dim3(8 * 22), dim3(64 * kGradWaves), 0, st, a);
     return hipGetLastError();
 }
 

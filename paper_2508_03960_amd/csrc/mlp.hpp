@@ -64,8 +64,8 @@ struct MlpTrainArgs {
     const float *tuples;   // [N][5]: f_z, f_B0, T1, T2, B1 scale
     const float *targets;  // [N][12]: K (precession-removed transition)
     int64_t N;
-    uint64_t pa, pc;  // sample j of the epoch is (pa * j + pc) mod N
-    int64_t j0;       // first sample of this batch within the epoch
+    uint64_t pa, first;  // sample s of the batch is (first + pa * s) mod N, pa and first below N
+    double inv_n;        // 1 / N, or 0 where the products pass 2^52
     int32_t B;        // batch size (multiple of 64)
     const uint4 *wf, *wb;
     const float *params;
