@@ -226,7 +226,8 @@ struct gbs_ctx {
     // second stream of the context (default priority): the copy of the final
     // state into the caller's order runs on it beside the ADC evaluation
     hipStream_t side = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr, checked = nullptr;
+    int *host_flag = nullptr;  // pinned: k_check_zero_m0's answer
     std::vector<hipEvent_t> pev;  // GBS_PROFILE: one (start, stop) pair per pass launch
     GroupedPlan gp;
     // learned surrogate (not owned)
@@ -333,7 +334,9 @@ int gbs_create(gbs_ctx **out, int device, void *stream) {
     }
     if (hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming) != hipSuccess) {
+        hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&ctx->checked, hipEventDisableTiming) != hipSuccess ||
+        hipHostMalloc((void **)&ctx->host_flag, 256, hipHostMallocDefault) != hipSuccess) {
         gbs_destroy(ctx);
         return GBS_E_HIP;
     }
@@ -362,6 +365,8 @@ int gbs_destroy(gbs_ctx *ctx) {
     for (auto &e : ctx->pev) (void)hipEventDestroy(e);
     if (ctx->fork) (void)hipEventDestroy(ctx->fork);
     if (ctx->join) (void)hipEventDestroy(ctx->join);
+    if (ctx->checked) (void)hipEventDestroy(ctx->checked);
+    if (ctx->host_flag) (void)hipHostFree(ctx->host_flag);
     if (ctx->side) (void)hipStreamDestroy(ctx->side);
     delete ctx;
     return GBS_OK;
@@ -443,12 +448,15 @@ int gbs_set_sequence(gbs_ctx *ctx, const gbs_block *blocks, int64_t n_blocks, co
     copy_sequence(ctx->seq, blocks, n_blocks, rf_re, rf_im, gx, gy, gz, total_steps, adc_idx, total_samples, dt);
     ctx->cls = classify(ctx->seq);
     std::vector<StepW> w((size_t)total_steps);
-    for (int64_t j = total_steps - 1; j >= 0; --j) {
+    for (int64_t j = 0; j < total_steps; ++j) {
         const double re = rf_re[j], im = rf_im[j];
         w[j] = StepW{rf_re[j], rf_im[j], (float)(re * re + im * im), gx[j], gy[j], gz[j], 1, 0.f};
-        // (bit for bit: -0 and +0 differ)
-        if (j + 1 < total_steps && w[j + 1].same < INT32_MAX && !std::memcmp(&w[j], &w[j + 1], 6 * sizeof(float)))
-            w[j].same = w[j + 1].same + 1;
+    }
+    for (int64_t j = total_steps - 2; j >= 0; --j) {  // runs of equal steps, bit for bit: -0 and +0 differ
+        uint64_t a[3], b[3];
+        std::memcpy(a, &w[j], sizeof(a));
+        std::memcpy(b, &w[j + 1], sizeof(b));
+        if (!((a[0] ^ b[0]) | (a[1] ^ b[1]) | (a[2] ^ b[2])) && w[j + 1].same < INT32_MAX) w[j].same = w[j + 1].same + 1;
     }
     ALLOC(ctx->d_wave, sizeof(StepW) * (size_t)total_steps);
     ALLOC(ctx->d_adc, sizeof(int32_t) * (size_t)total_samples);
@@ -1826,6 +1834,18 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
     char *jb = ctx->jobs.as<char>();
     ctx->partial = g.w_partial ? (double2 *)(ws + g.w_partial) : nullptr;
 
+    // The fast sweeps hold M / M0: an initial state that gives an isochromat with
+    // M0 = 0 a magnetization takes the general sweep instead.  Found out first,
+    // and waited for just before the sweeps: the stream has the compositions, the
+    // tables and the initial state to work on meanwhile (waited for at once, it
+    // stood still for 45 us of 480).
+    if (m_init) {
+        HIPCHK(launch_fill_f64(ctx->flag.as<double>(), 1, ctx->stream));
+        HIPCHK(launch_check_zero_m0(K, ctx->ph.m0, m_init, m_init + K, m_init + 2 * K, ctx->flag.as<int>(), ctx->stream));
+        HIPCHK(hipMemcpyAsync(ctx->host_flag, ctx->flag.p, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+        HIPCHK(hipEventRecord(ctx->checked, ctx->stream));
+    }
+
     // ---- prepare: combined transitions (Eq. 7) and map tables --------------
     // The compositions and folds run on this stream.  The group sums' clearing
     // and the map tables (which depend on the group table alone) run beside
@@ -1946,18 +1966,14 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
     const int64_t Kint = ctx->Kint;
     // the default initial state (0, 0, M0) is made by the first sweep itself
     const bool fresh = !m_init && !g.exec.empty() && g.exec.front().first == 0;
-    // the fast sweeps hold M / M0: an initial state that gives an isochromat
-    // with M0 = 0 a magnetization takes the general sweep instead
-    int force_general = 0;
-    if (m_init) {
-        HIPCHK(launch_fill_f64(ctx->flag.as<double>(), 1, ctx->stream));
-        HIPCHK(launch_check_zero_m0(K, ctx->ph.m0, m_init, m_init + K, m_init + 2 * K, ctx->flag.as<int>(), ctx->stream));
-        HIPCHK(hipMemcpyAsync(&force_general, ctx->flag.p, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
-        HIPCHK(hipStreamSynchronize(ctx->stream));
-    }
     if (!fresh)
         HIPCHK(launch_init_state(Kint, ctx->Kpad, ctx->perm.as<int32_t>(), m_init, m_init ? m_init + K : nullptr,
                                  m_init ? m_init + 2 * K : nullptr, ctx->m0i.as<float>(), mx, my, mz, ctx->stream));
+    int force_general = 0;
+    if (m_init) {
+        HIPCHK(hipEventSynchronize(ctx->checked));
+        force_general = *ctx->host_flag;
+    }
     SweepArgs base{};
     base.n4 = Kint / 4;
     base.mx = (float4 *)mx;

@@ -156,12 +156,17 @@ WaveSym symmetric_pulse(const HostSeq &s, int64_t offset, int64_t n) {
     for (int64_t j = 0; j < n; ++j) {
         for (const float *v : w)
             if (v[j] != v[n - 1 - j]) return WaveSym{0, 0, 0.0, 0.0};
-        const double m = std::hypot((double)w[0][j], (double)w[1][j]);
+        const double m = (double)w[0][j] * w[0][j] + (double)w[1][j] * w[1][j];
         if (m > peak) {
             peak = m;
-            re = w[0][j] / m;
-            im = w[1][j] / m;
+            re = w[0][j];
+            im = w[1][j];
         }
+    }
+    if (peak > 0.0) {
+        peak = std::sqrt(peak);
+        re /= peak;
+        im /= peak;
     }
     // out of plane by less than rounding of the FP64 products
     for (int64_t j = 0; j < n; ++j)
