@@ -886,8 +886,18 @@ static bool in_partial_kernel(int need, bool coils) {
 // y moment before a transition that meets a transverse magnetization (the
 // first one meets none), and the emissions' y moments on an even grid.
 // A run costs one lane of the sweep and, per 256 grid lines and coil, a fixed
-// part of a product besides its members' share; below kRunMinMembers members
-// the sweep over the isochromats is as fast.
+// part of a product besides its members' share: it takes kRunMinMembers members
+// (with several coils kRunMinCoilMembers).  208 k isochromats in runs of 2.6,
+// us per call by runs and swept: 64 EPI lines 190 and 194, an 8 x 8 FSE 207 and
+// 243, the EPI with 8 coils 692 and 632.
+// So does a schedule of few operations: the sums Y are made for 128 lines and
+// more.  us per call, by runs and swept: 595 k isochromats, 8 EPI lines 104 and
+// 101, 16 lines 109 and 114; with 8 coils 16 lines 244 and 210, 32 lines 266
+// and 333; 6.4 M isochromats, 8 lines 238 and 222, 16 lines 241 and 253, with 4
+// coils 535 and 392, 553 and 577; 29 k isochromats, 8 lines 85 and 90, with 8
+// coils 110 and 126.
+constexpr int64_t kRunMinCoilMembers = 4;
+constexpr size_t kRunMinOps[3] = {8, 12, 20};  // fewer than 131072 isochromats; more, one coil; more, several coils
 constexpr int kRunMaxLines = 2048;
 constexpr size_t kRunWsFloor = (size_t)64 << 20;  // Y of all runs at once up to this workspace
 constexpr size_t kRunWsCap = (size_t)2 << 30;     // and batches of kRunMinBatch runs up to this one
@@ -896,7 +906,8 @@ constexpr int64_t kRunMinBatch = 65536;           // runs per launch that still 
 static int plan_runs(gbs_ctx *ctx, const std::vector<SweepOp> &sops, std::vector<RunOp> &rops) {
     GroupedPlan &g = ctx->gp;
     const int64_t R = ctx->n_lruns;
-    if (sops.empty() || ctx->xrun.empty()) return GBS_OK;
+    if (ctx->n_coils > 1 && ctx->K < kRunMinCoilMembers * R) return GBS_OK;
+    if (ctx->xrun.empty() || sops.size() < kRunMinOps[ctx->K < (1 << 17) ? 0 : ctx->n_coils == 1 ? 1 : 2]) return GBS_OK;
     for (const auto &it : g.exec)
         if (it.first != 0) return GBS_OK;
     std::vector<double> cy;
