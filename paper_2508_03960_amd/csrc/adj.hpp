@@ -87,6 +87,10 @@ struct AdjPulseArgs {
     double *acc_rf, *acc_t;           // [n_rf][2], [n_classes][2]
 };
 
+struct AdjDecay {
+    double e2, e1, om1;  // exp(-tau / T2), exp(-tau / T1), 1 - exp(-tau / T1)
+};
+
 struct AdjGroupArgs {
     int64_t K, G;
     const int32_t *order, *gid;  // [K] isochromats sorted by group, and their groups
@@ -105,12 +109,12 @@ struct AdjGroupArgs {
     double2 *gt_part;   // [grid][n_classes]
     const double *total;
     double *gsum;
-    const float2 *decay;  // [relaxations' coef][n_classes]: 1 - exp(-tau / T1), 1 - exp(-tau / T2)
+    const AdjDecay *decay;  // [relaxations' coef][n_classes]
 };
 
 hipError_t launch_adjg_transitions(const AdjPulseArgs &a, hipStream_t st);
 // tau: duration of every coef; fills decay
-hipError_t launch_adjg_forward(const AdjGroupArgs &a, int n_coef, const double *tau, float2 *decay, hipStream_t st);
+hipError_t launch_adjg_forward(const AdjGroupArgs &a, int n_coef, const double *tau, AdjDecay *decay, hipStream_t st);
 hipError_t launch_adjg_backward(const AdjGroupArgs &a, const AdjPulseArgs &p, hipStream_t st);
 hipError_t launch_adjg_results(const AdjPulseArgs &p, int n_rf, float *grad_rf, double *g1, double *g2, hipStream_t st);
 

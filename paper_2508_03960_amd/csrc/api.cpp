@@ -2626,7 +2626,7 @@ static int adj_forward_groups(gbs_ctx *ctx, const AdjArgs &old, const std::vecto
     const size_t o_t = u.take(seg), o_pre = u.take(seg), o_suf = u.take(seg), o_tot = u.take(pul), o_sum = u.take(pul),
                  o_ts = u.take(sizeof(double) * 2 * (size_t)ns * (size_t)G),
                  o_acc = u.take(sizeof(double) * 2 * (size_t)(old.n_rf + old.n_classes)),
-                 o_decay = u.take(sizeof(float2) * std::max<size_t>(g.tau.size(), 1) * (size_t)old.n_classes);
+                 o_decay = u.take(sizeof(AdjDecay) * std::max<size_t>(g.tau.size(), 1) * (size_t)old.n_classes);
     ALLOC(ctx->adj_group, u.off);
     char *ub = ctx->adj_group.as<char>();
     AdjPulseArgs p{};
@@ -2687,9 +2687,9 @@ static int adj_forward_groups(gbs_ctx *ctx, const AdjArgs &old, const std::vecto
     a.gt_part = ctx->adj_gt.as<double2>();
     a.total = p.total;
     a.gsum = p.gsum;
-    a.decay = (const float2 *)(ub + o_decay);
+    a.decay = (const AdjDecay *)(ub + o_decay);
     HIPCHK(launch_adjg_transitions(p, ctx->stream));
-    HIPCHK(launch_adjg_forward(a, (int)g.tau.size(), (const double *)(pb + o_tau), (float2 *)(ub + o_decay), ctx->stream));
+    HIPCHK(launch_adjg_forward(a, (int)g.tau.size(), (const double *)(pb + o_tau), (AdjDecay *)(ub + o_decay), ctx->stream));
     HIPCHK(launch_adj_rows(a.sig_part, grid, a.N, sig_out, ctx->stream));
     ctx->adjg = a;
     ctx->adjp = p;

@@ -21,7 +21,8 @@
 //  k_adjg_gradient  back through every segment: dL/dB1 per step, and the T1, T2 terms
 //  k_adjg_classes   those terms to the classes
 // 1 M isochromats in 768 groups, 8 lines of a 3000-step pulse and 64 samples:
-// @FIGURES@
+// forward 1.0 ms and backward 2.1 ms for the isochromats, 0.1 and 0.2 ms for the
+// groups' steps, 0.4 ms for the grouping; stepped (k_adjoint.hip), 61 and 190 ms.
 #include "adj.hpp"
 #include "consts.hpp"
 #include "device_math.hpp"
@@ -294,9 +295,12 @@ __global__ __launch_bounds__(64) void k_adjg_classes(AdjPulseArgs a) {
 
 // ---- the isochromats -------------------------------------------------------
 // One isochromat per thread, sorted by group; operations are relaxations (all
-// raster steps without RF between two samples are one) and pulses.  State
-// pairs and relaxation coefficients as in k_adjoint.hip; the coefficients of
-// equal operations (the dwells of a readout) are computed once.
+// raster steps without RF between two samples are one) and pulses.  State and
+// adjoint state are FP64: a relaxation is 5 FP64 instructions, which issue at
+// the rate of FP32 ones, where the stepped form's pairs (hi, lo) take 44.
+// The coefficients of equal operations (the dwells of a readout) are computed
+// once.  Both passes issue VALU instructions about half of the time, the rest
+// are the operations' scalar work and the chains of five wavefronts per SIMD.
 namespace {
 
 struct IsoG {
@@ -319,114 +323,93 @@ __device__ __forceinline__ IsoG load_iso(const AdjGroupArgs &a, int64_t i, bool 
 }
 
 struct RelaxG {
-    float c1, cl, sn, sl, om2, om1;  // cos = 1 - (c1 + cl), sin = sn + sl, E = 1 - om
+    double c, s, e1, r1;  // E2 cos, E2 sin of the phase of Eq. 4, E1, (1 - E1) M0
 };
 
-// (the decays, by duration and class, come from a table: their two expm1 cost
-// more than the rotation)
+// (the decays, by duration and class, come from a table: their exponentials
+// cost more than the rotation)
 __device__ __forceinline__ RelaxG coefs_of(const AdjGroupArgs &a, const AdjGOp &op, const IsoG &s) {
     const double cyc = op.cyc[0] * s.x + op.cyc[1] * s.y + op.cyc[2] * s.z + s.df * op.tau;
-    RelaxG r;
-    double sh, ch;
-    sincospi(cyc - rint(cyc), &sh, &ch);  // half angle
-    const double sn = 2.0 * sh * ch;
-    r.sn = (float)sn;
-    r.sl = (float)(sn - (double)r.sn);
-    const double c1 = 2.0 * sh * sh;  // (rounded to FP32, its error would add up over a readout's equal dwells)
-    r.c1 = (float)c1;
-    r.cl = (float)(c1 - (double)r.c1);
-    const float2 om = a.decay[(int64_t)op.coef * a.n_classes + s.cls];
-    r.om1 = om.x;
-    r.om2 = om.y;
-    return r;
+    const AdjDecay d = a.decay[(int64_t)op.coef * a.n_classes + s.cls];
+    double sn, cs;
+    sincospi(cyc - rint(cyc), &sn, &cs);  // half angle
+    // 1 - cos and the decays' 1 - E in FP32, as the stepped form holds them: its
+    // error is theirs (repeated by every dwell of a readout), and the two forms
+    // agree on every phantom to the rounding of their sums
+    const double c = 1.0 - (double)(float)(2.0 * sn * sn);
+    return RelaxG{d.e2 * c, d.e2 * (2.0 * sn * cs), d.e1, d.om1 * s.m0};
 }
 
-__device__ __forceinline__ void two_sum(float &hi, float &lo, float d) {
-    const float b = d + lo;
-    const float t = hi + b;
-    const float bb = t - hi;
-    lo = (hi - (t - bb)) + (b - bb);
-    hi = t;
-}
-
-// v: the rotated state before the decay
-__device__ __forceinline__ void relax_step(const RelaxG &r, float m0, float *H, float *L, float *v) {
-    const float rx = (-r.c1 * H[0] + r.sn * H[1]) + ((-r.c1 * L[0] + r.sn * L[1]) + (r.sl * H[1] - r.cl * H[0]));
-    const float ry = (-r.c1 * H[1] - r.sn * H[0]) + ((-r.c1 * L[1] - r.sn * L[0]) - (r.sl * H[0] + r.cl * H[1]));
-    v[0] = H[0] + rx;
-    v[1] = H[1] + ry;
-    v[2] = H[2];
-    two_sum(H[0], L[0], rx - r.om2 * v[0]);
-    two_sum(H[1], L[1], ry - r.om2 * v[1]);
-    two_sum(H[2], L[2], r.om1 * (m0 - (H[2] + L[2])));
-}
-
-__device__ __forceinline__ void pulse_step(const AdjGroupArgs &a, int32_t id, const IsoG &s, float *H, float *L) {
+__device__ __forceinline__ void pulse_step(const AdjGroupArgs &a, int32_t id, const IsoG &s, double *M) {
     const double *T = a.total + 12 * (int64_t)id * a.G + s.g;
-    const double x = (double)H[0] + L[0], y = (double)H[1] + L[1], z = (double)H[2] + L[2], m = s.m0;
     double o[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
-        o[i] = T[i * a.G] * x + T[(3 + i) * a.G] * y + T[(6 + i) * a.G] * z + T[(9 + i) * a.G] * m;
+        o[i] = T[i * a.G] * M[0] + T[(3 + i) * a.G] * M[1] + T[(6 + i) * a.G] * M[2] + T[(9 + i) * a.G] * (double)s.m0;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        H[i] = (float)o[i];
-        L[i] = (float)(o[i] - (double)H[i]);
-    }
+    for (int i = 0; i < 3; ++i) M[i] = o[i];
+}
+
+// Rotation by -phi about z (Eq. 4) and the decays.
+__device__ __forceinline__ void relax_step(const RelaxG &r, double *M) {
+    const double x = r.c * M[0] + r.s * M[1];
+    M[1] = r.c * M[1] - r.s * M[0];
+    M[0] = x;
+    M[2] = r.e1 * M[2] + r.r1;
 }
 
 __device__ __forceinline__ void forward_op(const AdjGroupArgs &a, const AdjGOp &op, const IsoG &s, RelaxG &c,
-                                           int32_t &have, float *H, float *L, float *v) {
+                                           int32_t &have, double *M) {
     if (op.pulse >= 0) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) v[i] = H[i];
-        pulse_step(a, op.pulse, s, H, L);
+        pulse_step(a, op.pulse, s, M);
     } else {
         if (op.coef != have) {
             c = coefs_of(a, op, s);
             have = op.coef;
         }
-        relax_step(c, s.m0, H, L, v);
+        relax_step(c, M);
     }
 }
 
 }  // namespace
 
-// om1, om2 of every relaxation and class
+// the decays of every relaxation and class
 __global__ void k_adjg_decay(const AdjGroupArgs a, int32_t n_coef, const double *__restrict__ tau,
-                             float2 *__restrict__ out) {
+                             AdjDecay *__restrict__ out) {
     const int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x;
     if (i >= (int64_t)n_coef * a.n_classes) return;
     const double t = tau[i / a.n_classes];
     const int c = (int)(i % a.n_classes);
-    out[i] = make_float2((float)(-expm1(-t / (double)a.t1c[c])), (float)(-expm1(-t / (double)a.t2c[c])));
+    const double om1 = (float)-expm1(-t / (double)a.t1c[c]), om2 = (float)-expm1(-t / (double)a.t2c[c]);
+    out[i] = AdjDecay{1.0 - om2, 1.0 - om1, om1};
 }
 
-// Samples (Eq. 6) wait in LDS, 16 of them for every lane of a wavefront; then a
-// lane adds 32 lanes' part of one sample and component in FP64.  Against a DPP
-// reduction per sample (24 instructions and a barrier each) 8 instructions a
+// Samples (Eq. 6) wait in LDS, 8 of them for every lane of a wavefront; then a
+// lane adds 16 lanes' part of one sample and component in FP64.  Against a DPP
+// reduction per sample (24 instructions and two barriers each) 8 instructions a
 // sample, and the sum over a wavefront's 64 isochromats is not rounded to FP32.
-constexpr int kHeld = 16, kHeldPitch = 65;
+constexpr int kHeld = 8, kHeldPitch = 66;
 
-__global__ __launch_bounds__(kAdjWG) void k_adjg_forward(AdjGroupArgs a) {
+__global__ __launch_bounds__(kAdjWG) __attribute__((amdgpu_waves_per_eu(5))) void k_adjg_forward(AdjGroupArgs a) {
     __shared__ float held[kAdjWG / 64][2][kHeld][kHeldPitch];
     __shared__ double2 sums[kAdjWG / 64][kHeld];
     const int64_t i = (int64_t)blockIdx.x * kAdjWG + threadIdx.x;
     const bool act = i < a.K;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const IsoG s = load_iso(a, i, act);
-    float H[3] = {0.f, 0.f, s.m0}, L[3] = {0.f, 0.f, 0.f}, v[3];
+    double M[3] = {0.0, 0.0, s.m0};
     RelaxG c{};
     int32_t have = -1;
     int first = 0, n_held = 0;  // samples [first, first + n_held) of the list wait
     auto flush = [&]() {        // uniform in the workgroup
         __syncthreads();
-        const int n = lane & (kHeld - 1), comp = (lane >> 4) & 1, half = lane >> 5;
+        const int n = lane & (kHeld - 1), comp = (lane >> 3) & 1, part = lane >> 4;
         double t = 0.0;
-#pragma unroll 8
-        for (int j = 0; j < 32; ++j) t += held[wave][comp][n][32 * half + j];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) t += held[wave][comp][n][16 * part + j];
+        t += __shfl_xor(t, 16);
         t += __shfl_xor(t, 32);
-        const double im = __shfl_xor(t, 16);
+        const double im = __shfl_xor(t, 8);
         if (lane < kHeld) sums[wave][lane] = make_double2(t, im);
         __syncthreads();
         if ((int)threadIdx.x < n_held) {
@@ -450,37 +433,35 @@ __global__ __launch_bounds__(kAdjWG) void k_adjg_forward(AdjGroupArgs a) {
             left = a.every;
             if (act) {
                 float *q = a.ckpt + (int64_t)(p / a.every) * 3 * a.K + i;
-                q[0] = H[0];
-                q[a.K] = H[1];
-                q[2 * a.K] = H[2];
+                q[0] = (float)M[0];
+                q[a.K] = (float)M[1];
+                q[2 * a.K] = (float)M[2];
             }
         }
         --left;
         for (int n = 0; n < op.samples; ++n) {  // samples at this boundary
-            held[wave][0][n_held][lane] = H[0] + L[0];
-            held[wave][1][n_held][lane] = H[1] + L[1];
+            held[wave][0][n_held][lane] = (float)M[0];
+            held[wave][1][n_held][lane] = (float)M[1];
             if (++n_held == kHeld) flush();
         }
         if (p == a.n_ops) break;
-        forward_op(a, op, s, c, have, H, L, v);
+        forward_op(a, op, s, c, have, M);
     }
     if (n_held) flush();
 }
 
-__device__ __forceinline__ void add_cotangent(const AdjGroupArgs &a, const AdjGOp &op, float *LH, float *LL) {
+__device__ __forceinline__ void add_cotangent(const AdjGroupArgs &a, const AdjGOp &op, double *L) {
     for (int n = 0; n < op.samples; ++n) {
         const double2 w = uniform(a.w, a.sid[op.sample0 + n]);
-        const float wx = (float)w.x, wy = (float)w.y;
-        two_sum(LH[0], LL[0], wx + (float)(w.x - (double)wx));
-        two_sum(LH[1], LL[1], wy + (float)(w.y - (double)wy));
+        L[0] += w.x;
+        L[1] += w.y;
     }
 }
 
 // gsum[pulse][3 k + i][g] += sum over the wavefront's lanes of group g
 __device__ __forceinline__ void add_group_sums(const AdjGroupArgs &a, int32_t pulse, const IsoG &s, bool act,
-                                               const float *M, const float *LH, const float *LL) {
+                                               const float *M, const double *L) {
     const double m[4] = {M[0], M[1], M[2], s.m0};
-    const double l[3] = {(double)LH[0] + LL[0], (double)LH[1] + LL[1], (double)LH[2] + LL[2]};
     uint64_t rest = __ballot(act);
     while (rest) {
         const int32_t g = __builtin_amdgcn_readlane(s.g, __builtin_ctzll(rest));
@@ -491,36 +472,41 @@ __device__ __forceinline__ void add_group_sums(const AdjGroupArgs &a, int32_t pu
         for (int k = 0; k < 4; ++k)
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
-                const double t = wave_sum_lane63_f64(in ? m[k] * l[i] : 0.0);
+                const double t = wave_sum_lane63_f64(in ? m[k] * L[i] : 0.0);
                 if ((threadIdx.x & 63) == 63) atomicAdd(out + (3 * k + i) * a.G, t);
             }
     }
 }
 
-__global__ __launch_bounds__(kAdjWG) void k_adjg_backward(AdjGroupArgs a) {
+// Back through every operation with lambda' behind it and lambda before it:
+//   relaxations:  T2 += lambda'_xy . M'_xy tau,  T1 += lambda'_z (M'_z - M0) tau  (over T^2 at the end),
+//                 lambda = the transpose of the operation's map, lambda';
+//   pulses:       the group sums, and lambda = A^T lambda'.
+__global__ __launch_bounds__(kAdjWG) __attribute__((amdgpu_waves_per_eu(5))) void k_adjg_backward(AdjGroupArgs a) {
     __shared__ double tg[kAdjMaxClasses][2];
-    __shared__ float V[kAdjSub][3][kAdjWG];  // the rotated (relaxations) or incoming (pulses) states of a sub-segment
+    // of a sub-segment's operations: M'_x, M'_y, M'_z - M0 (relaxations) or the incoming state (pulses)
+    __shared__ float V[kAdjSub][3][kAdjWG];
     const int tid = threadIdx.x;
     const int64_t i = (int64_t)blockIdx.x * kAdjWG + tid;
     const bool act = i < a.K;
     for (int j = tid; j < kAdjMaxClasses * 2; j += kAdjWG) tg[j >> 1][j & 1] = 0.0;
     __syncthreads();
     const IsoG s = load_iso(a, i, act);
-    float LH[3] = {0.f, 0.f, 0.f}, LL[3] = {0.f, 0.f, 0.f};
+    double L[3] = {0.0, 0.0, 0.0};
     double x1 = 0.0, x2 = 0.0;
     RelaxG c{};
     int32_t have = -1;
-    add_cotangent(a, uniform(a.ops, a.n_ops), LH, LL);
+    add_cotangent(a, uniform(a.ops, a.n_ops), L);
     const int n_seg = (a.n_ops + a.every - 1) / a.every;
     for (int seg = n_seg - 1; seg >= 0; --seg) {
         const int p0 = seg * a.every, p1 = min(p0 + a.every, a.n_ops);
-        float H[3] = {0.f, 0.f, 0.f}, L[3] = {0.f, 0.f, 0.f}, v[3];
-        if (act) {
-            const float *q = a.ckpt + (int64_t)seg * 3 * a.K + i;
-            H[0] = q[0];
-            H[1] = q[a.K];
-            H[2] = q[2 * a.K];
-        }
+        double M[3] = {0.0, 0.0, 0.0};
+        auto load_state = [&](const float *q) {
+            M[0] = q[0];
+            M[1] = q[a.K];
+            M[2] = q[2 * a.K];
+        };
+        if (act) load_state(a.ckpt + (int64_t)seg * 3 * a.K + i);
         const int last = p0 + (p1 - p0 - 1) / kAdjSub * kAdjSub;  // start of the last sub-segment
         if (a.every > kAdjSub) {  // step to the sub-segments' starts
             AdjGOp next = uniform(a.ops, p0);
@@ -529,26 +515,26 @@ __global__ __launch_bounds__(kAdjWG) void k_adjg_backward(AdjGroupArgs a) {
                 next = uniform(a.ops, p + 1);
                 if (act && ((p - p0) & (kAdjSub - 1)) == 0) {
                     float *q = a.sub + (int64_t)((p - p0) / kAdjSub) * 3 * a.K + i;
-                    q[0] = H[0];
-                    q[a.K] = H[1];
-                    q[2 * a.K] = H[2];
+                    q[0] = (float)M[0];
+                    q[a.K] = (float)M[1];
+                    q[2 * a.K] = (float)M[2];
                 }
-                if (p < last) forward_op(a, op, s, c, have, H, L, v);
+                if (p < last) forward_op(a, op, s, c, have, M);
             }
         }
         for (int q0 = last; q0 >= p0; q0 -= kAdjSub) {
             const int q1 = min(q0 + kAdjSub, p1);
-            float SL[3] = {0.f, 0.f, 0.f};
-            if (act && a.every > kAdjSub) {
-                const float *q = a.sub + (int64_t)((q0 - p0) / kAdjSub) * 3 * a.K + i;
-                H[0] = q[0];
-                H[1] = q[a.K];
-                H[2] = q[2 * a.K];
-            }
+            if (act && a.every > kAdjSub) load_state(a.sub + (int64_t)((q0 - p0) / kAdjSub) * 3 * a.K + i);
             AdjGOp op = uniform(a.ops, q0);
             for (int p = q0; p < q1; ++p) {
                 const AdjGOp next = uniform(a.ops, p + 1);
-                forward_op(a, op, s, c, have, H, SL, v);
+                float v[3] = {(float)M[0], (float)M[1], (float)M[2]};
+                forward_op(a, op, s, c, have, M);
+                if (op.pulse < 0) {
+                    v[0] = (float)M[0];
+                    v[1] = (float)M[1];
+                    v[2] = (float)(M[2] - (double)s.m0);
+                }
 #pragma unroll
                 for (int d = 0; d < 3; ++d) V[p - q0][d][tid] = v[d];
                 op = next;
@@ -557,36 +543,29 @@ __global__ __launch_bounds__(kAdjWG) void k_adjg_backward(AdjGroupArgs a) {
             for (int p = q1 - 1; p >= q0; --p) {
                 op = before;
                 before = uniform(a.ops, max(p - 1, 0));
+                float v[3];
 #pragma unroll
                 for (int d = 0; d < 3; ++d) v[d] = V[p - q0][d][tid];
                 if (op.pulse >= 0) {
-                    add_group_sums(a, op.pulse, s, act, v, LH, LL);
+                    add_group_sums(a, op.pulse, s, act, v, L);
                     const double *T = a.total + 12 * (int64_t)op.pulse * a.G + s.g;
-                    const double x = (double)LH[0] + LL[0], y = (double)LH[1] + LL[1], z = (double)LH[2] + LL[2];
+                    const double x = L[0], y = L[1], z = L[2];
 #pragma unroll
-                    for (int d = 0; d < 3; ++d) {
-                        const double o = T[3 * d * a.G] * x + T[(3 * d + 1) * a.G] * y + T[(3 * d + 2) * a.G] * z;
-                        LH[d] = (float)o;
-                        LL[d] = (float)(o - (double)LH[d]);
-                    }
+                    for (int d = 0; d < 3; ++d)
+                        L[d] = T[3 * d * a.G] * x + T[(3 * d + 1) * a.G] * y + T[(3 * d + 2) * a.G] * z;
                 } else {
                     if (op.coef != have) {
                         c = coefs_of(a, op, s);
                         have = op.coef;
                     }
-                    const float ex = v[0] - c.om2 * v[0], ey = v[1] - c.om2 * v[1];
-                    const float Mz = v[2] + c.om1 * (s.m0 - v[2]);
-                    x2 += (double)(LH[0] * ex + LH[1] * ey) * op.tau;
-                    x1 += (double)(LH[2] * (Mz - s.m0)) * op.tau;
-                    // mu = E2 lambda'_xy; lambda_xy = P(phi) mu (the transpose of the forward's rotation by -phi)
-                    const float mx = LH[0] - c.om2 * LH[0], my = LH[1] - c.om2 * LH[1];
-                    const float rx = (-c.c1 * mx - c.sn * my) - (c.sl * my + c.cl * mx);
-                    const float ry = (-c.c1 * my + c.sn * mx) + (c.sl * mx - c.cl * my);
-                    two_sum(LH[0], LL[0], (mx - LH[0]) + rx);
-                    two_sum(LH[1], LL[1], (my - LH[1]) + ry);
-                    two_sum(LH[2], LL[2], -c.om1 * LH[2]);
+                    x2 += (L[0] * v[0] + L[1] * v[1]) * op.tau;
+                    x1 += L[2] * v[2] * op.tau;
+                    const double x = c.c * L[0] - c.s * L[1];
+                    L[1] = c.c * L[1] + c.s * L[0];
+                    L[0] = x;
+                    L[2] *= c.e1;
                 }
-                add_cotangent(a, op, LH, LL);
+                add_cotangent(a, op, L);
             }
         }
     }
@@ -618,7 +597,7 @@ hipError_t launch_adjg_transitions(const AdjPulseArgs &a, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_adjg_forward(const AdjGroupArgs &a, int n_coef, const double *tau, float2 *decay, hipStream_t st) {
+hipError_t launch_adjg_forward(const AdjGroupArgs &a, int n_coef, const double *tau, AdjDecay *decay, hipStream_t st) {
     const int64_t n = (int64_t)n_coef * a.n_classes;
     if (n > 0) hipLaunchKernelGGL(k_adjg_decay, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, st, a, n_coef, tau, decay);
     hipLaunchKernelGGL(k_adjg_forward, dim3((unsigned)((a.K + kAdjWG - 1) / kAdjWG)), dim3(kAdjWG), 0, st, a);
