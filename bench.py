@@ -9,9 +9,10 @@ Throughput = K * (raster steps inside RF and ADC blocks) / time.
 
 Also reported: the EPI workload (grouped), the plain per-isochromat method
 on the same GPU (FSE: first shot of the sequence at full K; EPI: whole),
-the grouped-vs-plain speedup, the roofline of the dominant kernel (the
-fused grouped sweep k_sweep: algorithmic FP32 flops per launch over its
-HIP-event-timed duration) and the FP64 CPU oracle timed on the host cores.
+the grouped-vs-plain speedup, the roofline of the dominant kernels (the sums
+over the members of every run, k_run_y, and the sweep over the runs,
+k_run_sweep: algorithmic FP32 flops of both over their HIP-event-timed
+durations) and the FP64 CPU oracle timed on the host cores.
 
 Prints one JSON line.  Usage: python bench.py [--gpus 1] [--steps 20] [--warmup 3]
 """
@@ -126,40 +127,48 @@ def subset_errors(gb, ph, seq, M_full, idx, M_ref, sig_ref):
 # raster step; a step with a larger angle executes the longer series, which
 # these figures do not count.
 # k_plain (FP64): field 6, |B|^2 2, rotation series and coefficients 23, the
-#   increment of the rotation 35 (cross products 9, B.M 5, three increments
-#   18, adds 3), relaxation 7 -> 73 with B1; without B1 the rotation about z
-#   costs 10 and |B|^2 1 -> 47.
-PLAIN_FLOPS_B1, PLAIN_FLOPS_NO_B1 = 73, 47
-# k_adj_forward (FP32), per raster op: w and |w|^2 14, series S, C, D3 24,
-#   rotation increment 27, rotated state 3, relaxation increment 7, three
-#   compensated adds 21 -> 96.  k_adj_backward per raster op: the op is
-#   stepped twice (segment and sub-segment, 192), then its transpose: T1/T2
-#   terms 14, D lambda 6, coefficients 38, RF gradient (parameter steps) 46,
-#   rotation increment 27, compensated adds 21 -> 344.
-ADJ_FWD_FLOPS, ADJ_BWD_FLOPS = 96, 344
+#   rotation M += B x (a M + b (B x M)) 30, relaxation 7 -> 68 with B1; without
+#   B1 a step like the one before it costs the rotation about z 8 and the
+#   relaxation 7 -> 15 (its coefficients are kept).
+PLAIN_FLOPS_B1, PLAIN_FLOPS_NO_B1 = 68, 15
+# The adjoint by groups (FP64, per isochromat): a relaxation 8 forward; backward
+#   again 8, the T1/T2 terms 8 and its transpose 7.  A pulse 24 forward, and
+#   backward 24, the group sums 24 and the transpose 15.  (Its raster steps are
+#   walked per group, a thousandth of them.)
+ADJ_FWD_FLOPS, ADJ_BWD_FLOPS = (8, 24), (23, 63)
 
 
 def adjoint_raster_ops(seq, param_blocks):
     """Raster ops of the adjoint's flattened sequence: steps of parameter
-    blocks and steps with B1 != 0 (runs without RF become closed-form ops)."""
+    blocks and steps with B1 != 0 (runs without RF become closed-form ops);
+    with the relaxations (those runs, cut at the samples, and the relaxation
+    blocks) and pulses that are left for every isochromat."""
     import numpy as np
     pb = set(int(b) for b in param_blocks)
-    n = 0
+    n, relax, pulses = 0, 0, 0
     for b in range(seq.n_blocks):
         if seq.btype[b] == 3:
+            relax += 1
             continue
         o, k = int(seq.step_offset[b]), int(seq.n_steps[b])
+        rf = (np.asarray(seq.rf_re[o:o + k]) != 0) | (np.asarray(seq.rf_im[o:o + k]) != 0)
         if b in pb:
             n += k
+            pulses += 1
+        elif rf.any():
+            n += int(np.count_nonzero(rf))
+            pulses += 1
         else:
-            n += int(np.count_nonzero((np.asarray(seq.rf_re[o:o + k]) != 0) | (np.asarray(seq.rf_im[o:o + k]) != 0)))
-    return n
+            so = int(seq.sample_offset[b])
+            relax += len(set(seq.adc_idx[so:so + int(seq.n_samples[b])]) - {0, k}) + 1
+    return n, relax, pulses
 
 
 # FP64 flops of one raster step of the per-isochromat composition [A | b] <- D R [A | b]
 # (k_cached, compose mode; FMA = 2): field and |B|^2 11, rotation coefficients 23
 # (the six-term series, as for k_plain), rows of D R 32, the 3x3 by 3x4 product 60,
-# T1 recovery 1.
+# T1 recovery 1.  Pulses that are symmetric in time (these all are) are composed
+# from half of their steps.
 COMPOSE_FLOPS_PER_ISO_STEP = 127
 FP64_PEAK_TFLOPS = 78.6  # MI355X FP64 vector
 
@@ -189,7 +198,7 @@ def cached_leg(sim, gb, seq, m_out, sig, steps, ref_M=None, ref_sig=None):
                 comp_steps += n
     n_apply = last["n_rf_cached"] - last["n_distinct_rf"]
     ms_c, ms_a, ms_d = (float(np.mean([x[k] for x in st])) for k in ("ms_compose", "ms_apply", "ms_adc_direct"))
-    flops_c = K * comp_steps * COMPOSE_FLOPS_PER_ISO_STEP
+    flops_c = K * (comp_steps / 2) * COMPOSE_FLOPS_PER_ISO_STEP
     # apply launches: FP64 state in and out (48 B), cached rows (48 B), M0 (4 B); the
     # closed-form pre map adds x, y, z, df, T1, T2 (24 B); map-only launches are counted alike
     n_samples = int(seq.total_samples)
@@ -340,23 +349,22 @@ def adjoint_leg(gb, steps):
             fwd.append(t_f)
             bwd.append(t_b)
     S = seq.stepped_count()
-    n_raster = adjoint_raster_ops(seq, pb)
+    n_raster, n_relax, n_pulse = adjoint_raster_ops(seq, pb)
     f, b = float(np.mean(fwd)), float(np.mean(bwd))
     sim.close()
-    fl_f, fl_b = ADJ_FWD_FLOPS * n_raster * ph.K, ADJ_BWD_FLOPS * n_raster * ph.K
+    fl_f, fl_b = (float(ph.K) * (c[0] * n_relax + c[1] * n_pulse) for c in (ADJ_FWD_FLOPS, ADJ_BWD_FLOPS))
     rl = lambda kernel, fl, t: {"kernel": kernel, "bound": "alu", "flops": fl,
-                                "achieved": fl / t / 1e12, "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
-                                "frac": fl / t / 1e12 / FP32_PEAK_TFLOPS,
-                                "frac_of_nonpacked_fp32": fl / t / 1e12 / FP32_NONPACKED_TFLOPS,
-                                "time": "whole call (kernel dominated)"}
+                                "achieved": fl / t / 1e12, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s (FP64)",
+                                "frac": fl / t / 1e12 / FP64_PEAK_TFLOPS,
+                                "time": "whole call (grouping, host work and kernels)"}
     return {"workload": f"GRE {ph.K} isochromats (256x256x16), {len(pb)} TRs of a 3000-sample complex sinc RF, "
                         f"{seq.total_samples} samples; gradient wrt 3000 complex RF samples + 6 (T1, T2) pairs",
             "forward_ms": f * 1e3, "backward_ms": b * 1e3, "backward_over_forward": b / f,
             "forward_iso_steps_per_s": ph.K * S / f, "backward_iso_steps_per_s": ph.K * S / b,
             "checkpoint_every": 256, "raster_ops": n_raster,
-            "precision": "compensated FP32 state (hi + lo pairs), FP64 sums over isochromats",
-            "roofline_forward": rl("k_adj_forward", fl_f, f),
-            "roofline_backward": rl("k_adj_backward", fl_b, b)}
+            "precision": "FP64 state, steps and sums",
+            "roofline_forward": rl("k_adjg_forward", fl_f, f),
+            "roofline_backward": rl("k_adjg_backward", fl_b, b)}
 
 
 def main():
@@ -452,7 +460,7 @@ def main():
                    "K": K, "stepped_steps": S_fse, "mode": "grouped", "n_groups_xyz": info["n_groups"]},
         "roofline": {"bound": "alu", "achieved": achieved, "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / FP32_PEAK_TFLOPS, "traffic": traffic_per_launch(),
-                     "kernel": "k_sweep", "flops_per_launch": flops_launch, "bytes_per_launch": bytes_launch,
+                     "kernel": "k_run_y + k_run_sweep", "flops_per_launch": flops_launch, "bytes_per_launch": bytes_launch,
                      "avg_launch_ms": sweep_ms, "launches_per_step": n_sw,
                      "hbm_GBs": bytes_launch / (sweep_ms * 1e-3) / 1e9,
                      "frac_of_nonpacked_fp32": achieved / FP32_NONPACKED_TFLOPS,

@@ -900,7 +900,7 @@ constexpr int64_t kRunMinCoilMembers = 4;
 constexpr size_t kRunMinOps[3] = {8, 12, 20};  // fewer than 131072 isochromats; more, one coil; more, several coils
 constexpr int kRunMaxLines = 2048;
 constexpr size_t kRunWsFloor = (size_t)64 << 20;  // Y of all runs at once up to this workspace
-constexpr size_t kRunWsCap = (size_t)2 << 30;     // and batches of kRunMinBatch runs up to this one
+constexpr size_t kRunWsCap = (size_t)3 << 30;     // and batches of kRunMinBatch runs up to this one
 constexpr int64_t kRunMinBatch = 65536;           // runs per launch that still fill the chip (64 per wavefront)
 
 static int plan_runs(gbs_ctx *ctx, const std::vector<SweepOp> &sops, std::vector<RunOp> &rops) {
@@ -1917,7 +1917,11 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
         ya.out_coil = g.run_batch * g.lines.n_lines;
         ya.r0 = 0;
         ya.n = g.batches.front().r1;
-        if (plan.n_adc_grouped && g.pair_jobs.empty()) HIPCHK(launch_run_y(ya, side));
+        if (plan.n_adc_grouped && g.pair_jobs.empty()) {
+            if (profile) HIPCHK(hipEventRecord(ctx->pev[2], side));
+            HIPCHK(launch_run_y(ya, side));
+            if (profile) HIPCHK(hipEventRecord(ctx->pev[3], side));
+        }
     }
     if (forked) HIPCHK(hipEventRecord(ctx->join, side));
     for (const auto &pj : g.pair_jobs) {
@@ -1958,7 +1962,7 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
             HIPCHK(launch_run_sweep(sa, ctx->stream));
         }
         if (profile) HIPCHK(hipEventRecord(ctx->pev[1], ctx->stream));
-        *n_timed = profile ? 1 : 0;
+        *n_timed = !profile ? 0 : plan.n_adc_grouped && g.pair_jobs.empty() ? 2 : 1;  // the sweeps, and Y of the first batch
         if (st) HIPCHK(hipEventRecord(ctx->ev[2], ctx->stream));
         if (forked) {
             HIPCHK(hipEventRecord(ctx->fork, ctx->stream));
