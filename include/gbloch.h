@@ -483,10 +483,12 @@ int gbs_set_surrogate(gbs_ctx *ctx, gbs_mlp *m, float tol, int32_t n_check, uint
  *
  * Reverse-mode differentiation of the plain simulation (Eq. 2 with U = D R
  * of Eq. A1, A2 per raster step; Eq. 4, 5 for relaxation blocks; Eq. 6) of
- * the context's phantom and sequence, in FP32 with FP64 sums over
- * isochromats.  The magnetization and the adjoint state are compensated
- * FP32 pairs (hi + lo, each op's increment added by a two-sum), so that the
- * small per-step changes are not rounded away coherently.  Parameters: a
+ * the context's phantom and sequence.  Where at least four isochromats on
+ * average share the coordinates along the RF steps' gradients, dB0 and class,
+ * runs of RF steps are one FP64 transition per such group, and their gradient
+ * is taken per group; otherwise every isochromat is stepped, its
+ * magnetization and adjoint state compensated FP32 pairs (hi + lo, each op's
+ * increment added by a two-sum).  Sums over isochromats are FP64.  Parameters: a
  * complex "parameter pulse" of n_rf samples,
  * played by every listed RF block in place of its own B1, and per-class T1
  * and T2 (isochromat k has class cls[k]; the phantom's own T1/T2 arrays are
@@ -500,7 +502,8 @@ int gbs_set_surrogate(gbs_ctx *ctx, gbs_mlp *m, float tol, int32_t n_check, uint
  * forward pass stores the state (hi) every `every` ops (3 * K floats per
  * checkpoint, owned by the context); the backward pass steps each segment again from its checkpoint,
  * keeping the state every 8 ops of the segment (3 * K * every / 8 floats,
- * also owned by the context).
+ * also owned by the context).  By groups there are far fewer ops, and the
+ * interval is 8 where that takes no more memory than stepping with `every`.
  */
 
 /* Forward pass.  cls: device int32[K] in [0, n_classes), n_classes <= 64;
