@@ -277,6 +277,7 @@ int gbs::ctx_fail(gbs_ctx *ctx, int code, const char *msg) { return fail(ctx, co
 static int refresh_plans(gbs_ctx *ctx);
 static int build_coil_layout(gbs_ctx *ctx);
 static int build_grouped_plan(gbs_ctx *ctx);
+static int build_cached_surrogate(gbs_ctx *ctx);
 
 #define HIPCHK(expr)                                                                           \
     do {                                                                                       \
@@ -383,6 +384,7 @@ int gbs_set_phantom(gbs_ctx *ctx, int64_t K, const float *x, const float *y, con
     ctx->groups_valid = false;
     ctx->gp.valid = false;
     ctx->adj_ready = false;
+    const bool had_coils = ctx->coil_re != nullptr;
     ctx->n_coils = 1;  // sensitivities belong to the previous phantom
     ctx->coil_re = ctx->coil_im = nullptr;
     ctx->coil_l_valid = false;
@@ -397,6 +399,8 @@ int gbs_set_phantom(gbs_ctx *ctx, int64_t K, const float *x, const float *y, con
     ctx->K = K;
     ctx->ph = ph;
     ctx->has_ph = true;
+    // the plain and cached schedules depend on the sequence and the coils alone
+    if (ctx->has_seq && ctx->pplan_valid && ctx->cplan_valid && !had_coils) return build_cached_surrogate(ctx);
     return refresh_plans(ctx);  // one coil again: stepped launches take 256 samples
 }
 

@@ -229,7 +229,7 @@ __global__ __launch_bounds__(kPlainBlock) void k_plain(PlainArgs a, PlainCoils c
             while (j < jend) {
                 if (j == head) {
                     next.set(w);
-                    next_end = min(end + w.same, a.n_steps);
+                    next_end = end + min(w.same, a.n_steps - end);
                     w = load_step(wave_ptr, min(next_end, last));
                     const bool small = next.template series<HAS_B1>(X, Y, Z, boff, gdt, k2);
                     apply();
