@@ -64,8 +64,11 @@ struct AdjSeg {
 // samples at the end.
 struct AdjGOp {
     int32_t pulse;  // distinct pulse, or -1: relaxation
-    int32_t coef;   // relaxations: equal (tau, cyc) have equal numbers
+    int32_t coef;   // relaxations: their AdjGCoef
     int32_t sample0, samples;
+};
+
+struct AdjGCoef {  // a relaxation, once for all operations with the same numbers
     double tau, cyc[3];
 };
 
@@ -99,6 +102,7 @@ struct AdjGroupArgs {
     const float *t1c, *t2c;
     int32_t n_classes;
     const AdjGOp *ops;  // [n_ops + 1]
+    const AdjGCoef *coefs;
     int32_t n_ops;
     const int32_t *sid;
     int32_t every;
@@ -106,6 +110,7 @@ struct AdjGroupArgs {
     int32_t N;
     double2 *sig_part;  // [grid][N]
     const double2 *w;
+    double2 *wl;        // [N] w in the order of the list
     double2 *gt_part;   // [grid][n_classes]
     const double *total;
     double *gsum;
@@ -113,8 +118,8 @@ struct AdjGroupArgs {
 };
 
 hipError_t launch_adjg_transitions(const AdjPulseArgs &a, hipStream_t st);
-// tau: duration of every coef; fills decay
-hipError_t launch_adjg_forward(const AdjGroupArgs &a, int n_coef, const double *tau, AdjDecay *decay, hipStream_t st);
+// fills decay
+hipError_t launch_adjg_forward(const AdjGroupArgs &a, int n_coef, AdjDecay *decay, hipStream_t st);
 hipError_t launch_adjg_backward(const AdjGroupArgs &a, const AdjPulseArgs &p, hipStream_t st);
 hipError_t launch_adjg_results(const AdjPulseArgs &p, int n_rf, float *grad_rf, double *g1, double *g2, hipStream_t st);
 

@@ -2533,7 +2533,7 @@ struct AdjSchedule {
     std::vector<AdjStep> steps;
     std::vector<AdjSeg> segs;
     std::vector<int2> pulses;
-    std::vector<double> tau;  // of every coef
+    std::vector<AdjGCoef> coefs;
     int64_t n_raster = 0, n_played = 0;  // raster steps, pulses played
     uint32_t axes = 0;                   // axes of their gradients
 };
@@ -2543,14 +2543,13 @@ static void schedule_pulses(const std::vector<AdjOp> &ops, const int32_t *sstart
     std::vector<std::pair<int32_t, int32_t>> range;  // steps of every pulse
     std::map<std::array<double, 4>, int32_t> coef;
     std::vector<AdjStep> run;
-    auto at = [&](int64_t p) { return AdjGOp{-1, -1, sstart[p], sstart[p + 1] - sstart[p], 0.0, {0.0, 0.0, 0.0}}; };
+    auto at = [&](int64_t p) { return AdjGOp{-1, -1, sstart[p], sstart[p + 1] - sstart[p]}; };
     for (int64_t p = 0; p < n_ops;) {
         AdjGOp o = at(p);
         if (ops[p].kind != 0) {
-            o.tau = ops[p].tau;
-            for (int i = 0; i < 3; ++i) o.cyc[i] = ops[p].cyc[i];
-            const auto it = coef.emplace(std::array<double, 4>{o.tau, o.cyc[0], o.cyc[1], o.cyc[2]}, (int32_t)coef.size());
-            if (it.second) g.tau.push_back(o.tau);
+            const AdjGCoef k{ops[p].tau, {ops[p].cyc[0], ops[p].cyc[1], ops[p].cyc[2]}};
+            const auto it = coef.emplace(std::array<double, 4>{k.tau, k.cyc[0], k.cyc[1], k.cyc[2]}, (int32_t)coef.size());
+            if (it.second) g.coefs.push_back(k);
             o.coef = it.first->second;
             g.ops.push_back(o);
             ++p;
@@ -2618,14 +2617,14 @@ static int adj_forward_groups(gbs_ctx *ctx, const AdjArgs &old, const std::vecto
     WsCarve v;
     const size_t o_ops = v.take(sizeof(AdjGOp) * g.ops.size()), o_steps = v.take(sizeof(AdjStep) * g.steps.size()),
                  o_segs = v.take(sizeof(AdjSeg) * g.segs.size()), o_pulses = v.take(sizeof(int2) * g.pulses.size()),
-                 o_tau = v.take(sizeof(double) * g.tau.size());
+                 o_coefs = v.take(sizeof(AdjGCoef) * g.coefs.size());
     ALLOC(ctx->adj_pulse, v.off);
     std::vector<char> h(v.off);
     std::memcpy(&h[o_ops], g.ops.data(), sizeof(AdjGOp) * g.ops.size());
     std::memcpy(&h[o_steps], g.steps.data(), sizeof(AdjStep) * g.steps.size());
     std::memcpy(&h[o_segs], g.segs.data(), sizeof(AdjSeg) * g.segs.size());
     std::memcpy(&h[o_pulses], g.pulses.data(), sizeof(int2) * g.pulses.size());
-    if (!g.tau.empty()) std::memcpy(&h[o_tau], g.tau.data(), sizeof(double) * g.tau.size());
+    if (!g.coefs.empty()) std::memcpy(&h[o_coefs], g.coefs.data(), sizeof(AdjGCoef) * g.coefs.size());
     HIPCHK(hipMemcpy(ctx->adj_pulse.p, h.data(), v.off, hipMemcpyHostToDevice));
     const char *pb = ctx->adj_pulse.as<char>();
     // group arrays
@@ -2634,7 +2633,8 @@ static int adj_forward_groups(gbs_ctx *ctx, const AdjArgs &old, const std::vecto
     const size_t o_t = u.take(seg), o_pre = u.take(seg), o_suf = u.take(seg), o_tot = u.take(pul), o_sum = u.take(pul),
                  o_ts = u.take(sizeof(double) * 2 * (size_t)ns * (size_t)G),
                  o_acc = u.take(sizeof(double) * 2 * (size_t)(old.n_rf + old.n_classes)),
-                 o_decay = u.take(sizeof(AdjDecay) * std::max<size_t>(g.tau.size(), 1) * (size_t)old.n_classes);
+                 o_wl = u.take(sizeof(double2) * (size_t)std::max(old.N, 1)),
+                 o_decay = u.take(sizeof(AdjDecay) * std::max<size_t>(g.coefs.size(), 1) * (size_t)old.n_classes);
     ALLOC(ctx->adj_group, u.off);
     char *ub = ctx->adj_group.as<char>();
     AdjPulseArgs p{};
@@ -2685,6 +2685,7 @@ static int adj_forward_groups(gbs_ctx *ctx, const AdjArgs &old, const std::vecto
     a.t2c = old.t2c;
     a.n_classes = old.n_classes;
     a.ops = (const AdjGOp *)(pb + o_ops);
+    a.coefs = (const AdjGCoef *)(pb + o_coefs);
     a.n_ops = (int32_t)n_ops;
     a.sid = old.sid;
     a.every = every;
@@ -2696,8 +2697,9 @@ static int adj_forward_groups(gbs_ctx *ctx, const AdjArgs &old, const std::vecto
     a.total = p.total;
     a.gsum = p.gsum;
     a.decay = (const AdjDecay *)(ub + o_decay);
+    a.wl = (double2 *)(ub + o_wl);
     HIPCHK(launch_adjg_transitions(p, ctx->stream));
-    HIPCHK(launch_adjg_forward(a, (int)g.tau.size(), (const double *)(pb + o_tau), (AdjDecay *)(ub + o_decay), ctx->stream));
+    HIPCHK(launch_adjg_forward(a, (int)g.coefs.size(), (AdjDecay *)(ub + o_decay), ctx->stream));
     HIPCHK(launch_adj_rows(a.sig_part, grid, a.N, sig_out, ctx->stream));
     ctx->adjg = a;
     ctx->adjp = p;

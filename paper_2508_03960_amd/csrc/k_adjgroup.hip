@@ -21,8 +21,12 @@
 //  k_adjg_gradient  back through every segment: dL/dB1 per step, and the T1, T2 terms
 //  k_adjg_classes   those terms to the classes
 // 1 M isochromats in 768 groups, 8 lines of a 3000-step pulse and 64 samples:
-// forward 1.0 ms and backward 2.1 ms for the isochromats, 0.1 and 0.2 ms for the
+// forward 0.93 ms and backward 1.79 ms for the isochromats, 0.1 and 0.2 ms for the
 // groups' steps, 0.4 ms for the grouping; stepped (k_adjoint.hip), 61 and 190 ms.
+// Both isochromat kernels are bound by their chain of scalar loads and FP64 steps:
+// operations of 16 bytes with their coefficients in a table that is read when
+// they change, and cotangents in the list's order and an operation ahead, take
+// 1.05 and 1.96 ms down to the figures above.
 #include "adj.hpp"
 #include "consts.hpp"
 #include "device_math.hpp"
@@ -324,12 +328,14 @@ __device__ __forceinline__ IsoG load_iso(const AdjGroupArgs &a, int64_t i, bool 
 
 struct RelaxG {
     double c, s, e1, r1;  // E2 cos, E2 sin of the phase of Eq. 4, E1, (1 - E1) M0
+    double tau;
 };
 
 // (the decays, by duration and class, come from a table: their exponentials
 // cost more than the rotation)
 __device__ __forceinline__ RelaxG coefs_of(const AdjGroupArgs &a, const AdjGOp &op, const IsoG &s) {
-    const double cyc = op.cyc[0] * s.x + op.cyc[1] * s.y + op.cyc[2] * s.z + s.df * op.tau;
+    const AdjGCoef k = uniform(a.coefs, op.coef);
+    const double cyc = k.cyc[0] * s.x + k.cyc[1] * s.y + k.cyc[2] * s.z + s.df * k.tau;
     const AdjDecay d = a.decay[(int64_t)op.coef * a.n_classes + s.cls];
     double sn, cs;
     sincospi(cyc - rint(cyc), &sn, &cs);  // half angle
@@ -337,7 +343,7 @@ __device__ __forceinline__ RelaxG coefs_of(const AdjGroupArgs &a, const AdjGOp &
     // error is theirs (repeated by every dwell of a readout), and the two forms
     // agree on every phantom to the rounding of their sums
     const double c = 1.0 - (double)(float)(2.0 * sn * sn);
-    return RelaxG{d.e2 * c, d.e2 * (2.0 * sn * cs), d.e1, d.om1 * s.m0};
+    return RelaxG{d.e2 * c, d.e2 * (2.0 * sn * cs), d.e1, d.om1 * s.m0, k.tau};
 }
 
 __device__ __forceinline__ void pulse_step(const AdjGroupArgs &a, int32_t id, const IsoG &s, double *M) {
@@ -374,11 +380,10 @@ __device__ __forceinline__ void forward_op(const AdjGroupArgs &a, const AdjGOp &
 }  // namespace
 
 // the decays of every relaxation and class
-__global__ void k_adjg_decay(const AdjGroupArgs a, int32_t n_coef, const double *__restrict__ tau,
-                             AdjDecay *__restrict__ out) {
+__global__ void k_adjg_decay(const AdjGroupArgs a, int32_t n_coef, AdjDecay *__restrict__ out) {
     const int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x;
     if (i >= (int64_t)n_coef * a.n_classes) return;
-    const double t = tau[i / a.n_classes];
+    const double t = a.coefs[i / a.n_classes].tau;
     const int c = (int)(i % a.n_classes);
     const double om1 = (float)-expm1(-t / (double)a.t1c[c]), om2 = (float)-expm1(-t / (double)a.t2c[c]);
     out[i] = AdjDecay{1.0 - om2, 1.0 - om1, om1};
@@ -450,12 +455,23 @@ __global__ __launch_bounds__(kAdjWG) __attribute__((amdgpu_waves_per_eu(5))) voi
     if (n_held) flush();
 }
 
-__device__ __forceinline__ void add_cotangent(const AdjGroupArgs &a, const AdjGOp &op, double *L) {
+// The cotangents in the order in which the operations meet them.
+__global__ void k_adjg_order(AdjGroupArgs a) {
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    if (q < a.N) a.wl[q] = a.w[a.sid[q]];
+}
+
+// The samples at the boundary before op; first: the cotangent of the first one,
+// loaded an operation ahead.
+__device__ __forceinline__ void add_cotangent(const AdjGroupArgs &a, const AdjGOp &op, double2 first, double *L) {
     for (int n = 0; n < op.samples; ++n) {
-        const double2 w = uniform(a.w, a.sid[op.sample0 + n]);
+        const double2 w = n ? uniform((const double2 *)a.wl, op.sample0 + n) : first;
         L[0] += w.x;
         L[1] += w.y;
     }
+}
+__device__ __forceinline__ double2 first_cotangent(const AdjGroupArgs &a, const AdjGOp &op) {
+    return op.samples ? uniform((const double2 *)a.wl, op.sample0) : make_double2(0.0, 0.0);
 }
 
 // gsum[pulse][3 k + i][g] += sum over the wavefront's lanes of group g
@@ -496,7 +512,10 @@ __global__ __launch_bounds__(kAdjWG) __attribute__((amdgpu_waves_per_eu(5))) voi
     double x1 = 0.0, x2 = 0.0;
     RelaxG c{};
     int32_t have = -1;
-    add_cotangent(a, uniform(a.ops, a.n_ops), L);
+    {
+        const AdjGOp end = uniform(a.ops, a.n_ops);
+        add_cotangent(a, end, first_cotangent(a, end), L);
+    }
     const int n_seg = (a.n_ops + a.every - 1) / a.every;
     for (int seg = n_seg - 1; seg >= 0; --seg) {
         const int p0 = seg * a.every, p1 = min(p0 + a.every, a.n_ops);
@@ -540,9 +559,12 @@ __global__ __launch_bounds__(kAdjWG) __attribute__((amdgpu_waves_per_eu(5))) voi
                 op = next;
             }
             AdjGOp before = uniform(a.ops, q1 - 1);
+            double2 wn = first_cotangent(a, before);
             for (int p = q1 - 1; p >= q0; --p) {
                 op = before;
+                const double2 w = wn;
                 before = uniform(a.ops, max(p - 1, 0));
+                wn = first_cotangent(a, before);
                 float v[3];
 #pragma unroll
                 for (int d = 0; d < 3; ++d) v[d] = V[p - q0][d][tid];
@@ -558,14 +580,14 @@ __global__ __launch_bounds__(kAdjWG) __attribute__((amdgpu_waves_per_eu(5))) voi
                         c = coefs_of(a, op, s);
                         have = op.coef;
                     }
-                    x2 += (L[0] * v[0] + L[1] * v[1]) * op.tau;
-                    x1 += L[2] * v[2] * op.tau;
+                    x2 += (L[0] * v[0] + L[1] * v[1]) * c.tau;
+                    x1 += L[2] * v[2] * c.tau;
                     const double x = c.c * L[0] - c.s * L[1];
                     L[1] = c.c * L[1] + c.s * L[0];
                     L[0] = x;
                     L[2] *= c.e1;
                 }
-                add_cotangent(a, op, L);
+                add_cotangent(a, op, w, L);
             }
         }
     }
@@ -597,14 +619,15 @@ hipError_t launch_adjg_transitions(const AdjPulseArgs &a, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_adjg_forward(const AdjGroupArgs &a, int n_coef, const double *tau, AdjDecay *decay, hipStream_t st) {
+hipError_t launch_adjg_forward(const AdjGroupArgs &a, int n_coef, AdjDecay *decay, hipStream_t st) {
     const int64_t n = (int64_t)n_coef * a.n_classes;
-    if (n > 0) hipLaunchKernelGGL(k_adjg_decay, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, st, a, n_coef, tau, decay);
+    if (n > 0) hipLaunchKernelGGL(k_adjg_decay, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, st, a, n_coef, decay);
     hipLaunchKernelGGL(k_adjg_forward, dim3((unsigned)((a.K + kAdjWG - 1) / kAdjWG)), dim3(kAdjWG), 0, st, a);
     return hipGetLastError();
 }
 
 hipError_t launch_adjg_backward(const AdjGroupArgs &a, const AdjPulseArgs &p, hipStream_t st) {
+    if (a.N > 0) hipLaunchKernelGGL(k_adjg_order, dim3((unsigned)((a.N + 255) / 256)), dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_adjg_backward, dim3((unsigned)((a.K + kAdjWG - 1) / kAdjWG)), dim3(kAdjWG), 0, st, a);
     if (p.n_pulses > 0) {
         const unsigned gb = (unsigned)((p.G + 63) / 64);
