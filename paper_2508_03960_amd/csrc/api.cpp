@@ -896,10 +896,10 @@ static bool in_partial_kernel(int need, bool coils) {
 // 243, the EPI with 8 coils 692 and 632.
 // So does a schedule of few operations: the sums Y are made for 128 lines and
 // more.  us per call, by runs and swept: 595 k isochromats, 8 EPI lines 104 and
-// 101, 16 lines 109 and 114; with 8 coils 16 lines 244 and 210, 32 lines 266
+// 101, 16 lines 109 and 114; with 8 coils 16 lines 221 and 219, 32 lines 239
 // and 333; 6.4 M isochromats, 8 lines 238 and 222, 16 lines 241 and 253, with 4
-// coils 535 and 392, 553 and 577; 29 k isochromats, 8 lines 85 and 90, with 8
-// coils 110 and 126.
+// coils 488 and 392, 506 and 577; 29 k isochromats, 8 lines 85 and 90, with 8
+// coils 99 and 126.
 constexpr int64_t kRunMinCoilMembers = 4;
 constexpr size_t kRunMinOps[3] = {8, 12, 20};  // fewer than 131072 isochromats; more, one coil; more, several coils
 constexpr int kRunMaxLines = 2048;

@@ -272,12 +272,13 @@ __global__ __launch_bounds__(64) void k_run_sweep(RunSweepArgs a) {
     // byte offsets (32 bits: checked at the launch); lanes of a wavefront lie in
     // at most five tiles of Y from its first one on
     const int64_t t0 = (w0 - a.r0) / kRunTile;
-    const float2 *yb = a.y + t0 * (int64_t)a.n_lines * kRunTile;
+    const int coil0 = MC * (int)blockIdx.y;  // the wavefront's coils
+    const float2 *yb = a.y + coil0 * a.y_coil + t0 * (int64_t)a.n_lines * kRunTile;
     const uint32_t oy = (uint32_t)(8 * ((rl / kRunTile - t0) * (int64_t)a.n_lines * kRunTile + rl % kRunTile));
     const uint32_t ox = 16u * (uint32_t)gx, oz = 8u * (uint32_t)gz;
     const uint32_t otx = 48u * (uint32_t)gx, otz = 48u * (uint32_t)gz, otr = 48u * (uint32_t)r;
 
-    const int n_coils = a.n_coils;
+    const int n_coils = min(a.n_coils - coil0, MC);
     const int64_t y_coil = a.y_coil;
     struct Meta {  // of an operation whose rows are in flight
         int flags, stride;
@@ -332,7 +333,7 @@ __global__ __launch_bounds__(64) void k_run_sweep(RunSweepArgs a) {
             seg_add<0x143>(mb31, sr);
             seg_add<0x143>(mb31, si);
             if (end) {
-                double2 *g = op.gsum + (int64_t)p * op.stride + gx;
+                double2 *g = op.gsum + (int64_t)(coil0 + p) * op.stride + gx;
                 if (own) {
                     store_pair(g, (double)sr, (double)si);
                 } else {
@@ -392,20 +393,22 @@ __global__ __launch_bounds__(64) void k_run_sweep(RunSweepArgs a) {
         else
             walk(std::integral_constant<int, MC == 1 ? 4 : 2>{}, part, fetch_full, full);
     }
-    if (act) a.m[a.slot[r]] = make_float4(mx, my, mz, 0.f);
+    if (act && coil0 == 0) a.m[a.slot[r]] = make_float4(mx, my, mz, 0.f);
 }
 
 hipError_t launch_run_sweep(const RunSweepArgs &a, hipStream_t st) {
     if (a.n_waves <= 0) return hipSuccess;
     if (a.n_parts < 1 || a.n_parts > kRunMaxParts || a.n_coils < 1 || a.n_coils > 8 || a.r0 % kRunTile) return hipErrorInvalidValue;
     if (a.n_runs > kRunMaxRuns || a.n_lines > (1 << 20)) return hipErrorInvalidValue;  // 32-bit byte offsets
-    const int32_t blocks = a.n_waves;
+    // Several coils: four per wavefront, which repeats the steps of its runs for
+    // each four.  With all eight in one the chip had a wavefront per SIMD or
+    // less.  EPI of 128 lines with 8 coils, us per call: 29 k isochromats 267 and
+    // 208, 595 k 443 and 381; 6.8 M (256 lines) 3084 and 3083, the kernel itself
+    // 934 and 872 (two coils per wavefront 1012, one 1320).
     if (a.n_coils == 1)
-        hipLaunchKernelGGL(k_run_sweep<1>, dim3((unsigned)blocks), dim3(64), 0, st, a);
-    else if (a.n_coils <= 4)
-        hipLaunchKernelGGL(k_run_sweep<4>, dim3((unsigned)blocks), dim3(64), 0, st, a);
+        hipLaunchKernelGGL(k_run_sweep<1>, dim3((unsigned)a.n_waves), dim3(64), 0, st, a);
     else
-        hipLaunchKernelGGL(k_run_sweep<8>, dim3((unsigned)blocks), dim3(64), 0, st, a);
+        hipLaunchKernelGGL(k_run_sweep<4>, dim3((unsigned)a.n_waves, (unsigned)((a.n_coils + 3) / 4)), dim3(64), 0, st, a);
     return hipGetLastError();
 }
 
