@@ -893,7 +893,8 @@ static bool in_partial_kernel(int need, bool coils) {
 // part of a product besides its members' share: it takes kRunMinMembers members
 // (with several coils kRunMinCoilMembers).  208 k isochromats in runs of 2.6,
 // us per call by runs and swept: 64 EPI lines 190 and 194, an 8 x 8 FSE 207 and
-// 243, the EPI with 8 coils 692 and 632.
+// 243, the EPI with 8 coils 692 and 632 (with eight coils per wavefront of the
+// run sweep; it takes four).
 // So does a schedule of few operations: the sums Y are made for 128 lines and
 // more.  us per call, by runs and swept: 595 k isochromats, 8 EPI lines 104 and
 // 101, 16 lines 109 and 114; with 8 coils 16 lines 221 and 219, 32 lines 239
