@@ -32,6 +32,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // holding row l % 16 and column l % 16 of member l / 16.  Evaluated in the lanes
 // of the product instead, the 32 phases of a member took 95 VALU cycles per
 // step, against 64 of the matrix core (27.3M members, 256 lines: 555 us).
+// The matrix core adds the members of one chunk, the chunks' sums add in FP32
+// eight at a time, and those in FP64: 2.4e-7 of the signal off at any length.
+// All of a run's members in one FP32 accumulator were 1.4e-4 off at 16384 equal
+// terms and 9e-3 at 2^20, measurably from 64 on; that took 1 to 2.5 % less time
+// (27.3M isochromats, FSE of 256 lines 1271 and 1299 us, EPI of 128 821 and 831).
 // A phase coefficient (turns per metre) as two floats: c y mod 1 then takes
 // four FP32 instructions with one rounding of the reduced phase (the FMA of
 // hi y - rint(hi y) is exact up to it), instead of five at FP64.
@@ -55,6 +60,7 @@ __device__ __forceinline__ float2 turned(const float2 &p, const float2 &q) {
 }
 
 constexpr int kRunChunk = 32;
+constexpr int kRunFlush = 8;  // chunks whose sums add in FP32
 
 // HALF: at most 128 lines (b-phases 0 .. 3), columns 0 .. 7 with the real and
 // 8 .. 15 with the imaginary part of the weight: one matrix instruction per step.
@@ -113,8 +119,10 @@ __global__ __launch_bounds__(256) void k_run_y(RunYArgs a) {
         const int next = nj < kRunTile && rn < rend ? first_slot(rn) : last;
         f32x4 dr = {0.f, 0.f, 0.f, 0.f}, di = {0.f, 0.f, 0.f, 0.f};
         if (r < rend) {
-            const int s1 = first_slot(r + 1);
-            for (int base = first_slot(r); base < s1; base += kRunChunk) {
+            const int s0 = first_slot(r), s1 = first_slot(r + 1);
+            f32x4 tr = dr, ti = di;
+            double ar[4] = {0.0, 0.0, 0.0, 0.0}, ai[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int base = s0; base < s1; base += kRunChunk) {
                 float2 p[8];
                 p[0] = phase_at(f0, yv);
                 const float2 q1 = phase_at(f1, yv), q4 = phase_at(f4, yv), w = phase_at(c0, yv);
@@ -137,6 +145,19 @@ __global__ __launch_bounds__(256) void k_run_y(RunYArgs a) {
                 const int left = s1 - base;
                 fetch(left > kRunChunk ? base + kRunChunk : next);
                 const int steps = min(left, kRunChunk) / 4;
+                if (base > s0) {
+                    tr += dr;
+                    ti += di;
+                    dr = di = f32x4{0.f, 0.f, 0.f, 0.f};
+                    if ((base - s0) % (kRunFlush * kRunChunk) == 0) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            ar[v] += (double)tr[v];
+                            if (!HALF) ai[v] += (double)ti[v];
+                        }
+                        tr = ti = f32x4{0.f, 0.f, 0.f, 0.f};
+                    }
+                }
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 for (int t = 0; t < steps; t += 4) {  // (members past the run's end have weight 0)
                     float pa[4], pb[4];
@@ -158,6 +179,15 @@ __global__ __launch_bounds__(256) void k_run_y(RunYArgs a) {
                     }
                 }
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            }
+            dr += tr;
+            di += ti;
+            if (s1 - s0 > kRunFlush * kRunChunk) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    dr[v] = (float)(ar[v] + (double)dr[v]);
+                    if (!HALF) di[v] = (float)(ai[v] + (double)di[v]);
+                }
             }
         }
         // lane (column 2 jb + t, rows 4 kq ..): element v of the tiles is
