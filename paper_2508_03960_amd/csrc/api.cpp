@@ -201,6 +201,7 @@ struct gbs_ctx {
     // two-axis groups (GBS_AX_XZ): the layout's runs of equal (x-group,
     // z-group); run of every 4-slot quad, and (x, T1, T2, df), z per run
     int64_t n_runs = -1;
+    int64_t n_pairs = -1;  // of different (x-group, z-group): long ones are several runs
     DevBuf run_of4, rtab, rz;
     // the same runs whenever z groups are built (n_lruns, else 0): first quad,
     // x- and z-group per run, run of each isochromat in the caller's order
@@ -588,7 +589,7 @@ int gbs_build_groups(gbs_ctx *ctx, uint32_t axes) {
         *gout[a] = ctx->gid[a].as<int32_t>();
     }
     // the runs of equal (x-group, z-group) in the layout (the two-axis groups)
-    ctx->n_runs = -1;
+    ctx->n_runs = ctx->n_pairs = -1;
     ctx->n_lruns = 0;
     ctx->xrun.clear();
     if (zg) {
@@ -627,6 +628,7 @@ int gbs_build_groups(gbs_ctx *ctx, uint32_t axes) {
                                     ctx->t1i.as<float>(), ctx->t2i.as<float>(), ctx->dfi.as<float>(),
                                     ctx->rtab.as<float4>(), ctx->rz.as<float>(), ctx->stream));
             ctx->n_runs = R;
+            ctx->n_pairs = lay.pairs;
         }
     }
     if (!zg) {
@@ -664,7 +666,7 @@ int gbs_get_info(gbs_ctx *ctx, gbs_info *info) {
     info->device = ctx->device;
     info->n_tissue_groups = ctx->groups_valid ? ctx->n_tissue : -1;
     info->n_coils = ctx->n_coils;
-    info->n_xz_groups = ctx->groups_valid ? ctx->n_runs : -1;
+    info->n_xz_groups = ctx->groups_valid ? ctx->n_pairs : -1;
     return GBS_OK;
 }
 

@@ -12,6 +12,7 @@ namespace gbs {
 constexpr int kFields = 6;  // x, y, z, T1, T2, dB0
 constexpr int kFieldCap = 8192;  // distinct values of a field up to which phantoms are grouped without a sort
 constexpr int kFieldSlots = 2 * kFieldCap;
+constexpr int kRunPiece = 512;  // isochromats: runs of twice as many and more are cut into pieces
 
 // Pieces of the grouping scratch, 256-byte aligned (null when it is used up).
 struct Carve {
@@ -65,10 +66,12 @@ struct SortedAxis {
 // The padded layout's order and runs (arrays in the grouping scratch).
 struct Layout {
     int64_t K, R, kint;  // isochromats, runs, padded count (a multiple of 8)
+    int64_t pairs;       // (x-group, z-group) pairs: the runs less the cuts of long ones
     int32_t *order;      // [K] isochromats by (x-group, z-group, index)
     int32_t *rid;        // [K] their run, 1-based
     int32_t *rstart, *pstart, *plen;  // [R] first sorted and first padded position, padded length
     int32_t *gx, *gz;    // [R] groups
+    int32_t *cuts;       // runs that go on with the pair of the one before
     Carve free;          // the rest of the scratch
 };
 

@@ -44,13 +44,23 @@ static hipError_t exclusive_sum(void *tmp, size_t *bytes, const int32_t *in, int
     return rocprim::exclusive_scan(tmp, *bytes, in, out, (int32_t)0, (size_t)n, rocprim::plus<int32_t>(), st);
 }
 
-// 1 where a sorted key differs from the one before it
+// 1 where a run of the sorted keys starts: where a key differs from the one
+// before it, and inside longer stretches of one key at the multiples of
+// kRunPiece that have kRunPiece positions of it on either side.  So no run is
+// longer than 3 kRunPiece - 2 positions, and a stretch below 2 kRunPiece is one
+// run: a run's sum over its members (k_run_y) is one wavefront's work, and one
+// run of 2^20 isochromats kept the whole chip waiting for 15.7 ms.
 struct HeadFlag {
     const uint64_t *key;
-    __device__ int32_t operator()(int64_t i) const { return i == 0 || key[i] != key[i - 1] ? 1 : 0; }
+    int64_t n;
+    __device__ bool key_starts(int64_t i) const { return i == 0 || key[i] != key[i - 1]; }
+    __device__ int32_t operator()(int64_t i) const {
+        if (key_starts(i)) return 1;
+        return i % kRunPiece == 0 && i + kRunPiece <= n && key[i - kRunPiece] == key[i + kRunPiece - 1];
+    }
 };
-static auto head_flags(const uint64_t *key) {
-    return rocprim::make_transform_iterator(rocprim::make_counting_iterator<int64_t>(0), HeadFlag{key});
+static auto head_flags(const uint64_t *key, int64_t n) {
+    return rocprim::make_transform_iterator(rocprim::make_counting_iterator<int64_t>(0), HeadFlag{key, n});
 }
 
 __device__ __forceinline__ uint32_t ordered_bits(float f) {
@@ -559,7 +569,7 @@ hipError_t adjoint_groups(int64_t K, const float *const coord[3], const float *d
 
 // ---- padded group-sorted layout ---------------------------------------------
 // Isochromats are ordered by (x-group, z-group, index) and every run of equal
-// (x-group, z-group) is padded to a multiple of 8 with copies of its first
+// (x-group, z-group), or piece of a long one, is padded to a multiple of 8 with copies of its first
 // member carrying M0 = 0.  A thread's 8 (or 4) consecutive isochromats then always
 // share both groups.  The sort takes the bits that the group counts need: 3
 // passes of 8 bits instead of 8, for the 6.8 M isochromats above 0.2 ms
@@ -572,9 +582,11 @@ __global__ void k_pair_keys(int64_t K, const int32_t *__restrict__ gx, const int
     }
 }
 
-// rid = inclusive scan of the run starts (1-based); rstart and the run's groups
+// rid = inclusive scan of the run starts (1-based); rstart and the run's groups.
+// *cuts (zero before) += runs that go on with the key of the one before
 __global__ void k_run_start(int64_t K, const uint64_t *__restrict__ key, int zbits, const int32_t *__restrict__ rid,
-                            int32_t *__restrict__ rstart, int32_t *__restrict__ gx, int32_t *__restrict__ gz) {
+                            int32_t *__restrict__ rstart, int32_t *__restrict__ gx, int32_t *__restrict__ gz,
+                            int32_t *__restrict__ cuts) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < K; i += (int64_t)gridDim.x * blockDim.x) {
         const int32_t r = rid[i] - 1;
         if (i == 0 || rid[i - 1] - 1 != r) {
@@ -582,6 +594,7 @@ __global__ void k_run_start(int64_t K, const uint64_t *__restrict__ key, int zbi
             rstart[r] = (int32_t)i;
             gx[r] = (int32_t)(k >> zbits);
             gz[r] = (int32_t)(k & (((uint64_t)1 << zbits) - 1));
+            if (i > 0 && key[i - 1] == k) atomicAdd(cuts, 1);
         }
     }
 }
@@ -600,15 +613,16 @@ static hipError_t sort_runs(Layout *l, const int32_t *gid_x, const int32_t *gid_
     size_t b1 = 0, b2 = 0;
     hipError_t e;
     if ((e = sort_pairs(nullptr, &b1, key, key2, idx, l->order, l->K, (unsigned)bits, st)) != hipSuccess) return e;
-    if ((e = inclusive_sum(nullptr, &b2, head_flags(key2), l->rid, l->K, st)) != hipSuccess) return e;
+    if ((e = inclusive_sum(nullptr, &b2, head_flags(key2, l->K), l->rid, l->K, st)) != hipSuccess) return e;
     char *tmp = w.take<char>(b1 > b2 ? b1 : b2);
     if (!key || !key2 || !idx || !tmp) return hipErrorInvalidValue;
     const dim3 g = grid_for(l->K);
     hipLaunchKernelGGL(k_pair_keys, g, dim3(256), 0, st, l->K, gid_x, gid_z, zbits, key, idx);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = sort_pairs(tmp, &b1, key, key2, idx, l->order, l->K, (unsigned)bits, st)) != hipSuccess) return e;
-    if ((e = inclusive_sum(tmp, &b2, head_flags(key2), l->rid, l->K, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_run_start, g, dim3(256), 0, st, l->K, key2, zbits, l->rid, l->rstart, l->gx, l->gz);
+    if ((e = inclusive_sum(tmp, &b2, head_flags(key2, l->K), l->rid, l->K, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, st, (int64_t)1, l->cuts);
+    hipLaunchKernelGGL(k_run_start, g, dim3(256), 0, st, l->K, key2, zbits, l->rid, l->rstart, l->gx, l->gz, l->cuts);
     return hipGetLastError();
 }
 
@@ -622,13 +636,16 @@ hipError_t build_layout(int64_t K, const int32_t *gid_x, int64_t Gx, const int32
     int32_t **arr[] = {&l->order, &l->rid, &l->rstart, &l->pstart, &l->plen, &l->gx, &l->gz};
     for (int32_t **a : arr)
         if (!(*a = w.take<int32_t>(K))) return hipErrorInvalidValue;
+    if (!(l->cuts = w.take<int32_t>(1))) return hipErrorInvalidValue;
     const int zbits = gid_z ? bits_for(Gz) : 0, bits = zbits + bits_for(Gx);
     hipError_t e = sort_runs(l, gid_x, gid_z, zbits, bits < 1 ? 1 : bits, w, st);
     if (e != hipSuccess) return e;
-    int32_t R = 0;
+    int32_t R = 0, cuts = 0;
     if ((e = hipMemcpyAsync(&R, l->rid + (K - 1), sizeof(int32_t), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
+    if ((e = hipMemcpyAsync(&cuts, l->cuts, sizeof(int32_t), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
     l->R = R;
+    l->pairs = R - cuts;
     l->free = w;
     hipLaunchKernelGGL(k_run_plen, grid_for(R), dim3(256), 0, st, (int64_t)R, K, l->rstart, l->plen);
     size_t b = 0;
@@ -822,7 +839,7 @@ size_t group_scratch_bytes(int64_t K) {
     // the largest of group_axis (4 u64 + 4 i32 arrays), build_layout (2 u64 + 8 i32)
     // and dense_groups (2 i32 per cell and the field tables), plus tmp
     const size_t sorted = 48 * (size_t)K, dense = 8 * (size_t)n + 4 * (kFieldZero + kFieldFound);
-    return (sorted > dense ? sorted : dense) + tmp + 16 * 256;
+    return (sorted > dense ? sorted : dense) + tmp + 17 * 256;
 }
 
 // Group one axis by sorting, ids in the order of (coord, T1, T2, df) or, with

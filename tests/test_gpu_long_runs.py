@@ -54,3 +54,59 @@ def test_equal_terms(gb, R, L, name, ky):  # noqa: F811
     rel = float(np.linalg.norm(s - ref) / np.linalg.norm(ref))
     print(f"[gpu] long runs R={R} L={L} {name}: rel {rel:.2e}", flush=True)
     assert rel <= TOL, (R, L, name, rel)
+
+
+@pytest.mark.parametrize("sizes", [[1023], [1024], [1025], [1534, 1], [1, 1534], [2, 1535, 7], [511, 512, 513, 1024],
+                                   [5000], [3, 2048, 3, 2047, 9, 700, 4096]])
+@pytest.mark.parametrize("axis", [(0, 0, 1), (0.3, 0, 1)])
+def test_pieces(gb, sizes, axis):  # noqa: F811
+    """Runs around the length from which they are cut: state and signal, with
+    transitions per z-group and per run, and the count of two-axis groups."""
+    rng = np.random.default_rng(len(sizes))
+    x = np.repeat(np.linspace(-0.02, 0.02, len(sizes)), sizes)
+    K = x.size
+    f = lambda v: np.ascontiguousarray(v, np.float32)
+    order = rng.permutation(K)
+    ph = synth.Phantom(f(x[order]), f(rng.uniform(-0.1, 0.1, K)), f(0 * x + 1e-3), f(0 * x + 0.9), f(0 * x + 0.08),
+                       f(0 * x + 5.0), f(rng.uniform(0.1, 1.0, K)))
+    seq = sequence(range(-5, 6), rf_axis=axis)
+    Mr, sr = oracle.simulate(ph, seq)
+    sim = gb.Simulator(0)
+    sim.set_phantom(ph)
+    sim.set_sequence(seq)
+    sim.build_groups()
+    assert sim.info()["n_xz_groups"] == len(sizes)
+    sim.close()
+    for explicit in (False, True):  # by runs, and the sweep over the isochromats
+        M, s = grouped(gb, ph, seq, explicit=explicit)
+        dm, rel = float(np.max(np.abs(M - Mr))), float(np.linalg.norm(s - sr) / np.linalg.norm(sr))
+        print(f"[gpu] pieces {sizes} {axis} explicit={explicit}: max|dM|={dm:.2e} rel {rel:.2e}", flush=True)
+        assert dm <= 1e-5 and rel <= 1e-4, (sizes, axis, explicit, dm, rel)
+
+
+@pytest.mark.parametrize("R", [1, 8])
+def test_long_runs_fill_the_chip(gb, R):  # noqa: F811
+    """2^18 isochromats in one or eight runs take no more than four times as long
+    as in 256 runs (one wavefront per run: 14 to 60 times as long)."""
+    import time
+    import torch
+
+    def us(R):
+        sim = gb.Simulator(0)
+        sim.set_phantom(column_phantom(R, (1 << 18) // R))
+        sim.set_sequence(sequence(range(-8, 8)))
+        sim.build_groups()
+        best = 1e9
+        for _ in range(6):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            for _ in range(5):
+                sim.simulate(gb.GBS_GROUPED)
+            torch.cuda.synchronize()
+            best = min(best, (time.perf_counter() - t) / 5 * 1e6)
+        sim.close()
+        return best
+
+    few, many = us(R), us(256)
+    print(f"[gpu] 2^18 isochromats in {R} runs {few:.1f} us, in 256 {many:.1f} us", flush=True)
+    assert few <= 4.0 * many
