@@ -38,7 +38,7 @@ struct Fields {
     uint32_t *list[kFields];    // [kFieldCap] distinct values as found
     uint32_t *sorted[kFields];  // [kFieldCap] in ascending order
     uint64_t *rank[kFields];    // [kFieldSlots] (value << 32 | rank), zero before k_field_ranks
-    int32_t *count;             // [kFields], zero before k_field_values
+    int32_t *count;             // [kFields], 0 or given up before k_field_values
 };
 
 // Cells: axis a's block [base[a], base[a + 1]) of the products coordinate x

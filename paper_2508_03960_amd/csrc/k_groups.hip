@@ -199,12 +199,59 @@ __device__ __forceinline__ bool seen_before(uint32_t *seen, uint32_t v) {
     return false;  // no room: v goes to the shared table each time
 }
 
+// Clears the tables; and gives up at once (count beyond kFieldCap) a field
+// that has more than kFieldCap values among kSampled isochromats.  Where every
+// isochromat has a value of its own (a measured dB0 map, free positions), the
+// table below fills up under all of the chip's threads at once, and their probes
+// past the L2 took 5 ms; this takes 15 us, beside the clearing.  Fields that
+// pass have seldom more values than twice kFieldCap slots.
+constexpr int kSampled = 3 * kFieldCap / 2, kSampleWG = 1024;
+
+__global__ __launch_bounds__(kSampleWG) void k_field_start(int64_t K, Fields f, int64_t n_zero, int32_t *zero) {
+    if (blockIdx.x >= kFields) {
+        const int64_t stride = (int64_t)(gridDim.x - kFields) * kSampleWG;
+        for (int64_t i = (int64_t)(blockIdx.x - kFields) * kSampleWG + threadIdx.x; i < n_zero; i += stride) zero[i] = 0;
+        return;
+    }
+    __shared__ uint32_t seen[kFieldSlots];
+    __shared__ int found;
+    const float *val = f.val[blockIdx.x];
+    if (!val || K <= kFieldCap) {
+        if (threadIdx.x == 0) f.count[blockIdx.x] = 0;
+        return;
+    }
+    for (int i = threadIdx.x; i < kFieldSlots; i += kSampleWG) seen[i] = 0;
+    if (threadIdx.x == 0) found = 0;
+    constexpr int kEach = kSampled / kSampleWG;
+    const int n = K < kSampled ? (int)K : kSampled;
+    uint32_t v[kEach];
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+        const int i = j * kSampleWG + threadIdx.x;
+        v[j] = i < n ? ordered_bits(val[(int64_t)i * K / n]) : 0u;
+    }
+    __syncthreads();
+    int mine = 0;
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) {
+        if (v[j] == 0) continue;
+        uint32_t s = hash_of(v[j]) >> 18, cur;
+        while ((cur = atomicCAS(seen + s, 0u, v[j])) != 0 && cur != v[j]) s = (s + 1) % kFieldSlots;  // (a quarter stays empty)
+        mine += cur == 0;
+    }
+    atomicAdd(&found, mine);
+    __syncthreads();
+    if (threadIdx.x == 0) f.count[blockIdx.x] = found > kFieldCap ? kFieldCap + 1 : 0;
+}
+
 __global__ __launch_bounds__(256) void k_field_values(int64_t K, Fields f) {
     __shared__ uint32_t seen[kSeen];
     __shared__ int stop;
     const int q = blockIdx.y;
     const float *val = f.val[q];
-    if (!val) return;
+    bool given_up = false;
+    for (int p = 0; p < kFields; ++p) given_up = given_up || f.count[p] > kFieldCap;
+    if (!val || given_up) return;
     for (int i = threadIdx.x; i < kSeen; i += 256) seen[i] = 0;
     if (threadIdx.x == 0) stop = 0;
     __syncthreads();
@@ -377,35 +424,42 @@ __global__ void k_zero_i32(int64_t n, int32_t *v) {
 
 int64_t dense_cell_limit(int64_t K) { return K > (1 << 20) ? K : (1 << 20); }
 
-constexpr size_t kFieldZero = 64 + kFields * 3 * kFieldSlots;  // counts, rank and value tables: zero at the start
+constexpr size_t kFieldCounts = 64, kFieldTables = kFields * 3 * kFieldSlots;  // rank and value tables: zero at the start
 constexpr size_t kFieldFound = kFields * 2 * kFieldCap;          // lists and sorted values
 
 static bool carve_fields(const float *const val[kFields], Carve &w, Fields &f) {
-    // the words that start at zero, then the others
-    int32_t *z = w.take<int32_t>(kFieldZero), *u = w.take<int32_t>(kFieldFound);
+    int32_t *z = w.take<int32_t>(kFieldCounts + kFieldTables), *u = w.take<int32_t>(kFieldFound);
     if (!z || !u) return false;
     f.count = z;
     for (int q = 0; q < kFields; ++q) {
         f.val[q] = val[q];
-        f.rank[q] = (uint64_t *)(z + 64) + q * kFieldSlots;
-        f.set[q] = (uint32_t *)(z + 64 + kFields * 2 * kFieldSlots) + q * kFieldSlots;
+        f.rank[q] = (uint64_t *)(z + kFieldCounts) + q * kFieldSlots;
+        f.set[q] = (uint32_t *)(z + kFieldCounts + kFields * 2 * kFieldSlots) + q * kFieldSlots;
         f.list[q] = (uint32_t *)u + q * 2 * kFieldCap;
         f.sorted[q] = f.list[q] + kFieldCap;
     }
     return true;
 }
 
-// Tables of the fields' values and their counts (synchronizes the stream).
-static hipError_t rank_fields(int64_t K, const Fields &f, int32_t (&count)[kFields], hipStream_t st) {
-    hipLaunchKernelGGL(k_zero_i32, grid_for(kFieldZero), dim3(256), 0, st, (int64_t)kFieldZero, f.count);
+// The fields' distinct values and their counts (synchronizes the stream).
+static hipError_t count_fields(int64_t K, const Fields &f, int32_t (&count)[kFields], hipStream_t st) {
+    hipLaunchKernelGGL(k_field_start, dim3(kFields + (kFieldTables + kSampleWG - 1) / kSampleWG), dim3(kSampleWG), 0, st, K, f,
+                       (int64_t)kFieldTables, f.count + kFieldCounts);
     const int64_t need = (K + 255) / 256;
     hipLaunchKernelGGL(k_field_values, dim3((unsigned)(need < kValueBlocks ? need : kValueBlocks), kFields), dim3(256), 0,
                        st, K, f);
-    hipLaunchKernelGGL(k_field_ranks, dim3(kFieldCap / 256, kFields), dim3(256), 0, st, f);
     hipError_t e;
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = hipMemcpyAsync(count, f.count, sizeof(count), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
     return hipStreamSynchronize(st);
+}
+
+// Their rank tables, once the counts say that the phantom takes them.
+static hipError_t rank_fields(const Fields &f, const int32_t (&count)[kFields], hipStream_t st) {
+    int32_t most = 1;
+    for (int32_t n : count) most = n > most ? n : most;
+    hipLaunchKernelGGL(k_field_ranks, dim3((unsigned)((most + 255) / 256), kFields), dim3(256), 0, st, f);
+    return hipGetLastError();
 }
 
 // Groups of all requested axes (coord[a] null: not requested) by cells; gid[a]
@@ -423,9 +477,10 @@ hipError_t dense_groups(int64_t K, const float *const coord[3], const float *t1,
     const float *const val[kFields] = {coord[0], coord[1], coord[2], t1, t2, df};
     if (!carve_fields(val, w, f)) return hipErrorInvalidValue;
     int32_t count[kFields];
-    hipError_t e = rank_fields(K, f, count, st);
+    hipError_t e = count_fields(K, f, count, st);
     if (e != hipSuccess) return e;
     if (!cell_blocks(count, dense_cell_limit(K), c)) return hipSuccess;
+    if ((e = rank_fields(f, count, st)) != hipSuccess) return e;
     const int64_t n = c.base[4];
     d->d_total = w.take<int32_t>(4);
     c.flag = w.take<int32_t>((size_t)n);
@@ -527,17 +582,18 @@ hipError_t adjoint_groups(int64_t K, const float *const coord[3], const float *d
     const float *const val[kFields] = {coord[0], coord[1], coord[2], df, nullptr, nullptr};
     if (!carve_fields(val, w, f)) return hipErrorInvalidValue;
     int32_t count[kFields];
-    hipError_t e = rank_fields(K, f, count, st);
+    hipError_t e = count_fields(K, f, count, st);
     if (e != hipSuccess) return e;
     AdjCells c{};
     c.n = c.C = n_classes;
-    for (int q = 0; q < 4; ++q) {
-        if (count[q] > kFieldCap) return hipSuccess;
+    for (int q = 0; q < 4; ++q) {  // (every value of a field is in a group of its own)
+        if (count[q] > kFieldCap || count[q] > max_groups) return hipSuccess;
         c.nv[q] = f.val[q] ? count[q] : 1;
         c.shift[q] = rank_shift(count[q]);
         c.n *= c.nv[q];
         if (c.n > dense_cell_limit(K)) return hipSuccess;
     }
+    if ((e = rank_fields(f, count, st)) != hipSuccess) return e;
     c.flag = w.take<int32_t>((size_t)c.n);
     c.ids = w.take<int32_t>((size_t)c.n);
     uint64_t *key = w.take<uint64_t>(K), *sorted = w.take<uint64_t>(K);
@@ -838,7 +894,7 @@ size_t group_scratch_bytes(int64_t K) {
     if (!sized) tmp = ((size_t)64 << 20) + 16 * (size_t)K;
     // the largest of group_axis (4 u64 + 4 i32 arrays), build_layout (2 u64 + 8 i32)
     // and dense_groups (2 i32 per cell and the field tables), plus tmp
-    const size_t sorted = 48 * (size_t)K, dense = 8 * (size_t)n + 4 * (kFieldZero + kFieldFound);
+    const size_t sorted = 48 * (size_t)K, dense = 8 * (size_t)n + 4 * (kFieldCounts + kFieldTables + kFieldFound);
     return (sorted > dense ? sorted : dense) + tmp + 17 * 256;
 }
 
