@@ -122,7 +122,8 @@ struct GroupedPlan {
     size_t gsum_count = 0;
     int64_t max_rf_groups = 0, max_tab = 0;
     int max_adc_groups = 0, max_adc_samples = 0;
-    int n_rf = 0, n_fold = 0, n_tab = 0, n_adc = 0, n_adclin = 0, max_adclin_groups = 0;
+    int n_rf = 0, n_rf_sym = 0;  // the last n_rf_sym jobs are symmetric pulses
+    int n_fold = 0, n_tab = 0, n_adc = 0, n_adclin = 0, max_adclin_groups = 0;
     int64_t max_fold_groups = 0;
     size_t o_rf = 0, o_fold = 0, o_tab = 0, o_adc = 0, o_adclin = 0, o_sweep = 0;
     // execution: runs of grouped ops fused into sweeps, plain steps between
@@ -1251,6 +1252,10 @@ static int build_grouped_plan(gbs_ctx *ctx) {
     }
     std::vector<RfJobDev> rj_surr(rj);  // GBS_SURROGATE: the network's transition is not composed
     if (g.surr_rf >= 0) rj_surr[g.surr_rf].n_groups = 0;
+    auto mirrored = [](const RfJobDev &r) { return r.sym.sym && r.n_steps >= kMirrorMinSteps; };
+    g.n_rf_sym = (int)std::count_if(rj.begin(), rj.end(), mirrored);
+    for (auto *v : {&rj, &rj_surr})
+        std::stable_partition(v->begin(), v->end(), [&](const RfJobDev &r) { return !mirrored(r); });
     if (g.surr_rf >= 0) {
         // tuples, network output, spot-check indices (seeded, distinct) and exact values
         const int64_t G = ctx->ng[2];
@@ -1894,8 +1899,10 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
                                  (float *)(sb + g.s_res), fb, ctx->stream));
         HIPCHK(mlp_exact_async(m, tuples, nullptr, g.surr_groups, fb, T64, ctx->stream));
     }
-    HIPCHK(launch_compose((const RfJobDev *)(jb + (surr ? g.o_rf_surr : g.o_rf)), g.n_rf, g.max_rf_groups, s.dt,
-                          ctx->stream));
+    const RfJobDev *rf = (const RfJobDev *)(jb + (surr ? g.o_rf_surr : g.o_rf));
+    const int n_full = g.n_rf - g.n_rf_sym;
+    HIPCHK(launch_compose(rf, n_full, g.max_rf_groups, false, s.dt, ctx->stream));
+    HIPCHK(launch_compose(rf + n_full, g.n_rf_sym, g.max_rf_groups, true, s.dt, ctx->stream));
     if (forked) HIPCHK(hipStreamWaitEvent(side, ctx->fork, 0));
     const bool use_runs = g.runs && !m_init && ws_bytes >= g.run_ws_bytes;
     if (!use_runs || g.run_cut)  // (wavefronts that hold whole x-groups store every sum)

@@ -56,8 +56,12 @@ __device__ __forceinline__ void aff_compose(const Aff &L, const Aff &R, Aff &r) 
     }
 }
 
+// SYM: jobs of symmetric pulses (kernels.hpp, kMirrorMinSteps), which also carry the
+// sum of the partial products' z rows.  Carried by all jobs, and taken for short
+// pulses too, it cost what it saves many times over: see launch_compose.
+template <bool SYM>
 __global__ __launch_bounds__(256) void k_compose(const RfJobDev *__restrict__ jobs, double dt) {
-    __shared__ double lds[kComposeGroupsPerWG][64][15];  // A, b, sum of the partial products' z rows
+    __shared__ double lds[kComposeGroupsPerWG][64][SYM ? 15 : 12];  // A, b (and the z rows)
     const RfJobDev j = jobs[blockIdx.y];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t g = (int64_t)blockIdx.x * kComposeGroupsPerWG + wave;
@@ -68,7 +72,7 @@ __global__ __launch_bounds__(256) void k_compose(const RfJobDev *__restrict__ jo
     const double e1 = exp(-dt / t1), e2 = exp(-dt / t2);
     const double gdt = kTwoPi * kGammaBar * dt, k2 = gdt * gdt;
     const StepConst sc{coord, 0.0, 0.0, boff, e1, e2, -expm1(-dt / t1), gdt, k2};
-    const bool half = j.sym.sym && can_mirror(sc);  // one group per wavefront: uniform
+    const bool half = SYM && j.sym.sym && can_mirror(sc);  // one group per wavefront: uniform
     const int n = half ? j.n_steps / 2 : j.n_steps;
     const int lo = (int)(((int64_t)n * lane) >> 6), hi = (int)(((int64_t)n * (lane + 1)) >> 6);
     // (B1 re, B1 im, gradient on the job's axis) of step s, through the
@@ -110,6 +114,7 @@ __global__ __launch_bounds__(256) void k_compose(const RfJobDev *__restrict__ jo
     aff_identity(T);
     double z0 = 0.0, z1 = 0.0, z2 = 0.0;
     auto rows = [&](const Aff &t) {
+        if (!SYM) return;
         z0 += t.a[6];
         z1 += t.a[7];
         z2 += t.a[8];
@@ -151,9 +156,11 @@ __global__ __launch_bounds__(256) void k_compose(const RfJobDev *__restrict__ jo
     lds[wave][lane][9] = T.b[0];
     lds[wave][lane][10] = T.b[1];
     lds[wave][lane][11] = T.b[2];
-    lds[wave][lane][12] = z0;
-    lds[wave][lane][13] = z1;
-    lds[wave][lane][14] = z2;
+    if constexpr (SYM) {
+        lds[wave][lane][12] = z0;
+        lds[wave][lane][13] = z1;
+        lds[wave][lane][14] = z2;
+    }
     __syncthreads();
     for (int d = 1; d < 64; d <<= 1) {
         Aff L, R, r;
@@ -170,10 +177,12 @@ __global__ __launch_bounds__(256) void k_compose(const RfJobDev *__restrict__ jo
                 R.b[i] = lds[wave][lane][9 + i];
                 L.b[i] = lds[wave][lane + d][9 + i];
             }
-            const double *lz = &lds[wave][lane + d][12];
+            if constexpr (SYM) {
+                const double *lz = &lds[wave][lane + d][12];
 #pragma unroll
-            for (int i = 0; i < 3; ++i)
-                zr[i] = lds[wave][lane][12 + i] + (lz[0] * R.a[i] + lz[1] * R.a[3 + i] + lz[2] * R.a[6 + i]);
+                for (int i = 0; i < 3; ++i)
+                    zr[i] = lds[wave][lane][12 + i] + (lz[0] * R.a[i] + lz[1] * R.a[3 + i] + lz[2] * R.a[6 + i]);
+            }
             aff_compose(L, R, r);
         }
         __syncthreads();
@@ -183,42 +192,51 @@ __global__ __launch_bounds__(256) void k_compose(const RfJobDev *__restrict__ jo
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
                 lds[wave][lane][9 + i] = r.b[i];
-                lds[wave][lane][12 + i] = zr[i];
+                if constexpr (SYM) lds[wave][lane][12 + i] = zr[i];
             }
         }
         __syncthreads();
     }
-    if (half && lane == 0) {  // the second half of a symmetric pulse
-        const double *t = lds[wave][0];
-        Stretch p;
-        double o[3][4];
+    if constexpr (SYM) {
+        if (half && lane == 0) {  // the second half of a symmetric pulse
+            const double *t = lds[wave][0];
+            Stretch p;
+            double o[3][4];
 #pragma unroll
-        for (int i = 0; i < 9; ++i) p.a[i / 3][i % 3] = t[i];
+            for (int i = 0; i < 9; ++i) p.a[i / 3][i % 3] = t[i];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            p.a[i][3] = t[9 + i];
-            p.s[i] = t[12 + i];
+            for (int i = 0; i < 3; ++i) {
+                p.a[i][3] = t[9 + i];
+                p.s[i] = t[12 + i];
+            }
+            StepW mid{};  // the field of the middle step as step_u takes it: the job's axis alone
+            const float3 w = step_in(n);
+            mid.b1r = w.x;
+            mid.b1i = w.y;
+            mid.gx = w.z;
+            finish_mirrored(sc, mid, j.n_steps, j.sym.nx, j.sym.ny, p, o);
+#pragma unroll
+            for (int i = 0; i < 9; ++i) lds[wave][0][i] = o[i / 3][i % 3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) lds[wave][0][9 + i] = o[i][3];
         }
-        StepW mid{};  // the field of the middle step as step_u takes it: the job's axis alone
-        const float3 w = step_in(n);
-        mid.b1r = w.x;
-        mid.b1i = w.y;
-        mid.gx = w.z;
-        finish_mirrored(sc, mid, j.n_steps, j.sym.nx, j.sym.ny, p, o);
-#pragma unroll
-        for (int i = 0; i < 9; ++i) lds[wave][0][i] = o[i / 3][i % 3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) lds[wave][0][9 + i] = o[i][3];
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     if (act && lane < 12) j.out[12 * g + lane] = lds[wave][0][lane];
 }
 
-hipError_t launch_compose(const RfJobDev *jobs, int n_jobs, int64_t max_groups, double dt,
+// Half the steps pay from kMirrorMinSteps on: the tree over the 64 partial products
+// does not get shorter with the pulse, and the z rows make it a quarter longer.
+// us for 202500 groups, all steps and half: 16 steps 404 and 671, 800 steps 700
+// and 847, 1000 steps 912 and 939, 1024 steps 903 and 801, 4000 steps 2526 and 1752.
+hipError_t launch_compose(const RfJobDev *jobs, int n_jobs, int64_t max_groups, bool symmetric, double dt,
                           hipStream_t st) {
     if (n_jobs <= 0 || max_groups <= 0) return hipSuccess;
     dim3 grid((unsigned)((max_groups + kComposeGroupsPerWG - 1) / kComposeGroupsPerWG), n_jobs);
-    hipLaunchKernelGGL(k_compose, grid, dim3(256), 0, st, jobs, dt);
+    if (symmetric)
+        hipLaunchKernelGGL(k_compose<true>, grid, dim3(256), 0, st, jobs, dt);
+    else
+        hipLaunchKernelGGL(k_compose<false>, grid, dim3(256), 0, st, jobs, dt);
     return hipGetLastError();
 }
 

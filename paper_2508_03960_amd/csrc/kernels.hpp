@@ -212,8 +212,10 @@ int plain_iso(int64_t K);  // isochromats per thread of the plain mode
 hipError_t launch_sweep(const SweepArgs &a, hipStream_t st);
 hipError_t launch_tables(const TabJob *jobs, int n_jobs, int max_n, const float4 *gtab_x,
                          const float4 *gtab_z, hipStream_t st);
-hipError_t launch_compose(const RfJobDev *jobs, int n_jobs, int64_t max_groups, double dt,
+// symmetric: all of them are jobs whose sym may be used (at least kMirrorMinSteps)
+hipError_t launch_compose(const RfJobDev *jobs, int n_jobs, int64_t max_groups, bool symmetric, double dt,
                           hipStream_t st);
+constexpr int32_t kMirrorMinSteps = 1024;
 hipError_t launch_fold(const FoldJob *jobs, int n_jobs, int64_t max_groups, hipStream_t st);
 hipError_t launch_adc_eval(const AdcJobDev *jobs, int n_jobs, int max_groups, int max_samples,
                            double *sig, hipStream_t st);
