@@ -41,7 +41,11 @@ constexpr int kAdcMmRows = 64;    // rows per workgroup
 constexpr int kAdcMmCols = 128;   // samples per workgroup
 constexpr int kAdcMmSub = 32;     // groups staged at a time
 constexpr int kAdcMmSplit = 224;  // most groups whose terms add in FP32 (as in k_adc_lin: 28 per thread, 8 threads)
-constexpr int kAdcMmMinRows = 4;
+// Rows that a tile needs: its cost is that of 64 rows.  us for a tile of 64 by the
+// product and for r rows by k_adc_lin: 400000 groups, 64 samples 270 and 6.8 r,
+// 128 samples 290 and 9.5 r, 256 samples 550 and 15.8 r; 60000 groups 64 and 1.2 r,
+// 69 and 1.65 r, 120 and 2.7 r.  Rows that fill no tile are evaluated one by one.
+__host__ __device__ constexpr int adc_mm_min_rows(int n_samples) { return n_samples <= 64 ? 56 : 48; }
 // Terms (rows x samples x groups) from which the product is the faster one: 97 x 131
 // x 8700 take 42 us either way, 32 x 64 x 700 take 8.9 us in k_adc_lin's one
 // launch and 12 us in the product's two.

@@ -1356,14 +1356,16 @@ static int build_grouped_plan(gbs_ctx *ctx) {
         int64_t off = 0;
         for (size_t c = 0; c < timing.size(); ++c) {
             const AdcLinJob &j = timing[c].first;
-            const int n_rows = timing[c].second;
-            if (n_rows < kAdcMmMinRows || (double)n_rows * j.n_samples * j.n_groups < kAdcMmMinTerms) {
-                for (size_t i : members[c]) {
-                    g.lin_rest.push_back(lj[i]);
-                    g.max_adcrest_groups = std::max(g.max_adcrest_groups, lj[i].n_groups);
-                }
-                continue;
+            int n_rows = timing[c].second;
+            if (n_rows % kAdcMmRows < adc_mm_min_rows(j.n_samples)) n_rows -= n_rows % kAdcMmRows;
+            if ((double)n_rows * j.n_samples * j.n_groups < kAdcMmMinTerms) n_rows = 0;
+            for (size_t k = (size_t)n_rows; k < members[c].size(); ++k) {
+                const size_t i = members[c][k];
+                g.lin_rest.push_back(lj[i]);
+                g.max_adcrest_groups = std::max(g.max_adcrest_groups, lj[i].n_groups);
             }
+            if (n_rows == 0) continue;
+            members[c].resize((size_t)n_rows);
             const int64_t tiles = (int64_t)((n_rows + kAdcMmRows - 1) / kAdcMmRows) *
                                   ((j.n_samples + kAdcMmCols - 1) / kAdcMmCols);
             // groups per workgroup: the most that FP32 adds, fewer while the product has less than 512 workgroups

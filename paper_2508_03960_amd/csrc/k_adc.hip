@@ -22,10 +22,9 @@
 // in FP64 (one FP64 atomic pair per sample and workgroup).
 //
 // k_adc_mm: the same for many readouts of equal timing at once, as a matrix
-// product (below).  k_adc_lin takes what is left: timings with fewer than
-// kAdcMmMinRows readouts, whose rows would fill too little of a tile, or few
-// terms, and calls
-// whose workspace has no room for the product's partial sums.
+// product (below).  k_adc_lin takes what is left: readouts that would fill too
+// little of a tile (adc_mm_min_rows), timings with few terms, and calls whose
+// workspace has no room for the product's partial sums.
 #include "adc.hpp"
 #include "device_math.hpp"
 
