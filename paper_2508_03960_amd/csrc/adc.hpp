@@ -40,7 +40,7 @@ struct AdcTile {  // rows [row, row + n_rows) of one class, samples from n0 on
 constexpr int kAdcMmRows = 64;    // rows per workgroup
 constexpr int kAdcMmCols = 128;   // samples per workgroup
 constexpr int kAdcMmSub = 32;     // groups staged at a time
-constexpr int kAdcMmSplit = 224;  // most groups whose terms add in FP32 (as in k_adc_lin: 28 per thread, 8 threads)
+constexpr int kAdcMmSplit = 224;  // most groups per workgroup, 32 at a time (k_adc_lin: 28 per thread, 8 threads)
 // Rows that a tile needs: its cost is that of 64 rows.  us for a tile of 64 by the
 // product and for r rows by k_adc_lin: 400000 groups, 64 samples 270 and 6.8 r,
 // 128 samples 290 and 9.5 r, 256 samples 550 and 15.8 r; 60000 groups 64 and 1.2 r,

@@ -192,18 +192,21 @@ __global__ __launch_bounds__(kAdcLinWG) void k_adc_lin(const AdcLinJob *__restri
 // the lanes that hold it, four real v_mfma_f32_16x16x4_f32 per complex 16 x 16
 // tile and four groups.  A wavefront holds all 64 rows of its 32 samples, so
 // each factor is made once per 64 readouts: VALU work is a fifth of the matrix
-// core's, which bounds the kernel.  Partial sums of at most 224 groups in FP32
-// (as in k_adc_lin), FP64 from there (k_adc_mm_sum); no atomics.
+// core's, which bounds the kernel.  The 32 groups of a stage add in the matrix
+// core, the stages in FP32 (up to seven), FP64 from there (k_adc_mm_sum); no
+// atomics.  (All 224 groups in the matrix core's FP32 sums erred by 6.0e-7 of the
+// signal for equal terms of 100000 groups, where k_adc_lin errs by 3.0e-7; this
+// by 2.3e-7, in the same time.)
 typedef float adc_f32x4 __attribute__((ext_vector_type(4)));
 
 struct AdcGroup {
     double x, df;
 };
 
-__global__ __launch_bounds__(256) void k_adc_mm(const AdcClass *__restrict__ classes, const AdcRow *__restrict__ rows,
+__global__ __launch_bounds__(256, 2) void k_adc_mm(const AdcClass *__restrict__ classes, const AdcRow *__restrict__ rows,
                                                 const AdcTile *__restrict__ tiles, float2 *__restrict__ part,
                                                 int64_t part_stride) {
-    constexpr int ET = kAdcMmRows / 16, NT = kAdcMmCols / 64;
+    constexpr int ET = kAdcMmRows / 16, NT = kAdcMmCols / 64, RQ = kAdcMmRows / 8;
     constexpr int LD = kAdcMmSub + 4;
     __shared__ float2 sA[kAdcMmRows * LD];
     __shared__ AdcGroup sg[kAdcMmSub];
@@ -217,15 +220,15 @@ __global__ __launch_bounds__(256) void k_adc_mm(const AdcClass *__restrict__ cla
     const int i = lane & 15, kq = lane >> 4;
     // staging: thread t loads group t % 32 of the rows t / 32 + 8 q
     const int sgp = threadIdx.x & 31, srow = threadIdx.x >> 5;
-    const double2 *src[kAdcMmRows / 8];
+    const double2 *src[RQ];
 #pragma unroll
-    for (int q = 0; q < kAdcMmRows / 8; ++q) src[q] = rows[tl.row + min(srow + 8 * q, tl.n_rows - 1)].gsum;
-    double2 sv[kAdcMmRows / 8];
+    for (int q = 0; q < RQ; ++q) src[q] = rows[tl.row + min(srow + 8 * q, tl.n_rows - 1)].gsum;
+    double2 sv[RQ];
     float4 gv = make_float4(0.f, 1.f, 1.f, 0.f);
     auto load = [&](int g) {  // groups g .. g + 31 (indices clamped; groups past the end are zeroed when stored)
         const int k = min(g + sgp, g1 - 1);
 #pragma unroll
-        for (int q = 0; q < kAdcMmRows / 8; ++q) sv[q] = adc_sum(src[q], k);
+        for (int q = 0; q < RQ; ++q) sv[q] = adc_sum(src[q], k);
         if (threadIdx.x < kAdcMmSub) gv = adc_row(c.gtab, k);
     };
     double cyc[NT], tau[NT];
@@ -237,18 +240,18 @@ __global__ __launch_bounds__(256) void k_adc_mm(const AdcClass *__restrict__ cla
         cyc[t] = c.cyc0 + n * c.dcyc;
         mtau[t] = -(float)tau[t];
     }
-    adc_f32x4 dr[ET][NT], di[ET][NT];
+    adc_f32x4 tr[ET][NT], ti[ET][NT];
 #pragma unroll
     for (int e = 0; e < ET; ++e)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) dr[e][t] = di[e][t] = adc_f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < NT; ++t) tr[e][t] = ti[e][t] = adc_f32x4{0.f, 0.f, 0.f, 0.f};
     const bool live = tl.n0 + 16 * NT * wave < c.n_samples;
     load(g0);
     for (int g = g0; g < g1; g += kAdcMmSub) {
         __syncthreads();  // the previous groups have been read
         const bool in = g + sgp < g1;
 #pragma unroll
-        for (int q = 0; q < kAdcMmRows / 8; ++q)
+        for (int q = 0; q < RQ; ++q)
             sA[(srow + 8 * q) * LD + sgp] = in ? make_float2((float)sv[q].x, (float)sv[q].y) : make_float2(0.f, 0.f);
         if (threadIdx.x < kAdcMmSub) {
             sg[threadIdx.x] = AdcGroup{(double)gv.x, (double)gv.w};
@@ -257,6 +260,11 @@ __global__ __launch_bounds__(256) void k_adc_mm(const AdcClass *__restrict__ cla
         __syncthreads();
         if (g + kAdcMmSub < g1) load(g + kAdcMmSub);
         if (!live) continue;
+        adc_f32x4 dr[ET][NT], di[ET][NT];
+#pragma unroll
+        for (int e = 0; e < ET; ++e)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) dr[e][t] = di[e][t] = adc_f32x4{0.f, 0.f, 0.f, 0.f};
         const int steps = (min(kAdcMmSub, g1 - g) + 3) / 4;
         for (int s = 0; s < steps; ++s) {
             const AdcGroup p = sg[4 * s + kq];
@@ -282,6 +290,13 @@ __global__ __launch_bounds__(256) void k_adc_mm(const AdcClass *__restrict__ cla
                 }
             }
         }
+#pragma unroll
+        for (int e = 0; e < ET; ++e)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                tr[e][t] += dr[e][t];
+                ti[e][t] += di[e][t];
+            }
     }
     if (!live) return;
     // element v of a tile: row 4 kq + v, column i
@@ -296,7 +311,7 @@ __global__ __launch_bounds__(256) void k_adc_mm(const AdcClass *__restrict__ cla
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const int n = tl.n0 + 16 * (NT * wave + t) + i;
-                if (n < c.n_samples) o[n] = make_float2(dr[e][t][v], di[e][t][v]);
+                if (n < c.n_samples) o[n] = make_float2(tr[e][t][v], ti[e][t][v]);
             }
         }
 }
