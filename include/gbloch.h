@@ -234,7 +234,8 @@ int gbs_build_groups(gbs_ctx *ctx, uint32_t axes);
  *     call from (0, 0, M0) steps the runs of equal (x, z, T1, T2, dB0)
  *     instead of their members, room for their sums of M0 exp(-i phi_y): 8
  *     bytes per run, coil and phase-encode line (of batches of runs when
- *     many coils need much).
+ *     many coils need much), at most 3 GiB; and partial sums of readouts of
+ *     equal timing, at most 256 MiB.
  *   GBS_CACHED: the FP64 state (24 bytes per isochromat), the transition
  *     cache of Sec. 2.2 (48 bytes per isochromat and distinct with-RF
  *     waveform) and partial sample sums.
@@ -255,7 +256,10 @@ int gbs_workspace_size(gbs_ctx *ctx, int mode, size_t *bytes);
  *          may reuse it between calls; concurrent calls need separate
  *          workspaces.  Passing the same workspace as the last call avoids
  *          a small upload of the grouped schedule's descriptors.
- * ws_bytes: its size.
+ * ws_bytes: its size.  GBS_GROUPED also takes less, down to the workspace
+ *          without the sums of runs and the partial sums of readouts: it then
+ *          sweeps over the isochromats, and evaluates the readouts one by one.
+ *          The message of a refusal names that size.
  * m_init: device float[3*K] SoA (Mx, My, Mz) or NULL for (0, 0, M0).
  * m_out: device float[3*K] SoA final magnetization (may alias m_init).
  * sig_out: device double[2*n_coils*total_samples], interleaved (re, im), Eq. (6),
@@ -289,7 +293,7 @@ int gbs_simulate(gbs_ctx *ctx, int mode, uint32_t flags, void *workspace, size_t
  * GBS_STATIC_WORKSPACE_BYTES that the library holds on every device it runs
  * on until the process ends.  Same arguments, results and errors as
  * gbs_simulate otherwise; calls no allocating routine.  A call whose
- * gbs_workspace_size exceeds the array returns GBS_E_WORKSPACE with the two
+ * least workspace exceeds the array returns GBS_E_WORKSPACE with the two
  * sizes in gbs_last_error.  Every context on one device shares that device's
  * array, so calls that overlap in time on one device (from different streams
  * or threads) race and must be serialized by the caller; nothing is kept in

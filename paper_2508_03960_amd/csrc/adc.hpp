@@ -31,12 +31,20 @@ struct AdcClass {
 struct AdcRow {
     const double2 *gsum;
     int64_t sig_offset;
-    int64_t part;  // first entry of the row in a split's partial sums
+    int64_t part, stride;  // first entry of the row in the first split's partial sums, and from split to split
     int32_t cls, pad;
 };
 struct AdcTile {  // rows [row, row + n_rows) of one class, samples from n0 on
     int32_t cls, row, n_rows, n0;
 };
+// Tiles [tile0, tile0 + n_tiles) and their rows in one launch, n_part partial sums.
+struct AdcBatch {
+    int32_t tile0, n_tiles, row0, n_rows, max_split, max_samples;
+    int64_t n_part;
+};
+// Partial sums of one launch: all of a 27M FSE (42 MB, with 8 coils in two); a
+// timing whose tiles alone take more is evaluated one by one.
+constexpr size_t kAdcPartCap = (size_t)256 << 20;
 constexpr int kAdcMmRows = 64;    // rows per workgroup
 constexpr int kAdcMmCols = 128;   // samples per workgroup
 constexpr int kAdcMmSub = 32;     // groups staged at a time
@@ -51,10 +59,10 @@ __host__ __device__ constexpr int adc_mm_min_rows(int n_samples) { return n_samp
 // launch and 12 us in the product's two.
 constexpr double kAdcMmMinTerms = 1.5e8;
 
-// part[split * part_stride + row.part + n] <- the partial sums (FP32), then
+// part[row.part + split * row.stride + n] <- the partial sums (FP32), then
 // sig += their FP64 sums
-hipError_t launch_adc_mm(const AdcClass *cls, const AdcRow *rows, const AdcTile *tiles, int n_tiles, int max_split,
-                         int n_rows, int max_samples, float2 *part, int64_t part_stride, double *sig, hipStream_t st);
+hipError_t launch_adc_mm(const AdcClass *cls, const AdcRow *rows, const AdcTile *tiles, const AdcBatch &b, float2 *part,
+                         double *sig, hipStream_t st);
 
 hipError_t launch_adc_lin(const AdcLinJob *jobs, int n_jobs, int max_groups, double *sig, hipStream_t st);
 

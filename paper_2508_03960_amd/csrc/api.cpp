@@ -150,9 +150,9 @@ struct GroupedPlan {
     // readouts of equal timing as matrix products (AdcClass); the readouts of
     // lin_rest are not in one.  Used when the workspace reaches adc_end.
     std::vector<AdcLinJob> lin_rest;
-    int n_adccls = 0, n_adcrow = 0, n_adctile = 0, adc_max_split = 0, adc_max_ns = 0, max_adcrest_groups = 0;
+    std::vector<AdcBatch> adc_batches;
+    int max_adcrest_groups = 0;
     size_t o_adccls = 0, o_adcrow = 0, o_adctile = 0, o_adcrest = 0, w_adcpart = 0, adc_end = 0;
-    int64_t adc_stride = 0;
     // per-run form of the whole simulation (runs.hpp), for calls that start
     // from (0, 0, M0): batches of runs whose Y fits the workspace
     bool runs = false;
@@ -1353,46 +1353,46 @@ static int build_grouped_plan(gbs_ctx *ctx) {
         }
         std::vector<std::vector<size_t>> members(timing.size());
         for (size_t i = 0; i < lj.size(); ++i) members[(size_t)cls_of[i]].push_back(i);
-        int64_t off = 0;
         for (size_t c = 0; c < timing.size(); ++c) {
             const AdcLinJob &j = timing[c].first;
             int n_rows = timing[c].second;
             if (n_rows % kAdcMmRows < adc_mm_min_rows(j.n_samples)) n_rows -= n_rows % kAdcMmRows;
             if ((double)n_rows * j.n_samples * j.n_groups < kAdcMmMinTerms) n_rows = 0;
+            const int cols = (j.n_samples + kAdcMmCols - 1) / kAdcMmCols;  // tiles per 64 rows
+            const int64_t tiles = (int64_t)((n_rows + kAdcMmRows - 1) / kAdcMmRows) * cols;
+            // groups per workgroup: the most that a workgroup takes, fewer while the product has less than 512 workgroups
+            int split = kAdcMmSplit;
+            while (split > kAdcMmSub && tiles * ((j.n_groups + split - 1) / split) < 512) split -= kAdcMmSub;
+            const int n_split = (j.n_groups + split - 1) / split;
+            const int64_t per_row = (int64_t)n_split * j.n_samples;  // partial sums
+            if (sizeof(float2) * (size_t)(kAdcMmRows * per_row) > kAdcPartCap || cols > 32767) n_rows = 0;
             for (size_t k = (size_t)n_rows; k < members[c].size(); ++k) {
                 const size_t i = members[c][k];
                 g.lin_rest.push_back(lj[i]);
                 g.max_adcrest_groups = std::max(g.max_adcrest_groups, lj[i].n_groups);
             }
             if (n_rows == 0) continue;
-            members[c].resize((size_t)n_rows);
-            const int64_t tiles = (int64_t)((n_rows + kAdcMmRows - 1) / kAdcMmRows) *
-                                  ((j.n_samples + kAdcMmCols - 1) / kAdcMmCols);
-            // groups per workgroup: the most that FP32 adds, fewer while the product has less than 512 workgroups
-            int split = kAdcMmSplit;
-            while (split > kAdcMmSub && tiles * ((j.n_groups + split - 1) / split) < 512) split -= kAdcMmSub;
-            const int n_split = (j.n_groups + split - 1) / split;
-            const int row0 = (int)arow.size();
-            for (size_t i : members[c]) {
-                arow.push_back(AdcRow{lj[i].gsum, lj[i].sig_offset, off, (int32_t)acls.size(), 0});
-                off += j.n_samples;
+            for (int r = 0; r < n_rows; r += kAdcMmRows) {
+                const int n = std::min(kAdcMmRows, n_rows - r);
+                if (g.adc_batches.empty() || g.adc_batches.back().n_tiles + cols > 65535 ||
+                    sizeof(float2) * (size_t)(g.adc_batches.back().n_part + n * per_row) > kAdcPartCap)
+                    g.adc_batches.push_back(AdcBatch{(int32_t)atile.size(), 0, (int32_t)arow.size(), 0, 0, 0, 0});
+                AdcBatch &b = g.adc_batches.back();
+                const int row0 = (int)arow.size();
+                for (int k = 0; k < n; ++k) {
+                    const AdcLinJob &m = lj[members[c][(size_t)(r + k)]];
+                    arow.push_back(AdcRow{m.gsum, m.sig_offset, b.n_part + (int64_t)k * j.n_samples, (int64_t)n * j.n_samples,
+                                          (int32_t)acls.size(), 0});
+                }
+                for (int n0 = 0; n0 < j.n_samples; n0 += kAdcMmCols) atile.push_back(AdcTile{(int32_t)acls.size(), row0, n, n0});
+                b.n_part += n * per_row;
+                b.n_rows += n;
+                b.n_tiles += cols;
+                b.max_split = std::max(b.max_split, n_split);
+                b.max_samples = std::max(b.max_samples, j.n_samples);
             }
-            for (int r = 0; r < n_rows; r += kAdcMmRows)
-                for (int n = 0; n < j.n_samples; n += kAdcMmCols)
-                    atile.push_back(AdcTile{(int32_t)acls.size(), row0 + r, std::min(kAdcMmRows, n_rows - r), n});
             acls.push_back(AdcClass{j.tau0, j.dtau, j.cyc0, j.dcyc, j.gtab, j.n_groups, j.n_samples, split, n_split});
-            g.adc_max_split = std::max(g.adc_max_split, n_split);
-            g.adc_max_ns = std::max(g.adc_max_ns, j.n_samples);
         }
-        g.adc_stride = off;
-        if (atile.size() > 65535 || g.adc_max_ns > 64 * 65535) {  // (grid limits: millions of readouts or of samples) all of them one by one
-            acls.clear();
-            arow.clear();
-            atile.clear();
-        }
-        g.n_adccls = (int)acls.size();
-        g.n_adcrow = (int)arow.size();
-        g.n_adctile = (int)atile.size();
     }
 
     // ---- sweep ops: grouped ops in schedule order; consecutive ones fuse
@@ -1693,9 +1693,11 @@ static int build_grouped_plan(gbs_ctx *ctx) {
     std::vector<RunOp> rops;
     if (ctx->n_lruns > 0)
         if (int rc = plan_runs(ctx, sops, rops)) return rc;
-    if (g.n_adccls) {  // partial sums of the readout products, after everything else
+    if (!g.adc_batches.empty()) {  // partial sums of the readout products, after everything else
+        int64_t most = 0;
+        for (const AdcBatch &b : g.adc_batches) most = std::max(most, b.n_part);
         g.w_adcpart = align256(std::max(g.ws_bytes, g.run_ws_bytes));
-        g.adc_end = align256(g.w_adcpart + sizeof(float2) * (size_t)g.adc_stride * (size_t)g.adc_max_split);
+        g.adc_end = align256(g.w_adcpart + sizeof(float2) * (size_t)most);
     }
     for (auto &sg : g.segs) sg.bytes_per_iso = sweep_bytes_per_iso(sg.need, sg.write_m, false, false);
     g.n_ops = (int64_t)sops.size();
@@ -1817,10 +1819,10 @@ static int finish_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const char *j
     // ---- ADC samples from the group sums (Eq. 8, Eq. 10) --------------------
     HIPCHK(launch_adc_eval((const AdcJobDev *)(jb + g.o_adc), g.n_adc, g.max_adc_groups, g.max_adc_samples,
                            sig_out, ctx->stream));
-    if (g.n_adccls && ws_bytes >= g.adc_end) {
-        HIPCHK(launch_adc_mm((const AdcClass *)(jb + g.o_adccls), (const AdcRow *)(jb + g.o_adcrow),
-                             (const AdcTile *)(jb + g.o_adctile), g.n_adctile, g.adc_max_split, g.n_adcrow, g.adc_max_ns,
-                             (float2 *)(ws + g.w_adcpart), g.adc_stride, sig_out, ctx->stream));
+    if (!g.adc_batches.empty() && ws_bytes >= g.adc_end) {
+        for (const AdcBatch &b : g.adc_batches)
+            HIPCHK(launch_adc_mm((const AdcClass *)(jb + g.o_adccls), (const AdcRow *)(jb + g.o_adcrow),
+                                 (const AdcTile *)(jb + g.o_adctile), b, (float2 *)(ws + g.w_adcpart), sig_out, ctx->stream));
         HIPCHK(launch_adc_lin((const AdcLinJob *)(jb + g.o_adcrest), (int)g.lin_rest.size(), g.max_adcrest_groups,
                               sig_out, ctx->stream));
     } else {
@@ -2414,11 +2416,6 @@ extern "C" int gbs_workspace_size(gbs_ctx *ctx, int mode, size_t *bytes) {
 
 extern "C" int gbs_simulate(gbs_ctx *ctx, int mode, uint32_t flags, void *workspace, size_t ws_bytes,
                             const float *m_init, float *m_out, double *sig_out, gbs_stats *stats) {
-    return gbs::simulate_in(ctx, mode, flags, workspace, ws_bytes, false, m_init, m_out, sig_out, stats);
-}
-
-int gbs::simulate_in(gbs_ctx *ctx, int mode, uint32_t flags, void *workspace, size_t ws_bytes, bool least,
-                     const float *m_init, float *m_out, double *sig_out, gbs_stats *stats) {
     if (!ctx) return GBS_E_INVALID;
     if (!ctx->has_ph) return fail(ctx, GBS_E_STATE, "gbs_simulate before gbs_set_phantom");
     if (!ctx->has_seq) return fail(ctx, GBS_E_STATE, "gbs_simulate before gbs_set_sequence");
@@ -2432,9 +2429,8 @@ int gbs::simulate_in(gbs_ctx *ctx, int mode, uint32_t flags, void *workspace, si
     const bool use_surr = (flags & GBS_SURROGATE) != 0;
     if (use_surr && (mode == GBS_PLAIN || !ctx->mlp))
         return fail(ctx, GBS_E_INVALID, "GBS_SURROGATE needs GBS_GROUPED or GBS_CACHED and gbs_set_surrogate");
-    size_t need = 0, need_least = 0;
-    if (int rc = workspace_bytes(ctx, mode, &need, &need_least)) return rc;
-    if (least) need = need_least;
+    size_t full = 0, need = 0;
+    if (int rc = workspace_bytes(ctx, mode, &full, &need)) return rc;
     if (!workspace || ws_bytes < need)
         return fail(ctx, GBS_E_WORKSPACE, "workspace of " + std::to_string(workspace ? ws_bytes : 0) +
                                               " bytes; this mode needs " + std::to_string(need) +

@@ -204,8 +204,7 @@ struct AdcGroup {
 };
 
 __global__ __launch_bounds__(256, 2) void k_adc_mm(const AdcClass *__restrict__ classes, const AdcRow *__restrict__ rows,
-                                                const AdcTile *__restrict__ tiles, float2 *__restrict__ part,
-                                                int64_t part_stride) {
+                                                const AdcTile *__restrict__ tiles, float2 *__restrict__ part) {
     constexpr int ET = kAdcMmRows / 16, NT = kAdcMmCols / 64, RQ = kAdcMmRows / 8;
     constexpr int LD = kAdcMmSub + 4;
     __shared__ float2 sA[kAdcMmRows * LD];
@@ -300,14 +299,14 @@ __global__ __launch_bounds__(256, 2) void k_adc_mm(const AdcClass *__restrict__ 
     }
     if (!live) return;
     // element v of a tile: row 4 kq + v, column i
-    float2 *out = part + (int64_t)blockIdx.x * part_stride;
 #pragma unroll
     for (int e = 0; e < ET; ++e)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int r = 16 * e + 4 * kq + v;
             if (r >= tl.n_rows) continue;
-            float2 *o = out + rows[tl.row + r].part;
+            const AdcRow &row = rows[tl.row + r];
+            float2 *o = part + row.part + blockIdx.x * row.stride;
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const int n = tl.n0 + 16 * (NT * wave + t) + i;
@@ -322,8 +321,7 @@ __global__ __launch_bounds__(256, 2) void k_adc_mm(const AdcClass *__restrict__ 
 // as long for 128 rows of 290 splits).
 constexpr int kAdcSumWaves = 16;
 __global__ __launch_bounds__(64 * kAdcSumWaves) void k_adc_mm_sum(const AdcClass *__restrict__ classes, const AdcRow *__restrict__ rows,
-                                                    const float2 *__restrict__ part, int64_t part_stride,
-                                                    double *__restrict__ sig) {
+                                                    const float2 *__restrict__ part, double *__restrict__ sig) {
     __shared__ double2 red[kAdcSumWaves][64];
     const AdcRow r = rows[blockIdx.x];
     const int ns = classes[r.cls].n_samples, n_split = classes[r.cls].n_split;
@@ -337,7 +335,7 @@ __global__ __launch_bounds__(64 * kAdcSumWaves) void k_adc_mm_sum(const AdcClass
     for (; s + 3 * W < n_split; s += 4 * W) {  // four loads in flight
         float2 v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = p[(int64_t)(s + W * q) * part_stride];
+        for (int q = 0; q < 4; ++q) v[q] = p[(s + W * q) * r.stride];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             sr += v[q].x;
@@ -345,7 +343,7 @@ __global__ __launch_bounds__(64 * kAdcSumWaves) void k_adc_mm_sum(const AdcClass
         }
     }
     for (; s < n_split; s += W) {
-        const float2 v = p[(int64_t)s * part_stride];
+        const float2 v = p[s * r.stride];
         sr += v.x;
         si += v.y;
     }
@@ -364,16 +362,16 @@ __global__ __launch_bounds__(64 * kAdcSumWaves) void k_adc_mm_sum(const AdcClass
     }
 }
 
-hipError_t launch_adc_mm(const AdcClass *cls, const AdcRow *rows, const AdcTile *tiles, int n_tiles, int max_split,
-                         int n_rows, int max_samples, float2 *part, int64_t part_stride, double *sig, hipStream_t st) {
-    if (n_tiles <= 0 || max_split <= 0 || n_rows <= 0) return hipSuccess;
-    if (n_tiles > 65535 || max_samples > 64 * 65535) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_adc_mm, dim3((unsigned)max_split, (unsigned)n_tiles), dim3(256), 0, st, cls, rows, tiles, part,
-                       part_stride);
+hipError_t launch_adc_mm(const AdcClass *cls, const AdcRow *rows, const AdcTile *tiles, const AdcBatch &b, float2 *part,
+                         double *sig, hipStream_t st) {
+    if (b.n_tiles <= 0) return hipSuccess;
+    if (b.n_tiles > 65535 || b.max_samples > 64 * 65535 || b.max_split <= 0 || b.n_rows <= 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_adc_mm, dim3((unsigned)b.max_split, (unsigned)b.n_tiles), dim3(256), 0, st, cls, rows,
+                       tiles + b.tile0, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_adc_mm_sum, dim3((unsigned)n_rows, (unsigned)((max_samples + 63) / 64)),
-                       dim3(64 * kAdcSumWaves), 0, st, cls, rows, part, part_stride, sig);
+    hipLaunchKernelGGL(k_adc_mm_sum, dim3((unsigned)b.n_rows, (unsigned)((b.max_samples + 63) / 64)),
+                       dim3(64 * kAdcSumWaves), 0, st, cls, rows + b.row0, part, sig);
     return hipGetLastError();
 }
 

@@ -63,5 +63,5 @@ extern "C" int gbs_simulate_static(gbs_ctx *ctx, int mode, uint32_t flags, const
                                 "holds " + std::to_string(kStaticScratchBytes) + " (use gbs_simulate)";
         return gbs::ctx_fail(ctx, GBS_E_WORKSPACE, msg.c_str());
     }
-    return gbs::simulate_in(ctx, mode, flags, ws, kStaticScratchBytes, true, m_init, m_out, sig_out, stats);
+    return gbs_simulate(ctx, mode, flags, ws, kStaticScratchBytes, m_init, m_out, sig_out, stats);
 }

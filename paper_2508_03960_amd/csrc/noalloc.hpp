@@ -14,9 +14,6 @@ int ctx_device(const gbs_ctx *ctx);
 // The least workspace a call of `mode` runs with (gbs_workspace_size may name
 // a larger one, with which it runs faster).
 int ctx_least_workspace(gbs_ctx *ctx, int mode, size_t *bytes);
-// gbs_simulate; with `least` a workspace between the two sizes is taken too.
-int simulate_in(gbs_ctx *ctx, int mode, uint32_t flags, void *workspace, size_t ws_bytes, bool least,
-                const float *m_init, float *m_out, double *sig_out, gbs_stats *stats);
 int ctx_fail(gbs_ctx *ctx, int code, const char *msg);
 
 }  // namespace gbs
