@@ -2271,7 +2271,7 @@ static int run_cached(gbs_ctx *ctx, char *ws, const float *m_init, float *m_out,
             a.coil_re = ctx->coil_re;
             a.coil_im = ctx->coil_im;
             a.n_coils = ctx->coil_re ? ctx->n_coils : 1;
-            const int lin = ctx->clin[oi];
+            const int lin = a.n_samples >= adc_product_min_samples(K, a.n_coils) ? ctx->clin[oi] : -1;
             const int sgrid = lin >= 0 ? std::min(adc_product_grid(K), agrid) : agrid;
             if (lin >= 0)
                 HIPCHK(launch_adc_product(a, ctx->clin_samp[(size_t)lin], sgrid, ctx->stream));

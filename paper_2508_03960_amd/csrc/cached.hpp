@@ -73,9 +73,19 @@ struct LinSamples {
     double c0[3], dc[3], tau0, dtau;
 };
 // Samples from which the product is the faster one: its cost hardly falls below
-// 128 samples (2.1M isochromats: 297 us per 256 samples by k_direct_adc, which
-// is proportional to them).
-constexpr int kAdcProductMinSamples = 48;
+// 128 samples, and it makes the phases again for every coil, which k_direct_adc
+// makes once (whose cost steps up at 86, where its 256 threads hold two samples'
+// slices instead of three).  us per readout of 2.1M isochromats, direct and product:
+// one coil, 48 samples 78 and 64, 256 samples 313 and 83; 4 coils, 64 samples 227
+// and 228; 8 coils, 48 samples 286 and 443, 80 samples 412 and 450, 88 samples 547 and
+// 450, 128 samples 581 and 454.  114 k isochromats, 8 coils, 48 samples: 61 and 61.
+constexpr int kAdcProductMinSamples = 48, kAdcProductStep = 86;
+constexpr int64_t kAdcProductSmallK = 1 << 17;
+inline int adc_product_min_samples(int64_t K, int32_t n_coils) {
+    const int n = 28 + 10 * n_coils;
+    if (K < kAdcProductSmallK || n < kAdcProductMinSamples) return kAdcProductMinSamples;
+    return n < kAdcProductStep ? n : kAdcProductStep;
+}
 int adc_product_grid(int64_t K);
 hipError_t launch_adc_product(const DirectAdcArgs &a, const LinSamples &l, int grid, hipStream_t st);
 
