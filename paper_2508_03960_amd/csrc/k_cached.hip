@@ -226,11 +226,18 @@ __global__ __launch_bounds__(kAdcBlock) void k_direct_adc(DirectAdcArgs a) {
 // (l < 32) or B of isochromat l % 32, each directly (phase reduced in FP64,
 // hardware sin/cos and exp2, as k_direct_adc per sample), and leaves them in
 // LDS for the lanes of the product.  Per isochromat that is 32 evaluations in
-// place of 256; the rest is 32 cycles of the matrix core per SIMD.  FP32 sums of
-// at most 256 isochromats, then FP64, as in k_direct_adc.
+// place of 256; the rest is 32 cycles of the matrix core per SIMD.  The 32
+// isochromats of a chunk add in the matrix core, FP64 from there.
+// V_SIN and V_COS cut their result off: over the turn the pair is short by
+// kTurnBias on average, which a sum over many phases shows, and a term here holds
+// two such pairs where k_direct_adc's holds one.  M makes up for both.  Errors of
+// the signal, k_direct_adc and this: 66 k isochromats of a brain phantom, 48
+// samples 5.1e-8 and 3.5e-8 (9.0e-8 without the two), 256 samples 9.0e-8 and 5.0e-8;
+// equal isochromats, 64 samples 9.5e-8 and 6.2e-8 (1.3e-7).  2.1M isochromats: 67 us
+// for 48 to 128 samples (65 with 256 isochromats between FP64 sums), 85 for 256 (83).
 typedef float cached_f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kProdChunk = 32;
-constexpr int kProdFlush = 256 / kProdChunk;  // chunks whose terms add in FP32
+constexpr double kTurnBias = 3.234e-8;  // measured over 2^24 phases
 constexpr int kProdPad = 36;                  // floats per isochromat and side; 32 used (36: 16-byte rows, fewer bank conflicts)
 
 template <int NT>  // column tiles: 8 values of j each
@@ -266,6 +273,7 @@ __global__ __launch_bounds__(256) void k_adc_product(DirectAdcArgs a, LinSamples
     };
     const int64_t stride = (int64_t)gridDim.x * 4 * kProdChunk;
     int64_t base = ((int64_t)blockIdx.x * 4 + wave) * kProdChunk;
+    constexpr double kGain = 1.0 + 2.0 * kTurnBias;
     // the next chunk's isochromats are loaded during this one's product
     float x = 0.f, y = 0.f, z = 0.f, df = 0.f, t2 = 1.f, cr = 1.f, ci = 0.f;
     double mx = 0.0, my = 0.0;
@@ -289,7 +297,7 @@ __global__ __launch_bounds__(256) void k_adc_product(DirectAdcArgs a, LinSamples
         }
     };
     if (base < K) load(base);
-    for (int n = 1; base < K; base += stride, ++n) {
+    for (; base < K; base += stride) {
         const double step = fma(l.dc[0], (double)x, fma(l.dc[1], (double)y, fma(l.dc[2], (double)z, l.dtau * (double)df)));
         const double first = fma(l.c0[0], (double)x, fma(l.c0[1], (double)y, fma(l.c0[2], (double)z, l.tau0 * (double)df)));
         double p0 = half ? first - rint(first) : 0.0, dp = step - rint(step);
@@ -302,8 +310,8 @@ __global__ __launch_bounds__(256) void k_adc_product(DirectAdcArgs a, LinSamples
         // the factor of every value of this side: 1 (A), or M S (B; 0 past the end)
         float wr = 1.f, wi = 0.f;
         if (half) {
-            wr = base + mb < K ? (float)mx : 0.f;
-            wi = base + mb < K ? (float)my : 0.f;
+            wr = base + mb < K ? (float)(mx * kGain) : 0.f;
+            wi = base + mb < K ? (float)(my * kGain) : 0.f;
             if (sre) {
                 const float t = wr * cr - wi * ci;
                 wi = wr * ci + wi * cr;
@@ -337,9 +345,8 @@ __global__ __launch_bounds__(256) void k_adc_product(DirectAdcArgs a, LinSamples
                     d[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(pa[16 * r + i], pb[16 * c + i], d[r][c], 0, 0, 0);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (n % kProdFlush == 0) flush();
+        flush();
     }
-    flush();
     // Element v of tile (r, c): row 4 kq + v = {Re, Im} A_{8 r + 2 kq + v / 2}, column
     // i = {Re, Im} B_{8 c + i / 2}.  The neighbouring lane holds the other part of B.
     double2 *sum = (double2 *)val;  // [wave][sample]

@@ -1,8 +1,8 @@
 """Cached readouts with receive coils at the edges of the rule that takes the
 matrix product (48 samples; with coils 28 + 10 P, at most 86, from 2^17
-isochromats on): the
-signal against GBS_PLAIN, which steps in FP64 (bars of the other parity tests), and
-the time of the shortest product against one sample less, which is never one."""
+isochromats on): the signal against GBS_PLAIN, which steps in FP64 (bars of the
+other parity tests), and the time and the error of the shortest product against
+one sample less, which is never one."""
 import numpy as np
 import pytest
 
@@ -64,3 +64,34 @@ def test_one_sample_more_costs_no_more(gb, coils):  # noqa: F811
         sim.close()
     print(f"[gpu] cached readouts, {coils} coils: 47 samples {ms[0] * 250:.1f} us, 48 samples {ms[1] * 250:.1f} us", flush=True)
     assert ms[1] <= 1.1 * ms[0]
+
+
+@pytest.mark.parametrize("equal", [False, True])
+def test_product_errs_no_more_than_direct(gb, equal):  # noqa: F811
+    """48 samples (a product) against GBS_PLAIN err by no more than 47 (evaluated
+    directly) and a quarter, for random isochromats and for equal ones (whose
+    roundings go one way)."""
+    import torch
+    K = 100000
+    rng = np.random.default_rng(5)
+    f = lambda v: np.ascontiguousarray(v, np.float32)
+    u = (lambda a, b: np.full(K, 0.37 * a + 0.63 * b)) if equal else (lambda a, b: rng.uniform(a, b, K))
+    ph = synth.Phantom(f(rng.uniform(-0.1, 0.1, K)), f(u(-0.1, 0.1)), f(u(-1e-3, 1e-3)), f(u(0.6, 1.0)), f(u(0.05, 0.09)),
+                       f(u(-4, 4)), f(u(0.5, 1.0)))
+    err = []
+    for n_read in (47, 48):
+        sb = SeqBuilder(1e-6, "errors")
+        for i in range(6):
+            sb.rf(synth.sinc_pulse(200, 1e-6, 0.5), (0.0, 0.0, 0.01))
+            sb.relax(5e-4, (-3e-9 if i % 2 else -2e-8, 0.0, -1e-6))
+            sb.adc(4 * n_read, (2e-4, 0.0, 0.0), 4 * np.arange(n_read) + 2)
+            sb.relax(1e-3, (1e-9, 0.0, 0.0))
+        sim = gb.Simulator(0)
+        sim.set_phantom(ph)
+        sim.set_sequence(sb.build())
+        s = sim.simulate(gb.GBS_CACHED)[1].cpu().numpy()
+        ref = sim.simulate(gb.GBS_PLAIN)[1].cpu().numpy()
+        sim.close()
+        err.append(float(np.linalg.norm(s - ref) / np.linalg.norm(ref)))
+    print(f"[gpu] cached readouts, equal={equal}: direct errs by {err[0]:.2e}, product by {err[1]:.2e}", flush=True)
+    assert err[1] <= 1.25 * err[0]
