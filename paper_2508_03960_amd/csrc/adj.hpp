@@ -49,6 +49,7 @@ struct AdjArgs {
 // ---- by groups (k_adjgroup.hip) ---------------------------------------------
 constexpr int kAdjSeg = 16;          // raster steps per segment of a pulse
 constexpr int kAdjGroupMin = 4;      // isochromats per group from which the pulses are walked per group
+constexpr int kAdjMinSteps = 128;    // raster steps (less one per pulse) from which they are
 
 struct AdjStep {  // raster step of a pulse
     float b1r, b1i, gx, gy, gz;

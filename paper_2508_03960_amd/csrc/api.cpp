@@ -229,7 +229,7 @@ struct gbs_ctx {
     // state into the caller's order runs on it beside the ADC evaluation
     hipStream_t side = nullptr;
     hipEvent_t fork = nullptr, join = nullptr, checked = nullptr;
-    int *host_flag = nullptr;  // pinned: k_check_zero_m0's answer
+    int *host_flag = nullptr;  // pinned, 64: k_check_zero_m0's answer; from 16 and 32 on the adjoint's
     std::vector<hipEvent_t> pev;  // GBS_PROFILE: one (start, stop) pair per pass launch
     GroupedPlan gp;
     // learned surrogate (not owned)
@@ -2546,9 +2546,25 @@ struct AdjSchedule {
     uint32_t axes = 0;                   // axes of their gradients
 };
 
-static void schedule_pulses(const std::vector<AdjOp> &ops, const int32_t *sstart, AdjSchedule &g) {
+// Counts of that schedule: raster steps, and the pulses that they are played in.
+static void count_pulses(const std::vector<AdjOp> &ops, const int32_t *sstart, AdjSchedule &g) {
+    for (size_t p = 0; p < ops.size(); ++p) {
+        if (ops[p].kind != 0) continue;
+        ++g.n_raster;
+        if (p == 0 || ops[p - 1].kind != 0 || sstart[p + 1] != sstart[p]) ++g.n_played;
+    }
+}
+
+// Bytes of the group arrays per group.
+static size_t adj_group_bytes(const AdjSchedule &g) {
+    return sizeof(double) * (38 * g.segs.size() + 24 * g.pulses.size());
+}
+
+// The schedule itself; stops where one group would take more than max_bytes.
+static void schedule_pulses(const std::vector<AdjOp> &ops, const int32_t *sstart, size_t max_bytes, AdjSchedule &g) {
     const int64_t n_ops = (int64_t)ops.size();
     std::vector<std::pair<int32_t, int32_t>> range;  // steps of every pulse
+    std::vector<uint64_t> hashes;
     std::map<std::array<double, 4>, int32_t> coef;
     std::vector<AdjStep> run;
     auto at = [&](int64_t p) { return AdjGOp{-1, -1, sstart[p], sstart[p + 1] - sstart[p]}; };
@@ -2573,53 +2589,69 @@ static void schedule_pulses(const std::vector<AdjOp> &ops, const int32_t *sstart
         } while (e < n_ops && ops[e].kind == 0 && sstart[e + 1] == sstart[e]);
         p = e;
         const int32_t n = (int32_t)run.size();
+        const uint64_t h = hash_bytes((uint64_t)n, run.data(), sizeof(AdjStep) * run.size());
         size_t id = 0;
-        while (id < range.size() && !(range[id].second == n &&
+        while (id < range.size() && !(hashes[id] == h && range[id].second == n &&
                                       !std::memcmp(&g.steps[range[id].first], run.data(), sizeof(AdjStep) * run.size())))
             ++id;
         if (id == range.size()) {
             const int32_t s0 = (int32_t)g.steps.size(), seg0 = (int32_t)g.segs.size();
             range.emplace_back(s0, n);
+            hashes.push_back(h);
             g.steps.insert(g.steps.end(), run.begin(), run.end());
             for (int32_t j = 0; j < n; j += kAdjSeg) g.segs.push_back(AdjSeg{s0 + j, std::min(kAdjSeg, n - j)});
             g.pulses.push_back(int2{seg0, (int32_t)g.segs.size()});
+            if (g.segs.size() > 65535 || adj_group_bytes(g) > max_bytes) return;
         }
         o.pulse = (int32_t)id;
-        g.n_raster += n;
-        ++g.n_played;
         g.ops.push_back(o);
-        // too many short or different pulses for the form: the caller steps every isochromat
-        if (g.n_raster < kAdjSeg * g.n_played && g.n_played > 64) return;
-        if (g.segs.size() > 65535) return;
     }
     g.ops.push_back(at(n_ops));
 }
 
+// The limits of the adjoint by groups: its group count, and the cells of the
+// fields' values that it is found in.
+struct AdjLimits {
+    size_t bytes = 0;
+    int64_t groups = 0, cells = 0;
+};
+
+// Whether the form comes into question: long pulses, and raster steps that are
+// worth the grouping.  Stepped, 65536 isochromats and fewer take 2 us per raster
+// step (forward and backward), the grouping and the groups' steps take 100 to 150
+// us, and a pulse up to 30 us for its sums where four isochromats share a group
+// (2 us for each of a wavefront's groups).  us per call, stepped and by groups:
+// 65536 isochromats in groups of four, 3 pulses of 16 steps 586 and 728, 30 pulses
+// 2412 and 2485, 8 of 64 steps 1698 and 1043; groups of eight, 30 of 16 steps 2405
+// and 1916; 10^6 isochromats in groups of 16, 10 of 16 steps 7369 and 2790.
+static bool adj_takes_groups(const AdjArgs &old, const std::vector<AdjOp> &ops, const int32_t *sstart, size_t old_bytes,
+                             AdjSchedule &g, AdjLimits &l) {
+    count_pulses(ops, sstart, g);
+    if (g.n_played == 0 || g.n_raster < kAdjSeg * g.n_played || g.n_raster < kAdjMinSteps + g.n_played) return false;
+    l.bytes = std::max(old_bytes, (size_t)64 << 20);
+    schedule_pulses(ops, sstart, l.bytes, g);
+    if (g.segs.size() > 65535) return false;
+    l.groups = std::min(old.K / kAdjGroupMin, (int64_t)(l.bytes / adj_group_bytes(g)));
+    l.cells = (int64_t)((double)old.K / 64.0 * (double)(g.n_raster - kAdjMinSteps) / (double)g.n_played);
+    return l.groups >= 1;
+}
+
 // Sets the context up for the adjoint by groups and runs its forward pass;
-// *done stays false where the isochromats have to be stepped one by one: no
-// long pulses, fewer than kAdjGroupMin isochromats per group, or more memory
-// than the stepping's checkpoints (old_bytes) and 64 MiB.
-static int adj_forward_groups(gbs_ctx *ctx, const AdjArgs &old, const std::vector<AdjOp> &ops, const int32_t *sstart,
-                              size_t old_bytes, double *sig_out, bool *done) {
-    AdjSchedule g;
-    schedule_pulses(ops, sstart, g);
-    if (g.n_played == 0 || g.n_raster < kAdjSeg * g.n_played || g.segs.size() > 65535) return GBS_OK;
+// *done stays false where the isochromats have to be stepped one by one: fewer
+// than kAdjGroupMin isochromats per group, more memory than the stepping's
+// checkpoints (old_bytes) and 64 MiB, or more cells than the raster steps are
+// worth.
+static int adj_forward_groups(gbs_ctx *ctx, const AdjArgs &old, const AdjSchedule &g, const AdjLimits &l,
+                              AdjValues &values, size_t old_bytes, double *sig_out, bool *done) {
     const int64_t K = old.K, np = (int64_t)g.pulses.size(), ns = (int64_t)g.segs.size();
-    const size_t per_group = sizeof(double) * (size_t)(38 * ns + 24 * np);
-    const int64_t fit = (int64_t)(std::max(old_bytes, (size_t)64 << 20) / per_group);
-    const int64_t most = std::min(K / kAdjGroupMin, fit);
-    if (most < 1) return GBS_OK;
     WsCarve w;
-    const size_t o_order = w.take(4 * (size_t)K), o_gid = w.take(4 * (size_t)K), o_tab = w.take(sizeof(float4) * (size_t)most),
-                 o_cls = w.take(4 * (size_t)most);
+    const size_t o_order = w.take(4 * (size_t)K), o_gid = w.take(4 * (size_t)K), o_tab = w.take(sizeof(float4) * (size_t)l.groups),
+                 o_cls = w.take(4 * (size_t)l.groups);
     ALLOC(ctx->adj_order, w.off);
     char *b = ctx->adj_order.as<char>();
-    ALLOC(ctx->gscratch, adjoint_group_scratch(K));
-    const float *coord[3] = {(g.axes & 1) ? old.x : nullptr, (g.axes & 2) ? old.y : nullptr, (g.axes & 4) ? old.z : nullptr};
     int64_t G = 0;
-    HIPCHK(adjoint_groups(K, coord, old.df, old.cls, old.n_classes, most, ctx->gscratch.p, adjoint_group_scratch(K),
-                          (int32_t *)(b + o_order), (int32_t *)(b + o_gid), (float4 *)(b + o_tab),
-                          (int32_t *)(b + o_cls), &G, ctx->stream));
+    HIPCHK(adjoint_groups(values, old.cls, old.n_classes, l.cells, (int32_t *)(b + o_order), (int32_t *)(b + o_gid),
+                          (float4 *)(b + o_tab), (int32_t *)(b + o_cls), &G, ctx->stream));
     if (G < 0) return GBS_OK;
     // schedule arrays
     WsCarve v;
@@ -2816,14 +2848,6 @@ extern "C" int gbs_adj_forward(gbs_ctx *ctx, const int32_t *cls, int32_t n_class
     const int64_t n_ckpt = (n_ops + every - 1) / every;
     ALLOC(ctx->adj_samp, sizeof(int32_t) * samp.size());
     ALLOC(ctx->flag, 256);
-    // inputs: class indices in range, T1/T2 > 0 (checked on the device)
-    HIPCHK(launch_fill_f64(ctx->flag.as<double>(), 1, ctx->stream));
-    HIPCHK(launch_adj_validate(K, cls, n_classes, t1c, t2c, ctx->flag.as<int>(), ctx->stream));
-    int bad = 0;
-    HIPCHK(hipMemcpyAsync(&bad, ctx->flag.p, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(hipStreamSynchronize(ctx->stream));
-    if (bad) return fail(ctx, GBS_E_INVALID, "class index out of range or T1/T2 <= 0");
-    HIPCHK(hipMemcpy(ctx->adj_samp.p, samp.data(), sizeof(int32_t) * samp.size(), hipMemcpyHostToDevice));
     AdjArgs a{};
     a.K = K;
     a.x = ctx->ph.x;
@@ -2846,7 +2870,28 @@ extern "C" int gbs_adj_forward(gbs_ctx *ctx, const int32_t *cls, int32_t n_class
     const size_t ckpt_bytes = sizeof(float) * 3 * (size_t)K * (size_t)std::max<int64_t>(n_ckpt, 1),
                  sub_bytes = sizeof(float) * 3 * (size_t)K * (size_t)(every / kAdjSub);
     ctx->adj_grouped = false;
-    if (int rc = adj_forward_groups(ctx, a, ops, samp.data(), ckpt_bytes + sub_bytes, sig_out, &ctx->adj_grouped)) return rc;
+    AdjSchedule sched;
+    AdjLimits limits;
+    AdjValues values;
+    const bool by_groups = adj_takes_groups(a, ops, samp.data(), ckpt_bytes + sub_bytes, sched, limits);
+    if (by_groups) ALLOC(ctx->gscratch, adjoint_group_scratch(K));
+    // inputs: class indices in range, T1/T2 > 0 (checked on the device); and the
+    // counts of the values to group by, waited for with the answer
+    int *const answer = ctx->host_flag + 16, *const counts = ctx->host_flag + 32;
+    HIPCHK(launch_fill_f64(ctx->flag.as<double>(), 1, ctx->stream));
+    HIPCHK(launch_adj_validate(K, cls, n_classes, t1c, t2c, ctx->flag.as<int>(), ctx->stream));
+    HIPCHK(hipMemcpyAsync(answer, ctx->flag.p, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+    if (by_groups) {
+        const float *coord[3] = {(sched.axes & 1) ? a.x : nullptr, (sched.axes & 2) ? a.y : nullptr,
+                                 (sched.axes & 4) ? a.z : nullptr};
+        HIPCHK(adjoint_values(K, coord, a.df, limits.groups, ctx->gscratch.p, adjoint_group_scratch(K), counts, &values, ctx->stream));
+    }
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    if (*answer) return fail(ctx, GBS_E_INVALID, "class index out of range or T1/T2 <= 0");
+    HIPCHK(hipMemcpy(ctx->adj_samp.p, samp.data(), sizeof(int32_t) * samp.size(), hipMemcpyHostToDevice));
+    if (by_groups)
+        if (int rc = adj_forward_groups(ctx, a, sched, limits, values, ckpt_bytes + sub_bytes, sig_out, &ctx->adj_grouped))
+            return rc;
     if (ctx->adj_grouped) {
         HIPCHK(hipStreamSynchronize(ctx->stream));
         HIPCHK(hipGetLastError());

@@ -38,6 +38,7 @@ struct Fields {
     uint32_t *list[kFields];    // [kFieldCap] distinct values as found
     uint32_t *sorted[kFields];  // [kFieldCap] in ascending order
     uint64_t *rank[kFields];    // [kFieldSlots] (value << 32 | rank), zero before k_field_ranks
+    int32_t cap;                // values of a field from beyond which it is given up
     int32_t *count;             // [kFields], 0 or given up before k_field_values
 };
 
@@ -94,14 +95,26 @@ hipError_t dense_groups(int64_t K, const float *const coord[3], const float *t1,
                         hipStream_t st);
 hipError_t dense_tables(const DenseGroups &d, float4 *const gtab[3], float4 *ttab, int32_t *tmap, hipStream_t st);
 // Groups of the adjoint: isochromats of equal coord[a] (null: not compared),
-// dB0 and class, in that order.  Writes order and gid[K] (isochromats sorted by
-// group, their groups), and per group (coordinates or 0, dB0) and the class.
-// *n_groups = -1: too many distinct values, or more than max_groups groups.
-// scratch: adjoint_group_scratch bytes.  Synchronizes the stream.
+// dB0 and class, in that order.
+// adjoint_values collects the values of the coordinates and dB0 in the scratch
+// (adjoint_group_scratch bytes) and copies their counts to the pinned counts.
+// After the stream has been waited for, adjoint_groups writes order and gid[K]
+// (isochromats sorted by group, their groups), and per group (coordinates or 0,
+// dB0) and the class; *n_groups = -1: too many distinct values, more than
+// max_cells products of them, or more than max_groups groups.  It synchronizes
+// the stream.
+struct AdjValues {
+    int64_t K;
+    Fields f;
+    Carve free;  // the rest of the scratch
+    const int32_t *count;
+    int64_t max_groups;
+};
 size_t adjoint_group_scratch(int64_t K);
-hipError_t adjoint_groups(int64_t K, const float *const coord[3], const float *df, const int32_t *cls,
-                          int32_t n_classes, int64_t max_groups, void *scratch, size_t scratch_bytes, int32_t *order,
-                          int32_t *gid, float4 *gtab, int32_t *gcls, int64_t *n_groups, hipStream_t st);
+hipError_t adjoint_values(int64_t K, const float *const coord[3], const float *df, int64_t max_groups, void *scratch,
+                          size_t scratch_bytes, int32_t *counts, AdjValues *v, hipStream_t st);
+hipError_t adjoint_groups(const AdjValues &v, const int32_t *cls, int32_t n_classes, int64_t max_cells,
+                          int32_t *order, int32_t *gid, float4 *gtab, int32_t *gcls, int64_t *n_groups, hipStream_t st);
 hipError_t group_axis(int64_t K, bool coord_last, const float *coord, const float *t1, const float *t2, const float *df,
                       void *scratch, size_t scratch_bytes, int32_t *gid_nat, SortedAxis *s, int64_t *n_groups,
                       hipStream_t st);

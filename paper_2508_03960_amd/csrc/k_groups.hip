@@ -200,7 +200,7 @@ __device__ __forceinline__ bool seen_before(uint32_t *seen, uint32_t v) {
 }
 
 // Clears the tables; and gives up at once (count beyond kFieldCap) a field
-// that has more than kFieldCap values among kSampled isochromats.  Where every
+// that has more than f.cap values among kSampled isochromats.  Where every
 // isochromat has a value of its own (a measured dB0 map, free positions), the
 // table below fills up under all of the chip's threads at once, and their probes
 // past the L2 took 5 ms; this takes 15 us, beside the clearing.  Fields that
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(kSampleWG) void k_field_start(int64_t K, Fields f, 
     __shared__ uint32_t seen[kFieldSlots];
     __shared__ int found;
     const float *val = f.val[blockIdx.x];
-    if (!val || K <= kFieldCap) {
+    if (!val || K <= f.cap) {
         if (threadIdx.x == 0) f.count[blockIdx.x] = 0;
         return;
     }
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(kSampleWG) void k_field_start(int64_t K, Fields f, 
     }
     atomicAdd(&found, mine);
     __syncthreads();
-    if (threadIdx.x == 0) f.count[blockIdx.x] = found > kFieldCap ? kFieldCap + 1 : 0;
+    if (threadIdx.x == 0) f.count[blockIdx.x] = found > f.cap ? kFieldCap + 1 : 0;
 }
 
 __global__ __launch_bounds__(256) void k_field_values(int64_t K, Fields f) {
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(256) void k_field_values(int64_t K, Fields f) {
     const int q = blockIdx.y;
     const float *val = f.val[q];
     bool given_up = false;
-    for (int p = 0; p < kFields; ++p) given_up = given_up || f.count[p] > kFieldCap;
+    for (int p = 0; p < kFields; ++p) given_up = given_up || f.count[p] > f.cap;
     if (!val || given_up) return;
     for (int i = threadIdx.x; i < kSeen; i += 256) seen[i] = 0;
     if (threadIdx.x == 0) stop = 0;
@@ -427,10 +427,11 @@ int64_t dense_cell_limit(int64_t K) { return K > (1 << 20) ? K : (1 << 20); }
 constexpr size_t kFieldCounts = 64, kFieldTables = kFields * 3 * kFieldSlots;  // rank and value tables: zero at the start
 constexpr size_t kFieldFound = kFields * 2 * kFieldCap;          // lists and sorted values
 
-static bool carve_fields(const float *const val[kFields], Carve &w, Fields &f) {
+static bool carve_fields(const float *const val[kFields], int64_t cap, Carve &w, Fields &f) {
     int32_t *z = w.take<int32_t>(kFieldCounts + kFieldTables), *u = w.take<int32_t>(kFieldFound);
     if (!z || !u) return false;
     f.count = z;
+    f.cap = (int32_t)(cap < kFieldCap ? cap : kFieldCap);
     for (int q = 0; q < kFields; ++q) {
         f.val[q] = val[q];
         f.rank[q] = (uint64_t *)(z + kFieldCounts) + q * kFieldSlots;
@@ -441,8 +442,8 @@ static bool carve_fields(const float *const val[kFields], Carve &w, Fields &f) {
     return true;
 }
 
-// The fields' distinct values and their counts (synchronizes the stream).
-static hipError_t count_fields(int64_t K, const Fields &f, int32_t (&count)[kFields], hipStream_t st) {
+// The fields' distinct values; their counts to count[kFields] (asynchronous).
+static hipError_t count_fields(int64_t K, const Fields &f, int32_t *count, hipStream_t st) {
     hipLaunchKernelGGL(k_field_start, dim3(kFields + (kFieldTables + kSampleWG - 1) / kSampleWG), dim3(kSampleWG), 0, st, K, f,
                        (int64_t)kFieldTables, f.count + kFieldCounts);
     const int64_t need = (K + 255) / 256;
@@ -450,14 +451,13 @@ static hipError_t count_fields(int64_t K, const Fields &f, int32_t (&count)[kFie
                        st, K, f);
     hipError_t e;
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = hipMemcpyAsync(count, f.count, sizeof(count), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-    return hipStreamSynchronize(st);
+    return hipMemcpyAsync(count, f.count, sizeof(int32_t) * kFields, hipMemcpyDeviceToHost, st);
 }
 
 // Their rank tables, once the counts say that the phantom takes them.
-static hipError_t rank_fields(const Fields &f, const int32_t (&count)[kFields], hipStream_t st) {
+static hipError_t rank_fields(const Fields &f, const int32_t *count, hipStream_t st) {
     int32_t most = 1;
-    for (int32_t n : count) most = n > most ? n : most;
+    for (int q = 0; q < kFields; ++q) most = count[q] > most ? count[q] : most;
     hipLaunchKernelGGL(k_field_ranks, dim3((unsigned)((most + 255) / 256), kFields), dim3(256), 0, st, f);
     return hipGetLastError();
 }
@@ -475,10 +475,11 @@ hipError_t dense_groups(int64_t K, const float *const coord[3], const float *t1,
     Fields &f = d->f;
     Cells &c = d->c;
     const float *const val[kFields] = {coord[0], coord[1], coord[2], t1, t2, df};
-    if (!carve_fields(val, w, f)) return hipErrorInvalidValue;
+    if (!carve_fields(val, kFieldCap, w, f)) return hipErrorInvalidValue;
     int32_t count[kFields];
     hipError_t e = count_fields(K, f, count, st);
     if (e != hipSuccess) return e;
+    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
     if (!cell_blocks(count, dense_cell_limit(K), c)) return hipSuccess;
     if ((e = rank_fields(f, count, st)) != hipSuccess) return e;
     const int64_t n = c.base[4];
@@ -573,26 +574,35 @@ static int bits_for(int64_t n) {  // of the numbers below n
 
 size_t adjoint_group_scratch(int64_t K) { return group_scratch_bytes(K) + 20 * (size_t)K + 2048; }
 
-hipError_t adjoint_groups(int64_t K, const float *const coord[3], const float *df, const int32_t *cls,
-                          int32_t n_classes, int64_t max_groups, void *scratch, size_t scratch_bytes, int32_t *order,
-                          int32_t *gid, float4 *gtab, int32_t *gcls, int64_t *n_groups, hipStream_t st) {
-    *n_groups = -1;
-    Carve w{(char *)scratch, scratch_bytes};
-    Fields f;
+hipError_t adjoint_values(int64_t K, const float *const coord[3], const float *df, int64_t max_groups, void *scratch,
+                          size_t scratch_bytes, int32_t *counts, AdjValues *v, hipStream_t st) {
+    v->K = K;
+    v->free = Carve{(char *)scratch, scratch_bytes};
+    v->count = counts;
+    v->max_groups = max_groups;
     const float *const val[kFields] = {coord[0], coord[1], coord[2], df, nullptr, nullptr};
-    if (!carve_fields(val, w, f)) return hipErrorInvalidValue;
-    int32_t count[kFields];
-    hipError_t e = count_fields(K, f, count, st);
-    if (e != hipSuccess) return e;
+    if (!carve_fields(val, max_groups, v->free, v->f)) return hipErrorInvalidValue;
+    return count_fields(K, v->f, counts, st);
+}
+
+hipError_t adjoint_groups(const AdjValues &v, const int32_t *cls, int32_t n_classes, int64_t max_cells,
+                          int32_t *order, int32_t *gid, float4 *gtab, int32_t *gcls, int64_t *n_groups, hipStream_t st) {
+    *n_groups = -1;
+    const int64_t K = v.K;
+    const Fields &f = v.f;
+    const int32_t *count = v.count;
+    Carve w = v.free;
+    const int64_t cell_limit = max_cells < dense_cell_limit(K) ? max_cells : dense_cell_limit(K);
     AdjCells c{};
     c.n = c.C = n_classes;
-    for (int q = 0; q < 4; ++q) {  // (every value of a field is in a group of its own)
-        if (count[q] > kFieldCap || count[q] > max_groups) return hipSuccess;
+    for (int q = 0; q < 4; ++q) {  // (a field has no more values than there are groups)
+        if (count[q] > f.cap) return hipSuccess;
         c.nv[q] = f.val[q] ? count[q] : 1;
         c.shift[q] = rank_shift(count[q]);
         c.n *= c.nv[q];
-        if (c.n > dense_cell_limit(K)) return hipSuccess;
+        if (c.n > cell_limit) return hipSuccess;
     }
+    hipError_t e;
     if ((e = rank_fields(f, count, st)) != hipSuccess) return e;
     c.flag = w.take<int32_t>((size_t)c.n);
     c.ids = w.take<int32_t>((size_t)c.n);
@@ -610,7 +620,7 @@ hipError_t adjoint_groups(int64_t K, const float *const coord[3], const float *d
     int32_t G = 0;
     if ((e = hipMemcpyAsync(&G, c.ids + (c.n - 1), sizeof(G), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
-    if (G > max_groups) return hipSuccess;
+    if (G > v.max_groups) return hipSuccess;
     hipLaunchKernelGGL(k_adj_tables, dim3((unsigned)((c.n + 255) / 256)), dim3(256), 0, st, f, c, gtab, gcls);
     hipLaunchKernelGGL(k_adj_keys, grid_for(K), dim3(256), 0, st, K, c.ids, key, idx);
     if ((e = hipGetLastError()) != hipSuccess) return e;

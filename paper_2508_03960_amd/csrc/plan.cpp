@@ -198,8 +198,8 @@ Plan plan_plain(const HostSeq &s, int32_t max_samples) {
 
 // Four lanes of 64-bit words (a waveform of 3000 steps in 2 us; byte by byte,
 // the chain of multiplications took 25 us, most of the time of planning a long
-// sequence).  Equal hashes are compared bit for bit.
-static uint64_t hash_bytes(uint64_t h, const void *p, size_t n) {
+// sequence).
+uint64_t hash_bytes(uint64_t h, const void *p, size_t n) {
     constexpr uint64_t kMul = 0x9E3779B97F4A7C15ull;
     uint64_t lane[4] = {h, h ^ 0xA0761D6478BD642Full, h ^ 0xE7037ED1A0B428DBull, h ^ 0x8EBC6AF09C88C6E3ull};
     const unsigned char *c = (const unsigned char *)p;

@@ -124,6 +124,9 @@ struct Plan {
     int64_t n_rf_cached = 0, n_adc_direct = 0;  // plan_cached
 };
 
+// A hash of n bytes, chained through h.  Equal ones are compared bit for bit.
+uint64_t hash_bytes(uint64_t h, const void *p, size_t n);
+
 // Steps [offset, offset + n) of a waveform: symmetric in time, bit for bit, with
 // B1 in one plane through the z axis?
 WaveSym symmetric_pulse(const HostSeq &s, int64_t offset, int64_t n);
