@@ -2639,15 +2639,27 @@ static bool adj_takes_groups(const AdjArgs &old, const std::vector<AdjOp> &ops, 
 // Sets the context up for the adjoint by groups and runs its forward pass;
 // *done stays false where the isochromats have to be stepped one by one: fewer
 // than kAdjGroupMin isochromats per group, more memory than the stepping's
-// checkpoints (old_bytes) and 64 MiB, or more cells than the raster steps are
-// worth.
+// checkpoints (old_bytes) and 64 MiB, more cells than the raster steps are
+// worth, or not enough device memory.
 static int adj_forward_groups(gbs_ctx *ctx, const AdjArgs &old, const AdjSchedule &g, const AdjLimits &l,
                               AdjValues &values, size_t old_bytes, double *sig_out, bool *done) {
     const int64_t K = old.K, np = (int64_t)g.pulses.size(), ns = (int64_t)g.segs.size();
+    bool room = true;  // a failed allocation here is not the call's: stepping needs less
+    auto fits = [&](DevBuf &buf, size_t n) {
+        if (room && buf.ensure(n) != hipSuccess) {
+            (void)hipGetLastError();
+            room = false;
+        }
+        return room;
+    };
+    auto no_room = [&]() {
+        for (DevBuf *d : {&ctx->adj_order, &ctx->adj_pulse, &ctx->adj_group, &ctx->gscratch}) d->release();
+        return GBS_OK;
+    };
     WsCarve w;
     const size_t o_order = w.take(4 * (size_t)K), o_gid = w.take(4 * (size_t)K), o_tab = w.take(sizeof(float4) * (size_t)l.groups),
                  o_cls = w.take(4 * (size_t)l.groups);
-    ALLOC(ctx->adj_order, w.off);
+    if (!fits(ctx->adj_order, w.off)) return no_room();
     char *b = ctx->adj_order.as<char>();
     int64_t G = 0;
     HIPCHK(adjoint_groups(values, old.cls, old.n_classes, l.cells, (int32_t *)(b + o_order), (int32_t *)(b + o_gid),
@@ -2658,7 +2670,7 @@ static int adj_forward_groups(gbs_ctx *ctx, const AdjArgs &old, const AdjSchedul
     const size_t o_ops = v.take(sizeof(AdjGOp) * g.ops.size()), o_steps = v.take(sizeof(AdjStep) * g.steps.size()),
                  o_segs = v.take(sizeof(AdjSeg) * g.segs.size()), o_pulses = v.take(sizeof(int2) * g.pulses.size()),
                  o_coefs = v.take(sizeof(AdjGCoef) * g.coefs.size());
-    ALLOC(ctx->adj_pulse, v.off);
+    if (!fits(ctx->adj_pulse, v.off)) return no_room();
     std::vector<char> h(v.off);
     std::memcpy(&h[o_ops], g.ops.data(), sizeof(AdjGOp) * g.ops.size());
     std::memcpy(&h[o_steps], g.steps.data(), sizeof(AdjStep) * g.steps.size());
@@ -2675,7 +2687,7 @@ static int adj_forward_groups(gbs_ctx *ctx, const AdjArgs &old, const AdjSchedul
                  o_acc = u.take(sizeof(double) * 2 * (size_t)(old.n_rf + old.n_classes)),
                  o_wl = u.take(sizeof(double2) * (size_t)std::max(old.N, 1)),
                  o_decay = u.take(sizeof(AdjDecay) * std::max<size_t>(g.coefs.size(), 1) * (size_t)old.n_classes);
-    ALLOC(ctx->adj_group, u.off);
+    if (!fits(ctx->adj_group, u.off)) return no_room();
     char *ub = ctx->adj_group.as<char>();
     AdjPulseArgs p{};
     p.G = G;
@@ -2706,10 +2718,11 @@ static int adj_forward_groups(gbs_ctx *ctx, const AdjArgs &old, const AdjSchedul
     // sub-segment where that takes no more than the stepping's checkpoints, and
     // the backward pass steps everything once less
     const int32_t every = state * (size_t)n_sub <= old_bytes ? kAdjSub : old.every;
-    ALLOC(ctx->adj_ckpt, state * (size_t)((n_ops + every - 1) / every));
-    ALLOC(ctx->adj_sub, every == kAdjSub ? 1 : state * (size_t)std::min<int64_t>(every / kAdjSub, n_sub));
-    ALLOC(ctx->adj_sig, sizeof(double2) * (size_t)grid * (size_t)std::max(old.N, 1));
-    ALLOC(ctx->adj_gt, sizeof(double2) * (size_t)grid * (size_t)old.n_classes);
+    if (!fits(ctx->adj_ckpt, state * (size_t)((n_ops + every - 1) / every)) ||
+        !fits(ctx->adj_sub, every == kAdjSub ? 1 : state * (size_t)std::min<int64_t>(every / kAdjSub, n_sub)) ||
+        !fits(ctx->adj_sig, sizeof(double2) * (size_t)grid * (size_t)std::max(old.N, 1)) ||
+        !fits(ctx->adj_gt, sizeof(double2) * (size_t)grid * (size_t)old.n_classes))
+        return no_room();
     AdjGroupArgs a{};
     a.K = K;
     a.G = G;
@@ -2873,8 +2886,11 @@ extern "C" int gbs_adj_forward(gbs_ctx *ctx, const int32_t *cls, int32_t n_class
     AdjSchedule sched;
     AdjLimits limits;
     AdjValues values;
-    const bool by_groups = adj_takes_groups(a, ops, samp.data(), ckpt_bytes + sub_bytes, sched, limits);
-    if (by_groups) ALLOC(ctx->gscratch, adjoint_group_scratch(K));
+    bool by_groups = adj_takes_groups(a, ops, samp.data(), ckpt_bytes + sub_bytes, sched, limits);
+    if (by_groups && ctx->gscratch.ensure(adjoint_group_scratch(K)) != hipSuccess) {
+        (void)hipGetLastError();
+        by_groups = false;
+    }
     // inputs: class indices in range, T1/T2 > 0 (checked on the device); and the
     // counts of the values to group by, waited for with the answer
     int *const answer = ctx->host_flag + 16, *const counts = ctx->host_flag + 32;
