@@ -390,6 +390,7 @@ int gbs_set_phantom(gbs_ctx *ctx, int64_t K, const float *x, const float *y, con
     ctx->n_coils = 1;  // sensitivities belong to the previous phantom
     ctx->coil_re = ctx->coil_im = nullptr;
     ctx->coil_l_valid = false;
+    if (had_coils) ctx->pplan_valid = ctx->cplan_valid = false;  // (also if this phantom is refused)
     PhantomPtrs ph{x, y, z, t1, t2, df_hz, m0};
     ALLOC(ctx->flag, 256);
     HIPCHK(launch_fill_f64(ctx->flag.as<double>(), 1, ctx->stream));
@@ -402,7 +403,7 @@ int gbs_set_phantom(gbs_ctx *ctx, int64_t K, const float *x, const float *y, con
     ctx->ph = ph;
     ctx->has_ph = true;
     // the plain and cached schedules depend on the sequence and the coils alone
-    if (ctx->has_seq && ctx->pplan_valid && ctx->cplan_valid && !had_coils) return build_cached_surrogate(ctx);
+    if (ctx->has_seq && ctx->pplan_valid && ctx->cplan_valid) return build_cached_surrogate(ctx);
     return refresh_plans(ctx);  // one coil again: stepped launches take 256 samples
 }
 
