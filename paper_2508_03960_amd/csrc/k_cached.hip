@@ -228,16 +228,15 @@ __global__ __launch_bounds__(kAdcBlock) void k_direct_adc(DirectAdcArgs a) {
 // LDS for the lanes of the product.  Per isochromat that is 32 evaluations in
 // place of 256; the rest is 32 cycles of the matrix core per SIMD.  The 32
 // isochromats of a chunk add in the matrix core, FP64 from there.
-// V_SIN and V_COS cut their result off: over the turn the pair is short by
-// kTurnBias on average, which a sum over many phases shows, and a term here holds
-// two such pairs where k_direct_adc's holds one.  M makes up for both.  Errors of
+// A term here holds two sine/cosine pairs, each short by kTurnBias on average,
+// where k_direct_adc's holds one, and a sum over many isochromats shows it: M
+// makes up for both.  Errors of
 // the signal, k_direct_adc and this: 66 k isochromats of a brain phantom, 48
 // samples 5.1e-8 and 3.5e-8 (9.0e-8 without the two), 256 samples 9.0e-8 and 5.0e-8;
 // equal isochromats, 64 samples 9.5e-8 and 6.2e-8 (1.3e-7).  2.1M isochromats: 67 us
 // for 48 to 128 samples (65 with 256 isochromats between FP64 sums), 85 for 256 (83).
 typedef float cached_f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kProdChunk = 32;
-constexpr double kTurnBias = 3.234e-8;  // measured over 2^24 phases
 constexpr int kProdPad = 36;                  // floats per isochromat and side; 32 used (36: 16-byte rows, fewer bank conflicts)
 
 template <int NT>  // column tiles: 8 values of j each

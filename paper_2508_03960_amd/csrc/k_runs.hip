@@ -59,6 +59,9 @@ __device__ __forceinline__ float2 turned(const float2 &p, const float2 &q) {
     return make_float2(fmaf(p.x, q.x, -p.y * q.y), fmaf(p.x, q.y, p.y * q.x));
 }
 
+// V_SIN/V_COS pairs in phase e of a member (the first, the step, four steps)
+__device__ __forceinline__ int factors_of(int e) { return 1 + (e & 3) + (e >> 2); }
+
 constexpr int kRunChunk = 32;
 constexpr int kRunFlush = 8;  // chunks whose sums add in FP32
 
@@ -213,11 +216,13 @@ __global__ __launch_bounds__(256) void k_run_y(RunYArgs a) {
         trade(dr, rcc, rsc, rcs, rss);
         trade(di, icc, isc, ics, iss);
         const int ia = 2 * kq + (lane & 1), jb = HALF ? (i & 7) >> 1 : i >> 1;
+        const float gain = (float)(kTurnBias * ((a.lines.d != 0.0 ? factors_of(ia) + factors_of(jb) : 0) + (a.lines.c0 != 0.0)));
         // sum (wr + i wi)(cos t - i sin t), t = sa a + sb b
         auto put = [&](int line, float sa, float sb) {
             const float wrc = fmaf(-sa * sb, rss, rcc), wrs = fmaf(sa, rsc, sb * rcs);
             const float wic = fmaf(-sa * sb, iss, icc), wis = fmaf(sa, isc, sb * ics);
-            tile[line - l0][j] = make_float2(wrc + wis, wic - wrs);
+            const float re = wrc + wis, im = wic - wrs;
+            tile[line - l0][j] = make_float2(fmaf(re, gain, re), fmaf(im, gain, im));
         };
         // lines 0 .. 127: -b of the set (descending), 128 .. 255: +b
         // (HALF: a line from one of the two lanes that hold its sums)
