@@ -384,12 +384,13 @@ __global__ __launch_bounds__(64) void k_run_sweep(RunSweepArgs a) {
         cmul(mx, my, fr, fi);
         if (op.flags & kPreMz) mz = fmaf(d.px.z, mz - 1.f, 1.f);
         if (op.flags & kOpRf) {
-            const float nx = fmaf(d.t0.x, mx, fmaf(d.t0.y, my, fmaf(d.t0.z, mz, d.t0.w)));
-            const float ny = fmaf(d.t1.x, mx, fmaf(d.t1.y, my, fmaf(d.t1.z, mz, d.t1.w)));
-            const float nz = fmaf(d.t2.x, mx, fmaf(d.t2.y, my, fmaf(d.t2.z, mz, d.t2.w)));
-            mx = nx;
-            my = ny;
-            mz = nz;
+            // (the diagonal term, the largest, last: one rounding of its size)
+            const float px = fmaf(d.t0.y, my, fmaf(d.t0.z, mz, d.t0.w));
+            const float py = fmaf(d.t1.x, mx, fmaf(d.t1.z, mz, d.t1.w));
+            const float pz = fmaf(d.t2.x, mx, fmaf(d.t2.y, my, d.t2.w));
+            mx = fmaf(d.t0.x, mx, px);
+            my = fmaf(d.t1.y, my, py);
+            mz = fmaf(d.t2.z, mz, pz);
         }
         if (op.flags & kOpEmit) emit(op, d);
     };
@@ -471,14 +472,16 @@ __global__ __launch_bounds__(256) void k_run_state(RunStateArgs a, int64_t n) {
 #pragma unroll
     for (int c = 0; c < V; ++c) {
         const float4 m = gather_row(a.m, run[c]);
-        float mx = m.x, my = m.y;
-        if (a.cy != 0.0) {
+        if (a.cy != 0.0) {  // in FP64, rounded once
             float s, co;
             sincos_rev(a.cy * (double)yv[c], &s, &co);
-            cmul(mx, my, co, -s);
+            const double w = (1.0 + kTurnBias) * (double)m0[c], x = m.x, y = m.y;
+            o[0][c] = (float)(w * (x * co + y * s));
+            o[1][c] = (float)(w * (y * co - x * s));
+        } else {
+            o[0][c] = m.x * m0[c];
+            o[1][c] = m.y * m0[c];
         }
-        o[0][c] = mx * m0[c];
-        o[1][c] = my * m0[c];
         o[2][c] = m.z * m0[c];
     }
     float *out[3] = {a.ox, a.oy, a.oz};
