@@ -161,7 +161,7 @@ struct GroupedPlan {
     double final_cy = 0.0;  // y phase of the last map, per isochromat
     size_t w_runy = 0, w_runm = 0, run_ws_bytes = 0, o_runop = 0;
     double run_flops = 0.0, run_bytes = 0.0;
-    // batches of whole x-groups: first run (a multiple of 16 is where its Y
+    // batches of whole x-groups: first run (a multiple of kRunTile is where its Y
     // starts), and its wavefronts [wave0, wave0 + waves) of ctx->run_waves
     struct RunBatch {
         int64_t r0, r1;
@@ -298,7 +298,7 @@ static int build_cached_surrogate(gbs_ctx *ctx);
     } while (0)
 
 constexpr int64_t kSideMinK = 1 << 22;  // isochromats from which a grouped simulation forks onto the side stream
-constexpr int64_t kLateComposeGroups = 1 << 16;
+constexpr int64_t kLateComposeGroups = 1 << 16;  // groups from which one stream composes last (below)
 constexpr int64_t kRunMinMembers = 2;  // mean members per run from which the per-run form is used (plan_runs)
 
 static const char *status_text(int s) {
@@ -973,7 +973,7 @@ static int plan_runs(gbs_ctx *ctx, const std::vector<SweepOp> &sops, std::vector
     int64_t fit = w.off + 256 < end ? std::min<int64_t>(tiles, (int64_t)((end - w.off - 256) / per_tile)) : 0;
     if (fit < tiles && fit * kRunTile < kRunMinBatch) return GBS_OK;
     // Batches of whole x-groups, each with at most fit tiles, its Y starting at
-    // the multiple of 16 at or below its first run; inside, wavefronts of whole
+    // the multiple of kRunTile at or below its first run; inside, wavefronts of whole
     // x-groups (a group of more than 64 runs takes several, and a group that
     // no batch can hold is cut).
     std::vector<int32_t> waves;
@@ -1883,7 +1883,13 @@ static int run_grouped(gbs_ctx *ctx, char *ws, size_t ws_bytes, const float *m_i
     // side stream's kernels are submitted after the compositions, so that the
     // compositions' few workgroups are placed first.
     // Small phantoms take one stream: there a fork and a join cost more than the
-    // overlap gives (4096 isochromats: 77 us, 122 us with the side stream).
+    // overlap gives.  One stream and two, us, at 0.26, 1.05, 3.4, 5.2, 6.8 and
+    // 13.6 M isochromats: FSE 165 and 179, 195 and 201, 265 and 271, 349 and 350,
+    // 440 and 427, 590 and 537; EPI 143 and 154, 169 and 176, 234 and 239, 303
+    // and 295, 369 and 357, 530 and 525; spin echo 377 and 389, 446 and 446, 841
+    // and 835, 1204 and 1184, 1494 and 1465, 2841 and 2824; only the GRE of 32
+    // lines, whose work is the final state alone, is faster on one up to the last
+    // size (91 and 115 .. 384 and 392).
     const bool forked = K >= kSideMinK;
     const hipStream_t side = forked ? ctx->side : ctx->stream;
     if (forked) HIPCHK(hipEventRecord(ctx->fork, ctx->stream));

@@ -23,8 +23,8 @@ namespace gbs {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------- k_run_y
-// One workgroup per 16 runs (a row of the Y layout), four runs per wavefront.
-// A wavefront takes a run's members 32 at a time.  Lane l first makes the
+// One workgroup per kRunTile runs (a row of the Y layout), which its four
+// wavefronts take one after the other.  A wavefront takes a run's members 32 at a time.  Lane l first makes the
 // eight a-phases (l < 32) or b-phases (l >= 32) of member l % 32: the first one,
 // the step and four steps directly (v_sin / v_cos take turns), the others by at
 // most four products of those, and the weight with the phase of c0; all of it
@@ -35,8 +35,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // The matrix core adds the members of one chunk, the chunks' sums add in FP32
 // eight at a time, and those in FP64: 2.4e-7 of the signal off at any length.
 // All of a run's members in one FP32 accumulator were 1.4e-4 off at 16384 equal
-// terms and 9e-3 at 2^20, measurably from 64 on; that took 1 to 2.5 % less time
-// (27.3M isochromats, FSE of 256 lines 1271 and 1299 us, EPI of 128 821 and 831).
+// terms and 9e-3 at 2^20, measurably from 64 on; that took 4 to 6 % less time
+// (27.3M isochromats: 256 lines 524 and 554 us, 128 lines 348 and 360).
 // A phase coefficient (turns per metre) as two floats: c y mod 1 then takes
 // four FP32 instructions with one rounding of the reduced phase (the FMA of
 // hi y - rint(hi y) is exact up to it), instead of five at FP64.
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(256) void k_run_y(RunYArgs a) {
     // e ^ (k / 4 % 4): writes and reads are free of bank conflicts without
     // padding.  With that and the tile of the lines that are made, HALF takes 26
     // KB and six workgroups fit a CU instead of four (27.3M members, 128 lines:
-    // 373 -> 348 us; 36 KB and four as before for 256 lines).
+    // 373 -> 348 us when that was done; 36 KB and four as before for 256 lines).
     __shared__ __attribute__((aligned(16))) float phases[4][2][kRunChunk][16];
     __shared__ float2 weight[4][kRunChunk];
     constexpr int l0 = HALF ? 64 : 0, l1 = HALF ? 192 : kRunLinesSet;  // the set's lines that are made
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(64) void k_run_sweep(RunSweepArgs a) {
     // does the x-group go on before or after the wavefront's runs?
     const bool own = key != (w0 > 0 ? a.gx[w0 - 1] : -1) && key != (w1 < a.n_runs ? a.gx[w1] : -1);
     // byte offsets (32 bits: checked at the launch); lanes of a wavefront lie in
-    // at most five tiles of Y from its first one on
+    // at most 64 / kRunTile + 1 tiles of Y from its first one on
     const int64_t t0 = (w0 - a.r0) / kRunTile;
     const int coil0 = MC * (int)blockIdx.y;  // the wavefront's coils
     const float2 *yb = a.y + coil0 * a.y_coil + t0 * (int64_t)a.n_lines * kRunTile;

@@ -1,7 +1,7 @@
 // Grouped simulation per run of the layout (k_runs.hip).
 //
-// A run of the group-sorted layout holds the isochromats of equal (x, z, T1,
-// T2, dB0).  When a simulation starts from (0, 0, M0) and no B1 = 0 map before
+// A run of the group-sorted layout holds isochromats of equal (x, z, T1, T2,
+// dB0), up to 3 kRunPiece - 2 of them.  When a simulation starts from (0, 0, M0) and no B1 = 0 map before
 // a transition carries a y moment, the members of a run differ in nothing
 // that moves M / M0: all of them keep one ratio m_r, so each run is stepped
 // once.  The group sums of a with-ADC subsequence (Eq. 9) become
@@ -28,8 +28,8 @@ constexpr int64_t kRunMaxSlots = (int64_t)1 << 30;  // 4-byte slots at 32-bit of
 constexpr int kRunTile = 8;      // runs per row of the Y layout
 constexpr int kRunLinesSet = 256;  // lines of one 16 x 16 pair of tiles
 
-// Y[coil][run / 16][line][run % 16] for the runs [r0, r0 + n) (r0 a multiple
-// of 16), stored from run r0 on.
+// Y[coil][run / kRunTile][line][run % kRunTile] for the runs [r0, r0 + n) (r0 a
+// multiple of kRunTile), stored from run r0 on.
 struct RunYArgs {
     int64_t r0, n, n_runs;
     const int32_t *first4;  // first 4-slot quad of each run, n_runs + 1 entries
