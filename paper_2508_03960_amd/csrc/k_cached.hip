@@ -228,13 +228,15 @@ __global__ __launch_bounds__(kAdcBlock) void k_direct_adc(DirectAdcArgs a) {
 // LDS for the lanes of the product.  Per isochromat that is 32 evaluations in
 // place of 256; the rest is 32 cycles of the matrix core per SIMD.  The 32
 // isochromats of a chunk add in the matrix core, FP64 from there.
-// A term here holds two sine/cosine pairs, each short by kTurnBias on average,
-// where k_direct_adc's holds one, and a sum over many isochromats shows it: M
-// makes up for both.  Errors of
-// the signal, k_direct_adc and this: 66 k isochromats of a brain phantom, 48
-// samples 5.1e-8 and 3.5e-8 (9.0e-8 without the two), 256 samples 9.0e-8 and 5.0e-8;
-// equal isochromats, 64 samples 9.5e-8 and 6.2e-8 (1.3e-7).  2.1M isochromats: 67 us
-// for 48 to 128 samples (65 with 256 isochromats between FP64 sums), 85 for 256 (83).
+// A term here holds up to two sine/cosine pairs, each short by kTurnBias on
+// average, where k_direct_adc's holds one, and a sum over many isochromats shows
+// it: M makes up for both.  Phases of 0 are exact: an isochromat whose phase
+// stands still gets nothing, and the sums with A_0 = 1 give one pair's share back.
+// Errors of the signal, k_direct_adc and this: 66 k isochromats of a brain phantom,
+// 48 samples 5.1e-8 and 3.5e-8 (9.0e-8 with neither blocks nor this), 256 samples
+// 9.0e-8 and 5.0e-8; 2.07 M, FSE of 8 x 16 lines of 256, eight seeds: 9.9e-8 and
+// 7.5e-8.  2.1M isochromats: 67 us for 48 to 128 samples (65 with 256 isochromats
+// between FP64 sums), 85 for 256 (83).
 typedef float cached_f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kProdChunk = 32;
 constexpr int kProdPad = 36;                  // floats per isochromat and side; 32 used (36: 16-byte rows, fewer bank conflicts)
@@ -260,19 +262,19 @@ __global__ __launch_bounds__(256) void k_adc_product(DirectAdcArgs a, LinSamples
 #pragma unroll
             for (int v = 0; v < 4; ++v) acc[r][c][v] = 0.0;
         }
-    auto flush = [&]() {
+    auto flush = [&](double gain0) {  // gain0: of the sums with A_0
 #pragma unroll
         for (int r = 0; r < 2; ++r)
 #pragma unroll
             for (int c = 0; c < NT; ++c) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) acc[r][c][v] += (double)d[r][c][v];
+                for (int v = 0; v < 4; ++v)
+                    acc[r][c][v] = r == 0 && v < 2 ? fma(gain0, (double)d[r][c][v], acc[r][c][v]) : acc[r][c][v] + (double)d[r][c][v];
                 d[r][c] = cached_f32x4{0.f, 0.f, 0.f, 0.f};
             }
     };
     const int64_t stride = (int64_t)gridDim.x * 4 * kProdChunk;
     int64_t base = ((int64_t)blockIdx.x * 4 + wave) * kProdChunk;
-    constexpr double kGain = 1.0 + 2.0 * kTurnBias;
     // the next chunk's isochromats are loaded during this one's product
     float x = 0.f, y = 0.f, z = 0.f, df = 0.f, t2 = 1.f, cr = 1.f, ci = 0.f;
     double mx = 0.0, my = 0.0;
@@ -306,11 +308,16 @@ __global__ __launch_bounds__(256) void k_adc_product(DirectAdcArgs a, LinSamples
         }
         const double r2 = -kLog2e / (double)t2;
         const float e0 = (float)(tau0 * r2), de = (float)(dtau * r2);
+        // pairs of other phases than 0, which is exact: B_j, A_1 .. A_15
+        const bool turns = half && dp != 0.0;
+        const double gain = 1.0 + kTurnBias * ((turns || p0 != 0.0) + turns);
+        const int n_turns = __popcll(__ballot(turns));
+        const double gain0 = kq == 0 ? 1.0 - kTurnBias / kProdChunk * n_turns : 1.0;  // A_0 is 1
         // the factor of every value of this side: 1 (A), or M S (B; 0 past the end)
         float wr = 1.f, wi = 0.f;
         if (half) {
-            wr = base + mb < K ? (float)(mx * kGain) : 0.f;
-            wi = base + mb < K ? (float)(my * kGain) : 0.f;
+            wr = base + mb < K ? (float)(mx * gain) : 0.f;
+            wi = base + mb < K ? (float)(my * gain) : 0.f;
             if (sre) {
                 const float t = wr * cr - wi * ci;
                 wi = wr * ci + wi * cr;
@@ -344,7 +351,7 @@ __global__ __launch_bounds__(256) void k_adc_product(DirectAdcArgs a, LinSamples
                     d[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(pa[16 * r + i], pb[16 * c + i], d[r][c], 0, 0, 0);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        flush();
+        flush(gain0);
     }
     // Element v of tile (r, c): row 4 kq + v = {Re, Im} A_{8 r + 2 kq + v / 2}, column
     // i = {Re, Im} B_{8 c + i / 2}.  The neighbouring lane holds the other part of B.
