@@ -24,9 +24,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------- k_run_y
 // One workgroup per kRunTile runs (a row of the Y layout), which its four
-// wavefronts take one after the other.  A wavefront takes a run's members 32 at a time.  Lane l first makes the
-// eight a-phases (l < 32) or b-phases (l >= 32) of member l % 32: the first one,
-// the step and four steps directly (v_sin / v_cos take turns), the others by at
+// wavefronts take one after the other.  A wavefront takes a run's members 32 at a
+// time.  Lane l first makes the eight a-phases (l < 32) or b-phases (l >= 32) of
+// member l % 32: the first one, the step and four steps directly (v_sin / v_cos take turns), the others by at
 // most four products of those, and the weight with the phase of c0; all of it
 // goes to LDS.  Then every step of the product reads four members, lane l
 // holding row l % 16 and column l % 16 of member l / 16.  Evaluated in the lanes
@@ -110,6 +110,7 @@ __global__ __launch_bounds__(256) void k_run_y(RunYArgs a) {
     // taken before the one ahead of it is summed, so its first members are
     // loaded in time.
     __shared__ int taken;
+    __shared__ float2 still[4];  // the weights of a run's members at y = 0
     if (threadIdx.x == 0) taken = 4;
     __syncthreads();
     int j = wave;
@@ -121,6 +122,7 @@ __global__ __launch_bounds__(256) void k_run_y(RunYArgs a) {
         const int64_t r = tile0 + j, rn = tile0 + nj;
         const int next = nj < kRunTile && rn < rend ? first_slot(rn) : last;
         f32x4 dr = {0.f, 0.f, 0.f, 0.f}, di = {0.f, 0.f, 0.f, 0.f};
+        bool any_still = false;
         if (r < rend) {
             const int s0 = first_slot(r), s1 = first_slot(r + 1);
             f32x4 tr = dr, ti = di;
@@ -140,6 +142,15 @@ __global__ __launch_bounds__(256) void k_run_y(RunYArgs a) {
                     v = make_float2(fmaf(pr, w.x, pi * w.y), fmaf(pi, w.x, -pr * w.y));
                 } else {
                     v = make_float2(m * w.x, -m * w.y);
+                }
+                if (__ballot(yv == 0.f && m != 0.f)) {
+                    const bool at0 = yv == 0.f && !half;
+                    const float sx = wave_sum_lane63(at0 ? v.x : 0.f), sy = wave_sum_lane63(at0 ? v.y : 0.f);
+                    if (lane == 63) {
+                        const float2 o = any_still ? still[wave] : make_float2(0.f, 0.f);
+                        still[wave] = make_float2(o.x + sx, o.y + sy);
+                    }
+                    any_still = true;
                 }
                 float4 *ph = (float4 *)phases[wave][half][mb];
 #pragma unroll
@@ -217,12 +228,14 @@ __global__ __launch_bounds__(256) void k_run_y(RunYArgs a) {
         trade(di, icc, isc, ics, iss);
         const int ia = 2 * kq + (lane & 1), jb = HALF ? (i & 7) >> 1 : i >> 1;
         const float gain = (float)(kTurnBias * ((a.lines.d != 0.0 ? factors_of(ia) + factors_of(jb) : 0) + (a.lines.c0 != 0.0)));
+        // (phases of members at y = 0 are exact: they get no gain)
+        const float2 w0 = any_still ? still[wave] : make_float2(0.f, 0.f);
         // sum (wr + i wi)(cos t - i sin t), t = sa a + sb b
         auto put = [&](int line, float sa, float sb) {
             const float wrc = fmaf(-sa * sb, rss, rcc), wrs = fmaf(sa, rsc, sb * rcs);
             const float wic = fmaf(-sa * sb, iss, icc), wis = fmaf(sa, isc, sb * ics);
             const float re = wrc + wis, im = wic - wrs;
-            tile[line - l0][j] = make_float2(fmaf(re, gain, re), fmaf(im, gain, im));
+            tile[line - l0][j] = make_float2(fmaf(re - w0.x, gain, re), fmaf(im - w0.y, gain, im));
         };
         // lines 0 .. 127: -b of the set (descending), 128 .. 255: +b
         // (HALF: a line from one of the two lanes that hold its sums)
@@ -475,7 +488,8 @@ __global__ __launch_bounds__(256) void k_run_state(RunStateArgs a, int64_t n) {
         if (a.cy != 0.0) {  // in FP64, rounded once
             float s, co;
             sincos_rev(a.cy * (double)yv[c], &s, &co);
-            const double w = (1.0 + kTurnBias) * (double)m0[c], x = m.x, y = m.y;
+            // (turns of 0 and 1/2 are exact)
+            const double w = (s == 0.f ? 1.0 : 1.0 + kTurnBias) * (double)m0[c], x = m.x, y = m.y;
             o[0][c] = (float)(w * (x * co + y * s));
             o[1][c] = (float)(w * (y * co - x * s));
         } else {
