@@ -362,7 +362,7 @@ def adjoint_leg(gb, steps):
             "forward_ms": f * 1e3, "backward_ms": b * 1e3, "backward_over_forward": b / f,
             "forward_iso_steps_per_s": ph.K * S / f, "backward_iso_steps_per_s": ph.K * S / b,
             "checkpoint_every": 256, "raster_ops": n_raster,
-            "precision": "FP64 state, steps and sums",
+            "precision": "FP64 steps and sums; kept states, 1 - cos and decays FP32",
             "roofline_forward": rl("k_adjg_forward", fl_f, f),
             "roofline_backward": rl("k_adjg_backward", fl_b, b)}
 
